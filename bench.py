@@ -836,10 +836,10 @@ def inflation_measure(args, name, plain=True, cpu=True):
     box = "true" if (rob.n_boxes > 0 or "env_boxes" in data) else "false"
     if dom == "bisect":
         sb = shapes.get("bisect")
-        instance = f"ezo::k_project_bisect<{sb['T']}, {sb['depth']}, {box}, false>" if sb else None
+        instance = f"ezo::k_project_bisect<{box}, false, {'true' if sb['stage'] else 'false'}>" if sb else None
     else:
         sc = shapes.get("check_flags")
-        instance = f"ezo::k_check<{sc['T']}, false, {box}>" if sc else None
+        instance = f"ezo::k_check<false, {box}, {'true' if sc['stage'] else 'false'}>" if sc else None
     roofline = {"bound": "alu", "achieved": achieved, "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s",
                 "frac": achieved / PEAK_FP32_TFLOPS,
                 "traffic": measured_traffic(name, instance, n_p_used) if instance else None,

@@ -564,7 +564,8 @@ ezo_status ezo_set_autotune(ezo_ctx *ctx, int32_t enable);
  * self_pairs, obstacles, log2_items, T, W, stage, depth and us (measured
  * time per launch).  For "bisect", T counts candidates per workgroup and
  * depth (1..3, optional on import, default 1) the bisection levels checked
- * per round, so a tile check holds T (2^depth - 1) configurations.  For
+ * per round when the candidates fill the device (fewer candidates take more
+ * levels), so a tile check holds T (2^depth - 1) configurations.  For
  * "samples" (the sample count N_p of ezo_inflate_edges), T is N_p and
  * tune_seed (export only) the Philox key of the timed inflations.  For
  * "sample", T is

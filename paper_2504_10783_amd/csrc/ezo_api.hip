@@ -50,31 +50,55 @@ namespace {
 // at least ~4 workgroups per CU; W waves split the obstacles.
 constexpr size_t kObsStageBytes = 32768;   // obstacle records staged in LDS up to this size
 
-int pick_T(const ezo_ctx* c, int64_t items, int S, int W, size_t extra = 0) {
+int grid_dim(int n_obs) { return n_obs >= 256 ? 32 : (n_obs >= 32 ? 16 : 8); }
+
+// LDS of a tile check by mode: signed distances hold every sphere and box of
+// a configuration, flags only the link frames and boxes.
+struct TileRows {
+    int slots, B, n_obs;
+    bool sd;
+    size_t tables;             // the robot's tables without the self pairs
+    TileRows(const ezo_robot* r, int n_obs_, bool sd_)
+        : slots(r->slots), B(r->B), n_obs(n_obs_), sd(sd_),
+          tables(robot_stage_bytes(r->S, r->view.n_blocks, r->P, false)) {}
+    size_t bytes(int T, int W) const {
+        return sd ? tile_smem_bytes(T, slots, W)
+                  : flag_tile_bytes(T, B, W) + flag_grid_bytes(n_obs, grid_dim(n_obs), 0) + tables;
+    }
+};
+
+// LDS of the bisection besides its tile, tables and staged obstacles: the
+// candidates' state and the self pairs.
+size_t bisect_extra_bytes(const ezo_robot* r, int rows) {
+    return 3 * sizeof(float) * kMaxDof * (size_t)rows + robot_stage_bytes(r->S, r->view.n_blocks, r->P, true) -
+           robot_stage_bytes(r->S, r->view.n_blocks, r->P, false);
+}
+
+int pick_T(const ezo_ctx* c, int64_t items, const TileRows& tr, int W, size_t extra = 0) {
     const int cand[4] = {64, 32, 16, 8};
     int fit = 0;
     for (int T : cand) {
-        if (tile_smem_bytes(T, S, W) + extra > c->lds_cap) continue;
+        if (tr.bytes(T, W) + extra > c->lds_cap) continue;
         if (!fit) fit = T;
         if (items / T >= 4 * kNumCU) return T;
     }
     if (!fit) {
         for (int T : {4, 2, 1})
-            if (tile_smem_bytes(T, S, W) + extra <= c->lds_cap) return T;
+            if (tr.bytes(T, W) + extra <= c->lds_cap) return T;
         return 0;
     }
     // few items: smallest fitting tile gives the most workgroups
     int best = fit;
     for (int T : cand)
-        if (tile_smem_bytes(T, S, W) + extra <= c->lds_cap) best = T;
+        if (tr.bytes(T, W) + extra <= c->lds_cap) best = T;
     return best;
 }
 
 // Obstacle records go to LDS when they fit beside a tile of T (and `extra`
 // bytes more: the bisection's staged robot tables).
-bool stage_fits(const ezo_ctx* c, int T, int S, int W, int n_obs, size_t extra = 0) {
+bool stage_fits(const ezo_ctx* c, int T, const TileRows& tr, int W, int n_obs, size_t extra = 0) {
     const size_t b = 16 * (size_t)n_obs;
-    return T > 0 && n_obs > 0 && b <= kObsStageBytes && tile_smem_bytes(T, S, W) + b + extra <= c->lds_cap;
+    return T > 0 && n_obs > 0 && b <= kObsStageBytes && tr.bytes(T, W) + b + extra <= c->lds_cap;
 }
 
 int pick_W(int n_obs) {
@@ -87,13 +111,11 @@ int pick_W(int n_obs) {
 constexpr int kGridCap = 128;
 static_assert(kGridCap % 8 == 0, "the sweep loads cell lists eight entries (16 bytes) at a time");
 
-int grid_dim(int n_obs) { return n_obs >= 256 ? 32 : (n_obs >= 32 ? 16 : 8); }
-
 // Obstacle records, the frame shift and the broad-phase grid for one call,
 // written to the given device buffers (every byte the kernels read later is
 // rewritten here: nothing needs to start at zero).
 ezo_status prep_obstacles_into(ezo_ctx* c, const ezo_robot* r, const float* obs, int n_obs, hipStream_t st,
-                               void* rec, void* centre, void* geom, void* count, void* list, ObsView* ov,
+                               void* rec, void* centre, void* geom, void* count, void* state, void* list, ObsView* ov,
                                GridView* gv, const EdgeInit* ei = nullptr) {
     const int G = grid_dim(n_obs);
     // indices above 65535 do not fit the list type: then every cell scans all
@@ -103,12 +125,15 @@ ezo_status prep_obstacles_into(ezo_ctx* c, const ezo_robot* r, const float* obs,
     const int clear_wg = (G * G * G + 2047) / 2048;
     const int init_wg = (ei && ei->n_edges > 0) ? (ei->n_edges + 255) / 256 : 0;
     hipLaunchKernelGGL(k_prep_obstacles, dim3(1 + clear_wg + init_wg), dim3(256), 0, st, obs, n_obs, (float4*)rec,
-                       (float4*)centre, (GridGeom*)geom, G, r ? r->r_max : 0.f, (int*)count, lists ? 0 : kGridCap + 1,
-                       clear_wg, init_wg ? *ei : EdgeInit{});
+                       (float4*)centre, (GridGeom*)geom, G, r ? r->r_max : 0.f, r ? r->r_min : -kHuge, (int*)count,
+                       lists ? 0 : kGridCap + 1, (unsigned*)state, lists ? 0u : 0x55555555u, clear_wg, init_wg ? *ei : EdgeInit{});
+    // four waves per obstacle until the obstacles alone fill the chip (512
+    // obstacles: 8.3 us against 12.6 with one wave; 4096: 16 us with one, 23.5
+    // with four)
     if (lists && n_obs > 0)
-        hipLaunchKernelGGL(k_grid_scatter, dim3((unsigned)(((int64_t)n_obs * 64 + 255) / 256)), dim3(256), 0, st,
-                           (const float4*)rec, n_obs, (const GridGeom*)geom, G, kGridCap, (int*)count,
-                           (unsigned short*)list);
+        hipLaunchKernelGGL(k_grid_scatter, dim3((unsigned)n_obs), dim3(n_obs <= 1024 ? 256 : 64), 0, st, (const float4*)rec,
+                           (const GridGeom*)geom, G, kGridCap, (int*)count,
+                           (unsigned*)state, (unsigned short*)list);
     HIP_TRY(c, hipGetLastError());
     ov->n = n_obs;
     ov->lds_n = 0;
@@ -120,6 +145,7 @@ ezo_status prep_obstacles_into(ezo_ctx* c, const ezo_robot* r, const float* obs,
     gv->cap = kGridCap;
     gv->geom = (const GridGeom*)geom;
     gv->count = (const int*)count;
+    gv->state = (const unsigned*)state;
     gv->list = (const unsigned short*)list;
     gv->tests = nullptr;
     return EZO_OK;
@@ -129,14 +155,15 @@ ezo_status prep_obstacles_into(ezo_ctx* c, const ezo_robot* r, const float* obs,
 ezo_status prep_obstacles(ezo_ctx* c, const ezo_robot* r, const float* obs, int n_obs, hipStream_t st,
                           ObsView* ov, GridView* gv, const EdgeInit* ei = nullptr) {
     ezo_status s;
-    void *rec, *centre, *geom, *count, *list;
+    void *rec, *centre, *geom, *count, *state, *list;
     const size_t cells = (size_t)grid_dim(n_obs) * grid_dim(n_obs) * grid_dim(n_obs);
     if ((s = ezo_ws_get(c, W_OBS_REC, sizeof(float4) * (size_t)std::max(n_obs, 1), &rec)) != EZO_OK) return s;
     if ((s = ezo_ws_get(c, W_OBS_CENTRE, sizeof(float4), &centre)) != EZO_OK) return s;
     if ((s = ezo_ws_get(c, W_GRID_GEOM, sizeof(GridGeom), &geom)) != EZO_OK) return s;
     if ((s = ezo_ws_get(c, W_GRID_COUNT, sizeof(int) * cells, &count)) != EZO_OK) return s;
+    if ((s = ezo_ws_get(c, W_GRID_STATE, sizeof(unsigned) * state_words(grid_dim(n_obs)), &state)) != EZO_OK) return s;
     if ((s = ezo_ws_get(c, W_GRID_LIST, sizeof(unsigned short) * cells * kGridCap, &list)) != EZO_OK) return s;
-    return prep_obstacles_into(c, r, obs, n_obs, st, rec, centre, geom, count, list, ov, gv, ei);
+    return prep_obstacles_into(c, r, obs, n_obs, st, rec, centre, geom, count, state, list, ov, gv, ei);
 }
 
 // ---------------------------------------------------------------------------
@@ -153,7 +180,8 @@ constexpr size_t kScrCentre = kScrRec + 16 * (size_t)EZO_NOALLOC_MAX_OBSTACLES;
 constexpr size_t kScrGeom = kScrCentre + 256;
 constexpr size_t kScrCount = kScrGeom + 256;
 constexpr size_t kScrCells = 32 * 32 * 32;
-constexpr size_t kScrList = kScrCount + sizeof(int) * kScrCells;
+constexpr size_t kScrState = kScrCount + sizeof(int) * kScrCells;
+constexpr size_t kScrList = kScrState + kScrCells / 4;
 constexpr size_t kScrBytes = kScrList + sizeof(unsigned short) * kScrCells * kGridCap;
 static_assert(sizeof(GridGeom) <= 256, "grid geometry slot");
 static_assert(kScrList % 256 == 0, "list slot alignment");
@@ -175,7 +203,12 @@ bool pow2_tile(int T) { return T == 1 || T == 2 || T == 4 || T == 8 || T == 16 |
 
 // Configurations per tile check: T for a check; T candidates x (2^depth - 1)
 // bisection points for the bisection.
-int tile_configs(const TileCfg& g, bool bisect) { return bisect ? g.T * ((1 << g.depth) - 1) : g.T; }
+// (room for one candidate's points at kMaxLevels levels and its projection).
+int tile_configs(const TileCfg& g, bool bisect) {
+    return bisect ? std::max(g.T * ((1 << g.depth) - 1), 1 << kMaxLevels) : g.T;
+}
+
+BisectShape bisect_shape(const TileCfg& g) { return BisectShape{g.T, g.depth, tile_configs(g, true), 0}; }
 
 // Bisection shapes that have a kernel instance.
 bool bisect_shape_built(const TileCfg& g) {
@@ -183,13 +216,14 @@ bool bisect_shape_built(const TileCfg& g) {
 }
 
 // A shape is usable when its LDS fits and staging is possible where asked.
-bool cfg_valid(const ezo_ctx* c, const TileCfg& g, int S, int P, int NB, int n_obs, bool sd, bool bisect = false) {
+bool cfg_valid(const ezo_ctx* c, const TileCfg& g, const ezo_robot* r, int n_obs, bool sd, bool bisect = false) {
     if (!pow2_tile(g.T) || g.W < 1 || g.W > 16 || g.depth < 1 || g.depth > 3) return false;
     if (bisect ? !bisect_shape_built(g) : g.depth != 1) return false;
     const int T = tile_configs(g, bisect);
-    const size_t rs = bisect ? robot_stage_bytes(S, P, NB) : 0;
-    if (g.stage && (sd || !stage_fits(c, T, S, g.W, n_obs, rs))) return false;
-    return tile_smem_bytes(T, S, g.W) + (g.stage ? 16 * (size_t)n_obs : 0) + rs <= c->lds_cap;
+    const TileRows tr(r, n_obs, sd);
+    const size_t rs = bisect ? bisect_extra_bytes(r, bisect_state_rows(bisect_shape(g))) : 0;
+    if (g.stage && (sd || !stage_fits(c, T, tr, g.W, n_obs, rs))) return false;
+    return tr.bytes(T, g.W) + (g.stage ? 16 * (size_t)n_obs : 0) + rs <= c->lds_cap;
 }
 
 TuneKey tune_key(const ezo_ctx* c, const ezo_robot* r, TuneKind kind, int n_obs, int64_t items) {
@@ -209,8 +243,9 @@ TuneKey tune_key(const ezo_ctx* c, const ezo_robot* r, TuneKind kind, int n_obs,
 TileCfg heuristic_check(const ezo_ctx* c, const ezo_robot* r, int n_obs, int64_t items, bool sd) {
     TileCfg g;
     g.W = sd ? pick_W(n_obs) : 4;
-    g.T = pick_T(c, items, r->slots, g.W);
-    g.stage = (!sd && stage_fits(c, g.T, r->slots, g.W, n_obs)) ? 1 : 0;
+    const TileRows tr(r, n_obs, sd);
+    g.T = pick_T(c, items, tr, g.W);
+    g.stage = (!sd && stage_fits(c, g.T, tr, g.W, n_obs)) ? 1 : 0;
     return g;
 }
 
@@ -219,23 +254,23 @@ TileCfg heuristic_bisect(const ezo_ctx* c, const ezo_robot* r, int n_obs, int64_
     TileCfg g;
     g.W = 4;
     g.depth = 1;
-    const size_t rs = robot_stage_bytes(r->slots, r->P, r->view.n_blocks);
-    g.T = std::max(std::min(pick_T(c, items, r->slots, g.W, rs), 64), 2);
-    g.stage = stage_fits(c, g.T, r->slots, g.W, n_obs, rs) ? 1 : 0;
+    const TileRows tr(r, n_obs, false);
+    g.T = std::max(std::min(pick_T(c, items, tr, g.W, bisect_extra_bytes(r, 64)), 64), 2);
+    g.stage = stage_fits(c, tile_configs(g, true), tr, g.W, n_obs, bisect_extra_bytes(r, 64)) ? 1 : 0;
     return g;
 }
 
-TileCfg resolve_cfg(const ezo_ctx* c, const TuneKey& k, const TileCfg& fallback, int S, int P, int NB, int n_obs, bool sd,
+TileCfg resolve_cfg(const ezo_ctx* c, const TuneKey& k, const TileCfg& fallback, const ezo_robot* r, int n_obs, bool sd,
                     bool bisect = false) {
     TileCfg g;
-    if (ezo_tune_lookup(k, &g) && cfg_valid(c, g, S, P, NB, n_obs, sd, bisect)) return g;
+    if (ezo_tune_lookup(k, &g) && cfg_valid(c, g, r, n_obs, sd, bisect)) return g;
     return fallback;
 }
 
 // Candidate shapes: every fitting T x W x staging (x bisection depth 1..2);
 // T = configurations (check, 4..64) or candidates (bisection, 1..64) per
 // workgroup; items = configurations or candidate slots.
-std::vector<TileCfg> tile_candidates(const ezo_ctx* c, int S, int P, int NB, int n_obs, bool sd, std::initializer_list<int> Ws,
+std::vector<TileCfg> tile_candidates(const ezo_ctx* c, const ezo_robot* r, int n_obs, bool sd, std::initializer_list<int> Ws,
                                      int64_t items, bool bisect = false) {
     std::vector<TileCfg> v;
     // (bisection: one or two levels per round; three, seven points per
@@ -248,11 +283,15 @@ std::vector<TileCfg> tile_candidates(const ezo_ctx* c, int S, int P, int NB, int
             for (int W : Ws)
                 for (int st = 0; st <= (sd ? 0 : 1); ++st) {
                     TileCfg g{T, W, st, dp};
-                    if (cfg_valid(c, g, S, P, NB, n_obs, sd, bisect)) v.push_back(g);
+                    if (cfg_valid(c, g, r, n_obs, sd, bisect)) v.push_back(g);
                 }
         }
     return v;
 }
+
+// Waves of a flags launch over one batch: twice what the chip holds at the five
+// to seven waves per SIMD that the kernel's registers allow.
+constexpr int kFlagWaves = 2 * kNumCU * 24;
 
 template <bool SD>
 ezo_status launch_check(ezo_ctx* c, const ezo_robot* r, const ObsView& ov, const GridView& gv, const float* q, int64_t n,
@@ -266,34 +305,29 @@ ezo_status launch_check(ezo_ctx* c, const ezo_robot* r, const ObsView& ov, const
     } else {
         const int64_t items = n * n_batch;
         g = resolve_cfg(c, tune_key(c, r, SD ? TUNE_CHECK_SD : TUNE_CHECK_FLAGS, ov.n, items),
-                        heuristic_check(c, r, ov.n, items, SD), r->slots, r->P, r->view.n_blocks, ov.n, SD);
+                        heuristic_check(c, r, ov.n, items, SD), r, ov.n, SD);
     }
     const int T = g.T, W = g.W;
     if (T == 0) return ezo_fail(c, EZO_E_UNSUPPORTED, "robot too large for one tile");
     ObsView ovs = ov;
     ovs.lds_n = g.stage ? ov.n : 0;
-    const size_t lds = tile_smem_bytes(T, r->slots, W) + 16 * (size_t)ovs.lds_n;
+    const size_t lds = TileRows(r, ov.n, SD).bytes(T, W) + 16 * (size_t)ovs.lds_n;
     const int64_t tiles = (n + T - 1) / T;
     if (tiles <= 0) return EZO_OK;
-    dim3 grid((unsigned)tiles, (unsigned)n_batch), block(64 * W);
+    // one batch in flags mode: at most kFlagWaves waves, each workgroup taking
+    // tiles in turn, so that the copy of the cell states is paid by several
+    const int64_t wgs = SD || n_batch > 1 ? tiles : std::min<int64_t>(tiles, kFlagWaves / W);
+    dim3 grid((unsigned)wgs, (unsigned)n_batch), block(64 * W);
     const bool box = r->B > 0 || ov.n_ebox > 0;
-#define EZO_LAUNCH_CHECK(TT)                                                                                   \
-    do {                                                                                                       \
-        if (box)                                                                                               \
-            EZO_KLAUNCH(c, (k_check<TT, SD, true>), grid, block, lds, st, r->view, ovs, gv, q, n, sn, sd, q_batch, \
-                        flags, min_sd, min_sd_self, out_batch, status, it, pred, margin, stats);               \
-        else                                                                                                   \
-            EZO_KLAUNCH(c, (k_check<TT, SD, false>), grid, block, lds, st, r->view, ovs, gv, q, n, sn, sd,      \
-                        q_batch, flags, min_sd, min_sd_self, out_batch, status, it, pred, margin, stats);      \
-    } while (0)
-    switch (T) {
-        case 64: EZO_LAUNCH_CHECK(64); break;
-        case 32: EZO_LAUNCH_CHECK(32); break;
-        case 16: EZO_LAUNCH_CHECK(16); break;
-        case 8: EZO_LAUNCH_CHECK(8); break;
-        case 4: EZO_LAUNCH_CHECK(4); break;
-        case 2: EZO_LAUNCH_CHECK(2); break;
-        default: EZO_LAUNCH_CHECK(1); break;
+#define EZO_LAUNCH_CHECK(BB, OO)                                                                                  \
+    EZO_KLAUNCH(c, (k_check<SD, BB, OO>), grid, block, lds, st, r->view, ovs, gv, T, q, n, sn, sd, q_batch, flags, \
+                min_sd, min_sd_self, out_batch, status, it, pred, margin, stats)
+    if (!SD && ovs.lds_n > 0) {
+        if (box) EZO_LAUNCH_CHECK(true, !SD);
+        else EZO_LAUNCH_CHECK(false, !SD);
+    } else {
+        if (box) EZO_LAUNCH_CHECK(true, false);
+        else EZO_LAUNCH_CHECK(false, false);
     }
 #undef EZO_LAUNCH_CHECK
     HIP_TRY(c, hipGetLastError());
@@ -398,21 +432,20 @@ ezo_status launch_sample(ezo_ctx* c, int dof, const float* A, const float* b, co
     return EZO_OK;
 }
 
+// The candidates come as a list over all edges (cl).
 ezo_status launch_project_bisect(ezo_ctx* c, const ezo_robot* r, const ObsView& ov, const GridView& gv,
-                                 const float* edges, int E,
-                                 const float* S, int64_t stride, const int* cand_idx, const int* n_cands,
-                                 int cand_cap, int n_b, float* c_star, float* a_dir, float* t_star,
-                                 uint8_t* pcol, uint8_t* pany, const int* status, hipStream_t st,
-                                 const TileCfg* shape = nullptr, int64_t s_edge = -1, const MlpView* screen = nullptr,
-                                 EdgeStatsDev* stats = nullptr) {
+                                 const float* edges, int E, const float* S, int64_t stride, const int* cand_idx,
+                                 const CandList& cl, int cand_cap, int n_b, float* c_star, float* a_dir, float* t_star,
+                                 uint8_t* pcol, uint8_t* pany, hipStream_t st, const TileCfg* shape = nullptr,
+                                 int64_t s_edge = -1, const MlpView* screen = nullptr, EdgeStatsDev* stats = nullptr) {
     if (s_edge < 0) s_edge = (int64_t)r->dof * stride;   // samples [E][dof][stride]
     TileCfg g;
+    const int64_t items = (int64_t)cand_cap * E;
     if (shape) {
         g = *shape;
     } else {
-        const int64_t items = (int64_t)cand_cap * E;
-        g = resolve_cfg(c, tune_key(c, r, TUNE_BISECT, ov.n, items), heuristic_bisect(c, r, ov.n, items), r->slots, r->P, r->view.n_blocks,
-                        ov.n, false, true);
+        g = resolve_cfg(c, tune_key(c, r, TUNE_BISECT, ov.n, items), heuristic_bisect(c, r, ov.n, items), r, ov.n, false,
+                        true);
     }
     const bool box = r->B > 0 || ov.n_ebox > 0;
     // the screened form (sphere robots): one bisection level per round, at
@@ -423,78 +456,60 @@ ezo_status launch_project_bisect(ezo_ctx* c, const ezo_robot* r, const ObsView& 
         g.T = std::min(std::max(g.T, 2), 16);
         g.W = std::max(g.W, 4);
     }
-    const int TC = g.T, W = g.W, dp = g.depth;
+    const int W = g.W;
     if (!bisect_shape_built(g) || W < 1 || W > 16)
-        return ezo_fail(c, EZO_E_INVALID, "bisection shape T=%d W=%d depth=%d", TC, W, dp);
-    ObsView ovs = ov;
-    ovs.lds_n = g.stage ? ov.n : 0;
-    size_t lds = tile_smem_bytes(tile_configs(g, true), r->slots, W) + 16 * (size_t)ovs.lds_n +
-                 robot_stage_bytes(r->slots, r->P, r->view.n_blocks);
+        return ezo_fail(c, EZO_E_INVALID, "bisection shape T=%d W=%d depth=%d", g.T, W, g.depth);
+    BisectShape bs = bisect_shape(g);
+    bool ost = g.stage && ov.n > 0;
+    size_t lds = TileRows(r, ov.n, false).bytes(bs.Tcap, W) + (ost ? 16 * (size_t)ov.n : 0) +
+                 bisect_extra_bytes(r, bisect_state_rows(bs));
     if (scr) {
-        lds += mlp_tile_smem_bytes(1) + 16 * sizeof(float);
-        if (lds > c->lds_cap && ovs.lds_n > 0) {        // drop the obstacle staging first
-            lds -= 16 * (size_t)ovs.lds_n;
-            ovs.lds_n = 0;
+        lds += mlp_tile_smem_bytes(1) + 16 * (1 + kMaxDof) * sizeof(float);
+        if (lds > c->lds_cap && ost) {                  // drop the obstacle staging first
+            lds -= 16 * (size_t)ov.n;
+            ost = false;
         }
     }
-    if (lds > c->lds_cap) return ezo_fail(c, EZO_E_UNSUPPORTED, "robot too large for one tile");
-    dim3 grid((unsigned)((cand_cap + TC - 1) / TC), (unsigned)E), block(64 * W);
+    if (lds > c->lds_max) return ezo_fail(c, EZO_E_UNSUPPORTED, "robot too large for one tile");
+    // workgroups that run at once: by LDS (160 KB a CU) and by registers (five
+    // waves a SIMD); the grid holds every tile of full lists, up to eight
+    // rounds of those (a workgroup then takes several)
+    bs.resident = kNumCU * std::max(1, std::min((int)(163840 / lds), 24 / W));
+    const int64_t tiles = std::max<int64_t>((items + bs.T - 1) / bs.T, std::min<int64_t>(items, bs.resident));
+    dim3 grid((unsigned)std::min<int64_t>(tiles, 8LL * bs.resident)), block(64 * W);
     const MlpView mv = scr ? *screen : MlpView{0, 0, nullptr, nullptr, nullptr, 0.f};
+#define EZO_LAUNCH_PB(BB, SS, OO)                                                                                   \
+    EZO_KLAUNCH(c, (k_project_bisect<BB, SS, OO>), grid, block, lds, st, r->view, ov, gv, bs, cl, edges, S, stride, \
+                s_edge, cand_idx, cand_cap, n_b, c_star, a_dir, t_star, pcol, pany, mv, stats)
     if (scr) {
-        switch (TC) {
-            case 16: EZO_KLAUNCH(c, (k_project_bisect<16, 1, false, true>), grid, block, lds, st, r->view, ovs, gv,
-                                 edges, S, stride, s_edge, cand_idx, n_cands, cand_cap, n_b, c_star, a_dir, t_star,
-                                 pcol, pany, status, mv, stats); break;
-            case 8: EZO_KLAUNCH(c, (k_project_bisect<8, 1, false, true>), grid, block, lds, st, r->view, ovs, gv,
-                                edges, S, stride, s_edge, cand_idx, n_cands, cand_cap, n_b, c_star, a_dir, t_star,
-                                pcol, pany, status, mv, stats); break;
-            case 4: EZO_KLAUNCH(c, (k_project_bisect<4, 1, false, true>), grid, block, lds, st, r->view, ovs, gv,
-                                edges, S, stride, s_edge, cand_idx, n_cands, cand_cap, n_b, c_star, a_dir, t_star,
-                                pcol, pany, status, mv, stats); break;
-            default: EZO_KLAUNCH(c, (k_project_bisect<2, 1, false, true>), grid, block, lds, st, r->view, ovs, gv,
-                                 edges, S, stride, s_edge, cand_idx, n_cands, cand_cap, n_b, c_star, a_dir, t_star,
-                                 pcol, pany, status, mv, stats); break;
-        }
-        HIP_TRY(c, hipGetLastError());
-        return EZO_OK;
-    }
-#define EZO_LAUNCH_PB(TT, DD)                                                                                       \
-    do {                                                                                                            \
-        if (box)                                                                                                    \
-            EZO_KLAUNCH(c, (k_project_bisect<TT, DD, true>), grid, block, lds, st, r->view, ovs, gv, edges, S, stride, \
-                        s_edge, cand_idx, n_cands, cand_cap, n_b, c_star, a_dir, t_star, pcol, pany, status, mv,     \
-                        stats);                                                                                     \
-        else                                                                                                        \
-            EZO_KLAUNCH(c, (k_project_bisect<TT, DD, false>), grid, block, lds, st, r->view, ovs, gv, edges, S,       \
-                        stride, s_edge, cand_idx, n_cands, cand_cap, n_b, c_star, a_dir, t_star, pcol, pany, status, \
-                        mv, stats);                                                                                 \
-    } while (0)
-    if (dp == 1) {
-        switch (TC) {
-            case 64: EZO_LAUNCH_PB(64, 1); break;
-            case 32: EZO_LAUNCH_PB(32, 1); break;
-            case 16: EZO_LAUNCH_PB(16, 1); break;
-            case 8: EZO_LAUNCH_PB(8, 1); break;
-            case 4: EZO_LAUNCH_PB(4, 1); break;
-            default: EZO_LAUNCH_PB(2, 1); break;
-        }
-    } else if (dp == 2) {
-        switch (TC) {
-            case 16: EZO_LAUNCH_PB(16, 2); break;
-            case 8: EZO_LAUNCH_PB(8, 2); break;
-            case 4: EZO_LAUNCH_PB(4, 2); break;
-            case 2: EZO_LAUNCH_PB(2, 2); break;
-            default: EZO_LAUNCH_PB(1, 2); break;
-        }
+        if (ost) EZO_LAUNCH_PB(false, true, true);
+        else EZO_LAUNCH_PB(false, true, false);
+    } else if (box) {
+        if (ost) EZO_LAUNCH_PB(true, false, true);
+        else EZO_LAUNCH_PB(true, false, false);
     } else {
-        switch (TC) {
-            case 8: EZO_LAUNCH_PB(8, 3); break;
-            case 4: EZO_LAUNCH_PB(4, 3); break;
-            case 2: EZO_LAUNCH_PB(2, 3); break;
-            default: EZO_LAUNCH_PB(1, 3); break;
-        }
+        if (ost) EZO_LAUNCH_PB(false, false, true);
+        else EZO_LAUNCH_PB(false, false, false);
     }
 #undef EZO_LAUNCH_PB
+    HIP_TRY(c, hipGetLastError());
+    return EZO_OK;
+}
+
+// The candidate list of per-edge counts, in the context's workspace.
+ezo_status list_buffers(ezo_ctx* c, int64_t items, CandList* cl) {
+    ezo_status s;
+    void *le, *ln;
+    if ((s = ezo_ws_get(c, W_CAND_LIST, sizeof(int2) * (size_t)items, &le)) ||
+        (s = ezo_ws_get(c, W_LIST_N, sizeof(int), &ln)))
+        return s;
+    *cl = CandList{(int2*)le, (int*)ln};
+    return EZO_OK;
+}
+
+ezo_status list_candidates(ezo_ctx* c, const int* n_cands, int E, int cand_cap, const CandList& cl, hipStream_t st) {
+    hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, st, (uint32_t*)cl.n, (int64_t)1, 0u);
+    hipLaunchKernelGGL(k_list_candidates, dim3(E), dim3(256), 0, st, n_cands, cand_cap, cl);
     HIP_TRY(c, hipGetLastError());
     return EZO_OK;
 }
@@ -516,8 +531,8 @@ ezo_status tune_check_inplace(ezo_ctx* c, const ezo_robot* r, const ObsView& ov,
     if (!c->autotune || ezo_tune_lookup(k, &g)) return EZO_OK;
     const int64_t n_t = SD ? std::min<int64_t>(n, std::max<int64_t>(65536, (1LL << 28) / std::max(ov.n, 256)))
                            : std::min<int64_t>(n, 1LL << 19);
-    const auto cands = SD ? tile_candidates(c, r->slots, r->P, r->view.n_blocks, ov.n, true, {1, 2, 4, 8, 16}, n_t)
-                          : tile_candidates(c, r->slots, r->P, r->view.n_blocks, ov.n, false, {1, 2, 4, 8}, n_t);
+    const auto cands = SD ? tile_candidates(c, r, ov.n, true, {1, 2, 4, 8, 16}, n_t)
+                          : tile_candidates(c, r, ov.n, false, {1, 2, 4, 8}, n_t);
     if (cands.empty()) return EZO_OK;
     IterArgs it{nullptr, 0, 0, 0, 0};
     auto run = [&](const TileCfg& cfg) {
@@ -530,16 +545,16 @@ ezo_status tune_check_inplace(ezo_ctx* c, const ezo_robot* r, const ObsView& ov,
 // Driven projection + bisection: the call's own candidates (outputs only).
 ezo_status tune_bisect_inplace(ezo_ctx* c, const ezo_robot* r, const ObsView& ov, const GridView& gv,
                                const float* edges, int E, const float* S, int64_t stride, const int* cand_idx,
-                               const int* n_cands, int cand_cap, int n_b, float* c_star, float* a_dir, float* t_star,
+                               const CandList& cl, int cand_cap, int n_b, float* c_star, float* a_dir, float* t_star,
                                uint8_t* pcol, hipStream_t st) {
     const TuneKey k = tune_key(c, r, TUNE_BISECT, ov.n, (int64_t)cand_cap * E);
     TileCfg g;
     if (!c->autotune || ezo_tune_lookup(k, &g)) return EZO_OK;
-    const auto cands = tile_candidates(c, r->slots, r->P, r->view.n_blocks, ov.n, false, {1, 2, 4, 8, 16}, (int64_t)cand_cap * E, true);
+    const auto cands = tile_candidates(c, r, ov.n, false, {1, 2, 4, 8, 16}, (int64_t)cand_cap * E, true);
     if (cands.empty()) return EZO_OK;
     auto run = [&](const TileCfg& cfg) {
-        return launch_project_bisect(c, r, ov, gv, edges, E, S, stride, cand_idx, n_cands, cand_cap, n_b, c_star,
-                                     a_dir, t_star, pcol, nullptr, nullptr, st, &cfg);
+        return launch_project_bisect(c, r, ov, gv, edges, E, S, stride, cand_idx, cl, cand_cap, n_b, c_star,
+                                     a_dir, t_star, pcol, nullptr, st, &cfg);
     };
     return ezo_tune_search(c, k, cands, st, run, &g);
 }
@@ -571,7 +586,7 @@ constexpr int kPathBatch = 128;
 ezo_status tune_inflation(ezo_ctx* c, const ezo_robot* r, const ObsView& ov, const GridView& gv, const float* edges,
                           int E, const ezo_params* p, int S_cap, int64_t stride, float* A, float* b, int* n_faces,
                           float* w_s, uint8_t* w_f, int* w_ci, int* w_nc, float* w_cs, float* w_ad, float* w_ts,
-                          uint8_t* w_pc, const int* w_active, hipStream_t st, bool* launched) {
+                          uint8_t* w_pc, const int* w_active, const CandList& cl, hipStream_t st, bool* launched) {
     if (!c->autotune) return EZO_OK;
     const int dof = r->dof, cap = p->face_capacity, cand_cap = p->n_p;
     const TuneKey kc = tune_key(c, r, TUNE_CHECK_FLAGS, ov.n, (int64_t)S_cap * E);
@@ -598,27 +613,35 @@ ezo_status tune_inflation(ezo_ctx* c, const ezo_robot* r, const ObsView& ov, con
                                    stride, E, nullptr, it, st, nullptr, 0.f, nullptr, &cfg);
     };
     if (need_c) {
-        const auto cands = tile_candidates(c, r->slots, r->P, r->view.n_blocks, ov.n, false, {1, 2, 4, 8}, (int64_t)S_cap * E);
+        const auto cands = tile_candidates(c, r, ov.n, false, {1, 2, 4, 8}, (int64_t)S_cap * E);
         if (!cands.empty() && (s = ezo_tune_search(c, kc, cands, st, run_c, &g))) return s;
     }
     if (!need_b) return EZO_OK;
     if ((s = run_c(heuristic_check(c, r, ov.n, (int64_t)S_cap * E, false)))) return s;
     IterArgs sel{nullptr, 0, S_cap, -1, S_cap};     // T = -1: never accept, always select
     hipLaunchKernelGGL(k_test_select, dim3(E), dim3(1024), 0, st, w_f, stride, p->n_p, p->n_b, w_ci, cand_cap, w_nc,
-                       nullptr, nullptr, nullptr, nullptr, sel);
+                       nullptr, nullptr, nullptr, nullptr, sel, CandList{});
     HIP_TRY(c, hipGetLastError());
-    const auto cands = tile_candidates(c, r->slots, r->P, r->view.n_blocks, ov.n, false, {1, 2, 4, 8, 16}, (int64_t)cand_cap * E, true);
+    const auto cands = tile_candidates(c, r, ov.n, false, {1, 2, 4, 8, 16}, (int64_t)cand_cap * E, true);
     if (cands.empty()) return EZO_OK;
     const int light = std::max(16, (int)std::ceil(2.0 * p->eps * cand_cap));
     int* w_nc_light = reinterpret_cast<int*>(w_f);      // the flags are free once selected (E <= stride E / 4)
     hipLaunchKernelGGL(k_cap_counts, dim3((E + 255) / 256), dim3(256), 0, st, (const int*)w_nc, w_nc_light, E, light);
     HIP_TRY(c, hipGetLastError());
+    // the lists of the full counts (the loop's, emptied again when the edges
+    // are initialised) and of the light ones (their length behind the counts)
+    void* w_ll;
+    if ((s = ezo_ws_get(c, W_LIST_LIGHT, sizeof(int2) * (size_t)E * std::min(light, cand_cap), &w_ll))) return s;
+    const CandList cl_light{(int2*)w_ll, w_nc_light + E};
+    if ((s = list_candidates(c, w_nc, E, cand_cap, cl, st)) ||
+        (s = list_candidates(c, w_nc_light, E, cand_cap, cl_light, st)))
+        return s;
     auto run_b = [&](const TileCfg& cfg) {
-        ezo_status e = launch_project_bisect(c, r, ov, gv, edges, E, w_s, stride, w_ci, w_nc, cand_cap, p->n_b, w_cs,
-                                             w_ad, w_ts, w_pc, nullptr, nullptr, st, &cfg);
+        ezo_status e = launch_project_bisect(c, r, ov, gv, edges, E, w_s, stride, w_ci, cl, cand_cap, p->n_b, w_cs,
+                                             w_ad, w_ts, w_pc, nullptr, st, &cfg);
         for (int i = 0; i < 3 && e == EZO_OK; ++i)
-            e = launch_project_bisect(c, r, ov, gv, edges, E, w_s, stride, w_ci, w_nc_light, cand_cap, p->n_b, w_cs,
-                                      w_ad, w_ts, w_pc, nullptr, nullptr, st, &cfg);
+            e = launch_project_bisect(c, r, ov, gv, edges, E, w_s, stride, w_ci, cl_light, cand_cap, p->n_b, w_cs,
+                                      w_ad, w_ts, w_pc, nullptr, st, &cfg);
         return e;
     };
     c->bisect_key = kb;
@@ -652,8 +675,10 @@ ezo_status ezo_ctx_create(int32_t device, ezo_ctx** out) {
     }
     if (c->arch.empty()) c->arch = "unknown";
     int lds = 0;
-    if (hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, device) == hipSuccess && lds > 0)
+    if (hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, device) == hipSuccess && lds > 0) {
         c->lds_cap = std::min<size_t>((size_t)lds, 65536);
+        c->lds_max = (size_t)lds;
+    }
     // this device's copy of the no-allocation entry point's scratch (device
     // current); nullptr makes that entry point report an error
     c->scratch = scratch_address();
@@ -781,8 +806,8 @@ ezo_status ezo_robot_create(ezo_ctx* c, const ezo_robot_desc* d, ezo_robot** out
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return d->sphere_link[a] < d->sphere_link[b]; });
     std::vector<int> orig_to_sorted(S);
     for (int s = 0; s < S; ++s) orig_to_sorted[order[s]] = s;
-    std::vector<float4> dh(dof), sph(std::max(S, 1));
-    std::vector<int> link_begin(dof + 1, 0), s2o(std::max(S, 1));
+    std::vector<float4> dh(kMaxDof, make_float4(0.f, 0.f, 0.f, 0.f)), sph(std::max(S, 1));
+    std::vector<int> link_begin(dof + 1, 0), s2o(std::max(S, 1)), sph_link(std::max(S, 1), 0);
     std::vector<int2> pairs(std::max(P, 1));
     std::vector<float> lim(2 * dof);
     for (int j = 0; j < dof; ++j) {
@@ -796,6 +821,7 @@ ezo_status ezo_robot_create(ezo_ctx* c, const ezo_robot_desc* d, ezo_robot** out
         sph[s] = make_float4((float)d->sphere_xyz[3 * o], (float)d->sphere_xyz[3 * o + 1], (float)d->sphere_xyz[3 * o + 2],
                              (float)d->sphere_r[o]);
         s2o[s] = o;
+        sph_link[s] = d->sphere_link[o];
         link_begin[d->sphere_link[o] + 1]++;
     }
     for (int j = 0; j < dof; ++j) link_begin[j + 1] += link_begin[j];
@@ -816,7 +842,8 @@ ezo_status ezo_robot_create(ezo_ctx* c, const ezo_robot_desc* d, ezo_robot** out
     for (int p = 0; p < P; ++p) {
         const int a = orig_to_sorted[d->self_pairs[2 * p]], bb = orig_to_sorted[d->self_pairs[2 * p + 1]];
         const int pa = part_of(a), pb = part_of(bb);
-        keyed[p] = {{std::min(pa, pb), std::max(pa, pb)}, make_int2(a, bb)};
+        // the lower part's sphere first (the sweep places each side in its part's link frame)
+        keyed[p] = {{std::min(pa, pb), std::max(pa, pb)}, pa <= pb ? make_int2(a, bb) : make_int2(bb, a)};
     }
     std::stable_sort(keyed.begin(), keyed.end(),
                      [](const auto& x, const auto& y) { return x.first < y.first; });
@@ -851,7 +878,11 @@ ezo_status ezo_robot_create(ezo_ctx* c, const ezo_robot_desc* d, ezo_robot** out
         // small relative + absolute pad covers FP32 rounding of the transformed centres
         lbound[j] = make_float4((float)cc[0], (float)cc[1], (float)cc[2], (float)(R * (1.0 + 1e-5) + 1e-5));
     }
-    for (int s2 = 0; s2 < S; ++s2) r_max = std::max(r_max, sph[s2].w);
+    float r_min = S > 0 ? sph[0].w : -kHuge;
+    for (int s2 = 0; s2 < S; ++s2) {
+        r_max = std::max(r_max, sph[s2].w);
+        r_min = std::min(r_min, sph[s2].w);
+    }
     // boxes sorted by link (stable); four float4 each: (centre, h_x), (rotation
     // row 0, h_y), (row 1, h_z), (row 2, bounding radius |h| padded for FP32)
     const int B = d->n_boxes, Q = d->n_box_pairs;
@@ -860,11 +891,12 @@ ezo_status ezo_robot_create(ezo_ctx* c, const ezo_robot_desc* d, ezo_robot** out
     std::stable_sort(border.begin(), border.end(), [&](int x, int y) { return d->box_link[x] < d->box_link[y]; });
     std::vector<int> box_o2s(std::max(B, 1));
     std::vector<float4> boxv(4 * (size_t)std::max(B, 1), make_float4(0.f, 0.f, 0.f, 0.f));
-    std::vector<int> box_begin(dof + 1, 0);
+    std::vector<int> box_begin(dof + 1, 0), box_link(std::max(B, 1), 0);
     std::vector<int2> bpairs(std::max(Q, 1), make_int2(0, 0));
     for (int k = 0; k < B; ++k) {
         const int o = border[k];
         box_o2s[o] = k;
+        box_link[k] = d->box_link[o];
         const double* ps = d->box_pose + 12 * (size_t)o;
         const double* h = d->box_half + 3 * (size_t)o;
         const double rad = std::sqrt(h[0] * h[0] + h[1] * h[1] + h[2] * h[2]);
@@ -876,9 +908,9 @@ ezo_status ezo_robot_create(ezo_ctx* c, const ezo_robot_desc* d, ezo_robot** out
     }
     for (int j = 0; j < dof; ++j) box_begin[j + 1] += box_begin[j];
     for (int p = 0; p < Q; ++p) bpairs[p] = make_int2(box_o2s[d->box_pairs[2 * p]], box_o2s[d->box_pairs[2 * p + 1]]);
-    // one allocation: [dh][sph][pairs][lbound][blocks][link_begin][s2o][limits][boxes][box_begin][box pairs]
+    // one allocation: [dh][sph][pairs][lbound][blocks][link_begin][s2o][limits][boxes][box_begin][box pairs][box links][tables for LDS]
     size_t off_dh = 0;
-    size_t off_sph = off_dh + sizeof(float4) * dof;
+    size_t off_sph = off_dh + sizeof(float4) * kMaxDof;
     size_t off_pairs = off_sph + sizeof(float4) * sph.size();
     size_t off_lbd = off_pairs + sizeof(int2) * pairs.size();
     size_t off_blk = off_lbd + sizeof(float4) * lbound.size();
@@ -888,9 +920,11 @@ ezo_status ezo_robot_create(ezo_ctx* c, const ezo_robot_desc* d, ezo_robot** out
     size_t off_box = (off_lim + sizeof(float) * lim.size() + 15) & ~(size_t)15;
     size_t off_bb = off_box + sizeof(float4) * boxv.size();
     size_t off_bp = off_bb + sizeof(int) * box_begin.size();
-    size_t total = off_bp + sizeof(int2) * bpairs.size();
+    size_t off_bl = off_bp + sizeof(int2) * bpairs.size();
+    size_t off_img = (off_bl + sizeof(int) * box_link.size() + 15) & ~(size_t)15;
+    size_t total = off_img + robot_stage_bytes(S, NB, P, true);
     std::vector<char> host(total);
-    memcpy(host.data() + off_dh, dh.data(), sizeof(float4) * dof);
+    memcpy(host.data() + off_dh, dh.data(), sizeof(float4) * dh.size());
     memcpy(host.data() + off_sph, sph.data(), sizeof(float4) * sph.size());
     memcpy(host.data() + off_pairs, pairs.data(), sizeof(int2) * pairs.size());
     memcpy(host.data() + off_lbd, lbound.data(), sizeof(float4) * lbound.size());
@@ -901,6 +935,15 @@ ezo_status ezo_robot_create(ezo_ctx* c, const ezo_robot_desc* d, ezo_robot** out
     memcpy(host.data() + off_box, boxv.data(), sizeof(float4) * boxv.size());
     memcpy(host.data() + off_bb, box_begin.data(), sizeof(int) * box_begin.size());
     memcpy(host.data() + off_bp, bpairs.data(), sizeof(int2) * bpairs.size());
+    memcpy(host.data() + off_bl, box_link.data(), sizeof(int) * box_link.size());
+    {
+        char* img = host.data() + off_img;
+        memcpy(img, lbound.data(), sizeof(float4) * lbound.size());
+        memcpy(img + sizeof(float4) * kMaxParts, blocks.data(), sizeof(int4) * NB);
+        memcpy(img + robot_image_off_sph(NB), sph.data(), sizeof(float4) * S);
+        memcpy(img + robot_image_off_link(S, NB), sph_link.data(), sizeof(int) * S);
+        memcpy(img + robot_image_off_pairs(S, NB), pairs.data(), sizeof(int2) * robot_staged_pairs(P));
+    }
     HIP_TRY(c, hipSetDevice(c->device));
     void* buf = nullptr;
     if (hipMalloc(&buf, total) != hipSuccess) return ezo_fail(c, EZO_E_NOMEM, "robot allocation failed");
@@ -921,6 +964,7 @@ ezo_status ezo_robot_create(ezo_ctx* c, const ezo_robot_desc* d, ezo_robot** out
     r->buf = buf;
     char* b = reinterpret_cast<char*>(buf);
     r->r_max = r_max;
+    r->r_min = r_min;
     r->view.dof = dof;
     r->view.prismatic = prismatic;
     r->view.n_spheres = S;
@@ -937,6 +981,8 @@ ezo_status ezo_robot_create(ezo_ctx* c, const ezo_robot_desc* d, ezo_robot** out
     r->view.box = reinterpret_cast<const float4*>(b + off_box);
     r->view.box_begin = reinterpret_cast<const int*>(b + off_bb);
     r->view.box_pairs = reinterpret_cast<const int2*>(b + off_bp);
+    r->view.box_link = reinterpret_cast<const int*>(b + off_bl);
+    r->view.image = reinterpret_cast<const float4*>(b + off_img);
     r->sorted_to_orig = reinterpret_cast<const int*>(b + off_s2o);
     r->q_lo = reinterpret_cast<const float*>(b + off_lim);
     r->q_hi = r->q_lo + dof;
@@ -1008,7 +1054,7 @@ ezo_status ezo_check_collisions_noalloc(ezo_ctx* c, const ezo_robot* r, const fl
     GridView gv;
     unsigned char* p = c->scratch;
     ezo_status s = prep_obstacles_into(c, r, obs, n_obs, st, p + kScrRec, p + kScrCentre, p + kScrGeom,
-                                       p + kScrCount, p + kScrList, &ov, &gv);
+                                       p + kScrCount, p + kScrState, p + kScrList, &ov, &gv);
     if (s) return s;
     // launch shapes: the tuning cache or the size heuristic (never a timing
     // search, which would write the outputs repeatedly)
@@ -1088,7 +1134,7 @@ ezo_status ezo_test_and_select(ezo_ctx* c, const uint8_t* flags, int32_t n_edges
     HIP_TRY(c, hipSetDevice(c->device));
     IterArgs it{nullptr, 0, (int)M, (int)std::min<int64_t>(T, 0x7fffffff), n_samples};
     hipLaunchKernelGGL(k_test_select, dim3(n_edges), dim3(1024), 0, as_stream(stream), flags, sample_stride, n_p, 0,
-                       cand_idx, cand_capacity, n_cands, accept, test_count, nullptr, nullptr, it);
+                       cand_idx, cand_capacity, n_cands, accept, test_count, nullptr, nullptr, it, CandList{});
     HIP_TRY(c, hipGetLastError());
     return EZO_OK;
 }
@@ -1109,11 +1155,14 @@ ezo_status ezo_project_bisect(ezo_ctx* c, const ezo_robot* r, const float* obs, 
     GridView gv;
     ezo_status s = prep_obstacles(c, r, obs, n_obs, st, &ov, &gv);
     if (s) return s;
-    if ((s = tune_bisect_inplace(c, r, ov, gv, edges, n_edges, samples, sample_stride, cand_idx, n_cands,
-                                 cand_capacity, n_b, c_star, a_dir, t_star, proj_collides, st)))
+    CandList cl;
+    if ((s = list_buffers(c, (int64_t)n_edges * cand_capacity, &cl)) ||
+        (s = list_candidates(c, n_cands, n_edges, cand_capacity, cl, st)) ||
+        (s = tune_bisect_inplace(c, r, ov, gv, edges, n_edges, samples, sample_stride, cand_idx, cl, cand_capacity,
+                                 n_b, c_star, a_dir, t_star, proj_collides, st)))
         return s;
-    return launch_project_bisect(c, r, ov, gv, edges, n_edges, samples, sample_stride, cand_idx, n_cands, cand_capacity,
-                                 n_b, c_star, a_dir, t_star, proj_collides, nullptr, nullptr, st);
+    return launch_project_bisect(c, r, ov, gv, edges, n_edges, samples, sample_stride, cand_idx, cl, cand_capacity,
+                                 n_b, c_star, a_dir, t_star, proj_collides, nullptr, st);
 }
 
 ezo_status ezo_place_hyperplanes(ezo_ctx* c, int32_t dof, const float* edges, int32_t n_edges, const float* c_star,
@@ -1246,6 +1295,8 @@ static ezo_status inflate_core(ezo_ctx* c, const ezo_robot* r, const float* obs,
         (s = ezo_ws_get(c, W_TABLE, sizeof(int4) * table.size(), &w_tb)) || (s = ezo_ws_get(c, W_KDEV, sizeof(int4), &w_k)) ||
         (s = ezo_ws_get(c, W_ACTIVE, sizeof(int), &w_ac)))
         return s;
+    CandList cl;
+    if ((s = list_buffers(c, (int64_t)E * cand_cap, &cl))) return s;
     if (p->surrogate) {
         if (p->surrogate->D != dof) return ezo_fail(c, EZO_E_INVALID, "screen dof %d != robot dof %d", p->surrogate->D, dof);
         if ((s = ezo_ws_get(c, W_PRED, sizeof(float) * (size_t)E * stride, &w_pred))) return s;
@@ -1270,12 +1321,12 @@ static ezo_status inflate_core(ezo_ctx* c, const ezo_robot* r, const float* obs,
     // count) is launched with the obstacle preparation; a tuning run in
     // between overwrites it, and then it is launched again below
     const EdgeInit ei{dof, r->q_lo, r->q_hi, edges, E, A, b, n_faces, cap, edge_status, (EdgeStatsDev*)w_st,
-                      (uint8_t*)w_pa, (int4*)w_k, (const int4*)w_tb, (int*)w_ac, skip};
+                      (uint8_t*)w_pa, (int4*)w_k, (const int4*)w_tb, (int*)w_ac, cl.n, skip};
     if ((s = prep_obstacles(c, r, obs, n_obs, st, &ov, &gv, &ei))) return s;
     bool tuned = false;
     if ((s = tune_inflation(c, r, ov, gv, edges, E, p, S_cap, stride, A, b, n_faces, (float*)w_s, (uint8_t*)w_f,
                             (int*)w_ci, (int*)w_nc, (float*)w_cs, (float*)w_ad, (float*)w_ts, (uint8_t*)w_pc,
-                            (const int*)w_ac, st, &tuned)))
+                            (const int*)w_ac, cl, st, &tuned)))
         return s;
     if (c->bisect_finalists.size() > 1 && !c->shape_trial) {
         tuned = true;
@@ -1395,20 +1446,19 @@ static ezo_status inflate_core(ezo_ctx* c, const ezo_robot* r, const float* obs,
         }
         mark(EZO_PHASE_TEST);
         EZO_KLAUNCH(c, k_test_select, dim3(E), dim3(1024), 0, st, (const uint8_t*)w_f, stride, p->n_p, p->n_b,
-                           (int*)w_ci, cand_cap, (int*)w_nc, nullptr, nullptr, edge_status, (EdgeStatsDev*)w_st, it);
+                           (int*)w_ci, cand_cap, (int*)w_nc, nullptr, nullptr, edge_status, (EdgeStatsDev*)w_st, it, cl);
         mark(EZO_PHASE_BISECT);
-        if ((ls = launch_project_bisect(c, r, ov, gvb, edges, E, (const float*)w_s, stride, (const int*)w_ci,
-                                        (const int*)w_nc, cand_cap, p->n_b, (float*)w_cs, (float*)w_ad,
-                                        (float*)w_ts, (uint8_t*)w_pc, (uint8_t*)w_pa, edge_status, st, nullptr, -1,
-                                        screen_mid ? &screen_view : nullptr, (EdgeStatsDev*)w_st))) {
+        if ((ls = launch_project_bisect(c, r, ov, gvb, edges, E, (const float*)w_s, stride, (const int*)w_ci, cl,
+                                        cand_cap, p->n_b, (float*)w_cs, (float*)w_ad, (float*)w_ts, (uint8_t*)w_pc,
+                                        (uint8_t*)w_pa, st, nullptr, -1, screen_mid ? &screen_view : nullptr, (EdgeStatsDev*)w_st))) {
             mark(EZO_NUM_PHASES);
             return ls;
         }
         mark(EZO_PHASE_PLACE);
         // one edge: the placement's single workgroup ends the iteration itself
         // (no k_advance launch; its phase then times nothing)
-        const IterEnd ie = E == 1 ? IterEnd{(int4*)w_k, (const int4*)w_tb, p->max_iters, (int*)w_ac, c->pinned_dev,
-                                            host_stats}
+        const IterEnd ie = E == 1 ? IterEnd{(int4*)w_k, (const int4*)w_tb, p->max_iters, (int*)w_ac, cl.n,
+                                            c->pinned_dev, host_stats}
                                   : IterEnd{};
         EZO_KLAUNCH(c, k_place, dim3(E), dim3(1024), (size_t)std::max(cand_cap, 16), st, dof, edges,
                            (const float*)w_cs, (const float*)w_ad, (const float*)w_ts, (const int*)w_nc, cand_cap,
@@ -1417,7 +1467,7 @@ static ezo_status inflate_core(ezo_ctx* c, const ezo_robot* r, const float* obs,
         mark(EZO_PHASE_ADVANCE);
         if (E != 1)
             EZO_KLAUNCH(c, k_advance, dim3(1), dim3(256), 0, st, (int4*)w_k, (const int4*)w_tb, p->max_iters,
-                        edge_status, E, (int*)w_ac, c->pinned_dev, (const EdgeStatsDev*)w_st, host_stats);
+                        edge_status, E, (int*)w_ac, cl.n, c->pinned_dev, (const EdgeStatsDev*)w_st, host_stats);
         mark(EZO_NUM_PHASES);
         if (ls == EZO_OK) {
             hipError_t le = hipGetLastError();
@@ -1480,9 +1530,9 @@ static ezo_status inflate_core(ezo_ctx* c, const ezo_robot* r, const float* obs,
         }
         for (const DevBuf& wb : c->ws) push(wb.p);
         const TileCfg gc = resolve_cfg(c, tune_key(c, r, TUNE_CHECK_FLAGS, ov.n, (int64_t)S_cap * E),
-                                       heuristic_check(c, r, ov.n, (int64_t)S_cap * E, false), r->slots, r->P, r->view.n_blocks, ov.n, false);
+                                       heuristic_check(c, r, ov.n, (int64_t)S_cap * E, false), r, ov.n, false);
         const TileCfg gb = resolve_cfg(c, tune_key(c, r, TUNE_BISECT, ov.n, (int64_t)cand_cap * E),
-                                       heuristic_bisect(c, r, ov.n, (int64_t)cand_cap * E), r->slots, r->P, r->view.n_blocks, ov.n, false, true);
+                                       heuristic_bisect(c, r, ov.n, (int64_t)cand_cap * E), r, ov.n, false, true);
         for (const TileCfg& g : {gc, gb}) {
             key.push_back((uintptr_t)g.T);
             key.push_back((uintptr_t)g.W);
@@ -1812,7 +1862,7 @@ ezo_status ezo_check_path(ezo_ctx* c, const ezo_robot* r, const float* obs, int3
     int* cnt = (int*)wcnt;
     hipLaunchKernelGGL(k_test_select, dim3(1), dim3(1024), 0, st, (const uint8_t*)wflags, N,
                        std::max(point_capacity, 1), 0, (int*)widx, std::max(point_capacity, 1), cnt, nullptr, cnt + 1,
-                       nullptr, nullptr, sel);
+                       nullptr, nullptr, sel, CandList{});
     if (point_capacity > 0)
         hipLaunchKernelGGL(k_gather_rows, dim3((point_capacity + 255) / 256), dim3(256), 0, st, dof,
                            (const float*)wpts, (const int*)widx, (const int*)cnt, point_capacity, points_out);
@@ -1854,14 +1904,16 @@ ezo_status ezo_update_polytopes(ezo_ctx* c, const ezo_robot* r, const float* obs
         (s = ezo_ws_get(c, W_RUN, sizeof(int) * (size_t)E, &w_run)) ||
         (s = ezo_ws_get(c, W_NPLACED, sizeof(int) * (size_t)E, &w_np)))
         return s;
+    CandList cl;
+    if ((s = list_buffers(c, (int64_t)E * N, &cl))) return s;
     // found collisions inside each editable set, in point order, become the candidates
     hipLaunchKernelGGL(k_rows_to_coords, dim3((N + 255) / 256), dim3(256), 0, st, dof, points, (int64_t)N,
-                       (float*)w_s);
+                       (float*)w_s, cl.n);
     hipLaunchKernelGGL(k_points_in_sets, dim3((N + 255) / 256, E), dim3(256), 0, st, dof, A, b, n_faces,
                        face_capacity, edge_status, (const float*)w_s, (int64_t)N, (uint8_t*)w_f);
     IterArgs sel{nullptr, 0, 0, -1, N};
     hipLaunchKernelGGL(k_test_select, dim3(E), dim3(1024), 0, st, (const uint8_t*)w_f, (int64_t)N, N, n_b,
-                       (int*)w_ci, N, (int*)w_nc, nullptr, nullptr, nullptr, nullptr, sel);
+                       (int*)w_ci, N, (int*)w_nc, nullptr, nullptr, nullptr, nullptr, sel, cl);
     hipLaunchKernelGGL(k_recover_begin, dim3((E + 255) / 256), dim3(256), 0, st, E, (const int*)w_nc, (int*)w_run,
                        (int*)w_np);
     HIP_TRY(c, hipMemsetAsync(w_pa, 0, (size_t)E, st));
@@ -1870,9 +1922,8 @@ ezo_status ezo_update_polytopes(ezo_ctx* c, const ezo_robot* r, const float* obs
     GridView gv;
     if ((s = prep_obstacles(c, r, obs, n_obs, st, &ov, &gv))) return s;
     // the last three steps of Alg. 1 on those candidates
-    if ((s = launch_project_bisect(c, r, ov, gv, edges, E, (const float*)w_s, N, (const int*)w_ci, (const int*)w_nc,
-                                   N, n_b, (float*)w_cs, (float*)w_ad, (float*)w_ts, (uint8_t*)w_pc,
-                                   (uint8_t*)w_pa, (const int*)w_run, st, nullptr, 0)))
+    if ((s = launch_project_bisect(c, r, ov, gv, edges, E, (const float*)w_s, N, (const int*)w_ci, cl, N, n_b, (float*)w_cs,
+                                   (float*)w_ad, (float*)w_ts, (uint8_t*)w_pc, (uint8_t*)w_pa, st, nullptr, 0)))
         return s;
     hipLaunchKernelGGL(k_place, dim3(E), dim3(1024), (size_t)std::max(N, 16), st, dof, edges, (const float*)w_cs,
                        (const float*)w_ad, (const float*)w_ts, (const int*)w_nc, N, n_f, (float)step_back_max,

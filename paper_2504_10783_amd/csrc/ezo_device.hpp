@@ -2,21 +2,13 @@
 // gfx950: Philox4x32-10, DH forward kinematics into LDS, and the workgroup
 // "tile check" that decides collision for a tile of configurations.
 //
-// Tile check layout (one workgroup = W waves of 64 lanes):
-//   * a tile holds T configurations (T in {8,16,32,64}); lane l of every
-//     wave works on configuration (l % T) and on the sphere subset
-//     (l / T) of that configuration, so one wave covers all T
-//     configurations with 64/T lanes each;
-//   * the W waves split the obstacle list into W contiguous slices.  The
-//     obstacle index is wave-uniform, so obstacle records are read with
-//     scalar loads and enter the pair arithmetic as SGPR operands;
-//   * sphere centres of the tile live in LDS as [sphere][config] float4
-//     (x, y, z, r), written once by the FK phase and read by every wave.
-// Collision test per robot/obstacle pair, in a frame whose origin is the
-// centre of the obstacle cloud (keeps |c|^2 and |o|^2 small):
-//   v = (|c|^2 - r_c^2) + (|o|^2 - r_o^2) - 2 c.o - 2 r_c r_o = |c-o|^2 - (r_c+r_o)^2
-// so a pair collides iff v < 0 (5 VALU ops + a running min).  The
-// signed-distance mode evaluates |c - o| - r_o directly (difference form).
+// Two tiles: flags mode (FlagTile below) holds the link frames of a tile's
+// configurations and skips every pair it can prove separated; signed-distance
+// mode (TileSmem) holds every sphere centre as [sphere][config] float4, lane l
+// of every wave working on configuration l % T, and the W waves split the
+// obstacles into contiguous slices, whose records are wave-uniform and come
+// through scalar loads.  Centres are kept in a frame whose origin is the
+// centre of the obstacle cloud.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -64,10 +56,11 @@ struct RobotView {
     int n_spheres;
     int n_self;
     int n_blocks;
-    const float4* dh;          // [dof] (a, d, cos alpha, sin alpha)
+    const float4* dh;          // [kMaxDof] (a, d, cos alpha, sin alpha), zero past dof
     const int* link_begin;     // [dof + 1] spheres of link i: [link_begin[i], link_begin[i+1])
     const float4* sph;         // [S] local (x, y, z), r -- sorted by link
-    const int2* pairs;         // [P] self pairs, indices into the sorted order, grouped by block
+    const int2* pairs;         // [P] self pairs, indices into the sorted order, grouped by block, the sphere
+                               // of the block's part a first
     const float4* lbound;      // [kPartsPerLink dof] bounding sphere of each part of a link (part
                                // p of link l = index kPartsPerLink l + p, a consecutive run of the
                                // link's spheres): centre in the link frame, radius
@@ -80,7 +73,8 @@ struct RobotView {
     const float4* box;         // [B][4]
     const int* box_begin;      // [dof + 1] boxes of link i: [box_begin[i], box_begin[i+1])
     const int2* box_pairs;     // [Q] box self pairs (sorted indices)
-    int staged;                // set by stage_robot: bit 0 blocks, bit 1 pairs in LDS (else 0)
+    const int* box_link;       // [B] link of each box (sorted order)
+    const float4* image;       // the tables that a flags check copies into LDS (robot_stage_bytes)
 };
 
 // LDS rows of a tile's pose array: one per sphere, four per box.
@@ -93,51 +87,26 @@ constexpr int kPartsPerLink = 2;
 constexpr int kItemLanes = 16;
 constexpr int kMaxParts = kPartsPerLink * kMaxDof;
 constexpr int kMaxPartPairs = kMaxParts * (kMaxParts + 1) / 2;   // part pairs, same-part pairs included
-static_assert(kMaxPartPairs < 1024, "work items hold (part pair << 6) | configuration in 16 bits");
 
-// Robot tables that a workgroup running many dependent tile checks (the
-// bisection) copies into LDS once: DH rows, part bounding spheres, link
-// sphere ranges, spheres, self-pair blocks and, up to kStagePairs of them,
-// the self pairs; their reads in FK and in the self-pair sweep then cost an
-// LDS access instead of a cache access.  At most this many bytes (slots >=
-// spheres, n_self = self pairs, n_blocks = self-pair blocks).
+// Robot tables of a flags check, copied into LDS by each workgroup from one
+// block of memory with the same layout (RobotView::image): part bounding
+// spheres, self-pair blocks, spheres, the spheres' links; then the self pairs,
+// which a workgroup with many dependent checks (the bisection) copies too, up
+// to kStagePairs of them.
 constexpr int kStagePairs = 2048;
 
 __host__ __device__ inline int robot_staged_pairs(int n_self) { return n_self <= kStagePairs ? n_self : 0; }
 
-__host__ __device__ inline size_t robot_stage_bytes(int slots, int n_self, int n_blocks) {
-    return 16 * (size_t)(kMaxDof + kMaxParts + (slots > 0 ? slots : 1) + (n_blocks > 0 ? n_blocks : 1)) +
-           16 * ((kMaxDof + 4) / 4) + 16 * (((size_t)robot_staged_pairs(n_self) + 1) / 2);
+__host__ __device__ inline size_t robot_image_off_sph(int n_blocks) { return 16 * (size_t)(kMaxParts + n_blocks); }
+__host__ __device__ inline size_t robot_image_off_link(int S, int n_blocks) {
+    return robot_image_off_sph(n_blocks) + 16 * (size_t)S;
 }
-
-// Copies the tables into LDS at `base` (16-byte aligned, robot_stage_bytes
-// long) and returns a view whose table pointers address the copies (box
-// tables, and self pairs beyond kStagePairs, stay in global memory).  The
-// caller places a barrier before the first use.
-__device__ inline RobotView stage_robot(const RobotView& rb, char* base) {
-    float4* dh = reinterpret_cast<float4*>(base);
-    float4* lb = dh + kMaxDof;
-    float4* sph = lb + kMaxParts;
-    int* lbeg = reinterpret_cast<int*>(sph + (rb.n_spheres > 0 ? rb.n_spheres : 1));
-    int4* blk = reinterpret_cast<int4*>(lbeg + 4 * ((kMaxDof + 4) / 4));
-    int2* prs = reinterpret_cast<int2*>(blk + (rb.n_blocks > 0 ? rb.n_blocks : 1));
-    const int np = robot_staged_pairs(rb.n_self);
-    const int tid = threadIdx.x, nt = blockDim.x;
-    for (int i = tid; i < rb.dof; i += nt) dh[i] = rb.dh[i];
-    for (int i = tid; i < kPartsPerLink * rb.dof; i += nt) lb[i] = rb.lbound[i];
-    for (int i = tid; i <= rb.dof; i += nt) lbeg[i] = rb.link_begin[i];
-    for (int i = tid; i < rb.n_blocks; i += nt) blk[i] = rb.blocks[i];
-    for (int i = tid; i < rb.n_spheres; i += nt) sph[i] = rb.sph[i];
-    for (int i = tid; i < np; i += nt) prs[i] = rb.pairs[i];
-    RobotView v = rb;
-    v.dh = dh;
-    v.lbound = lb;
-    v.blocks = blk;
-    v.sph = sph;
-    v.link_begin = lbeg;
-    if (np > 0) v.pairs = prs;
-    v.staged = 1 | (np > 0 ? 2 : 0);
-    return v;
+__host__ __device__ inline size_t robot_image_off_pairs(int S, int n_blocks) {
+    return robot_image_off_link(S, n_blocks) + 16 * (((size_t)S + 3) / 4);
+}
+// Bytes of the copy (a multiple of 16), with or without the pairs.
+__host__ __device__ inline size_t robot_stage_bytes(int S, int n_blocks, int n_self, bool pairs) {
+    return robot_image_off_pairs(S, n_blocks) + (pairs ? 16 * (((size_t)robot_staged_pairs(n_self) + 1) / 2) : 0);
 }
 
 // Uniform grid over the obstacle cloud (shifted frame).  Cell k lists every
@@ -146,18 +115,32 @@ __device__ inline RobotView stage_robot(const RobotView& rb, char* base) {
 // sphere centre c in the box has |c - o| >= that distance).  A sphere centre
 // outside the grid box is farther than r_sphere_max + r_o_max from every
 // obstacle.  count[k] > cap marks an overflowing cell (scan all).
+// state holds two bits per cell, what a sweep asks first: bit 0, the list is not
+// empty; bit 1, some obstacle collides with every robot sphere centred anywhere
+// in the cell (the farthest point of the cell's box is nearer to o than r_o +
+// r_sphere_min - slack), so that no list is needed.
+__host__ __device__ inline int state_words(int G) { return G * G * G / 16; }
+
 struct GridGeom {
     float ox, oy, oz;          // origin (min corner)
     float hx, hy, hz;          // cell size
     float ihx, ihy, ihz;       // 1 / cell size
     float reach;               // r_sphere_max + slack
+    float hit_reach;           // r_sphere_min - slack (hugely negative for a robot without spheres)
 };
+
+// Grid geometry through scalar loads (wave-uniform, written by earlier kernels).
+__device__ __forceinline__ GridGeom load_geom(const GridGeom* p) {
+    const __attribute__((address_space(4))) float* s = (const __attribute__((address_space(4))) float*)p;
+    return GridGeom{s[0], s[1], s[2], s[3], s[4], s[5], s[6], s[7], s[8], s[9], s[10]};
+}
 
 struct GridView {
     int G;                     // cells per axis
     int cap;                   // list capacity per cell
     const GridGeom* geom;
     const int* count;          // [G^3]
+    const unsigned* state;     // [G^3 / 16] two bits per cell
     const unsigned short* list;  // [G^3][cap] obstacle indices
     unsigned long long* tests;   // optional [kTestSlots] counters of sphere-sphere tests performed
 };
@@ -217,18 +200,21 @@ __device__ __forceinline__ uint32_t word_of(const U4& v, int i) {
 //        [0,   sa,     ca,    d   ]]
 // R is row-major 3x3, p the translation.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void dh_compose(float R[9], float p[3], float ct, float st, float4 dh) {
+// dh_compose_row: one row (r0, r1, r2 | p).
+__device__ __forceinline__ void dh_compose_row(float& r0, float& r1, float& r2, float& p, float ct, float st,
+                                               float4 dh) {
     const float a = dh.x, d = dh.y, ca = dh.z, sa = dh.w;
+    const float u = fmaf(r0, ct, r1 * st);        // new column 0
+    const float w = fmaf(r1, ct, -r0 * st);       // R * (-st, ct, 0)
+    p = fmaf(a, u, fmaf(d, r2, p));
+    r0 = u;
+    r1 = fmaf(w, ca, r2 * sa);
+    r2 = fmaf(r2, ca, -w * sa);
+}
+
+__device__ __forceinline__ void dh_compose(float R[9], float p[3], float ct, float st, float4 dh) {
 #pragma unroll
-    for (int r = 0; r < 3; ++r) {
-        const float r0 = R[3 * r + 0], r1 = R[3 * r + 1], r2 = R[3 * r + 2];
-        const float u = fmaf(r0, ct, r1 * st);        // new column 0
-        const float w = fmaf(r1, ct, -r0 * st);       // R * (-st, ct, 0)
-        R[3 * r + 0] = u;
-        R[3 * r + 1] = fmaf(w, ca, r2 * sa);
-        R[3 * r + 2] = fmaf(r2, ca, -w * sa);
-        p[r] = fmaf(a, u, fmaf(d, r2, p[r]));
-    }
+    for (int r = 0; r < 3; ++r) dh_compose_row(R[3 * r], R[3 * r + 1], R[3 * r + 2], p[r], ct, st, dh);
 }
 
 // ---------------------------------------------------------------------------
@@ -241,11 +227,7 @@ struct TileSmem {
                        // box's world pose as four rows (packed like RobotView::box)
     float4* lb;        // [kMaxParts][T] part bounding spheres (shifted frame)
     int* hit;          // [T] collision flag (flags mode) / validity
-    int* scr;          // [T] 1 = the learned screen cleared this configuration's self pairs
     float* red;        // [2][W][T] partial minima (signed-distance mode)
-    unsigned short* wl;  // [T][kMaxPartPairs] work list: (part pair << 6) | configuration, bounds overlapping
-    int* wl_n;         // [1] work list length
-    float4* obs;       // [lds_n] staged obstacle records (x, y, z, r), or NULL
 };
 
 __host__ __device__ inline size_t tile_smem_bytes(int T, int S, int W) {
@@ -254,26 +236,20 @@ __host__ __device__ inline size_t tile_smem_bytes(int T, int S, int W) {
     b += sizeof(float2) * (size_t)kMaxDof * T;
     b += sizeof(float4) * (size_t)(S > 0 ? S : 1) * T;
     b += sizeof(float4) * (size_t)kMaxParts * T;
-    b += sizeof(int) * 2 * (size_t)T;
+    b += sizeof(int) * (size_t)T;
     b += sizeof(float) * 2 * (size_t)W * T;
-    b += sizeof(unsigned short) * (size_t)T * kMaxPartPairs + sizeof(int);
     return (b + 15) & ~(size_t)15;
 }
 
-// Obstacle staging follows the tile region: tile_smem_bytes(T, S, W) + 16 lds_n.
-__device__ inline TileSmem carve_tile(char* base, int T, int S, int W, int lds_n = 0) {
+__device__ inline TileSmem carve_tile(char* base, int T, int S, int W) {
     TileSmem t;
-    t.obs = lds_n > 0 ? reinterpret_cast<float4*>(base + tile_smem_bytes(T, S, W)) : nullptr;
     char* p = base;
     t.cen = reinterpret_cast<float4*>(p);   p += sizeof(float4) * (size_t)(S > 0 ? S : 1) * T;
     t.lb = reinterpret_cast<float4*>(p);    p += sizeof(float4) * (size_t)kMaxParts * T;
     t.trig = reinterpret_cast<float2*>(p);  p += sizeof(float2) * (size_t)kMaxDof * T;
     t.q = reinterpret_cast<float*>(p);      p += sizeof(float) * (size_t)T * kMaxDof;
     t.red = reinterpret_cast<float*>(p);    p += sizeof(float) * 2 * (size_t)W * T;
-    t.hit = reinterpret_cast<int*>(p);      p += sizeof(int) * (size_t)T;
-    t.scr = reinterpret_cast<int*>(p);      p += sizeof(int) * (size_t)T;
-    t.wl = reinterpret_cast<unsigned short*>(p);  p += sizeof(unsigned short) * (size_t)T * kMaxPartPairs;
-    t.wl_n = reinterpret_cast<int*>(p);
+    t.hit = reinterpret_cast<int*>(p);
     return t;
 }
 
@@ -303,6 +279,28 @@ struct ItemWalk {
         }
     }
 };
+
+struct Frame { float4 r0, r1, r2; };     // rows (R | p) of a link's frame
+
+// A box's world pose, four rows at dst, dst + T, ...: centre and rotation
+// through the link's frame f.
+__device__ __forceinline__ void place_box(const Frame& f, float4 b0, float4 b1, float4 b2, float4 b3, float4* dst,
+                                          int T) {
+    const float R[9] = {f.r0.x, f.r0.y, f.r0.z, f.r1.x, f.r1.y, f.r1.z, f.r2.x, f.r2.y, f.r2.z};
+    const float L[9] = {b1.x, b1.y, b1.z, b2.x, b2.y, b2.z, b3.x, b3.y, b3.z};
+    float W[9];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            W[3 * i + j] = fmaf(R[3 * i], L[j], fmaf(R[3 * i + 1], L[3 + j], R[3 * i + 2] * L[6 + j]));
+    dst[0] = make_float4(fmaf(R[0], b0.x, fmaf(R[1], b0.y, fmaf(R[2], b0.z, f.r0.w))),
+                         fmaf(R[3], b0.x, fmaf(R[4], b0.y, fmaf(R[5], b0.z, f.r1.w))),
+                         fmaf(R[6], b0.x, fmaf(R[7], b0.y, fmaf(R[8], b0.z, f.r2.w))), b0.w);
+    dst[T] = make_float4(W[0], W[1], W[2], b1.w);
+    dst[2 * T] = make_float4(W[3], W[4], W[5], b2.w);
+    dst[3 * T] = make_float4(W[6], W[7], W[8], b3.w);
+}
 
 // FK phase: t.q[c][j] (c < n_valid) -> t.cen[s][c].  Ends with a barrier.
 // Only the n_valid >= 1 configurations of the tile are computed.
@@ -367,20 +365,9 @@ __device__ inline void tile_fk(const RobotView& rb, const ObsView& ob, const Til
             const int k1 = rb.box_begin[link + 1];
             for (int k = rb.box_begin[link] + part; k < k1; k += P) {
                 const float4 b0 = rb.box[4 * k], b1 = rb.box[4 * k + 1], b2 = rb.box[4 * k + 2], b3 = rb.box[4 * k + 3];
-                const float L[9] = {b1.x, b1.y, b1.z, b2.x, b2.y, b2.z, b3.x, b3.y, b3.z};
-                float4* dst = t.cen + (size_t)(S + 4 * k) * T + c;
-                float W[9];
-#pragma unroll
-                for (int i = 0; i < 3; ++i)
-#pragma unroll
-                    for (int j = 0; j < 3; ++j)
-                        W[3 * i + j] = fmaf(R[3 * i], L[j], fmaf(R[3 * i + 1], L[3 + j], R[3 * i + 2] * L[6 + j]));
-                dst[0] = make_float4(fmaf(R[0], b0.x, fmaf(R[1], b0.y, fmaf(R[2], b0.z, p[0]))),
-                                     fmaf(R[3], b0.x, fmaf(R[4], b0.y, fmaf(R[5], b0.z, p[1]))),
-                                     fmaf(R[6], b0.x, fmaf(R[7], b0.y, fmaf(R[8], b0.z, p[2]))), b0.w);
-                dst[T] = make_float4(W[0], W[1], W[2], b1.w);
-                dst[2 * T] = make_float4(W[3], W[4], W[5], b2.w);
-                dst[3 * T] = make_float4(W[6], W[7], W[8], b3.w);
+                place_box(Frame{make_float4(R[0], R[1], R[2], p[0]), make_float4(R[3], R[4], R[5], p[1]),
+                                make_float4(R[6], R[7], R[8], p[2])},
+                          b0, b1, b2, b3, t.cen + (size_t)(S + 4 * k) * T + c, T);
             }
         }
     }
@@ -515,14 +502,6 @@ __device__ inline float sat_value(const DBox& A, const DBox& B) {
     return best;
 }
 
-// Copy the obstacle records (x, y, z, r) into the workgroup's LDS copy.
-// Ends with a barrier.
-__device__ inline void stage_obstacles(const ObsView& ob, const TileSmem& t) {
-    if (t.obs)
-        for (int o = threadIdx.x; o < ob.lds_n; o += blockDim.x) t.obs[o] = ob.rec[o];
-    __syncthreads();
-}
-
 __device__ __forceinline__ int wave_id() {
     return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 }
@@ -630,45 +609,436 @@ __device__ inline void tile_pairs_sd(const RobotView& rb, const ObsView& ob, con
     __syncthreads();
 }
 
-// Flags-mode sweep with broad phase.  Self pairs: the bounding spheres of
-// the two links of every (configuration, link pair) are tested first; the
-// overlapping ones go to an LDS work list, and each wave then takes a work
-// item and tests its link pair's sphere pairs one per lane (coalesced pair
-// loads, no divergence).  Obstacles: a work item (configuration, sphere)
-// tests only the obstacles listed in the sphere's grid cell.  Every skipped
-// pair is provably separated, so the flag equals that of the all-pairs
-// test.  The pair test is |c - o|^2 < (r_c + r_o)^2 (difference form).
-// Needs *t.wl_n == 0 on entry.  Barrier at exit.
-// Returns the number of sphere-sphere tests this thread performed (bound
-// tests included).
+// ---------------------------------------------------------------------------
+// Flags mode: the tile of a collision check that only asks whether a
+// configuration collides.  Per configuration the LDS holds the link frames
+// (48 bytes a link), not the spheres: a sphere's centre is nine multiply-adds
+// from its link's frame, placed by the lane that tests it, and a
+// configuration takes 0.7 KB instead of the 1.9 KB that the 70 centres of a
+// 7-DOF arm made it, so that more than twice as many waves fit a CU.
+//
+// One check:
+//   1. eight lanes per configuration, lane j joint j: cosine and sine to LDS;
+//      three of them compose the frames, one row each (row r of [R | p]
+//      depends on row r of the previous link's only); all eight place the
+//      link parts' bounding spheres                                    | barrier
+//   2. obstacles: a lane per (configuration, link, sphere group) places its
+//      spheres and looks their grid cells up in the workgroup's copy of the
+//      cell states (8 KB of LDS for 32^3 cells): nothing near, certain hit, or
+//      a list.  Listed spheres go to the wave's own LDS list and are tested
+//      from there with full lanes.  Then self pairs: a lane per
+//      (configuration, part pair) tests the parts' bounding spheres;
+//      overlapping ones go to the wave's list, and kItemLanes lanes each test
+//      the sphere pairs of one.  (Boxes: placed, a barrier, their pairs) | barrier
+// Configurations found colliding drop out of everything that follows.  Every
+// pair not tested is provably separated (or its configuration already hit),
+// so the flag equals that of the all-pairs test; the pair test is
+// |c - o|^2 < (r_c + r_o)^2 on centres computed by the same FP32 operations
+// wherever they are placed.
+//
+// Bound by VALU issue when there are many configurations (the former tile, with
+// the centres in LDS and every sphere in the grid looking its list up, issued
+// 259 VALU instructions per configuration of the 7-DOF arm among 1024 spheres,
+// 87 % of what the chip issues), by latency when there are few.  Measured: 4 M
+// configurations 2.24 -> 1.55 ms; the check of an inflation's 10 000 samples
+// 10.2 -> 9.8 us, of 96 edges 33.3 -> 27.5 us a launch.
+// ---------------------------------------------------------------------------
+// Native vectors (HIP's vector classes cannot live in another address space).
+typedef lds_f4_t f4;
+typedef lds_i4_t i4;
+typedef float f2 __attribute__((ext_vector_type(2)));
+typedef int i2 __attribute__((ext_vector_type(2)));
+
+// A configuration's record in the tile, in 16-byte rows: the links' frames
+// (three rows (R | p) each, shifted frame), the parts' bounding spheres, each
+// joint's (cos, sin), each link's offset d (plus q for a prismatic joint), and
+// (collision flag, 1 = the learned screen cleared its self pairs).  The rows of
+// a record are at fixed offsets (no address arithmetic or registers for them),
+// and 47 rows, 188 words, put the records of a tile on distinct LDS banks.
+constexpr int kRecLb = 3 * kMaxDof, kRecTrig = kRecLb + kMaxParts, kRecD = kRecTrig + kMaxDof / 2,
+              kRecHit = kRecD + kMaxDof / 4, kRecRows = kRecHit + 1;
+static_assert(kRecRows % 2 == 1, "an odd number of 16-byte rows: distinct banks");
+
+struct FlagTile {
+    lds_ptr<f4> rec;        // [T][kRecRows]
+    lds_ptr<f4> box;        // [T][4 B] each box's world pose as four rows (packed like RobotView::box)
+    lds_ptr<unsigned> wl;   // [W][kWaveList] each wave's list
+    lds_ptr<unsigned> state;   // [state_words] the grid's cell states
+    lds_ptr<f4> obs;        // [lds_n] staged obstacle records (x, y, z, r)
+    // the robot's tables
+    lds_ptr<f4> lbound, sph;
+    lds_ptr<i4> blocks;
+    lds_ptr<int> link;
+    lds_ptr<i2> pairs;
+
+    __device__ __forceinline__ lds_ptr<f4> row(int c) const { return rec + c * kRecRows; }
+    __device__ __forceinline__ lds_ptr<volatile int> hit(int c) const {
+        return (lds_ptr<volatile int>)(rec + c * kRecRows + kRecHit);
+    }
+    __device__ __forceinline__ lds_ptr<int> scr(int c) const { return (lds_ptr<int>)(rec + c * kRecRows + kRecHit) + 1; }
+};
+
+// Entries of a wave's list: a step adds at most 128 (two spheres a lane) to at
+// most 63 left by the step before.
+constexpr int kWaveList = 192;
+
+__host__ __device__ inline size_t flag_tile_bytes(int T, int n_boxes, int W) {
+    return sizeof(float4) * (size_t)T * (kRecRows + 4 * n_boxes) + sizeof(unsigned) * (size_t)kWaveList * W;
+}
+
+// The cell states and the staged obstacles follow the tile region, then the
+// robot's tables.
+__host__ __device__ inline size_t flag_grid_bytes(int n_obs, int G, int lds_n) {
+    return (n_obs > 0 ? sizeof(unsigned) * (size_t)state_words(G) : 0) + sizeof(float4) * (size_t)lds_n;
+}
+
+// base: the workgroup's LDS (16-byte aligned); *end receives the first byte
+// after the robot's tables.
+__device__ inline FlagTile carve_flag_tile(char* base, int T, int W, const RobotView& rb, bool pairs, const ObsView& ob,
+                                           int lds_n, int G, char** end) {
+    FlagTile t;
+    lds_ptr<char> p = to_lds(base);
+    t.rec = (lds_ptr<f4>)p;         p += sizeof(f4) * kRecRows * T;
+    t.box = (lds_ptr<f4>)p;         p += sizeof(f4) * 4 * rb.n_boxes * T;
+    t.wl = (lds_ptr<unsigned>)p;
+    p = to_lds(base) + (int)flag_tile_bytes(T, rb.n_boxes, W);
+    t.state = (lds_ptr<unsigned>)p; p += ob.n > 0 ? (int)sizeof(unsigned) * state_words(G) : 0;
+    t.obs = (lds_ptr<f4>)p;         p += sizeof(f4) * lds_n;
+    t.lbound = (lds_ptr<f4>)p;
+    t.blocks = (lds_ptr<i4>)(t.lbound + kMaxParts);
+    t.sph = (lds_ptr<f4>)(p + (int)robot_image_off_sph(rb.n_blocks));
+    t.link = (lds_ptr<int>)(p + (int)robot_image_off_link(rb.n_spheres, rb.n_blocks));
+    t.pairs = (lds_ptr<i2>)(p + (int)robot_image_off_pairs(rb.n_spheres, rb.n_blocks));
+    if (end)
+        *end = base + flag_tile_bytes(T, rb.n_boxes, W) + flag_grid_bytes(ob.n, G, lds_n) +
+               robot_stage_bytes(rb.n_spheres, rb.n_blocks, rb.n_self, pairs);
+    return t;
+}
+
+// Copies n 16-byte words into LDS, four loads in flight a thread.
+__device__ __forceinline__ void copy_to_lds(lds_ptr<f4> dst, const float4* src, int n) {
+    const f4* s = reinterpret_cast<const f4*>(src);
+    const int nt = blockDim.x;
+    for (int i = threadIdx.x; i < n; i += 4 * nt) {
+        f4 v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = s[min(i + k * nt, n - 1)];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (i + k * nt < n) dst[i + k * nt] = v[k];
+    }
+}
+
+// The workgroup's copies of the cell states, (OST) the obstacle records and
+// the robot's tables; the caller places a barrier before their first use.
+template <bool OST>
+__device__ inline void stage_tables(const RobotView& rb, bool pairs, const ObsView& ob, const GridView& gv,
+                                    const FlagTile& t) {
+    if (ob.n > 0) {
+        copy_to_lds((lds_ptr<f4>)t.state, reinterpret_cast<const float4*>(gv.state), state_words(gv.G) / 4);
+        if constexpr (OST) copy_to_lds(t.obs, ob.rec, ob.n);
+    }
+    copy_to_lds(t.lbound, rb.image, (int)(robot_stage_bytes(rb.n_spheres, rb.n_blocks, rb.n_self, pairs) / 16));
+}
+
+// LDS written by some lanes of a wave and read by others of the same wave: a
+// wave's LDS accesses complete in order, so only the compiler is held.
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+struct LFrame { f4 r0, r1, r2; };
+
+__device__ __forceinline__ LFrame tile_frame(const FlagTile& t, int c, int link) {
+    const lds_ptr<f4> f = t.row(c) + 3 * link;
+    return LFrame{f[0], f[1], f[2]};
+}
+
+// Point (x, y, z) of the link's frame in the (shifted) world, w kept.
+__device__ __forceinline__ f4 place(const LFrame& f, f4 v) {
+    f4 o;
+    o.x = fmaf(f.r0.x, v.x, fmaf(f.r0.y, v.y, fmaf(f.r0.z, v.z, f.r0.w)));
+    o.y = fmaf(f.r1.x, v.x, fmaf(f.r1.y, v.y, fmaf(f.r1.z, v.z, f.r1.w)));
+    o.z = fmaf(f.r2.x, v.x, fmaf(f.r2.y, v.y, fmaf(f.r2.z, v.z, f.r2.w)));
+    o.w = v.w;
+    return o;
+}
+
+// Configuration x's pose by its eight lanes (of one wave), lane j with joint j's
+// value qj and link offset dj: the joint's cosine and sine, the link frames
+// (three lanes, one row each), the link parts' bounding spheres.  Straight-line
+// code: a taken branch costs a lone wave over 100 cycles, more than the
+// instructions it skips (lanes past the last joint or part write slots that
+// nothing reads).
+__device__ __forceinline__ void tile_pose(const RobotView& rb, float4 sh, const FlagTile& t, int x, int j, float qj,
+                                          float dj) {
+    const lds_ptr<f4> rec = t.row(x);
+    const bool prism = ((rb.prismatic >> j) & 1u) != 0;
+    // v_sin_f32 / v_cos_f32 take revolutions: q / (2 pi), rounded once
+    const float rev = qj * 0.15915494309189535f;
+    const float sn = __builtin_amdgcn_sinf(rev), cn = __builtin_amdgcn_cosf(rev);
+    f2 cs;
+    cs.x = prism ? 1.f : cn;
+    cs.y = prism ? 0.f : sn;
+    ((lds_ptr<f2>)(rec + kRecTrig))[j] = cs;
+    ((lds_ptr<float>)(rec + kRecD))[j] = prism ? dj + qj : dj;
+    wave_lds_sync();
+    if (j < 3) {
+        f4 c[4], d[2];
+#pragma unroll
+        for (int l = 0; l < 4; ++l) c[l] = rec[kRecTrig + l];
+        d[0] = rec[kRecD];
+        d[1] = rec[kRecD + 1];
+        float r0 = j == 0 ? 1.f : 0.f, r1 = j == 1 ? 1.f : 0.f, r2 = j == 2 ? 1.f : 0.f;
+        float p = -(j == 0 ? sh.x : (j == 1 ? sh.y : sh.z));
+        const lds_ptr<f4> out = rec + j;
+#pragma unroll
+        for (int l = 0; l < kMaxDof; ++l) {
+            if (l >= rb.dof) break;
+            float4 dh = cload4((const cfloat*)rb.dh + 4 * l);
+            dh.y = d[l / 4][l % 4];
+            dh_compose_row(r0, r1, r2, p, c[l / 2][2 * (l % 2)], c[l / 2][2 * (l % 2) + 1], dh);
+            f4 row;
+            row.x = r0; row.y = r1; row.z = r2; row.w = p;
+            out[3 * l] = row;
+        }
+    }
+    wave_lds_sync();
+    static_assert(kMaxParts == 16 && kPartsPerLink == 2, "two parts a lane");
+    const LFrame f0 = tile_frame(t, x, j / kPartsPerLink), f1 = tile_frame(t, x, j / kPartsPerLink + 4);
+    rec[kRecLb + j] = place(f0, t.lbound[j]);
+    rec[kRecLb + j + 8] = place(f1, t.lbound[j + 8]);
+}
+
+// The wave's list: entries appended by the lanes with a true predicate,
+// taken off its end.  n is wave-uniform.
+struct WaveList {
+    lds_ptr<unsigned> e;
+    int n;
+    __device__ WaveList(const FlagTile& t) : e(t.wl + kWaveList * wave_id()), n(0) {}
+    __device__ void push(bool p, unsigned v) {
+        const unsigned long long b = __ballot(p);
+        if (p) e[n + __popcll(b & ((1ull << (threadIdx.x & 63)) - 1ull))] = v;
+        n += __popcll(b);
+    }
+};
+
+// Grid cell of a sphere centre; in = false outside the grid (or not a number),
+// where the cell returned is some cell of the grid.
+__device__ __forceinline__ int grid_cell(const GridGeom& g, int G, f4 C, bool* in) {
+    const float fx = (C.x - g.ox) * g.ihx, fy = (C.y - g.oy) * g.ihy, fz = (C.z - g.oz) * g.ihz;
+    // IEEE 754-2019 minimum / maximum: a NaN coordinate stays NaN and is outside
+    const float lo = __builtin_elementwise_minimum(__builtin_elementwise_minimum(fx, fy), fz);
+    const float hi = __builtin_elementwise_maximum(__builtin_elementwise_maximum(fx, fy), fz);
+    *in = lo >= 0.f && hi < (float)G;
+    const int cx = (int)fx & (G - 1), cy = (int)fy & (G - 1), cz = (int)fz & (G - 1);    // G a power of two
+    return (cz * G + cy) * G + cx;
+}
+
+// Tests the last m <= 64 listed spheres (configuration | sphere << 6) against
+// the obstacles of their cells; with few entries several lanes share one, each
+// taking every so many groups of four list entries (records from LDS when
+// staged, else from global memory; the four records of a group are fetched
+// together and tested branch-free).
+template <class RecF>
+__device__ __forceinline__ void drain_spheres(WaveList& wl, int m, RecF rec, const ObsView& ob, const GridView& gv,
+                                              const GridGeom& g, const FlagTile& t, unsigned& ntest) {
+    wave_lds_sync();
+    const int lane = threadIdx.x & 63;
+    const int sh = m > 32 ? 0 : (m > 16 ? 1 : (m > 8 ? 2 : 3));       // lanes per entry, as a shift
+    const int i = lane >> sh, sub = lane & ((1 << sh) - 1);
+    const unsigned e = wl.e[wl.n - m + min(i, m - 1)];
+    const int c = e & 63, s = e >> 6;
+    if (i < m && *t.hit(c) == 0) {
+        const f4 C = place(tile_frame(t, c, t.link[s]), t.sph[s]);
+        bool in;
+        const int cell = grid_cell(g, gv.G, C, &in);
+        // the cell's count and this lane's first four list entries together
+        // (cell lists are 8-byte aligned, cap >= 32)
+        const ushort4* lst4 = reinterpret_cast<const ushort4*>(gv.list + (size_t)cell * gv.cap);
+        const int cnt = gv.count[cell];
+        ushort4 v = lst4[sub];
+        const bool full = cnt > gv.cap;
+        const int n = full ? ob.n : cnt;
+        bool found = false;
+        for (int k0 = 4 * sub; k0 < n && !found; k0 += 4 << sh) {
+            int oi[4];
+            if (full) {
+                oi[0] = k0; oi[1] = k0 + 1; oi[2] = k0 + 2; oi[3] = k0 + 3;
+            } else {
+                if (k0 != 4 * sub) v = lst4[k0 >> 2];
+                oi[0] = v.x; oi[1] = v.y; oi[2] = v.z; oi[3] = v.w;
+            }
+            ntest += (unsigned)min(4, n - k0);
+            float4 O[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) O[k] = rec((k0 + k < n) ? oi[k] : oi[0]);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const bool ok = k0 + k < n;
+                const float ex = C.x - O[k].x, ey = C.y - O[k].y, ez = C.z - O[k].z;
+                const float Rr = C.w + O[k].w;
+                found |= ok && fmaf(ex, ex, fmaf(ey, ey, ez * ez)) < Rr * Rr;
+            }
+        }
+        if (found) *t.hit(c) = 1;
+    }
+    wl.n -= m;
+    wave_lds_sync();
+}
+
+// The spheres against the obstacles: a lane per (configuration, sphere), two a
+// step.
+template <class RecF>
+__device__ __forceinline__ void tile_obstacles(RecF rec, const RobotView& rb, const ObsView& ob, const GridView& gv,
+                                               const FlagTile& t, int n_valid, unsigned& ntest) {
+    const int S = rb.n_spheres;
+    const GridGeom g = load_geom(gv.geom);
+    const int G = gv.G;
+    WaveList wl(t);
+    ItemWalk w(n_valid);
+    // one step adds to the list or takes from it (each once in the code: the
+    // kernels of an inflation's iteration share 64 KB of instruction cache)
+    while (true) {
+        if (wl.n < 64 && __any(w.k < S)) {
+            const bool a0 = w.k < S;
+            const int c0 = w.c, s0 = a0 ? w.k : 0;
+            w.next(n_valid);
+            const bool a1 = w.k < S;
+            const int c1 = w.c, s1 = a1 ? w.k : 0;
+            w.next(n_valid);
+            const LFrame f0 = tile_frame(t, c0, t.link[s0]), f1 = tile_frame(t, c1, t.link[s1]);
+            const f4 C0 = place(f0, t.sph[s0]), C1 = place(f1, t.sph[s1]);
+            bool i0, i1;
+            const int k0 = grid_cell(g, G, C0, &i0), k1 = grid_cell(g, G, C1, &i1);
+            const unsigned n0 = a0 && i0 ? t.state[k0 >> 4] >> (2 * (k0 & 15)) : 0u;
+            const unsigned n1 = a1 && i1 ? t.state[k1 >> 4] >> (2 * (k1 & 15)) : 0u;
+            if (n0 & 2u) *t.hit(c0) = 1;
+            if (n1 & 2u) *t.hit(c1) = 1;
+            wl.push((n0 & 3u) == 1u && *t.hit(c0) == 0, (unsigned)c0 | (unsigned)s0 << 6);
+            wl.push((n1 & 3u) == 1u && *t.hit(c1) == 0, (unsigned)c1 | (unsigned)s1 << 6);
+        } else if (wl.n > 0) {
+            drain_spheres(wl, min(wl.n, 64), rec, ob, gv, g, t, ntest);
+        } else {
+            break;
+        }
+    }
+}
+
+// Tests the sphere pairs of the last m listed (configuration, part pair)
+// items: kItemLanes lanes each, 32 or 64 when there are at most two.
+template <class PairF>
+__device__ __forceinline__ void drain_parts(WaveList& wl, int m, PairF pair, const FlagTile& t,
+                                            unsigned& ntest) {
+    wave_lds_sync();
+    const int lane = threadIdx.x & 63;
+    const int L = m > 2 ? kItemLanes : (m > 1 ? 32 : 64);
+    const int sub = lane / L, li = lane % L;
+    for (int it0 = 0; it0 < m; it0 += 64 / L) {
+        const int it = it0 + sub;
+        const unsigned e = wl.e[wl.n - m + min(it, m - 1)];
+        const int c = e & 63;
+        if (it < m && *t.hit(c) == 0) {                   // uniform in the lane group
+            const i4 blk = t.blocks[e >> 6];
+            const LFrame fa = tile_frame(t, c, blk.x / kPartsPerLink), fb = tile_frame(t, c, blk.y / kPartsPerLink);
+            bool found = false;
+            for (int p = li; p < blk.w; p += L) {
+                const int2 pr = pair(blk.z + p);
+                const f4 a = place(fa, t.sph[pr.x]), b = place(fb, t.sph[pr.y]);
+                const float ex = a.x - b.x, ey = a.y - b.y, ez = a.z - b.z;
+                const float Rr = a.w + b.w;
+                ++ntest;
+                found |= fmaf(ex, ex, fmaf(ey, ey, ez * ez)) < Rr * Rr;
+            }
+            if (found) *t.hit(c) = 1;
+        }
+    }
+    wl.n -= m;
+    wave_lds_sync();
+}
+
+// The self pairs: a lane per (configuration, part pair).
+template <class PairF>
+__device__ __forceinline__ void tile_self_pairs(PairF pair, const RobotView& rb, const FlagTile& t, int n_valid,
+                                                unsigned& ntest) {
+    WaveList wl(t);
+    ItemWalk w(n_valid);
+    while (true) {
+        if (wl.n < 64 && __any(w.k < rb.n_blocks)) {
+            const bool on = w.k < rb.n_blocks;
+            const int c = w.c, bk = on ? w.k : 0;
+            w.next(n_valid);
+            const i4 blk = t.blocks[bk];
+            const f4 A = t.row(c)[kRecLb + blk.x], B = t.row(c)[kRecLb + blk.y];
+            const float dx = A.x - B.x, dy = A.y - B.y, dz = A.z - B.z;
+            const float R = A.w + B.w;
+            const bool test = on && (*t.hit(c) | *t.scr(c)) == 0;
+            ntest += test ? 1u : 0u;
+            wl.push(test && fmaf(dx, dx, fmaf(dy, dy, dz * dz)) < R * R, (unsigned)c | (unsigned)bk << 6);
+        } else if (wl.n > 0) {
+            drain_parts(wl, min(wl.n, 64), pair, t, ntest);
+        } else {
+            break;
+        }
+    }
+}
+
+// The boxes' world poses: a lane per (configuration, box).
+__device__ inline void tile_place_boxes(const RobotView& rb, const FlagTile& t, int n_valid) {
+    for (ItemWalk w(n_valid); w.k < rb.n_boxes; w.next(n_valid)) {
+        const int c = w.c, k = w.k;
+        const LFrame f = tile_frame(t, c, rb.box_link[k]);
+        const float4 b0 = rb.box[4 * k], b1 = rb.box[4 * k + 1], b2 = rb.box[4 * k + 2], b3 = rb.box[4 * k + 3];
+        float4 o[4];
+        place_box(Frame{make_float4(f.r0.x, f.r0.y, f.r0.z, f.r0.w), make_float4(f.r1.x, f.r1.y, f.r1.z, f.r1.w),
+                        make_float4(f.r2.x, f.r2.y, f.r2.z, f.r2.w)},
+                  b0, b1, b2, b3, o, 1);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            f4 r;
+            r.x = o[i].x; r.y = o[i].y; r.z = o[i].z; r.w = o[i].w;
+            t.box[4 * (c * rb.n_boxes + k) + i] = r;
+        }
+    }
+}
+
+__device__ __forceinline__ DBox flag_box(const FlagTile& t, int n_boxes, int k, int c) {
+    float4 b[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) b[i] = lds_load((lds_ptr<const float4>)t.box, 4 * (c * n_boxes + k) + i);
+    return unpack_box(b[0], b[1], b[2], b[3], make_float3(0.f, 0.f, 0.f));
+}
+
 // Box pairs of a tile, flags mode (after the sphere passes; configurations
 // already hit are skipped): the box self pairs, every robot box against every
 // obstacle sphere and obstacle box, every robot sphere against every obstacle
 // box.  Each pair is first bounded by the two bounding spheres (a pair they
 // prove apart cannot collide), then tested exactly.
-__device__ inline void tile_boxes_flags(const RobotView& rb, const ObsView& ob, const TileSmem& t, int T,
+template <bool OST>
+__device__ inline void tile_boxes_flags(const RobotView& rb, const ObsView& ob, const FlagTile& t,
                                         int n_valid) {
-    const lds_ptr<volatile int> hit = to_lds((volatile int*)t.hit);
     const int S = rb.n_spheres, B = rb.n_boxes;
     const float4 shv = ob.centre[0];
     const float3 sh = make_float3(shv.x, shv.y, shv.z);
     for (ItemWalk w(n_valid); w.k < rb.n_box_pairs; w.next(n_valid)) {
         const int c = w.c;
-        if (hit[c]) continue;
+        if (*t.hit(c)) continue;
         const int2 pr = rb.box_pairs[w.k];
-        const DBox X = tile_box(t, S, T, pr.x, c), Y = tile_box(t, S, T, pr.y, c);
+        const DBox X = flag_box(t, rb.n_boxes, pr.x, c), Y = flag_box(t, rb.n_boxes, pr.y, c);
         const float dx = X.c[0] - Y.c[0], dy = X.c[1] - Y.c[1], dz = X.c[2] - Y.c[2];
         const float Rr = X.rb + Y.rb;
         if (fmaf(dx, dx, fmaf(dy, dy, dz * dz)) >= Rr * Rr) continue;
-        if (sat_value<true>(X, Y) < 0.f) hit[c] = 1;
+        if (sat_value<true>(X, Y) < 0.f) *t.hit(c) = 1;
     }
     for (ItemWalk w(n_valid); w.k < B; w.next(n_valid)) {
         const int c = w.c;
-        if (hit[c]) continue;
-        const DBox X = tile_box(t, S, T, w.k, c);
+        if (*t.hit(c)) continue;
+        const DBox X = flag_box(t, rb.n_boxes, w.k, c);
         bool found = false;
         for (int o = 0; o < ob.n && !found; ++o) {
-            const float4 O = t.obs ? t.obs[o] : ob.rec[o];
+            const float4 O = OST ? lds_load((lds_ptr<const float4>)t.obs, o) : ob.rec[o];
             const float dx = O.x - X.c[0], dy = O.y - X.c[1], dz = O.z - X.c[2];
             const float Rr = X.rb + O.w;
             if (fmaf(dx, dx, fmaf(dy, dy, dz * dz)) < Rr * Rr && hit_sphere_box(X, O.x, O.y, O.z, O.w)) found = true;
@@ -679,13 +1049,13 @@ __device__ inline void tile_boxes_flags(const RobotView& rb, const ObsView& ob, 
             const float Rr = X.rb + E.rb;
             if (fmaf(dx, dx, fmaf(dy, dy, dz * dz)) < Rr * Rr && sat_value<true>(X, E) < 0.f) found = true;
         }
-        if (found) hit[c] = 1;
+        if (found) *t.hit(c) = 1;
     }
     if (ob.n_ebox > 0) {
         for (ItemWalk w(n_valid); w.k < S; w.next(n_valid)) {
             const int c = w.c;
-            if (hit[c]) continue;
-            const float4 C = t.cen[w.k * T + c];
+            if (*t.hit(c)) continue;
+            const f4 C = place(tile_frame(t, c, t.link[w.k]), t.sph[w.k]);
             bool found = false;
             for (int e = 0; e < ob.n_ebox && !found; ++e) {
                 const DBox E = unpack_box(ob.ebox[4 * e], ob.ebox[4 * e + 1], ob.ebox[4 * e + 2], ob.ebox[4 * e + 3], sh);
@@ -693,130 +1063,9 @@ __device__ inline void tile_boxes_flags(const RobotView& rb, const ObsView& ob, 
                 const float Rr = E.rb + C.w;
                 if (fmaf(dx, dx, fmaf(dy, dy, dz * dz)) < Rr * Rr && hit_sphere_box(E, C.x, C.y, C.z, C.w)) found = true;
             }
-            if (found) hit[c] = 1;
+            if (found) *t.hit(c) = 1;
         }
     }
-}
-
-// Self-pair items of the work list (kItemLanes lanes each; blocks and pairs
-// from LDS when the robot tables are staged, else from global memory).
-template <class BlkF, class PairF>
-__device__ __forceinline__ void tile_self_items(BlkF block, PairF pair, const TileSmem& t, int T,
-                                                lds_ptr<volatile int> hit, unsigned& ntest) {
-    // 64 / kItemLanes work items per wave, kItemLanes lanes each (a part
-    // pair holds a fraction of its link pair's sphere pairs)
-    constexpr int IPW = 64 / kItemLanes;
-    const int n_items = *t.wl_n;
-    const int lane = threadIdx.x & 63, sub = lane / kItemLanes, li = lane % kItemLanes;
-    const int nw = blockDim.x >> 6;
-    for (int it0 = IPW * wave_id(); it0 < n_items; it0 += IPW * nw) {
-        const int it = it0 + sub;
-        if (it >= n_items) continue;
-        const int item = t.wl[it];
-        const int c = item & 63;
-        if (hit[c]) continue;                          // uniform in the lane group
-        const int4 blk = block(item >> 6);
-        bool found = false;
-        for (int p = li; p < blk.w; p += kItemLanes) {
-            const int2 pr = pair(blk.z + p);
-            const float4 a = t.cen[pr.x * T + c];
-            const float4 b = t.cen[pr.y * T + c];
-            const float ex = a.x - b.x, ey = a.y - b.y, ez = a.z - b.z;
-            const float Rr = a.w + b.w;
-            ++ntest;
-            found |= fmaf(ex, ex, fmaf(ey, ey, ez * ez)) < Rr * Rr;
-        }
-        if (found) hit[c] = 1;
-    }
-}
-
-// Obstacle sweep: a (configuration, sphere) item tests the obstacles listed in
-// its grid cell (records from LDS when staged, else from global memory); the
-// four records of a list load are fetched together and tested branch-free.
-template <class RecF>
-__device__ __forceinline__ void tile_obstacle_items(RecF rec, const ObsView& ob, const GridView& gv, const TileSmem& t,
-                                                    int T, int n_valid, int S, lds_ptr<volatile int> hit,
-                                                    unsigned& ntest) {
-    const GridGeom g = *gv.geom;
-    const int G = gv.G;
-    for (ItemWalk w(n_valid); w.k < S; w.next(n_valid)) {
-        const int c = w.c, s = w.k;
-        if (hit[c]) continue;
-        const float4 C = t.cen[s * T + c];
-        const float fx = (C.x - g.ox) * g.ihx, fy = (C.y - g.oy) * g.ihy, fz = (C.z - g.oz) * g.ihz;
-        if (!(fx >= 0.f && fy >= 0.f && fz >= 0.f && fx < (float)G && fy < (float)G && fz < (float)G)) continue;
-        const int cx = min((int)fx, G - 1), cy = min((int)fy, G - 1), cz = min((int)fz, G - 1);
-        const int cell = (cz * G + cy) * G + cx;
-        const int cnt = gv.count[cell];
-        const bool full = cnt > gv.cap;
-        const int n = full ? ob.n : cnt;
-        // list entries four at a time (cell lists are 8-byte aligned)
-        const ushort4* lst4 = reinterpret_cast<const ushort4*>(gv.list + (size_t)cell * gv.cap);
-        bool found = false;
-        for (int k0 = 0; k0 < n && !found; k0 += 4) {
-            int oi[4];
-            if (full) {
-                oi[0] = k0; oi[1] = k0 + 1; oi[2] = k0 + 2; oi[3] = k0 + 3;
-            } else {
-                const ushort4 v = lst4[k0 >> 2];
-                oi[0] = v.x; oi[1] = v.y; oi[2] = v.z; oi[3] = v.w;
-            }
-            float4 O[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) O[e] = rec((k0 + e < n) ? oi[e] : oi[0]);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const bool ok = k0 + e < n;
-                ntest += ok ? 1u : 0u;
-                const float ex = C.x - O[e].x, ey = C.y - O[e].y, ez = C.z - O[e].z;
-                const float Rr = C.w + O[e].w;
-                found |= ok && fmaf(ex, ex, fmaf(ey, ey, ez * ez)) < Rr * Rr;
-            }
-        }
-        if (found) hit[c] = 1;
-    }
-}
-
-template <bool BOX>
-__device__ inline unsigned tile_pairs_grid(const RobotView& rb, const ObsView& ob, const GridView& gv,
-                                           const TileSmem& t, int T, int n_valid) {
-    const lds_ptr<volatile int> hit = to_lds((volatile int*)t.hit);
-    unsigned int ntest = 0;
-    if (rb.n_blocks > 0) {
-        const bool lblk = (rb.staged & 1) != 0, lprs = (rb.staged & 2) != 0;
-        const lds_ptr<const int4> blocks_l = to_lds(rb.blocks);
-        const lds_ptr<const int2> pairs_l = to_lds(rb.pairs);
-        for (ItemWalk w(n_valid); w.k < rb.n_blocks; w.next(n_valid)) {
-            const int c = w.c, bk = w.k;
-            if (hit[c] || t.scr[c]) continue;
-            const int4 blk = lblk ? lds_load(blocks_l, bk) : rb.blocks[bk];
-            const float4 A = t.lb[blk.x * T + c], B = t.lb[blk.y * T + c];
-            const float dx = A.x - B.x, dy = A.y - B.y, dz = A.z - B.z;
-            const float R = A.w + B.w;
-            ++ntest;
-            if (fmaf(dx, dx, fmaf(dy, dy, dz * dz)) < R * R)
-                t.wl[atomicAdd(t.wl_n, 1)] = (unsigned short)((bk << 6) | c);
-        }
-        __syncthreads();
-        if (lblk && lprs)
-            tile_self_items([=](int i) { return lds_load(blocks_l, i); }, [=](int i) { return lds_load(pairs_l, i); },
-                            t, T, hit, ntest);
-        else
-            tile_self_items([=](int i) { return rb.blocks[i]; }, [=](int i) { return rb.pairs[i]; }, t, T, hit, ntest);
-    }
-    if (ob.n > 0) {
-        if (t.obs) {
-            const lds_ptr<const float4> rl = to_lds((const float4*)t.obs);
-            tile_obstacle_items([=](int o) { return lds_load(rl, o); }, ob, gv, t, T, n_valid, rb.n_spheres, hit,
-                                ntest);
-        } else {
-            const float4* rg = ob.rec;
-            tile_obstacle_items([=](int o) { return rg[o]; }, ob, gv, t, T, n_valid, rb.n_spheres, hit, ntest);
-        }
-    }
-    if (BOX && (rb.n_boxes > 0 || ob.n_ebox > 0)) tile_boxes_flags(rb, ob, t, T, n_valid);
-    __syncthreads();
-    return ntest;
 }
 
 // Adds the wave's test counts to one of kTestSlots counters (spread by
@@ -830,22 +1079,45 @@ __device__ inline void flush_tests(unsigned long long* tests, unsigned n) {
     if ((threadIdx.x & 63) == 0) atomicAdd(tests + (blockIdx.x + 97u * blockIdx.y) % kTestSlots, v);
 }
 
-// Whole tile check on t.q[0..n_valid).  Flags mode fills t.hit; signed-
-// distance mode also fills t.red[c] (overall) and t.red[W*T + c] (self).
-// Returns the thread's count of pair tests (flags mode; 0 otherwise).
-template <bool SD, bool BOX>
-__device__ inline unsigned tile_check(const RobotView& rb, const ObsView& ob, const GridView& gv, const TileSmem& t,
-                                      int T, int n_valid) {
-    // cleared here, published by FK's barriers (every reader of the previous
-    // check's flags and work list is behind a barrier the caller placed)
-    if (threadIdx.x < (unsigned)T) t.hit[threadIdx.x] = (threadIdx.x < (unsigned)n_valid) ? 0 : 1;
-    if (threadIdx.x == 0) *t.wl_n = 0;
-    tile_fk<BOX>(rb, ob, t, T, n_valid);
-    if (SD) {
-        tile_pairs_sd<BOX>(rb, ob, t, T, n_valid);
-        return 0;
+// Step 2 on the frames and part bounds of t (written, and t.hit and t.scr set,
+// by the caller): fills t.hit.  Starts and ends with a barrier.  Returns the
+// thread's count of pair tests.  PST: the self pairs lie in LDS when they are
+// few enough; OST: the obstacle records do.
+template <bool BOX, bool PST, bool OST>
+__device__ inline unsigned tile_flags(const RobotView& rb, const ObsView& ob, const GridView& gv, const FlagTile& t,
+                                      int n_valid) {
+    unsigned ntest = 0;
+    __syncthreads();
+    if (ob.n > 0 && rb.n_spheres > 0) {
+        if constexpr (OST) {
+            const lds_ptr<const float4> rl = (lds_ptr<const float4>)t.obs;
+            tile_obstacles([=](int o) { return lds_load(rl, o); }, rb, ob, gv, t, n_valid, ntest);
+        } else {
+            const float4* rg = ob.rec;
+            tile_obstacles([=](int o) { return rg[o]; }, rb, ob, gv, t, n_valid, ntest);
+        }
     }
-    return tile_pairs_grid<BOX>(rb, ob, gv, t, T, n_valid);
+    if (rb.n_blocks > 0) {
+        const lds_ptr<const int2> pl = (lds_ptr<const int2>)t.pairs;
+        const int2* pg = rb.pairs;
+        const bool in_lds = PST && rb.n_self <= kStagePairs;
+        tile_self_pairs([=](int i) { return in_lds ? lds_load(pl, i) : pg[i]; }, rb, t, n_valid, ntest);
+    }
+    if (BOX && (rb.n_boxes > 0 || ob.n_ebox > 0)) {
+        tile_place_boxes(rb, t, n_valid);
+        __syncthreads();
+        tile_boxes_flags<OST>(rb, ob, t, n_valid);
+    }
+    __syncthreads();
+    return ntest;
+}
+
+// Whole tile check in signed-distance mode on t.q[0..n_valid): fills t.hit,
+// t.red[c] (overall) and t.red[W*T + c] (self).
+template <bool BOX>
+__device__ inline void tile_check_sd(const RobotView& rb, const ObsView& ob, const TileSmem& t, int T, int n_valid) {
+    tile_fk<BOX>(rb, ob, t, T, n_valid);
+    tile_pairs_sd<BOX>(rb, ob, t, T, n_valid);
 }
 
 }  // namespace ezo

@@ -26,7 +26,7 @@ struct DevBuf {
 
 // Workspace slots of a context (grown on demand, reused across calls).
 enum Slot {
-    W_OBS_REC, W_OBS_CENTRE, W_GRID_GEOM, W_GRID_COUNT, W_GRID_LIST, W_SAMPLES, W_FLAGS, W_CAND, W_NCAND, W_CSTAR,
+    W_OBS_REC, W_OBS_CENTRE, W_GRID_GEOM, W_GRID_COUNT, W_GRID_STATE, W_GRID_LIST, W_CAND_LIST, W_LIST_N, W_LIST_LIGHT, W_SAMPLES, W_FLAGS, W_CAND, W_NCAND, W_CSTAR,
     W_ADIR, W_TSTAR, W_PCOL, W_PANY, W_STATS, W_TABLE, W_KDEV, W_ACTIVE, W_PRED, W_SCREENED, W_MLP_H1, W_MLP_H2,
     W_MLP_CNT, W_PATH_M, W_PATH_OFF, W_PATH_PTS, W_PATH_IDX, W_PATH_CNT, W_RUN, W_NPLACED, W_PATH_EOFF,
     W_ROUND_EDGES, W_ROUND_IDS, W_ROUND_SKIP, W_ROUND_A, W_ROUND_B, W_ROUND_NF, W_ROUND_ST, W_MAP_COUNTS, W_NSLOTS
@@ -37,7 +37,8 @@ enum Slot {
 // ---------------------------------------------------------------------------
 // T configurations per workgroup, W waves per workgroup, obstacle records
 // staged in LDS (stage = 1) or read from global memory; for the bisection,
-// depth = bisection levels per round (T >> depth candidates per workgroup).
+// depth = bisection levels per round when the candidates fill the device
+// (T candidates, T (2^depth - 1) configurations per workgroup).
 // T = 0: not chosen.
 struct TileCfg {
     int T = 0, W = 0, stage = 0, depth = 1;
@@ -62,7 +63,8 @@ struct ezo_ctx {
     int device = 0;
     hipStream_t stream = nullptr;      // internal stream (default priority)
     hipEvent_t ev_in = nullptr, ev_out = nullptr;
-    size_t lds_cap = 65536;
+    size_t lds_cap = 65536;            // LDS per workgroup that launch shapes are chosen within
+    size_t lds_max = 65536;            // what the device allows (a large robot's smallest tile may need it)
     std::string err;
     std::vector<DevBuf> ws;            // named workspace slots
     int* pinned = nullptr;             // host-pinned poll word, written by the device
@@ -101,6 +103,7 @@ struct ezo_robot {
     int B = 0, Q = 0;                  // boxes, box self pairs
     int slots = 0;                     // LDS pose rows per configuration: S + 4 B
     float r_max = 0.f;                 // largest sphere radius
+    float r_min = 0.f;                 // smallest (hugely negative without spheres)
     void* buf = nullptr;               // one device allocation holding everything below
     ezo::RobotView view{};
     const int* sorted_to_orig = nullptr;

@@ -65,6 +65,7 @@ struct EdgeInit {
     int4* cur;
     const int4* table;
     int* active;
+    int* list_n;                       // the candidate list's length
     const uint8_t* skip;
 };
 
@@ -73,6 +74,7 @@ __device__ inline void init_edge(const EdgeInit& a, int e) {
     if (e == 0) {
         *a.cur = a.table[1];
         *a.active = a.n_edges;
+        *a.list_n = 0;
     }
     if (e >= a.n_edges) return;
     if (a.skip && a.skip[e]) {                  // not inflated: final from the start, no rows
@@ -117,24 +119,25 @@ constexpr float kGridSlack = 1e-4f;
 
 __global__ void __launch_bounds__(256) k_prep_obstacles(const float* __restrict__ obs, int n, float4* __restrict__ rec,
                                                         float4* __restrict__ centre, GridGeom* __restrict__ geom,
-                                                        int G, float r_sphere_max, int* __restrict__ count,
-                                                        int count_init, int clear_wg, EdgeInit ei) {
-    // Workgroups 1 .. clear_wg set the grid's cell counts to count_init (0
-    // before k_grid_scatter), the ones after them start the fused loop's edges
+                                                        int G, float r_sphere_max, float r_sphere_min,
+                                                        int* __restrict__ count, int count_init,
+                                                        unsigned* __restrict__ state, unsigned state_init, int clear_wg, EdgeInit ei) {
+    // Workgroups 1 .. clear_wg set the grid's cell counts and states to their
+    // start (0 before k_grid_scatter), the ones after them start the fused loop's edges
     // (independent work that would otherwise take launches of its own);
-    // workgroup 0 does the rest (and the counts too when clear_wg is 0).
+    // workgroup 0 does the rest.
     const int cells = G * G * G;
     if (blockIdx.x > 0 && (int)blockIdx.x <= clear_wg) {
         for (int k = (blockIdx.x - 1) * blockDim.x + threadIdx.x; k < cells; k += clear_wg * blockDim.x)
             count[k] = count_init;
+        for (int k = (blockIdx.x - 1) * blockDim.x + threadIdx.x; k < state_words(G); k += clear_wg * blockDim.x)
+            state[k] = state_init;
         return;
     }
     if ((int)blockIdx.x > clear_wg) {
         init_edge(ei, (int)((blockIdx.x - 1 - clear_wg) * blockDim.x + threadIdx.x));
         return;
     }
-    if (clear_wg == 0)
-        for (int k = threadIdx.x; k < cells; k += blockDim.x) count[k] = count_init;
     __shared__ float red[7][256];
     const int tid = threadIdx.x;
     float mn[3] = {kHuge, kHuge, kHuge}, mx[3] = {-kHuge, -kHuge, -kHuge}, rmax = 0.f;
@@ -175,6 +178,7 @@ __global__ void __launch_bounds__(256) k_prep_obstacles(const float* __restrict_
         g.hx = h[0]; g.hy = h[1]; g.hz = h[2];
         g.ihx = 1.f / h[0]; g.ihy = 1.f / h[1]; g.ihz = 1.f / h[2];
         g.reach = r_sphere_max + kGridSlack;
+        g.hit_reach = r_sphere_min - kGridSlack - 1e-5f * (h[0] + h[1] + h[2]);
         geom[0] = g;
     }
     for (int o = tid; o < n; o += blockDim.x) {
@@ -184,8 +188,8 @@ __global__ void __launch_bounds__(256) k_prep_obstacles(const float* __restrict_
     }
 }
 
-// Grid lists, built from the obstacles' side: one wave per obstacle, its
-// lanes over the block of cells its reach can touch (the cell-index range of
+// Grid lists, built from the obstacles' side: one workgroup per obstacle, its
+// threads over the block of cells its reach can touch (the cell-index range of
 // [o - R, o + R] widened by one cell on each side, R = r_o + reach), each
 // cell kept by the same exact test of the distance from o to the cell's box;
 // a kept obstacle takes the next slot of the cell by an atomic count
@@ -193,15 +197,17 @@ __global__ void __launch_bounds__(256) k_prep_obstacles(const float* __restrict_
 // what a cell-by-cell scan of all obstacles lists; their order within the
 // list is whatever the atomics leave (the flags sweep only asks whether any
 // of them collides).  A count above cap marks an overflowing cell (the sweep
-// then scans every obstacle).
-__global__ void __launch_bounds__(256) k_grid_scatter(const float4* __restrict__ rec, int n,
+// then scans every obstacle).  Bound by the chain of returning atomics (about
+// 1 us each), so few obstacles' cells (some 500 each) are spread over 256
+// threads (two or three steps) instead of the 64 of one wave.  A cell whose farthest point lies within r_o +
+// hit_reach of o is marked a certain hit in its state.
+__global__ void __launch_bounds__(256) k_grid_scatter(const float4* __restrict__ rec,
                                                       const GridGeom* __restrict__ geom, int G, int cap,
-                                                      int* __restrict__ count, unsigned short* __restrict__ list) {
-    const int o = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
-    const int lane = threadIdx.x & 63;
-    if (o >= n) return;
-    const GridGeom g = *geom;
-    const float4 O = rec[o];
+                                                      int* __restrict__ count, unsigned* __restrict__ state,
+                                                      unsigned short* __restrict__ list) {
+    const int o = blockIdx.x;
+    const GridGeom g = load_geom(geom);
+    const float4 O = cload4((const cfloat*)rec + 4 * o);
     const float R = O.w + g.reach;
     int lo[3], hi[3];
     const float oc[3] = {O.x, O.y, O.z}, orig[3] = {g.ox, g.oy, g.oz}, inv[3] = {g.ihx, g.ihy, g.ihz};
@@ -213,7 +219,7 @@ __global__ void __launch_bounds__(256) k_grid_scatter(const float4* __restrict__
     const int nx = hi[0] - lo[0] + 1, ny = hi[1] - lo[1] + 1, nz = hi[2] - lo[2] + 1;
     if (nx <= 0 || ny <= 0 || nz <= 0) return;
     const int total = nx * ny * nz;
-    for (int k = lane; k < total; k += 64) {
+    for (int k = threadIdx.x; k < total; k += blockDim.x) {
         const int cx = lo[0] + k % nx, cy = lo[1] + (k / nx) % ny, cz = lo[2] + k / (nx * ny);
         const float lx = g.ox + cx * g.hx, ly = g.oy + cy * g.hy, lz = g.oz + cz * g.hz;
         const float ux = lx + g.hx, uy = ly + g.hy, uz = lz + g.hz;
@@ -223,6 +229,11 @@ __global__ void __launch_bounds__(256) k_grid_scatter(const float4* __restrict__
         if (fmaf(dx, dx, fmaf(dy, dy, dz * dz)) < R * R) {
             const int cell = (cz * G + cy) * G + cx;
             const int pos = atomicAdd(&count[cell], 1);
+            const float mx = fmaxf(O.x - lx, ux - O.x), my = fmaxf(O.y - ly, uy - O.y), mz = fmaxf(O.z - lz, uz - O.z);
+            const float sure = O.w + g.hit_reach;
+            unsigned st = pos == 0 ? 1u : 0u;
+            if (sure > 0.f && fmaf(mx, mx, fmaf(my, my, mz * mz)) < sure * sure) st |= 2u;
+            if (st) atomicOr(&state[cell >> 4], st << (2 * (cell & 15)));
             if (pos < cap) list[(size_t)cell * cap + pos] = (unsigned short)o;
         }
     }
@@ -233,9 +244,9 @@ __global__ void __launch_bounds__(256) k_grid_scatter(const float4* __restrict__
 // blockIdx.x = tile.  q_b = q + b * q_batch; flags_b = flags + b * out_batch.
 // n = iteration's |S| when it.cur is set, else n_arg.
 // ---------------------------------------------------------------------------
-template <int T, bool SD, bool BOX>
-__global__ void __launch_bounds__(1024) k_check(RobotView rb, ObsView ob, GridView gv, const float* __restrict__ q, int64_t n_arg,
-                                                int64_t stride_n, int64_t stride_d, int64_t q_batch,
+template <bool SD, bool BOX, bool OST>
+__global__ void __launch_bounds__(1024, 6) k_check(RobotView rb, ObsView ob, GridView gv, int T, const float* __restrict__ q,
+                                                int64_t n_arg, int64_t stride_n, int64_t stride_d, int64_t q_batch,
                                                 uint8_t* __restrict__ flags, float* __restrict__ min_sd,
                                                 float* __restrict__ min_sd_self, int64_t out_batch,
                                                 const int* __restrict__ status, IterArgs it,
@@ -250,33 +261,54 @@ __global__ void __launch_bounds__(1024) k_check(RobotView rb, ObsView ob, GridVi
         n = iv.nS;
         screen_from = iv.M;               // the unadaptive test's samples are never screened
     }
-    const int64_t base = (int64_t)blockIdx.x * T;
+    int64_t base = (int64_t)blockIdx.x * T;
     if (base >= n) return;
-    const int nv = (int)((n - base) < T ? (n - base) : T);
     const int W = blockDim.x >> 6;
-    TileSmem t = carve_tile(smem, T, tile_slots(rb.n_spheres, rb.n_boxes), W, SD ? 0 : ob.lds_n);
-    if (!SD) stage_obstacles(ob, t);
     const float* qb = q + b * q_batch;
-    for (int i = threadIdx.x; i < T * rb.dof; i += blockDim.x) {
-        const int c = i % T, j = i / T;
-        if (c < nv) t.q[c * kMaxDof + j] = qb[(base + c) * stride_n + j * stride_d];
-    }
-    if (threadIdx.x < (unsigned)T) {
-        const int64_t g = base + threadIdx.x;
-        const bool s = !SD && pred && threadIdx.x < (unsigned)nv && g >= screen_from && pred[b * out_batch + g] >= margin;
-        t.scr[threadIdx.x] = s ? 1 : 0;
-        if (s && stats) atomicAdd((unsigned long long*)&stats[b].screened, 1ull);
-    }
-    __syncthreads();
-    const unsigned ntest = tile_check<SD, BOX>(rb, ob, gv, t, T, nv);
-    if (gv.tests) flush_tests(gv.tests, ntest);
-    if (threadIdx.x < (unsigned)nv) {
-        const int64_t g = b * out_batch + base + threadIdx.x;
-        flags[g] = (uint8_t)t.hit[threadIdx.x];
-        if (SD) {
+    if constexpr (SD) {
+        const int nv = (int)((n - base) < T ? (n - base) : T);
+        TileSmem t = carve_tile(smem, T, tile_slots(rb.n_spheres, rb.n_boxes), W);
+        for (int i = threadIdx.x; i < T * rb.dof; i += blockDim.x) {
+            const int c = i % T, j = i / T;
+            if (c < nv) t.q[c * kMaxDof + j] = qb[(base + c) * stride_n + j * stride_d];
+        }
+        __syncthreads();
+        tile_check_sd<BOX>(rb, ob, t, T, nv);
+        if (threadIdx.x < (unsigned)nv) {
+            const int64_t g = b * out_batch + base + threadIdx.x;
+            flags[g] = (uint8_t)t.hit[threadIdx.x];
             if (min_sd) min_sd[g] = t.red[threadIdx.x];
             if (min_sd_self) min_sd_self[g] = t.red[W * T + threadIdx.x];
         }
+    } else {
+        const FlagTile t = carve_flag_tile(smem, T, W, rb, false, ob, OST ? ob.n : 0, gv.G, nullptr);
+        stage_tables<OST>(rb, false, ob, gv, t);
+        const float4 sh = cload4((const cfloat*)ob.centre);
+        const int j = threadIdx.x & 7;       // eight lanes per configuration, lane j its joint j
+        const float dj = rb.dh[j].y;
+        unsigned ntest = 0;
+        __syncthreads();
+        // a workgroup takes several tiles when the launch has fewer
+        // workgroups than tiles (one copy of the tables serves them)
+        for (; base < n; base += (int64_t)gridDim.x * T) {
+            const int nv = (int)((n - base) < T ? (n - base) : T);
+            for (int c = threadIdx.x >> 3; c < nv; c += blockDim.x >> 3) {
+                const int64_t g = base + c;
+                const float qj = qb[g * stride_n + (j < rb.dof ? j : 0) * stride_d];
+                bool s = false;
+                if (pred) {
+                    s = g >= screen_from && pred[b * out_batch + g] >= margin;
+                    if (s && stats && j == 0) atomicAdd((unsigned long long*)&stats[b].screened, 1ull);
+                }
+                *t.scr(c) = s ? 1 : 0;
+                *t.hit(c) = 0;
+                tile_pose(rb, sh, t, c, j, qj, dj);
+            }
+            ntest += tile_flags<BOX, false, OST>(rb, ob, gv, t, nv);
+            if (threadIdx.x < (unsigned)nv) flags[b * out_batch + base + threadIdx.x] = (uint8_t)*t.hit(threadIdx.x);
+            __syncthreads();                 // flags read before the next tile resets them
+        }
+        if (gv.tests) flush_tests(gv.tests, ntest);
     }
 }
 
@@ -669,19 +701,25 @@ __device__ __forceinline__ int wave_sum_i32(int v) {
            __builtin_amdgcn_readlane(v, 48);
 }
 
+// The candidates of all edges as one list (edge, index), so that the bisection
+// fills its tiles across edges; *n (zero before the edges append) their number.
+// Edges append in any order.  e == NULL: no list.
+struct CandList {
+    int2* e;
+    int* n;
+};
+
 // ---------------------------------------------------------------------------
 // Unadaptive test + selection of the first N_p colliding samples.
 // One workgroup (1024 threads) per edge.
 // ---------------------------------------------------------------------------
-
-
 __global__ void __launch_bounds__(1024) k_test_select(const uint8_t* __restrict__ flags, int64_t stride, int n_p,
                                                       int n_b, int* __restrict__ cand_idx, int cand_cap,
                                                       int* __restrict__ n_cands, uint8_t* __restrict__ accept_out,
                                                       int* __restrict__ count_out, int* __restrict__ status,
-                                                      EdgeStatsDev* __restrict__ stats, IterArgs it) {
+                                                      EdgeStatsDev* __restrict__ stats, IterArgs it, CandList cl) {
     __shared__ int wsum[16];
-    __shared__ int s_base;
+    __shared__ int s_base, s_list;
     const int e = blockIdx.x;
     const IterVals iv = resolve(it);
     if (!edge_running(status, e)) {
@@ -766,6 +804,11 @@ __global__ void __launch_bounds__(1024) k_test_select(const uint8_t* __restrict_
         }
         taken = s_base < n_p ? s_base : n_p;
     }
+    if (cl.e && taken > 0) {                 // the edge's candidates, appended to the list of all edges'
+        if (tid == 0) s_list = atomicAdd(cl.n, taken);
+        __syncthreads();
+        for (int i = tid; i < taken; i += blockDim.x) cl.e[s_list + i] = make_int2(e, i);
+    }
     if (tid == 0) {
         if (n_cands) n_cands[e] = taken;
         if (accept_out) accept_out[e] = accept ? 1 : 0;
@@ -782,165 +825,232 @@ __global__ void __launch_bounds__(1024) k_test_select(const uint8_t* __restrict_
     }
 }
 
+// The list for given counts (one workgroup per edge; *cl.n zero before).
+__global__ void __launch_bounds__(256) k_list_candidates(const int* __restrict__ n_cands, int cand_cap, CandList cl) {
+    __shared__ int s_list;
+    const int e = blockIdx.x;
+    const int n = min(max(n_cands[e], 0), cand_cap);
+    if (threadIdx.x == 0) s_list = n > 0 ? atomicAdd(cl.n, n) : 0;
+    __syncthreads();
+    for (int i = threadIdx.x; i < n; i += blockDim.x) cl.e[s_list + i] = make_int2(e, i);
+}
+
 // ---------------------------------------------------------------------------
-// Projection + fail-fast check + N_b bisection steps.  blockIdx.y = edge,
-// blockIdx.x = a group of TC candidates; every check is a whole-workgroup
-// tile check of up to TC (2^DEPTH - 1) configurations.  Candidate j of edge e
-// is sample cand_idx[e][j], coordinate k at S[e s_edge + k stride + idx].
+// Projection + fail-fast check + N_b bisection steps of every listed candidate.
+// Candidate i of edge e is sample cand_idx[e][i], coordinate k at S[e s_edge +
+// k stride + idx].  A workgroup takes tiles of TC candidates; every check is a
+// whole-workgroup tile check.
 //
-// The first check is the projections c_proj (fail-fast).  The bisection then
-// runs DEPTH levels per round: a round checks, for every candidate, the
-// 2^lev - 1 points of the next lev <= DEPTH levels of its bisection tree
-// (heap order: node 1 = midpoint of [lo, hi]; the children of node i are the
-// midpoints of its two halves), then walks the tree with the flags.  These
-// are exactly the points, computed by the same FP32 operations, and the
-// decisions of one-midpoint-at-a-time bisection, in ceil(N_b / DEPTH)
-// dependent rounds instead of N_b.  Candidate state lives with the threads
-// c < TC; configuration c (2^lev - 1) + i - 1 holds node i of candidate c.
-// LDS: the tile, the staged obstacles (ob.lds_n records), then the robot
-// tables (robot_stage_bytes), read by every one of the dependent checks.
+// A round checks, for every candidate, the 2^lev - 1 points of the next lev
+// levels of its bisection tree (heap order: node 1 = midpoint of [lo, hi]; the
+// children of node i are the midpoints of its two halves), then walks the tree
+// with the flags: exactly the points, computed by the same FP32 operations,
+// and the decisions of one-midpoint-at-a-time bisection, in fewer dependent
+// rounds.  The first round holds the projections c_proj (fail-fast), alone, or
+// beside the points of its levels where the tile has room.
+//
+// How many levels: with one, a candidate costs 1 + N_b checks in as many
+// dependent rounds; with three, up to 2.5 times the checks in a third of the
+// rounds.  A round is latency (about 5 us whether a workgroup runs alone on
+// its CU or four do), so the kernel takes the most levels (at most kMaxLevels,
+// at least the shape's) whose tiles all run at once (`resident` workgroups),
+// and the shape's where there are more candidates than that.  Measured, 96
+// edges at N_p = 1000: the last iterations' launches (a few hundred candidates)
+// 70 -> 34 us, the first (55 000) 423 -> 320; one edge at N_p = 10000 (5 900,
+// then about 2 000 candidates) 74 / 55 / 51 -> 71 / 42 / 38 us.
+//
+// Eight lanes carry a candidate, lane j its coordinate j (the state in LDS);
+// point i - 1 of candidate c's np points is its node i, the last one of the
+// first round its projection.  LDS: the tile (Tcap configurations), the cell
+// states and staged obstacles, the candidates' state, then the robot tables
+// (robot_stage_bytes), read by every one of the dependent checks.
 // ---------------------------------------------------------------------------
-template <int TC, int DEPTH, bool BOX, bool SCR = false>
-__global__ void __launch_bounds__(1024) k_project_bisect(RobotView rg, ObsView ob, GridView gv, const float* __restrict__ edges,
+constexpr int kMaxLevels = 3;
+
+struct BisectShape {
+    int T, depth;      // candidates per tile and levels per round when there are many
+    int Tcap;          // configurations per tile the LDS holds
+    int resident;      // workgroups that run at once
+};
+
+__host__ __device__ inline int bisect_state_rows(const BisectShape& s) {
+    return s.T > s.Tcap / 3 ? s.T : s.Tcap / 3;
+}
+
+template <bool BOX, bool SCR, bool OST>
+__global__ void __launch_bounds__(1024, SCR ? 4 : 6) k_project_bisect(RobotView rb, ObsView ob, GridView gv, BisectShape shape,
+                                                         CandList cl, const float* __restrict__ edges,
                                                          const float* __restrict__ S, int64_t stride, int64_t s_edge,
-                                                         const int* __restrict__ cand_idx,
-                                                         const int* __restrict__ n_cands, int cand_cap, int n_b,
+                                                         const int* __restrict__ cand_idx, int cand_cap, int n_b,
                                                          float* __restrict__ c_star, float* __restrict__ a_dir,
                                                          float* __restrict__ t_star,
                                                          uint8_t* __restrict__ proj_collides,
-                                                         uint8_t* __restrict__ proj_any,
-                                                         const int* __restrict__ status, MlpView mv,
+                                                         uint8_t* __restrict__ proj_any, MlpView mv,
                                                          EdgeStatsDev* __restrict__ stats) {
-    static_assert(DEPTH >= 1 && DEPTH <= 3 && TC >= 1, "bisection depth per round");
-    static_assert(!SCR || (DEPTH == 1 && TC <= 16), "the screened bisection checks at most 16 points per round");
-    // (the screened form runs with at least four waves: the network's layers)
-    constexpr int NODES = (1 << DEPTH) - 1;
-    constexpr int T = TC * NODES;                   // configurations per tile check
+    // (the screened form runs with one level per round, at most 16 points per
+    // tile and at least four waves: the network's layers)
     extern __shared__ __align__(16) char smem[];
-    const int e = blockIdx.y;
-    if (!edge_running(status, e)) return;
-    const int nc = min(max(n_cands[e], 0), cand_cap);
-    const int base = blockIdx.x * TC;
-    if (base >= nc) return;
-    const int nv = (nc - base) < TC ? (nc - base) : TC;
-    const int dof = rg.dof;
-    const int W = blockDim.x >> 6;
-    const int slots = tile_slots(rg.n_spheres, rg.n_boxes);
-    TileSmem t = carve_tile(smem, T, slots, W, ob.lds_n);
-    char* rs_base = smem + tile_smem_bytes(T, slots, W) + 16 * (size_t)ob.lds_n;
-    const RobotView rb = stage_robot(rg, rs_base);
-    // screened form: the network's activations and predictions after the
-    // staged robot tables
-    __bf16* mlp_h = reinterpret_cast<__bf16*>(rs_base + robot_stage_bytes(slots, rg.n_self, rg.n_blocks));
+    const int total = *cl.n;
+    int depth = SCR ? 1 : shape.depth, TC = shape.T;
+    if (!SCR) {
+        for (int d = kMaxLevels; d > shape.depth; --d) {
+            const int tc = shape.Tcap / ((1 << d) - 1);
+            if (tc > 0 && (total + tc - 1) / tc <= shape.resident) {
+                depth = d;
+                TC = min(tc, max(1, (total + shape.resident - 1) / shape.resident));
+                break;
+            }
+        }
+    }
+    if ((int64_t)blockIdx.x * TC >= total) return;
+    const int dof = rb.dof, T = shape.Tcap, W = blockDim.x >> 6;
+    char* end;
+    const FlagTile t = carve_flag_tile(smem, T, W, rb, true, ob, OST ? ob.n : 0, gv.G, &end);
+    // the candidates' state, [rows][8]: colliding end, other end, projection
+    const int rows = bisect_state_rows(shape);
+    const lds_ptr<float> s_hi = to_lds(reinterpret_cast<float*>(end));
+    const lds_ptr<float> s_lo = s_hi + rows * kMaxDof, s_cp = s_lo + rows * kMaxDof;
+    // screened form: the points, the network's activations and its predictions
+    float* scr_q = reinterpret_cast<float*>(end) + 3 * rows * kMaxDof;
+    __bf16* mlp_h = reinterpret_cast<__bf16*>(scr_q + 16 * kMaxDof);
     float* mlp_y = reinterpret_cast<float*>(reinterpret_cast<char*>(mlp_h) + mlp_tile_smem_bytes(1));
-    stage_obstacles(ob, t);
+    stage_tables<OST>(rb, true, ob, gv, t);
+    const float4 sh = cload4((const cfloat*)ob.centre);
     const int tid = threadIdx.x;
-    const bool own = tid < nv;
-    if (tid < T) t.scr[tid] = 0;          // the projections (fail-fast) are always checked exactly
-    float lo[kMaxDof], hi[kMaxDof], cp[kMaxDof];
-    const float* v = edges + (size_t)e * 2 * dof;
-    if (own) {
-        const int idx = min(max(cand_idx[(size_t)e * cand_cap + base + tid], 0), (int)(stride - 1));
-        const float* Se = S + (size_t)e * s_edge;
-        float num = 0.f, den = 0.f;
-#pragma unroll
-        for (int j = 0; j < kMaxDof; ++j) {
-            hi[j] = j < dof ? Se[(size_t)j * stride + idx] : 0.f;
-            const float dv = j < dof ? v[dof + j] - v[j] : 0.f;
-            num = fmaf(hi[j] - (j < dof ? v[j] : 0.f), dv, num);
-            den = fmaf(dv, dv, den);
-        }
-        float alpha = 0.f;
-        if (den > 0.f) alpha = fminf(fmaxf(num / den, 0.f), 1.f);
-        float nrm = 0.f;
-#pragma unroll
-        for (int j = 0; j < kMaxDof; ++j) {
-            cp[j] = j < dof ? fmaf(alpha, v[dof + j], (1.f - alpha) * v[j]) : 0.f;
-            lo[j] = cp[j];
-            nrm = fmaf(hi[j] - cp[j], hi[j] - cp[j], nrm);
-        }
-        nrm = sqrtf(nrm);
-        const float inv = nrm > 0.f ? 1.f / nrm : 0.f;
-        for (int j = 0; j < dof; ++j) {
-            a_dir[((size_t)e * dof + j) * cand_cap + base + tid] = (hi[j] - cp[j]) * inv;
-            t.q[tid * kMaxDof + j] = cp[j];
-        }
-    }
+    // lane j of a candidate's (a configuration's) eight lanes
+    const int j = tid & 7, grp = tid >> 3, ngrp = blockDim.x >> 3;
+    const float dj = rb.dh[j].y;
+    unsigned ntest = 0;
     __syncthreads();
-    unsigned ntest = tile_check<false, BOX>(rb, ob, gv, t, T, nv);
-    if (own) {
-        const int h = t.hit[tid];
-        proj_collides[(size_t)e * cand_cap + base + tid] = (uint8_t)h;
-        if (h && proj_any) proj_any[e] = 1;
-    }
-    for (int done = 0; done < n_b;) {
-        const int lev = min(DEPTH, n_b - done);
-        const int npt = (1 << lev) - 1;
-        __syncthreads();                  // the previous check's reads of t.q are done
-        if (own) {
-            float* q0 = t.q + (size_t)tid * npt * kMaxDof;
+    for (int base = blockIdx.x * TC; base < total; base += gridDim.x * TC) {
+        const int nv = min(TC, total - base);
+        for (int c = grp; c < nv; c += ngrp) {
+            const int2 ej = cl.e[base + c];
+            const int idx = min(max(cand_idx[(size_t)ej.x * cand_cap + ej.y], 0), (int)(stride - 1));
+            const float* Se = S + (size_t)ej.x * s_edge;
+            const float* v = edges + (size_t)ej.x * 2 * dof;
+            // the projection needs every coordinate: each lane takes the sums
+            // over all of them, in order
+            float s[kMaxDof], v1[kMaxDof], v2[kMaxDof], p[kMaxDof];
 #pragma unroll
-            for (int j = 0; j < kMaxDof; ++j) {
-                if (j >= dof) break;
-                // node i's interval [L_i, H_i]; L_2i = L_i, H_2i = p_i, L_2i+1 = p_i, H_2i+1 = H_i
-                float Lv[NODES + 1], Hv[NODES + 1], pv[NODES + 1];
-                Lv[1] = lo[j];
-                Hv[1] = hi[j];
+            for (int i = 0; i < kMaxDof; ++i) {
+                const int k = min(i, dof - 1);
+                s[i] = Se[(size_t)k * stride + idx];
+                v1[i] = v[k];
+                v2[i] = v[dof + k];
+            }
+            float num = 0.f, den = 0.f;
 #pragma unroll
-                for (int i = 1; i <= NODES; ++i) {
-                    if (i > 1) {
-                        Lv[i] = (i & 1) ? pv[i >> 1] : Lv[i >> 1];
-                        Hv[i] = (i & 1) ? Hv[i >> 1] : pv[i >> 1];
+            for (int i = 0; i < kMaxDof; ++i) {
+                if (i >= dof) s[i] = v1[i] = v2[i] = 0.f;
+                const float dv = v2[i] - v1[i];
+                num = fmaf(s[i] - v1[i], dv, num);
+                den = fmaf(dv, dv, den);
+            }
+            float alpha = 0.f;
+            if (den > 0.f) alpha = fminf(fmaxf(num / den, 0.f), 1.f);
+            float nrm = 0.f;
+#pragma unroll
+            for (int i = 0; i < kMaxDof; ++i) {
+                p[i] = i < dof ? fmaf(alpha, v2[i], (1.f - alpha) * v1[i]) : 0.f;
+                nrm = fmaf(s[i] - p[i], s[i] - p[i], nrm);
+            }
+            nrm = sqrtf(nrm);
+            const float inv = nrm > 0.f ? 1.f / nrm : 0.f;
+            float sj = s[0], pj = p[0];
+#pragma unroll
+            for (int i = 1; i < kMaxDof; ++i) {
+                sj = i == j ? s[i] : sj;
+                pj = i == j ? p[i] : pj;
+            }
+            if (j < dof) a_dir[((size_t)ej.x * dof + j) * cand_cap + ej.y] = (sj - pj) * inv;
+            s_hi[c * kMaxDof + j] = sj;
+            s_lo[c * kMaxDof + j] = pj;
+            s_cp[c * kMaxDof + j] = pj;
+        }
+        bool first = true;
+        for (int done = 0;;) {
+            // levels of this round and points per candidate
+            int lev = min(depth, n_b - done);
+            if (first && (depth == 1 || (TC << lev) > T)) lev = 0;
+            const int np = (1 << lev) - (first ? 0 : 1);
+            // a candidate's state is written by its own eight lanes; with
+            // several points per candidate others read it (and reset its flags)
+            if (depth > 1 || SCR) __syncthreads();
+            for (int x = grp; x < nv * np; x += ngrp) {
+                const int c = np == 1 ? x : x / np, node = x - c * np + 1;
+                float lo = s_lo[c * kMaxDof + j], hi = s_hi[c * kMaxDof + j];
+                const float cp = s_cp[c * kMaxDof + j];
+                // node i's interval: its bits below the leading one say which
+                // half each level takes (0: the end at lo, 1: the end at hi)
+                const int d = 31 - __builtin_clz(node);
+                float m = 0.5f * (lo + hi);
+#pragma unroll
+                for (int b = kMaxLevels - 2; b >= 0; --b) {
+                    const bool up = (node >> b) & 1, on = b < d;
+                    lo = on && up ? m : lo;
+                    hi = on && !up ? m : hi;
+                    m = 0.5f * (lo + hi);
+                }
+                const float qj = first && node == np ? cp : m;
+                if constexpr (SCR) scr_q[x * kMaxDof + j] = qj;
+                *t.hit(x) = 0;
+                *t.scr(x) = 0;               // checked exactly (the screened form sets it below)
+                tile_pose(rb, sh, t, x, j, qj, dj);
+            }
+            if constexpr (SCR) {
+                // one-sided screen of the midpoints: exact self pairs are skipped
+                // iff the predicted self distance is >= the margin, so a point
+                // judged colliding is truly colliding and c* stays a collision
+                if (!first) {
+                    mlp_forward_tile<1, 4>(mv, scr_q, kMaxDof, nv, mlp_h, mlp_y);
+                    if (tid < nv && mlp_y[tid] >= mv.margin) {
+                        *t.scr(tid) = 1;
+                        if (stats) atomicAdd((unsigned long long*)&stats[cl.e[base + tid].x].screened, 1ull);
                     }
-                    pv[i] = 0.5f * (Lv[i] + Hv[i]);
-                    if (i <= npt) q0[(i - 1) * kMaxDof + j] = pv[i];
                 }
             }
-        }
-        __syncthreads();
-        if constexpr (SCR) {
-            // one-sided screen of the midpoints: exact self pairs are skipped
-            // iff the predicted self distance is >= the margin, so a point
-            // judged colliding is truly colliding and c* stays a collision
-            mlp_forward_tile<1, 4>(mv, t.q, kMaxDof, nv, mlp_h, mlp_y);
-            int screened = 0;
-            if (tid < T) {
-                const bool sc = tid < nv && mlp_y[tid] >= mv.margin;
-                t.scr[tid] = sc ? 1 : 0;
-                screened = sc ? 1 : 0;
-            }
-            if (stats && tid < 64) {
-                const unsigned long long b = __ballot(screened != 0);
-                if (tid == 0 && b) atomicAdd((unsigned long long*)&stats[e].screened, (unsigned long long)__popcll(b));
-            }
-        }
-        ntest += tile_check<false, BOX>(rb, ob, gv, t, T, nv * npt);
-        if (own) {
-            const int* h = t.hit + tid * npt;
-            const float* q0 = t.q + (size_t)tid * npt * kMaxDof;
-            int node = 1;
-            for (int d = 0; d < lev; ++d) {
-                const bool hc = h[node - 1] != 0;
-#pragma unroll
-                for (int j = 0; j < kMaxDof; ++j) {
-                    if (j < dof) {
-                        const float m = q0[(node - 1) * kMaxDof + j];
-                        if (hc) hi[j] = m;
-                        else lo[j] = m;
-                    }
+            ntest += tile_flags<BOX, true, OST>(rb, ob, gv, t, nv * np);
+            for (int c = grp; c < nv; c += ngrp) {
+                if (first && j == 0) {
+                    const int2 ej = cl.e[base + c];
+                    const int h = *t.hit(c * np + np - 1);
+                    proj_collides[(size_t)ej.x * cand_cap + ej.y] = (uint8_t)h;
+                    if (h && proj_any) proj_any[ej.x] = 1;
                 }
-                node = 2 * node + (hc ? 0 : 1);
+                // walk the tree with the flags: the same points, by the same operations
+                float lo = s_lo[c * kMaxDof + j], hi = s_hi[c * kMaxDof + j];
+                int node = 1;
+#pragma unroll
+                for (int d = 0; d < kMaxLevels; ++d) {
+                    if (d >= lev) break;
+                    const float m = 0.5f * (lo + hi);
+                    const bool h = *t.hit(c * np + node - 1) != 0;
+                    hi = h ? m : hi;
+                    lo = h ? lo : m;
+                    node = 2 * node + (h ? 0 : 1);
+                }
+                s_lo[c * kMaxDof + j] = lo;
+                s_hi[c * kMaxDof + j] = hi;
+            }
+            done += lev;
+            first = false;
+            if (done >= n_b) break;
+        }
+        for (int c = grp; c < nv; c += ngrp) {
+            wave_lds_sync();
+            const int2 ej = cl.e[base + c];
+            if (j < dof) c_star[((size_t)ej.x * dof + j) * cand_cap + ej.y] = s_hi[c * kMaxDof + j];
+            if (j == 0) {
+                float ts = 0.f;
+                for (int i = 0; i < dof; ++i) {
+                    const float d = s_hi[c * kMaxDof + i] - s_cp[c * kMaxDof + i];
+                    ts = fmaf(d, d, ts);
+                }
+                t_star[(size_t)ej.x * cand_cap + ej.y] = sqrtf(ts);
             }
         }
-        done += lev;
-    }
-    if (own) {
-        float ts = 0.f;
-        for (int j = 0; j < dof; ++j) {
-            c_star[((size_t)e * dof + j) * cand_cap + base + tid] = hi[j];
-            ts = fmaf(hi[j] - cp[j], hi[j] - cp[j], ts);
-        }
-        t_star[(size_t)e * cand_cap + base + tid] = sqrtf(ts);
+        __syncthreads();                 // the tile's flags and state are free again
     }
     if (gv.tests) flush_tests(gv.tests, ntest);
 }
@@ -1177,6 +1287,7 @@ struct IterEnd {
     const int4* table;
     int max_iters;
     int* active_count;
+    int* list_n;                      // the candidate list, emptied for the next iteration
     int* host_active;                 // pinned, or NULL
     EdgeStatsDev* host_stats;         // pinned, or NULL
 };
@@ -1256,6 +1367,7 @@ __global__ void __launch_bounds__(1024) k_place(int dof, const float* __restrict
             else running = 1;
         }
         *ie.active_count = running;
+        *ie.list_n = 0;
         *ie.cur = ie.table[min(k + 1, ie.max_iters + 1)];
         if (ie.host_active) *ie.host_active = running;
     }
@@ -1297,7 +1409,7 @@ __global__ void k_init_edges(EdgeInit ei) { init_edge(ei, blockIdx.x * blockDim.
 __global__ void __launch_bounds__(256) k_advance(int4* __restrict__ cur, const int4* __restrict__ table, int max_iters,
                                                  int* __restrict__ status,
                                                  int n_edges, int* __restrict__ active_count,
-                                                 int* __restrict__ host_active,
+                                                 int* __restrict__ list_n, int* __restrict__ host_active,
                                                  const EdgeStatsDev* __restrict__ stats,
                                                  EdgeStatsDev* __restrict__ host_stats) {
     // the edges' statistics after this iteration, for the host (pinned)
@@ -1318,6 +1430,7 @@ __global__ void __launch_bounds__(256) k_advance(int4* __restrict__ cur, const i
     __syncthreads();
     if (threadIdx.x == 0) {
         *active_count = cnt;
+        *list_n = 0;
         *cur = table[min(k + 1, max_iters + 1)];
         if (host_active) *host_active = cnt;
     }
@@ -1675,9 +1788,11 @@ __global__ void k_gather_rows(int dof, const float* __restrict__ rows, const int
     for (int k = 0; k < dof; ++k) out[(size_t)r * dof + k] = rows[(size_t)idx[r] * dof + k];
 }
 
-// Row-major [n][dof] -> coordinate-major [dof][n].
-__global__ void k_rows_to_coords(int dof, const float* __restrict__ rows, int64_t n, float* __restrict__ coords) {
+// Row-major [n][dof] -> coordinate-major [dof][n]; empties the candidate list.
+__global__ void k_rows_to_coords(int dof, const float* __restrict__ rows, int64_t n, float* __restrict__ coords,
+                                 int* __restrict__ list_n) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i == 0) *list_n = 0;
     if (i >= n) return;
     for (int k = 0; k < dof; ++k) coords[(size_t)k * n + i] = rows[(size_t)i * dof + k];
 }
