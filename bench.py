@@ -50,7 +50,8 @@ WORKLOADS = {
 }
 
 
-KERNEL_SOURCES = ("paper_2504_10783_amd/csrc/ezo_device.hpp", "paper_2504_10783_amd/csrc/ezo_kernels.hpp",
+KERNEL_SOURCES = ("paper_2504_10783_amd/csrc/ezo_device.hpp", "paper_2504_10783_amd/csrc/ezo_distance.hpp",
+                  "paper_2504_10783_amd/csrc/ezo_kernels.hpp",
                   "paper_2504_10783_amd/csrc/ezo_screen.hpp")
 
 

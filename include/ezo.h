@@ -209,7 +209,7 @@ ezo_status ezo_check_collisions(ezo_ctx *ctx, const ezo_robot *robot, const floa
  * ezo_check_collisions; the results are bit-identical to it.  Instead of the
  * context's growable workspace it uses a fixed scratch array in device
  * memory (obstacle records, frame shift, broad-phase grid counts and lists:
- * about 8.6 MB), one per device, allocated with the library's code object
+ * about 8.9 MB), one per device, allocated with the library's code object
  * and held until the process ends; the call itself allocates nothing and
  * never runs a launch-shape timing search (it uses the tuning cache, else
  * the size heuristic).  Limit: n_obs <= EZO_NOALLOC_MAX_OBSTACLES, else

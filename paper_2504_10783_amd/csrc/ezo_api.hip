@@ -111,26 +111,36 @@ int pick_W(int n_obs) {
 constexpr int kGridCap = 128;
 static_assert(kGridCap % 8 == 0, "the sweep loads cell lists eight entries (16 bytes) at a time");
 
-// Obstacle records, the frame shift and the broad-phase grid for one call,
-// written to the given device buffers (every byte the kernels read later is
-// rewritten here: nothing needs to start at zero).
+// What the call prepares besides the obstacle records and the frame shift: the
+// broad-phase grid of the flags sweep, the distance field, or neither (signed
+// distances over all pairs, no obstacles at all).
+enum PrepKind { PREP_GRID, PREP_NEAR, PREP_RECORDS };
+
+// Obstacle records, the frame shift and the broad-phase grid or the distance
+// field for one call, written to the given device buffers (every byte the
+// kernels read later is rewritten here: nothing needs to start at zero).
 ezo_status prep_obstacles_into(ezo_ctx* c, const ezo_robot* r, const float* obs, int n_obs, hipStream_t st,
-                               void* rec, void* centre, void* geom, void* count, void* state, void* list, ObsView* ov,
+                               PrepKind kind, void* near, void* rec, void* centre, void* geom, void* count, void* state, void* list, ObsView* ov,
                                GridView* gv, const EdgeInit* ei = nullptr) {
-    const int G = grid_dim(n_obs);
+    const int G = kind == PREP_NEAR ? kNearG : grid_dim(n_obs);
+    const bool grid = kind == PREP_GRID;
     // indices above 65535 do not fit the list type: then every cell scans all
     const bool lists = n_obs <= 65535;
     // the cell counts are cleared by extra workgroups (2048 cells each), and
     // the fused loop's edge start rides along as further workgroups (ei)
-    const int clear_wg = (G * G * G + 2047) / 2048;
+    const int clear_wg = grid ? (G * G * G + 2047) / 2048 : 0;
     const int init_wg = (ei && ei->n_edges > 0) ? (ei->n_edges + 255) / 256 : 0;
     hipLaunchKernelGGL(k_prep_obstacles, dim3(1 + clear_wg + init_wg), dim3(256), 0, st, obs, n_obs, (float4*)rec,
-                       (float4*)centre, (GridGeom*)geom, G, r ? r->r_max : 0.f, r ? r->r_min : -kHuge, (int*)count,
+                       (float4*)centre, (GridGeom*)geom, G, r ? r->r_max : 0.f, r ? r->r_min : -kHuge,
+                       kind == PREP_NEAR ? kNearGrow : 0.f, (int*)count,
                        lists ? 0 : kGridCap + 1, (unsigned*)state, lists ? 0u : 0x55555555u, clear_wg, init_wg ? *ei : EdgeInit{});
     // four waves per obstacle until the obstacles alone fill the chip (512
     // obstacles: 8.3 us against 12.6 with one wave; 4096: 16 us with one, 23.5
     // with four)
-    if (lists && n_obs > 0)
+    if (kind == PREP_NEAR && n_obs > 0)
+        hipLaunchKernelGGL(k_near_build, dim3(kNearCells / (kNearBlock * kNearBlock * kNearBlock)), dim3(512), 0, st,
+                           (const float4*)rec, n_obs, (const GridGeom*)geom, (uint2*)near, (unsigned short*)list);
+    if (grid && lists && n_obs > 0)
         hipLaunchKernelGGL(k_grid_scatter, dim3((unsigned)n_obs), dim3(n_obs <= 1024 ? 256 : 64), 0, st, (const float4*)rec,
                            (const GridGeom*)geom, G, kGridCap, (int*)count,
                            (unsigned*)state, (unsigned short*)list);
@@ -153,17 +163,25 @@ ezo_status prep_obstacles_into(ezo_ctx* c, const ezo_robot* r, const float* obs,
 
 // The same in the context's workspace.
 ezo_status prep_obstacles(ezo_ctx* c, const ezo_robot* r, const float* obs, int n_obs, hipStream_t st,
-                          ObsView* ov, GridView* gv, const EdgeInit* ei = nullptr) {
+                          ObsView* ov, GridView* gv, const EdgeInit* ei = nullptr, PrepKind kind = PREP_GRID,
+                          NearView* nv = nullptr) {
     ezo_status s;
-    void *rec, *centre, *geom, *count, *state, *list;
-    const size_t cells = (size_t)grid_dim(n_obs) * grid_dim(n_obs) * grid_dim(n_obs);
+    void *rec, *centre, *geom, *count = nullptr, *state = nullptr, *list = nullptr, *near = nullptr;
+    const size_t dim = kind == PREP_NEAR ? kNearG : grid_dim(n_obs), cells = dim * dim * dim;
+    static_assert(kNearCap == kGridCap, "one list size");
     if ((s = ezo_ws_get(c, W_OBS_REC, sizeof(float4) * (size_t)std::max(n_obs, 1), &rec)) != EZO_OK) return s;
     if ((s = ezo_ws_get(c, W_OBS_CENTRE, sizeof(float4), &centre)) != EZO_OK) return s;
     if ((s = ezo_ws_get(c, W_GRID_GEOM, sizeof(GridGeom), &geom)) != EZO_OK) return s;
-    if ((s = ezo_ws_get(c, W_GRID_COUNT, sizeof(int) * cells, &count)) != EZO_OK) return s;
-    if ((s = ezo_ws_get(c, W_GRID_STATE, sizeof(unsigned) * state_words(grid_dim(n_obs)), &state)) != EZO_OK) return s;
-    if ((s = ezo_ws_get(c, W_GRID_LIST, sizeof(unsigned short) * cells * kGridCap, &list)) != EZO_OK) return s;
-    return prep_obstacles_into(c, r, obs, n_obs, st, rec, centre, geom, count, state, list, ov, gv, ei);
+    if (kind == PREP_GRID) {
+        if ((s = ezo_ws_get(c, W_GRID_COUNT, sizeof(int) * cells, &count)) != EZO_OK) return s;
+        if ((s = ezo_ws_get(c, W_GRID_STATE, sizeof(unsigned) * state_words(grid_dim(n_obs)), &state)) != EZO_OK)
+            return s;
+    }
+    if (kind == PREP_NEAR && (s = ezo_ws_get(c, W_NEAR, sizeof(uint2) * cells, &near)) != EZO_OK) return s;
+    if (kind != PREP_RECORDS && (s = ezo_ws_get(c, W_GRID_LIST, sizeof(unsigned short) * cells * kGridCap, &list)) != EZO_OK)
+        return s;
+    if (nv) *nv = NearView{(const GridGeom*)geom, (const uint2*)near, (const unsigned short*)list};
+    return prep_obstacles_into(c, r, obs, n_obs, st, kind, near, rec, centre, geom, count, state, list, ov, gv, ei);
 }
 
 // ---------------------------------------------------------------------------
@@ -182,7 +200,9 @@ constexpr size_t kScrCount = kScrGeom + 256;
 constexpr size_t kScrCells = 32 * 32 * 32;
 constexpr size_t kScrState = kScrCount + sizeof(int) * kScrCells;
 constexpr size_t kScrList = kScrState + kScrCells / 4;
-constexpr size_t kScrBytes = kScrList + sizeof(unsigned short) * kScrCells * kGridCap;
+constexpr size_t kScrNear = kScrList + sizeof(unsigned short) * kScrCells * kGridCap;
+constexpr size_t kScrBytes = kScrNear + sizeof(uint2) * kNearCells;
+static_assert(kNearCells == kScrCells, "the distance field's lists take the grid lists' place");
 static_assert(sizeof(GridGeom) <= 256, "grid geometry slot");
 static_assert(kScrList % 256 == 0, "list slot alignment");
 
@@ -330,6 +350,40 @@ ezo_status launch_check(ezo_ctx* c, const ezo_robot* r, const ObsView& ov, const
         else EZO_LAUNCH_CHECK(false, false);
     }
 #undef EZO_LAUNCH_CHECK
+    HIP_TRY(c, hipGetLastError());
+    return EZO_OK;
+}
+
+// Signed distances of spheres by the distance field (k_distances), or over all
+// pairs: the field's build and launch (20 us for 200 obstacles, 95 for 4096)
+// pay from about kNearPairs pairs on (about 25 us at all pairs).
+constexpr double kNearPairs = 1.0e8;
+bool near_pays(const ezo_ctx* c, const ezo_robot* r, int64_t n, int n_obs) {
+    if (r->B > 0 || c->n_ebox > 0 || r->S == 0) return false;
+    return n_obs == 0 || (n_obs <= 65535 && (double)n * r->S * n_obs >= kNearPairs);
+}
+
+// Its shapes: W waves of T / W configurations each (tuned as the all-pairs
+// shapes are; 4 x 8 otherwise).
+bool near_shape(const TileCfg& g) {
+    return (g.W == 1 || g.W == 2 || g.W == 4) && pow2_tile(g.T) && g.T >= g.W && g.T <= 8 * g.W && g.stage == 0;
+}
+
+ezo_status launch_distances(ezo_ctx* c, const ezo_robot* r, const ObsView& ov, const NearView& nv, const float* q,
+                            int64_t n, int64_t sn, int64_t sd, uint8_t* flags, float* min_sd, float* min_sd_self,
+                            hipStream_t st, const TileCfg* shape = nullptr) {
+    TileCfg g{32, 4, 0, 1}, tuned;
+    if (shape)
+        g = *shape;
+    else if (ezo_tune_lookup(tune_key(c, r, TUNE_CHECK_SD, ov.n, n), &tuned) && near_shape(tuned))
+        g = tuned;
+    const int W = g.W, CW = g.T / W;
+    const size_t lds = robot_stage_bytes(r->S, r->view.n_blocks, r->P, false) + (size_t)W * sd_wave_bytes(CW);
+    static_assert(16 * (kMaxParts + kMaxPartPairs + EZO_MAX_SPHERES + EZO_MAX_SPHERES / 4) +
+                  4 * (16 * (8 * kRecRows + kSdList) + 128) <= 65536, "the largest robot's tables and the waves' shares fit the LDS");
+    const int64_t groups = (n + g.T - 1) / g.T;
+    hipLaunchKernelGGL(k_distances, dim3((unsigned)std::min<int64_t>(groups, kNumCU * 64 / W)), dim3(64 * W), lds, st,
+                       r->view, ov, nv, CW, q, n, sn, sd, flags, min_sd, min_sd_self);
     HIP_TRY(c, hipGetLastError());
     return EZO_OK;
 }
@@ -538,6 +592,20 @@ ezo_status tune_check_inplace(ezo_ctx* c, const ezo_robot* r, const ObsView& ov,
     auto run = [&](const TileCfg& cfg) {
         return launch_check<SD>(c, r, ov, gv, q, n_t, sn, sd, 0, flags, min_sd, min_sd_self, 0, 1, nullptr, it, st,
                                 nullptr, 0.f, nullptr, &cfg);
+    };
+    return ezo_tune_search(c, k, cands, st, run, &g);
+}
+
+ezo_status tune_distances_inplace(ezo_ctx* c, const ezo_robot* r, const ObsView& ov, const NearView& nv, const float* q,
+                                  int64_t n, int64_t sn, int64_t sd, uint8_t* flags, float* min_sd,
+                                  float* min_sd_self, hipStream_t st) {
+    const TuneKey k = tune_key(c, r, TUNE_CHECK_SD, ov.n, n);
+    TileCfg g;
+    if (!c->autotune || ezo_tune_lookup(k, &g)) return EZO_OK;
+    const std::vector<TileCfg> cands = {{32, 4, 0, 1}, {16, 4, 0, 1}, {16, 2, 0, 1}, {8, 2, 0, 1}, {8, 1, 0, 1}};
+    const int64_t n_t = std::min<int64_t>(n, 1LL << 19);
+    auto run = [&](const TileCfg& cfg) {
+        return launch_distances(c, r, ov, nv, q, n_t, sn, sd, flags, min_sd, min_sd_self, st, &cfg);
     };
     return ezo_tune_search(c, k, cands, st, run, &g);
 }
@@ -1022,15 +1090,25 @@ ezo_status ezo_check_collisions(ezo_ctx* c, const ezo_robot* r, const float* obs
     hipStream_t st = as_stream(stream);
     ObsView ov;
     GridView gv;
-    ezo_status s = prep_obstacles(c, r, obs, n_obs, st, &ov, &gv);
-    if (s) return s;
+    NearView nv{};
     IterArgs it{nullptr, 0, 0, 0, 0};
+    ezo_status s;
     if (min_sd || min_sd_self) {
+        const bool near = near_pays(c, r, n, n_obs);
+        if ((s = prep_obstacles(c, r, obs, n_obs, st, &ov, &gv, nullptr,
+                                near && n_obs > 0 ? PREP_NEAR : PREP_RECORDS, &nv)))
+            return s;
+        if (near) {
+            if ((s = tune_distances_inplace(c, r, ov, nv, q, n, stride_n, stride_d, flags, min_sd, min_sd_self, st)))
+                return s;
+            return launch_distances(c, r, ov, nv, q, n, stride_n, stride_d, flags, min_sd, min_sd_self, st);
+        }
         if ((s = tune_check_inplace<true>(c, r, ov, gv, q, n, stride_n, stride_d, flags, min_sd, min_sd_self, st)))
             return s;
         return launch_check<true>(c, r, ov, gv, q, n, stride_n, stride_d, 0, flags, min_sd, min_sd_self, 0, 1,
                                   nullptr, it, st);
     }
+    if ((s = prep_obstacles(c, r, obs, n_obs, st, &ov, &gv))) return s;
     if ((s = tune_check_inplace<false>(c, r, ov, gv, q, n, stride_n, stride_d, flags, nullptr, nullptr, st))) return s;
     return launch_check<false>(c, r, ov, gv, q, n, stride_n, stride_d, 0, flags, nullptr, nullptr, 0, 1, nullptr, it,
                                st);
@@ -1053,9 +1131,17 @@ ezo_status ezo_check_collisions_noalloc(ezo_ctx* c, const ezo_robot* r, const fl
     ObsView ov;
     GridView gv;
     unsigned char* p = c->scratch;
-    ezo_status s = prep_obstacles_into(c, r, obs, n_obs, st, p + kScrRec, p + kScrCentre, p + kScrGeom,
-                                       p + kScrCount, p + kScrState, p + kScrList, &ov, &gv);
+    const bool sd = min_sd || min_sd_self, near = sd && near_pays(c, r, n, n_obs);
+    ezo_status s = prep_obstacles_into(c, r, obs, n_obs, st,
+                                       !sd ? PREP_GRID : (near && n_obs > 0 ? PREP_NEAR : PREP_RECORDS), p + kScrNear,
+                                       p + kScrRec, p + kScrCentre, p + kScrGeom, p + kScrCount, p + kScrState,
+                                       p + kScrList, &ov, &gv);
     if (s) return s;
+    if (near) {
+        const NearView nv{(const GridGeom*)(p + kScrGeom), (const uint2*)(p + kScrNear),
+                          (const unsigned short*)(p + kScrList)};
+        return launch_distances(c, r, ov, nv, q, n, stride_n, stride_d, flags, min_sd, min_sd_self, st);
+    }
     // launch shapes: the tuning cache or the size heuristic (never a timing
     // search, which would write the outputs repeatedly)
     IterArgs it{nullptr, 0, 0, 0, 0};
@@ -1076,7 +1162,7 @@ ezo_status ezo_sphere_centres(ezo_ctx* c, const ezo_robot* r, const float* q, in
     hipStream_t st = as_stream(stream);
     ObsView ov;
     GridView gv;
-    ezo_status s = prep_obstacles(c, r, nullptr, 0, st, &ov, &gv);   // zero shift
+    ezo_status s = prep_obstacles(c, r, nullptr, 0, st, &ov, &gv, nullptr, PREP_RECORDS);   // zero shift
     if (s) return s;
     int T = 16;
     while (T > 1 && tile_smem_bytes(T, r->slots, 4) > c->lds_cap) T >>= 1;
@@ -1737,7 +1823,7 @@ ezo_status ezo_collision_map(ezo_ctx* c, const ezo_robot* r, const float* q, int
     if (n_nodes == 0) return EZO_OK;
     ObsView ov;
     GridView gv;
-    ezo_status s = prep_obstacles(c, r, nullptr, 0, st, &ov, &gv);   // zero shift: world frame
+    ezo_status s = prep_obstacles(c, r, nullptr, 0, st, &ov, &gv, nullptr, PREP_RECORDS);   // zero shift: world frame
     if (s) return s;
     ov.n_ebox = 0;                                                    // the map holds the robot only
     int T = 16;

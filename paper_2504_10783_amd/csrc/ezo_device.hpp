@@ -127,12 +127,13 @@ struct GridGeom {
     float ihx, ihy, ihz;       // 1 / cell size
     float reach;               // r_sphere_max + slack
     float hit_reach;           // r_sphere_min - slack (hugely negative for a robot without spheres)
+    float r_max;               // largest obstacle radius
 };
 
 // Grid geometry through scalar loads (wave-uniform, written by earlier kernels).
 __device__ __forceinline__ GridGeom load_geom(const GridGeom* p) {
     const __attribute__((address_space(4))) float* s = (const __attribute__((address_space(4))) float*)p;
-    return GridGeom{s[0], s[1], s[2], s[3], s[4], s[5], s[6], s[7], s[8], s[9], s[10]};
+    return GridGeom{s[0], s[1], s[2], s[3], s[4], s[5], s[6], s[7], s[8], s[9], s[10], s[11]};
 }
 
 struct GridView {

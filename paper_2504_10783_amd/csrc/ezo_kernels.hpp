@@ -7,6 +7,7 @@
 // is final (>= 0) are skipped by every kernel.
 #pragma once
 #include "ezo_device.hpp"
+#include "ezo_distance.hpp"
 #include "ezo_screen.hpp"
 
 namespace ezo {
@@ -119,7 +120,7 @@ constexpr float kGridSlack = 1e-4f;
 
 __global__ void __launch_bounds__(256) k_prep_obstacles(const float* __restrict__ obs, int n, float4* __restrict__ rec,
                                                         float4* __restrict__ centre, GridGeom* __restrict__ geom,
-                                                        int G, float r_sphere_max, float r_sphere_min,
+                                                        int G, float r_sphere_max, float r_sphere_min, float grow,
                                                         int* __restrict__ count, int count_init,
                                                         unsigned* __restrict__ state, unsigned state_init, int clear_wg, EdgeInit ei) {
     // Workgroups 1 .. clear_wg set the grid's cell counts and states to their
@@ -138,39 +139,49 @@ __global__ void __launch_bounds__(256) k_prep_obstacles(const float* __restrict_
         init_edge(ei, (int)((blockIdx.x - 1 - clear_wg) * blockDim.x + threadIdx.x));
         return;
     }
-    __shared__ float red[7][256];
+    __shared__ float red[7][4];
     const int tid = threadIdx.x;
-    float mn[3] = {kHuge, kHuge, kHuge}, mx[3] = {-kHuge, -kHuge, -kHuge}, rmax = 0.f;
-    for (int o = tid; o < n; o += blockDim.x) {
-        for (int k = 0; k < 3; ++k) {
-            const float v = obs[4 * (size_t)o + k];
-            mn[k] = fminf(mn[k], v);
-            mx[k] = fmaxf(mx[k], v);
-        }
-        rmax = fmaxf(rmax, obs[4 * (size_t)o + 3]);
-    }
-    for (int k = 0; k < 3; ++k) { red[k][tid] = mn[k]; red[3 + k][tid] = mx[k]; }
-    red[6][tid] = rmax;
-    __syncthreads();
-    for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-        if (tid < s) {
+    float v[7] = {kHuge, kHuge, kHuge, -kHuge, -kHuge, -kHuge, 0.f};   // min x y z, max x y z, max r
+    for (int o = tid; o < n; o += 4 * blockDim.x) {
+        // four records in flight a thread (a repeated last one changes nothing)
+        float x[4][4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) x[i][k] = obs[4 * (size_t)min(o + i * (int)blockDim.x, n - 1) + k];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+#pragma unroll
             for (int k = 0; k < 3; ++k) {
-                red[k][tid] = fminf(red[k][tid], red[k][tid + s]);
-                red[3 + k][tid] = fmaxf(red[3 + k][tid], red[3 + k][tid + s]);
+                v[k] = fminf(v[k], x[i][k]);
+                v[3 + k] = fmaxf(v[3 + k], x[i][k]);
             }
-            red[6][tid] = fmaxf(red[6][tid], red[6][tid + s]);
+            v[6] = fmaxf(v[6], x[i][3]);
         }
-        __syncthreads();
+    }
+#pragma unroll
+    for (int k = 0; k < 7; ++k) {
+        const bool lo = k < 3;
+        const float m = lo ? wave_min(v[k]) : -wave_min(-v[k]);
+        if ((tid & 63) == 0) red[k][tid >> 6] = m;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 7; ++k) {
+        const bool lo = k < 3;
+        v[k] = red[k][0];
+#pragma unroll
+        for (int w = 1; w < 4; ++w) v[k] = lo ? fminf(v[k], red[k][w]) : fmaxf(v[k], red[k][w]);
     }
     float c[3] = {0.f, 0.f, 0.f}, half[3] = {0.f, 0.f, 0.f};
     if (n > 0)
         for (int k = 0; k < 3; ++k) {
-            c[k] = 0.5f * (red[k][0] + red[3 + k][0]);
-            half[k] = 0.5f * (red[3 + k][0] - red[k][0]);
+            c[k] = 0.5f * (v[k] + v[3 + k]);
+            half[k] = 0.5f * (v[3 + k] - v[k]);
         }
     if (tid == 0) {
         centre[0] = make_float4(c[0], c[1], c[2], 0.f);
-        const float margin = r_sphere_max + red[6][0] + kGridSlack;
+        const float margin = r_sphere_max + v[6] + kGridSlack + 2.f * grow * fmaxf(half[0], fmaxf(half[1], half[2]));
         GridGeom g;
         float h[3];
         for (int k = 0; k < 3; ++k) h[k] = 2.f * (half[k] + margin) / (float)G;
@@ -178,6 +189,7 @@ __global__ void __launch_bounds__(256) k_prep_obstacles(const float* __restrict_
         g.hx = h[0]; g.hy = h[1]; g.hz = h[2];
         g.ihx = 1.f / h[0]; g.ihy = 1.f / h[1]; g.ihz = 1.f / h[2];
         g.reach = r_sphere_max + kGridSlack;
+        g.r_max = v[6];
         g.hit_reach = r_sphere_min - kGridSlack - 1e-5f * (h[0] + h[1] + h[2]);
         geom[0] = g;
     }
