@@ -76,6 +76,182 @@ __global__ void __launch_bounds__(256) k_mlp_out(RowSource src, int64_t rows, in
 }
 
 // ---------------------------------------------------------------------------
+// Whole forward pass of rows without batches, H = 64 HB <= 256: persistent
+// workgroups of 4 HB waves take 16 RB rows at a time; wave w owns units
+// 16 w .. + 15 of every layer and keeps their BF16 weights of both hidden layers
+// in registers (64 VGPRs at H = 256), so that a tile reads its inputs and
+// writes its outputs only: the activations of one layer go to the next through
+// LDS (two buffers).  Products are taken as W h: lane l of a 16x16 result holds
+// units 4 (l / 16) .. + 3 of row l % 16, four neighbours of one activation row.
+// Layer 1 is v_mfma_f32_16x16x4_f32 started from the bias (a chain of fmaf in
+// the order of the inputs); the hidden layers keep K ascending and the bias
+// after the sum.  The products of the next 16 rows stand between the activations
+// of these, and the next tile passes layer 1 beside this one's layer 3.
+// Bound by issue: ten VALU slots an activation, two of them transcendental
+// (0.34 ms for 1 M rows at H = 256), and the products (0.14 ms).  1 M rows at
+// H = 256: layer, two products and output as launches of their own, activations
+// through memory, 2540 us; this 480 us.
+// ---------------------------------------------------------------------------
+constexpr int kPredU = 1;                // 16-unit tiles per wave (two: 423 us against 345 at H = 192, 473 against 480 at 256)
+
+template <int HB>
+__host__ __device__ constexpr size_t predict_lds_bytes(int RB) {
+    return sizeof(__bf16) * (size_t)2 * 16 * RB * (64 * HB) + sizeof(float) * (size_t)4 * HB / kPredU * 16 * RB;
+}
+
+typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
+
+// z (+ b) through the activation, rounded to BF16
+__device__ __forceinline__ bf16x4 silu4(f32x4 z) {
+    bf16x4 h;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) h[r] = (__bf16)siluf(z[r]);
+    return h;
+}
+__device__ __forceinline__ bf16x4 silu4(f32x4 z, f32x4 b) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) z[r] += b[r];
+    return silu4(z);
+}
+
+template <int HB, int RB>
+__global__ void __launch_bounds__(256 * HB / kPredU, 4)
+k_mlp_predict(RowSource src, int D, const float* __restrict__ P, const __bf16* __restrict__ W2b,
+              const __bf16* __restrict__ W3b, float* __restrict__ y) {
+    constexpr int H = 64 * HB, LD = H, KS = H / 32, R = 16 * RB, U = kPredU, NW = 4 * HB / U;
+    extern __shared__ __attribute__((aligned(16))) __bf16 predict_lds[];
+    __bf16* const ha = predict_lds;
+    __bf16* const hb = ha + R * LD;
+    float* const red = reinterpret_cast<float*>(hb + R * LD);        // [NW][R] partial outputs
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, c = lane & 15, g = lane >> 4, n0 = 16 * U * w;
+    const MlpOffsets o = mlp_offsets(D, H);
+    // 16-byte chunk j of row r (r % 16 == c) stands at chunk j ^ sc of its row, so
+    // that the 16-lane groups of a 128-bit LDS read, which mix two values of g,
+    // touch every bank once
+    const int sc = HB % 2 ? c >> 1 : c;
+    auto at = [&](__bf16* h, int rb, int chunk) { return h + (16 * rb + c) * LD + 8 * (chunk ^ sc); };
+    const int wc = (n0 + 4 * g) >> 3, wo = 4 * (g & 1);              // where this lane's results go
+    bf16x8 w2[U][KS], w3[U][KS];
+    float w1[U][2];
+    f32x4 b1[U], b2[U], b3[U], w4[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int n = n0 + 16 * u + c;                               // this lane's unit as a weight row
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+            w2[u][k] = *reinterpret_cast<const bf16x8*>(W2b + n * H + 32 * k + 8 * g);
+            w3[u][k] = *reinterpret_cast<const bf16x8*>(W3b + n * H + 32 * k + 8 * g);
+        }
+#pragma unroll
+        for (int s = 0; s < 2; ++s) w1[u][s] = 4 * s + g < D ? P[o.W1 + n * D + 4 * s + g] : 0.f;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int m = n0 + 16 * u + 4 * g + r;                   // the units of its results
+            b1[u][r] = P[o.b1 + m];
+            b2[u][r] = P[o.b2 + m];
+            b3[u][r] = P[o.b3 + m];
+            w4[u][r] = P[o.W4 + m];
+        }
+    }
+    const float b4 = P[o.b4];
+    const int64_t tiles = (src.rows + R - 1) / R;
+    float x[RB][2];
+    auto load_x = [&](int64_t t) {
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            const int64_t r = t * R + 16 * rb + c;
+            const bool ok = r < src.rows;
+            const float* q = src.q + (ok ? r : 0) * src.sn + g * src.sd;
+#pragma unroll
+            for (int s = 0; s < 2; ++s) x[rb][s] = ok && 4 * s + g < D ? q[4 * s * src.sd] : 0.f;
+        }
+    };
+    auto layer1 = [&] {
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                f32x4 z = b1[u];
+#pragma unroll
+                for (int s = 0; s < 2; ++s)
+                    z = __builtin_amdgcn_mfma_f32_16x16x4f32(w1[u][s], x[rb][s] * kInvPi, z, 0, 0, 0);
+                *reinterpret_cast<bf16x4*>(at(ha, rb, wc + 2 * u) + wo) = silu4(z);
+            }
+    };
+    // both unit tiles of a hidden layer for one block of 16 rows
+    auto hidden = [&](__bf16* h, const bf16x8 (&wt)[U][KS], int rb, f32x4 (&z)[U]) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) z[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+            const bf16x8 a = *reinterpret_cast<const bf16x8*>(at(h, rb, 4 * k + g));
+#pragma unroll
+            for (int u = 0; u < U; ++u) z[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wt[u][k], a, z[u], 0, 0, 0);
+        }
+    };
+    // the matrix unit's work on the next 16 rows between the activations of these
+    auto mix = [&](bool next) {
+        if (next)
+#pragma unroll
+            for (int k = 0; k < U * KS; ++k) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);     // one MFMA
+                __builtin_amdgcn_sched_group_barrier(0x002, 40 / KS, 0);     // its share of the VALU work
+            }
+    };
+    auto store = [&](int64_t t) {
+        for (int r = tid; r < R; r += 64 * NW) {
+            float s = b4;
+#pragma unroll
+            for (int v = 0; v < NW; ++v) s += red[v * R + r];
+            if (t * R + r < src.rows) y[t * R + r] = s;
+        }
+    };
+    int64_t t = blockIdx.x, done = -1;
+    if (t >= tiles) return;
+    load_x(t);
+    layer1();
+    while (true) {
+        const int64_t tn = t + gridDim.x;
+        __syncthreads();
+        if (done >= 0) store(done);
+        if (tn < tiles) load_x(tn);
+        f32x4 z[2][U];
+        hidden(ha, w2, 0, z[0]);
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            if (rb + 1 < RB) hidden(ha, w2, rb + 1, z[(rb + 1) & 1]);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                *reinterpret_cast<bf16x4*>(at(hb, rb, wc + 2 * u) + wo) = silu4(z[rb & 1][u], b2[u]);
+            mix(rb + 1 < RB);
+        }
+        __syncthreads();
+        hidden(hb, w3, 0, z[0]);
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            if (rb + 1 < RB) hidden(hb, w3, rb + 1, z[(rb + 1) & 1]);
+            float s = 0.f;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const bf16x4 h = silu4(z[rb & 1][u], b3[u]);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) s = fmaf(w4[u][r], (float)h[r], s);
+            }
+            mix(rb + 1 < RB);
+            s += __shfl_xor(s, 16);
+            s += __shfl_xor(s, 32);
+            if (g == 0) red[w * R + 16 * rb + c] = s;
+        }
+        done = t;
+        if (tn >= tiles) break;
+        layer1();
+        t = tn;
+    }
+    __syncthreads();
+    store(done);
+}
+
+// ---------------------------------------------------------------------------
 // BF16 MFMA GEMM  C[M][N] = sum_k A(m, k) B(k, n)
 // A(m, k) = A[m*sam + k*sak] with AK: sak == 1 (K contiguous) else sam == 1
 // (M contiguous); B(k, n) = B[k*sbk + n*sbn] with BK: sbk == 1 else sbn == 1.

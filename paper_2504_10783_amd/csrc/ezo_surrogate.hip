@@ -176,6 +176,22 @@ ezo_status forward_backward(ezo_ctx* c, ezo_surrogate* s, const RowSource& src, 
     return EZO_OK;
 }
 
+// Whole forward pass in one launch: 64 rows a tile, 16 while tiles of 64 would
+// leave CUs without one (H = 256: 11 us up to 4096 rows, most of it the weights'
+// way into the registers).
+template <int HB>
+void predict(hipStream_t st, const ezo_surrogate* s, const RowSource& src, float* pred) {
+    const bool small = src.rows < 64 * 256;
+    const int64_t tiles = (src.rows + (small ? 15 : 63)) / (small ? 16 : 64);
+    const dim3 grid((unsigned)std::min<int64_t>(tiles, 256 * (4 / HB))), block(256 * HB / kPredU);
+    if (small)
+        hipLaunchKernelGGL((k_mlp_predict<HB, 1>), grid, block, predict_lds_bytes<HB>(1), st, src, s->D, s->P, s->W2b,
+                           s->W3b, pred);
+    else
+        hipLaunchKernelGGL((k_mlp_predict<HB, 4>), grid, block, predict_lds_bytes<HB>(4), st, src, s->D, s->P, s->W2b,
+                           s->W3b, pred);
+}
+
 bool valid_train(const ezo_train_params* hp) {
     return hp && hp->epochs >= 0 && hp->batch >= 64 && hp->batch % 64 == 0 && hp->lr > 0 && hp->beta1 >= 0 &&
            hp->beta1 < 1 && hp->beta2 >= 0 && hp->beta2 < 1 && hp->adam_eps > 0 && hp->huber_delta > 0 &&
@@ -209,6 +225,15 @@ ezo_status ezo_surrogate_reserve(ezo_ctx* c, const ezo_surrogate* s, int64_t row
 ezo_status ezo_surrogate_forward_rows(ezo_ctx* c, const ezo_surrogate* s, const RowSource& src, float* pred,
                                       const int* status, hipStream_t st) {
     const int D = s->D, H = s->H;
+    if (H <= 256 && !status && src.rows_per_batch == 0) {
+        if (src.rows <= 0) return EZO_OK;
+        if (H == 256) predict<4>(st, s, src, pred);
+        else if (H == 192) predict<3>(st, s, src, pred);
+        else if (H == 128) predict<2>(st, s, src, pred);
+        else predict<1>(st, s, src, pred);
+        HIP_TRY(c, hipGetLastError());
+        return EZO_OK;
+    }
     void *h1, *h2;
     const int64_t R = std::min<int64_t>(kChunkRows, round64(std::max<int64_t>(src.rows, 1)));
     ezo_status e;

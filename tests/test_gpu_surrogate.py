@@ -251,3 +251,45 @@ def test_trained_screen_gain(ezo, ctx):
     out = np.abs(sd) >= 1e-5
     print(f"screened run: {F - 14} planes, every c* colliding: {bool(np.all(f[out] == 1))}")
     assert np.all(f[out] == 1)
+
+
+@pytest.mark.parametrize("D,H", [(7, 256), (8, 192), (2, 128), (5, 64)])
+@pytest.mark.parametrize("n", [1, 15, 17, 16383, 16385, 70001])
+def test_fused_forward_matches_layers(ezo, ctx, D, H, n):
+    """Sizes around the 16- and 64-row tiles and several tiles per workgroup,
+    against the same network in FP32 with the same BF16 roundings.  An
+    activation whose last FP32 bits differ may round to the neighbouring BF16
+    number: 2^-8 of it, through weights below H^-1/2; the bound allows for a few
+    such flips per layer (unit gain, three layers: 8 2^-8 / sqrt(H))."""
+    print_case("screen forward", D, H, n)
+    s = ezo.Surrogate(ctx, D, H, seed=9)
+    q = torch.from_numpy(draw.uniform_q(61, n, np.full(D, -3.0, np.float32), np.full(D, 3.0, np.float32))).cuda()
+    q[n // 2] = 1.0e4                                       # far out: saturated activations
+    got = torch.full((n + 2,), 7.0, device="cuda")
+    s.predict(q, got[:n])
+    p = torch.from_numpy(np.asarray(s.get_params(), np.float32)).cuda()
+    cut = [H * D, H, H * H, H, H * H, H, H, 1]
+    W1, b1, W2, b2, W3, b3, W4, b4 = torch.split(p, cut)
+    act = lambda z: (z / (1.0 + torch.exp(-z))).bfloat16().float()
+    h = act((q / np.pi) @ W1.view(H, D).t() + b1)
+    h = act(h @ W2.view(H, H).bfloat16().float().t() + b2)
+    h = act(h @ W3.view(H, H).bfloat16().float().t() + b3)
+    want = h @ W4 + b4
+    torch.cuda.synchronize()
+    bound = 8 * 2.0 ** -8 / np.sqrt(H) * torch.clamp(h.abs().amax(1), min=1.0)
+    assert bool(((got[:n] - want).abs() <= bound).all())
+    assert got[n:].tolist() == [7.0, 7.0]
+
+
+def test_fused_forward_keeps_nonfinite_rows_apart(ezo, ctx):
+    D, H, n = 7, 256, 200
+    s = ezo.Surrogate(ctx, D, H, seed=9)
+    q = torch.from_numpy(draw.uniform_q(62, n, np.full(D, -3.0, np.float32), np.full(D, 3.0, np.float32))).cuda()
+    ref, got = torch.zeros(n, device="cuda"), torch.zeros(n, device="cuda")
+    s.predict(q, ref)
+    q[37, 2], q[150, 6] = float("nan"), float("inf")
+    s.predict(q, got)
+    torch.cuda.synchronize()
+    keep = torch.ones(n, dtype=torch.bool, device="cuda")
+    keep[37] = keep[150] = False
+    assert torch.equal(got[keep], ref[keep]) and bool(torch.isnan(got[37])) and bool(torch.isnan(got[150]))
