@@ -1613,147 +1613,273 @@ __device__ __forceinline__ void voxel_range(float x, float R, float lo, float in
     *i1 = (int)fminf(ceilf(b), (float)(n - 1));
 }
 
-// One workgroup per tile of T nodes: FK into LDS, then every (node, sphere)
-// and (node, box) item tests the voxels within reach and sets the node's bit
-// in each hit voxel's row.
-template <int T, bool BOX>
-__global__ void __launch_bounds__(256) k_collision_map(RobotView rb, ObsView ob, const float* __restrict__ q,
-                                                       int64_t n, float3 lo, float side, int3 dims,
+// kMapNodes nodes (one byte of every row) against `count` voxels from v0 on: FK
+// into LDS (T nodes at a time), then kMapLanes lanes per (node, sphere) test the
+// planes within reach and set the node's bit in an LDS table of one byte a voxel;
+// the nonzero bytes go to the (cleared) map.  Workgroups whose linear index is
+// the same mod 8 (one XCD) take neighbouring bytes, so that a line is completed
+// in one L2.  Bound by the tests' VALU work and the byte stores; a global
+// atomicOr per hit took 1375 us for 35 000 nodes x 36 100 voxels, this 157 (256
+// threads 219, 1024 260; four lanes per sphere 166, one 156).
+constexpr int kMapNodes = 8, kMapLanes = 2, kMapThreads = 512;
+
+template <bool BOX>
+__global__ void __launch_bounds__(kMapThreads) k_collision_map(RobotView rb, ObsView ob, const float* __restrict__ q,
+                                                       int64_t n, float3 lo, float side, int3 dims, int T, int span,
+                                                       int64_t n_voxels, int64_t group0, int64_t part0,
                                                        uint32_t* __restrict__ map, int64_t row_words) {
     extern __shared__ __align__(16) char smem[];
-    const int64_t base = (int64_t)blockIdx.x * T;
-    if (base >= n) return;
-    const int nv = (int)((n - base) < T ? (n - base) : T);
+    const int64_t group = group0 + (int64_t)(blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    if (group * kMapNodes >= n) return;
+    const int64_t v0 = (part0 + blockIdx.y) * span;
+    if (v0 >= n_voxels) return;
+    const int count = (int)((n_voxels - v0) < span ? (n_voxels - v0) : span);
     TileSmem t = carve_tile(smem, T, tile_slots(rb.n_spheres, rb.n_boxes), blockDim.x >> 6);
-    for (int i = threadIdx.x; i < T * rb.dof; i += blockDim.x) {
-        const int c = i % T, j = i / T;
-        if (c < nv) t.q[c * kMaxDof + j] = q[(base + c) * rb.dof + j];
-    }
-    __syncthreads();
-    tile_fk<BOX>(rb, ob, t, T, nv);
+    uint32_t* const bits = reinterpret_cast<uint32_t*>(smem + tile_smem_bytes(T, tile_slots(rb.n_spheres, rb.n_boxes),
+                                                                             blockDim.x >> 6));
+    for (int i = threadIdx.x; i < (count + 3) / 4; i += blockDim.x) bits[i] = 0u;
     const float rv = 0.866025403784438647f * side, inv = 1.f / side;
     const int S = rb.n_spheres;
-    for (ItemWalk w(nv); w.k < S; w.next(nv)) {
-        const int c = w.c;
-        const float4 C = t.cen[w.k * T + c];
-        if (!(isfinite(C.x) && isfinite(C.y) && isfinite(C.z))) continue;
-        const float R = C.w + rv;
-        int i0, i1, j0, j1, k0, k1;
-        voxel_range(C.x, R, lo.x, inv, dims.x, &i0, &i1);
-        voxel_range(C.y, R, lo.y, inv, dims.y, &j0, &j1);
-        voxel_range(C.z, R, lo.z, inv, dims.z, &k0, &k1);
-        const int64_t node = base + c;
-        const uint32_t bit = 1u << (node & 31);
-        for (int k = k0; k <= k1; ++k) {
-            const float dz = C.z - fmaf(side, (float)k + 0.5f, lo.z);
-            for (int j = j0; j <= j1; ++j) {
-                const float dy = C.y - fmaf(side, (float)j + 0.5f, lo.y);
-                const float dyz = fmaf(dy, dy, dz * dz);
-                for (int i = i0; i <= i1; ++i) {
-                    const float dx = C.x - fmaf(side, (float)i + 0.5f, lo.x);
-                    if (fmaf(dx, dx, dyz) < R * R) {
-                        const int64_t v = ((int64_t)k * dims.y + j) * dims.x + i;
-                        atomicOr(map + v * row_words + (node >> 5), bit);
+    const int64_t plane = (int64_t)dims.x * dims.y;
+    const int kmin = (int)(v0 / plane), kmax = (int)((v0 + count - 1) / plane);       // planes of this span
+    for (int sub = 0; sub < kMapNodes; sub += T) {
+        const int64_t base = group * kMapNodes + sub;
+        if (base >= n) break;
+        const int nv = (int)((n - base) < T ? (n - base) : T);
+        __syncthreads();
+        for (int i = threadIdx.x; i < T * rb.dof; i += blockDim.x) {
+            const int c = i % T, j = i / T;
+            if (c < nv) t.q[c * kMaxDof + j] = q[(base + c) * rb.dof + j];
+        }
+        __syncthreads();
+        tile_fk<BOX>(rb, ob, t, T, nv);
+        for (ItemWalk w(nv); w.k < S * kMapLanes; w.next(nv)) {
+            const int c = w.c;
+            const float4 C = t.cen[(w.k / kMapLanes) * T + c];
+            if (!(isfinite(C.x) && isfinite(C.y) && isfinite(C.z))) continue;
+            const float R = C.w + rv;
+            int i0, i1, j0, j1, k0, k1;
+            voxel_range(C.x, R, lo.x, inv, dims.x, &i0, &i1);
+            voxel_range(C.y, R, lo.y, inv, dims.y, &j0, &j1);
+            voxel_range(C.z, R, lo.z, inv, dims.z, &k0, &k1);
+            k0 = max(k0, kmin);
+            k1 = min(k1, kmax);
+            const float RR = R * R;
+            const int lane = w.k % kMapLanes, nj = j1 - j0 + 1;
+            if (nj <= 0) continue;
+            // eight voxels of a row at a time: their hits as bits, then the bytes
+            // of the up to three words that they lie in
+            for (int ib = i0; ib <= i1; ib += 8) {
+                float dx[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    dx[u] = ib + u <= i1 ? C.x - fmaf(side, (float)(ib + u) + 0.5f, lo.x) : INFINITY;
+                int j = j0 + lane, k = k0;
+                int64_t next = ((int64_t)k * dims.y + j) * dims.x + ib - v0;
+                while (true) {
+                    while (j > j1) {
+                        j -= nj;
+                        ++k;
+                        next += plane - (int64_t)nj * dims.x;
+                    }
+                    if (k > k1) break;
+                    const float dz = C.z - fmaf(side, (float)k + 0.5f, lo.z);
+                    const float dy = C.y - fmaf(side, (float)j + 0.5f, lo.y);
+                    const float dyz = fmaf(dy, dy, dz * dz);
+                    const int64_t first = next;
+                    j += kMapLanes;
+                    next += (int64_t)kMapLanes * dims.x;
+                    if (!(dyz < RR) || first <= -8 || first >= count) continue;
+                    unsigned m = 0;
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) m |= fmaf(dx[u], dx[u], dyz) < RR ? 1u << u : 0u;
+                    int v = (int)first;
+                    if (v < 0) {
+                        m >>= -v;
+                        v = 0;
+                    }
+                    if (count - v < 8) m &= (1u << (count - v)) - 1u;
+                    m <<= v & 3;
+#pragma unroll
+                    for (int u = 0; u < 3; ++u) {
+                        const unsigned nib = (m >> (4 * u)) & 15u;
+                        if (nib) atomicOr(&bits[(v >> 2) + u], ((nib * 0x204081u) & 0x1010101u) << (sub + c));
                     }
                 }
             }
         }
-    }
-    if (BOX) {
-        for (ItemWalk w(nv); w.k < rb.n_boxes; w.next(nv)) {
-            const int c = w.c;
-            const DBox X = tile_box(t, S, T, w.k, c);
-            if (!(isfinite(X.c[0]) && isfinite(X.c[1]) && isfinite(X.c[2]))) continue;
-            float e[3];                        // half widths of the box's world AABB
+        if (BOX) {
+            for (ItemWalk w(nv); w.k < rb.n_boxes * kMapLanes; w.next(nv)) {
+                const int c = w.c;
+                const DBox X = tile_box(t, S, T, w.k / kMapLanes, c);
+                if (!(isfinite(X.c[0]) && isfinite(X.c[1]) && isfinite(X.c[2]))) continue;
+                float e[3];                        // half widths of the box's world AABB
 #pragma unroll
-            for (int a = 0; a < 3; ++a)
-                e[a] = fmaf(X.h[0], fabsf(X.R[3 * a]), fmaf(X.h[1], fabsf(X.R[3 * a + 1]), X.h[2] * fabsf(X.R[3 * a + 2])));
-            int i0, i1, j0, j1, k0, k1;
-            voxel_range(X.c[0], e[0] + rv, lo.x, inv, dims.x, &i0, &i1);
-            voxel_range(X.c[1], e[1] + rv, lo.y, inv, dims.y, &j0, &j1);
-            voxel_range(X.c[2], e[2] + rv, lo.z, inv, dims.z, &k0, &k1);
-            const int64_t node = base + c;
-            const uint32_t bit = 1u << (node & 31);
-            for (int k = k0; k <= k1; ++k)
-                for (int j = j0; j <= j1; ++j)
-                    for (int i = i0; i <= i1; ++i) {
-                        const float x = fmaf(side, (float)i + 0.5f, lo.x), y = fmaf(side, (float)j + 0.5f, lo.y),
-                                    z = fmaf(side, (float)k + 0.5f, lo.z);
-                        if (hit_sphere_box(X, x, y, z, rv)) {
-                            const int64_t v = ((int64_t)k * dims.y + j) * dims.x + i;
-                            atomicOr(map + v * row_words + (node >> 5), bit);
+                for (int a = 0; a < 3; ++a)
+                    e[a] = fmaf(X.h[0], fabsf(X.R[3 * a]), fmaf(X.h[1], fabsf(X.R[3 * a + 1]), X.h[2] * fabsf(X.R[3 * a + 2])));
+                int i0, i1, j0, j1, k0, k1;
+                voxel_range(X.c[0], e[0] + rv, lo.x, inv, dims.x, &i0, &i1);
+                voxel_range(X.c[1], e[1] + rv, lo.y, inv, dims.y, &j0, &j1);
+                voxel_range(X.c[2], e[2] + rv, lo.z, inv, dims.z, &k0, &k1);
+                k0 = max(k0, kmin) + w.k % kMapLanes;
+                k1 = min(k1, kmax);
+                for (int k = k0; k <= k1; k += kMapLanes)
+                    for (int j = j0; j <= j1; ++j) {
+                        const int64_t row = ((int64_t)k * dims.y + j) * dims.x - v0;
+                        if (row + i1 < 0 || row + i0 >= count) continue;
+                        for (int i = i0; i <= i1; ++i) {
+                            const float x = fmaf(side, (float)i + 0.5f, lo.x), y = fmaf(side, (float)j + 0.5f, lo.y),
+                                        z = fmaf(side, (float)k + 0.5f, lo.z);
+                            const unsigned v = (unsigned)((int)row + i);
+                            if (v < (unsigned)count && hit_sphere_box(X, x, y, z, rv))
+                                atomicOr(&bits[v >> 2], 1u << (8 * (v & 3) + sub + c));
                         }
                     }
+            }
         }
+    }
+    __syncthreads();
+    uint8_t* const out = reinterpret_cast<uint8_t*>(map) + v0 * row_words * 4 + group;
+    for (int i = threadIdx.x; i < (count + 3) / 4; i += blockDim.x) {
+        const uint32_t b = bits[i];
+        if (b == 0u) continue;
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if ((b >> (8 * u)) & 255u) out[(int64_t)(4 * i + u) * row_words * 4] = (uint8_t)(b >> (8 * u));
     }
 }
 
-// Colliding nodes per voxel: popcount of each row.  One wave per row.
+// Colliding nodes per voxel: popcount of each row.  One wave per row, eight
+// loads in flight.
 __global__ void __launch_bounds__(256) k_row_popcount(const uint32_t* __restrict__ map, int64_t rows,
                                                       int64_t row_words, int64_t* __restrict__ counts) {
     const int64_t row = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     const int lane = threadIdx.x & 63;
     if (row >= rows) return;
+    const uint32_t* m = map + row * row_words;
     int64_t c = 0;
-    for (int64_t w = lane; w < row_words; w += 64) c += __popc(map[row * row_words + w]);
+    int64_t w = lane;
+    for (; w + 448 < row_words; w += 512) {
+        uint32_t x[8];
+        int s = 0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = m[w + 64 * u];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += __popc(x[u]);
+        c += s;
+    }
+    for (; w < row_words; w += 64) c += __popc(m[w]);
     for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off);
     if (lane == 0) counts[row] = c;
 }
 
 // Exclusive prefix sum of counts[0..n) into offsets[0..n] (offsets[n] = total).
-// One workgroup of 1024 threads, each summing a contiguous chunk.
+// Workgroup g sums all counts before its chunk (at most 64 chunks, so a count is
+// read at most 64 times), then scans the chunk 4096 counts at a time.  One
+// workgroup whose threads each walked their own run took 63 us for 36 100 rows;
+// this 9.
+constexpr int kScanTile = 4096, kScanGroups = 64;
+__host__ __device__ inline int64_t scan_chunk(int64_t n) {
+    const int64_t c = (n + kScanGroups - 1) / kScanGroups;
+    return (c + kScanTile - 1) / kScanTile * kScanTile;
+}
+
+// Inclusive sum over the wave's lanes.
+__device__ __forceinline__ int64_t wave_scan(int64_t v) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int64_t o = __shfl_up(v, off);
+        if (lane >= off) v += o;
+    }
+    return v;
+}
+
 __global__ void __launch_bounds__(1024) k_scan_counts(const int64_t* __restrict__ counts, int64_t n,
                                                       int64_t* __restrict__ offsets) {
-    __shared__ int64_t part[1024];
-    const int tid = threadIdx.x;
-    const int64_t chunk = (n + 1023) / 1024;
-    const int64_t a = min(n, tid * chunk), b = min(n, a + chunk);
-    int64_t sum = 0;
-    for (int64_t i = a; i < b; ++i) sum += counts[i];
-    part[tid] = sum;
+    __shared__ int64_t part[16];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int64_t chunk = scan_chunk(n), a = blockIdx.x * chunk, b = min(n, a + chunk);
+    int64_t before = 0;
+#pragma unroll 4
+    for (int64_t i = tid; i < a; i += 1024) before += counts[i];
+    before = __shfl(wave_scan(before), 63);
+    if (lane == 0) part[w] = before;
     __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {             // inclusive scan (Hillis-Steele)
-        const int64_t v = tid >= off ? part[tid - off] : 0;
+    before = 0;
+    for (int k = 0; k < 16; ++k) before += part[k];
+    for (int64_t t = a; t < b; t += kScanTile) {
+        const int64_t i = t + 4 * tid;
+        int64_t x[4], s = 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            x[u] = i + u < b ? counts[i + u] : 0;
+            s += x[u];
+        }
+        const int64_t incl = wave_scan(s);
+        __syncthreads();                                   // part[] has been read
+        if (lane == 63) part[w] = incl;
         __syncthreads();
-        part[tid] += v;
-        __syncthreads();
+        int64_t run = before + incl - s;
+        for (int k = 0; k < 16; ++k) {
+            if (k < w) run += part[k];
+            before += part[k];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (i + u < b) offsets[i + u] = run;
+            run += x[u];
+        }
     }
-    int64_t run = part[tid] - sum;
-    for (int64_t i = a; i < b; ++i) {
-        offsets[i] = run;
-        run += counts[i];
-    }
-    if (tid == 1023) offsets[n] = part[1023];
+    if (b == n && tid == 0) offsets[n] = before;
+}
+
+// Inclusive sum over the wave's lanes by DPP moves (row shifts, then the row and
+// half ends broadcast).
+__device__ __forceinline__ int wave_scan_dpp(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);     // row_shr:1, 2, 4, 8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);     // row_bcast:15
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);     // row_bcast:31
+    return v;
 }
 
 // Node ids of each row in increasing order at offsets[row]: one wave per row,
-// each lane one word at a time, the wave's exclusive prefix of the popcounts
-// placing the lanes' ids.
+// a lane one word of each group of 64 (four groups loaded ahead, empty ones
+// passed over), the wave's exclusive prefix of the popcounts placing the lanes'
+// ids.
 __global__ void __launch_bounds__(256) k_map_lists(const uint32_t* __restrict__ map, int64_t rows, int64_t row_words,
                                                    int64_t n_nodes, const int64_t* __restrict__ offsets,
                                                    int32_t* __restrict__ ids) {
     const int64_t row = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     const int lane = threadIdx.x & 63;
     if (row >= rows) return;
+    const uint32_t* m = map + row * row_words;
     int64_t pos = offsets[row];
-    for (int64_t w0 = 0; w0 < row_words; w0 += 64) {
-        const int64_t w = w0 + lane;
-        uint32_t bits = w < row_words ? map[row * row_words + w] : 0u;
-        const int cnt = __popc(bits);
-        int incl = cnt;
-        for (int off = 1; off < 64; off <<= 1) {
-            const int v = __shfl_up(incl, off);
-            if (lane >= off) incl += v;
+    if (pos == offsets[row + 1]) return;
+    constexpr int U = 4;
+    uint32_t x[U];
+    for (int64_t w0 = 0; w0 < row_words; w0 += 64 * U) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) x[u] = w0 + 64 * u + lane < row_words ? m[w0 + 64 * u + lane] : 0u;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            uint32_t bits = x[u];
+            if (__ballot(bits != 0u) == 0ull) continue;
+            const int64_t w = w0 + 64 * u + lane;
+            const int cnt = __popc(bits), incl = wave_scan_dpp(cnt);
+            int64_t p = pos + incl - cnt;
+            while (bits) {
+                const int b = __builtin_ctz(bits);
+                bits &= bits - 1u;
+                const int64_t node = w * 32 + b;
+                if (node < n_nodes) ids[p] = (int32_t)node;
+                ++p;
+            }
+            pos += __builtin_amdgcn_readlane(incl, 63);
         }
-        int64_t p = pos + incl - cnt;
-        while (bits) {
-            const int b = __builtin_ctz(bits);
-            bits &= bits - 1u;
-            const int64_t node = w * 32 + b;
-            if (node < n_nodes) ids[p] = (int32_t)node;
-            ++p;
-        }
-        pos += __shfl(incl, 63);
     }
 }
 

@@ -103,3 +103,48 @@ def test_map_lists_padding_and_empty(ezo, ctx):
     offsets, ids = ezo.collision_map_lists(ctx, m1[:, :0], 0)
     torch.cuda.synchronize()
     assert len(ids) == 0 and not bool(offsets.any())
+
+
+@pytest.mark.parametrize("name,n,dims,side", [("dof7", 1, (64, 64, 40), 0.05), ("boxes", 9, (70, 60, 33), 0.05),
+                                              ("dof7", 40, (9, 7, 5), 0.4), ("forest", 263, (61, 47, 37), 0.06)])
+def test_map_spans_and_node_bytes(ezo, ctx, name, n, dims, side):
+    """Voxels split over several workgroups (more than one table holds, or few
+    nodes) and node counts around a byte of a row."""
+    data, desc = load(name)
+    rob = ezo.Robot(ctx, desc)
+    q = draw.uniform_q(35, n, data["q_lo"], data["q_hi"])
+    lo = np.array([-0.5 * d * side for d in dims], np.float32)
+    print_case("map spans", name, n, dims)
+    V = int(np.prod(dims))
+    out = torch.full((V, (n + 31) // 32), -1, dtype=torch.int32, device="cuda")
+    ezo.collision_map(ctx, rob, torch.from_numpy(q).cuda(), lo, side, dims, out=out)
+    torch.cuda.synchronize()
+    got, pad = unpack(out, n)
+    assert not pad.any()
+    parts = max(-(-V // 49152), min((512 + (n + 7) // 8 - 1) // ((n + 7) // 8), V // 4096), 1)
+    span = -(-V // parts)
+    edges = [v + d for v in range(0, V, span) for d in range(-40, 40)]
+    near = np.argsort(-got.sum(1), kind="stable")[:300]
+    voxels = np.unique(np.clip(np.concatenate([edges, near, np.random.default_rng(8).choice(V, min(V, 400), replace=False)]), 0, V - 1).astype(int))
+    hits = check_rows(got, voxels, desc, q, lo, side, dims, BAND, name)
+    assert hits.any()
+
+
+@pytest.mark.parametrize("rows,words,density", [(1, 1, 0.5), (3, 64, 0.0), (4095, 3, 0.3), (4097, 65, 0.02),
+                                                (700, 511, 0.4), (300, 1100, 0.001), (300001, 2, 0.1)])
+def test_map_lists_of_any_rows(ezo, ctx, rows, words, density):
+    """Row counts around the scan's tiles and chunks, words around the loads in
+    flight, empty to dense rows: offsets and ids against numpy."""
+    rng = np.random.default_rng(rows)
+    bits = rng.random((rows, words * 32)) < density
+    if rows > 2:
+        bits[rows // 2] = True                                       # a full row
+        bits[rows // 3] = False
+    print_case("lists", rows, words, density)
+    packed = np.packbits(bits, axis=1, bitorder="little").view(np.int32)
+    offsets, ids = ezo.collision_map_lists(ctx, torch.from_numpy(packed.copy()).cuda(), words * 32)
+    torch.cuda.synchronize()
+    r, c = np.nonzero(bits)
+    want = np.zeros(rows + 1, np.int64)
+    np.cumsum(bits.sum(1), out=want[1:])
+    assert np.array_equal(offsets.cpu().numpy(), want) and np.array_equal(ids.cpu().numpy(), c)
