@@ -138,6 +138,8 @@ struct ezo_surrogate {
     float* v = nullptr;
     __bf16* W2b = nullptr;              // BF16 copies for the MFMA layers
     __bf16* W3b = nullptr;
+    __bf16* W2t = nullptr;              // their transposes (H <= 256: the backward pass)
+    __bf16* W3t = nullptr;
     int64_t adam_steps = 0;
     // training batch buffers
     int batch = 0;

@@ -12,6 +12,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "ezo_device.hpp"
 #include "ezo_screen.hpp"
 
 namespace ezo {
@@ -264,7 +265,8 @@ k_mlp_predict(RowSource src, int D, const float* __restrict__ P, const __bf16* _
 // B[k 8(l/16)..+7][col l%16] and returns C[rows 4(l/16)..+3][col l%16].
 // Split K: blockIdx.z takes K steps [z kc, (z + 1) kc); with gridDim.z > 1
 // only GEMM_STORE is allowed and slice z writes C + z M ldc (partial sums,
-// reduced by k_sum_slices).
+// reduced by k_sum_slices).  Slices from `slices` on are those of a second
+// product A2 B2 of the same shape.
 // Epilogues: STORE C = acc (FP32); FWD z = acc + bias[n] -> C (optional),
 // Hout = bf16(silu(z)); BWD Hout = bf16(acc * silu'(Z[m][n])).
 // ---------------------------------------------------------------------------
@@ -277,14 +279,20 @@ __global__ void __launch_bounds__(256) k_gemm_bf16(int M, int N, int K, int kc, 
                                                    const float* __restrict__ bias, __bf16* __restrict__ Hout,
                                                    int64_t ldh, const float* __restrict__ Z, int64_t ldz,
                                                    const int* __restrict__ status, int64_t rows_per_batch,
-                                                   int64_t rbase) {
+                                                   int64_t rbase, int slices, const __bf16* __restrict__ A2,
+                                                   const __bf16* __restrict__ B2) {
     __shared__ __attribute__((aligned(16))) __bf16 As[64][40];
     __shared__ __attribute__((aligned(16))) __bf16 Bs[64][40];
     const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
     if (m0 >= M || n0 >= N) return;
     // tiles of finished edges are skipped (rows_per_batch is a multiple of 64)
     if (status && rows_per_batch > 0 && status[(m0 + rbase) / rows_per_batch] >= 0) return;
-    const int kb0 = blockIdx.z * kc, kb1 = min(K, kb0 + kc);
+    const bool second = (int)blockIdx.z >= slices;
+    if (second) {
+        A = A2;
+        B = B2;
+    }
+    const int kb0 = ((int)blockIdx.z - (second ? slices : 0)) * kc, kb1 = min(K, kb0 + kc);
     if (gridDim.z > 1) C += (int64_t)blockIdx.z * M * ldc;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int wm = (w >> 1) * 32, wn = (w & 1) * 32;
@@ -482,12 +490,244 @@ __global__ void __launch_bounds__(256) k_mlp_grad_w1(RowSource src, int64_t B, i
     if (ok) out[t] = sum_slices_of(part, (int64_t)H * D, t);
 }
 
+// ---------------------------------------------------------------------------
+// Forward and backward pass of a batch, H = 64 HB <= 256, in one kernel: a
+// workgroup of 4 HB waves takes 16 rows through the three layers as
+// k_mlp_predict does (wave w: units 16 w .. + 15) and back, with the layers'
+// pre-activations in registers.  The weights, also transposed (W3t, W2t), are
+// read from L2 for each tile.  To memory go what the weight gradients of the
+// hidden layers contract over the batch, h1, h2, d2, d3 (BF16 [B][H]), and each
+// workgroup's sums over its rows of everything else: part[workgroup] =
+// dW4[H] db3[H] db2[H] db1[H] dW1[H][D] db4 loss.  x[r] is row idx[r] of q.
+// Bound by latency at a batch's size (the weights' way from L2 and six barriers
+// a tile): 4096 rows at H = 256 took 260 us of kernels in 19 launches, here 31 us
+// in this one and 20 in the contraction and the sums' last step.  Two blocks of
+// 16 rows a tile do not fit the 128 registers of 16 waves.
+// ---------------------------------------------------------------------------
+__host__ __device__ constexpr int train_part_floats(int H, int D) { return 4 * H + H * D + 2; }
+
+template <int HB>
+__host__ __device__ constexpr size_t train_lds_bytes() {
+    return sizeof(__bf16) * (size_t)2 * 16 * 64 * HB + sizeof(float) * (size_t)16 * (4 * HB + kMaxDof);
+}
+
+// sum over the 16 lanes of a row
+__device__ __forceinline__ float row_sum16(float v) {
+    auto add = [](float x, int b) { return x + __int_as_float(b); };
+    v = add(v, __builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, true));
+    v = add(v, __builtin_amdgcn_mov_dpp(__float_as_int(v), 0x4E, 0xF, 0xF, true));
+    v = add(v, __builtin_amdgcn_mov_dpp(__float_as_int(v), 0x141, 0xF, 0xF, true));
+    return add(v, __builtin_amdgcn_mov_dpp(__float_as_int(v), 0x140, 0xF, 0xF, true));
+}
+
+template <int HB>
+__global__ void __launch_bounds__(256 * HB, 4)
+k_mlp_train(const float* __restrict__ q, const int* __restrict__ idx, int64_t B, int D, const float* __restrict__ P,
+            const __bf16* __restrict__ W2b, const __bf16* __restrict__ W3b, const __bf16* __restrict__ W2t,
+            const __bf16* __restrict__ W3t, const float* __restrict__ target, float huber, float clip_lo, float clip_hi,
+            __bf16* __restrict__ h1, __bf16* __restrict__ h2, __bf16* __restrict__ d2, __bf16* __restrict__ d3,
+            float* __restrict__ part) {
+    constexpr int H = 64 * HB, KS = H / 32, R = 16, NW = 4 * HB;
+    extern __shared__ __attribute__((aligned(16))) __bf16 train_lds[];
+    __bf16* const la = train_lds;
+    __bf16* const lb = la + R * H;
+    float* const red = reinterpret_cast<float*>(lb + R * H);         // [NW][R] partial outputs
+    float* const xs = red + NW * R;                                  // [R][kMaxDof] q / pi
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, c = lane & 15, g = lane >> 4, n0 = 16 * w;
+    const MlpOffsets o = mlp_offsets(D, H);
+    const int sc = HB % 2 ? c >> 1 : c;                              // as in k_mlp_predict
+    auto at = [&](__bf16* h, int chunk) { return h + c * H + 8 * (chunk ^ sc); };
+    const int m0 = n0 + 4 * g, wc = m0 >> 3, wo = 4 * (g & 1);       // this lane's units of a result
+    f32x4 sw4 = {0.f, 0.f, 0.f, 0.f}, s3 = sw4, s2 = sw4, s1 = sw4, sw1 = sw4;
+    float sy = 0.f, sl = 0.f;
+    // product of 16 rows of W with the tile's rows
+    auto product = [&](__bf16* h, const bf16x8 (&wt)[KS]) {
+        f32x4 z = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < KS; ++k)
+            z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wt[k], *reinterpret_cast<const bf16x8*>(at(h, 4 * k + g)), z, 0,
+                                                        0, 0);
+        return z;
+    };
+    // (`fresh`, zero, keeps the loads inside the tile loop: all four matrices at
+    // once do not fit the registers)
+    int fresh = 0;
+    auto weights = [&](const __bf16* W, bf16x8 (&wt)[KS]) {
+        asm volatile("" : "+s"(fresh));
+#pragma unroll
+        for (int k = 0; k < KS; ++k) wt[k] = *reinterpret_cast<const bf16x8*>(W + fresh + (n0 + c) * H + 32 * k + 8 * g);
+    };
+    auto four = [&](int64_t off) {
+        f32x4 v;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = P[off + fresh + m0 + r];
+        return v;
+    };
+    auto put = [&](__bf16* l, __bf16* m, int64_t r0, bf16x4 v) {
+        *reinterpret_cast<bf16x4*>(at(l, wc) + wo) = v;
+        if (m) *reinterpret_cast<bf16x4*>(m + (r0 + c) * H + m0) = v;
+    };
+    for (int64_t t = blockIdx.x; t * R < B; t += gridDim.x) {
+        const int64_t r0 = t * R;
+        bf16x8 wt[KS];
+        f32x4 z1, z2, z3;
+        __syncthreads();                                             // the tile before is done with LDS
+        for (int i = tid; i < R * kMaxDof; i += 64 * NW) {
+            const int r = i / kMaxDof, j = i % kMaxDof;
+            xs[i] = j < D ? q[(int64_t)idx[r0 + r] * D + j] * kInvPi : 0.f;
+        }
+        weights(W2b, wt);
+        float w1[2];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) w1[s] = 4 * s + g < D ? P[o.W1 + (n0 + c) * D + 4 * s + g] : 0.f;
+        __syncthreads();
+        const f32x4 b1 = four(o.b1);
+        {
+            f32x4 z = b1;
+#pragma unroll
+            for (int s = 0; s < 2; ++s)
+                z = __builtin_amdgcn_mfma_f32_16x16x4f32(w1[s], xs[c * kMaxDof + 4 * s + g], z, 0, 0, 0);
+            z1 = z;
+            put(la, h1, r0, silu4(z));
+        }
+        const f32x4 b2 = four(o.b2);
+        __syncthreads();
+        {
+            z2 = product(la, wt) + b2;
+            put(lb, h2, r0, silu4(z2));
+        }
+        weights(W3b, wt);
+        const f32x4 b3 = four(o.b3), w4 = four(o.W4);
+        __syncthreads();
+        bf16x4 h3;
+        {
+            z3 = product(lb, wt) + b3;
+            h3 = silu4(z3);
+            float s = 0.f;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) s = fmaf(w4[r], (float)h3[r], s);
+            s += __shfl_xor(s, 16);
+            s += __shfl_xor(s, 32);
+            if (g == 0) red[w * R + c] = s;
+        }
+        weights(W3t, wt);
+        __syncthreads();
+        {
+            float y = P[o.b4];
+#pragma unroll
+            for (int v = 0; v < NW; ++v) y += red[v * R + c];
+            const float tv = fminf(fmaxf(target[idx[r0 + c]], clip_lo), clip_hi);
+            const float res = y - tv;
+            const float dy = (fabsf(res) <= huber ? res : (res > 0.f ? huber : -huber)) / (float)B;
+            if (w == 0 && g == 0) {
+                sy += dy;
+                sl += fabsf(res) <= huber ? 0.5f * res * res : huber * (fabsf(res) - 0.5f * huber);
+            }
+            bf16x4 d;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                d[r] = (__bf16)(dy * w4[r] * silu_gradf(z3[r]));
+                s3[r] += (float)d[r];
+                sw4[r] = fmaf(dy, (float)h3[r], sw4[r]);
+            }
+            put(la, d3, r0, d);
+        }
+        __syncthreads();
+        {
+            const f32x4 v = product(la, wt);
+            bf16x4 d;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                d[r] = (__bf16)(v[r] * silu_gradf(z2[r]));
+                s2[r] += (float)d[r];
+            }
+            put(lb, d2, r0, d);
+        }
+        weights(W2t, wt);
+        __syncthreads();
+        {
+            const f32x4 v = product(lb, wt);
+            bf16x4 d;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                d[r] = (__bf16)(v[r] * silu_gradf(z1[r]));
+                s1[r] += (float)d[r];
+            }
+            put(la, nullptr, r0, d);                             // read back by this wave only
+        }
+        // dW1: this wave's units against the inputs, the rows as K
+#pragma unroll
+        for (int k = 0; k < R / 4; ++k) {
+            const int row = 4 * k + g, rc = row & 15, unit = n0 + c;
+            const float a = (float)la[row * H + 8 * ((unit >> 3) ^ (HB % 2 ? rc >> 1 : rc)) + (unit & 7)];
+            sw1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a, c < kMaxDof ? xs[row * kMaxDof + (c & 7)] : 0.f, sw1, 0, 0, 0);
+        }
+    }
+    float* const out = part + (int64_t)blockIdx.x * train_part_floats(H, D);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const float a = row_sum16(sw4[r]), b = row_sum16(s3[r]), d = row_sum16(s2[r]), e = row_sum16(s1[r]);
+        if (c == 0) {
+            out[m0 + r] = a;
+            out[H + m0 + r] = b;
+            out[2 * H + m0 + r] = d;
+            out[3 * H + m0 + r] = e;
+        }
+        if (c < D) out[4 * H + (m0 + r) * D + c] = sw1[r];
+    }
+    sy = row_sum16(sy);
+    sl = row_sum16(sl);
+    if (tid == 0) {
+        out[4 * H + H * D] = sy;
+        out[4 * H + H * D + 1] = sl;
+    }
+}
+
+// The gradient from k_mlp_train's sums (part[groups][train_part_floats]) and the
+// K slices of the hidden layers' products (w: slices of dW3, then of dW2):
+// blocks below `nb` take 64 of the sums' columns each, four of their rows side
+// by side, the others 256 elements of the products.  Fixed order: deterministic.
+__global__ void __launch_bounds__(256) k_mlp_grad_sum(int D, int H, int groups, const float* __restrict__ part,
+                                                      int slices, const float* __restrict__ w, int nb,
+                                                      float* __restrict__ G, float* __restrict__ loss) {
+    const MlpOffsets o = mlp_offsets(D, H);
+    const int tid = threadIdx.x, n = train_part_floats(H, D);
+    if ((int)blockIdx.x >= nb) {
+        const int64_t HH = (int64_t)H * H, i = (int64_t)(blockIdx.x - nb) * 256 + tid;
+        if (i >= 2 * HH) return;
+        const float* p = w + (i < HH ? 0 : slices * HH) + i % HH;
+        float s = 0.f;
+        for (int z = 0; z < slices; ++z) s += p[z * HH];
+        G[(i < HH ? o.W3 : o.W2) + i % HH] = s;
+        return;
+    }
+    __shared__ float red[4][64];
+    const int lane = tid & 63, g = tid >> 6, j = blockIdx.x * 64 + lane;
+    float s = 0.f;
+    if (j < n) {
+#pragma unroll 8
+        for (int r = g; r < groups; r += 4) s += part[(int64_t)r * n + j];
+    }
+    red[g][lane] = s;
+    __syncthreads();
+    if (g != 0 || j >= n) return;
+    s = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
+    if (j < H) G[o.W4 + j] = s;
+    else if (j < 2 * H) G[o.b3 + j - H] = s;
+    else if (j < 3 * H) G[o.b2 + j - 2 * H] = s;
+    else if (j < 4 * H) G[o.b1 + j - 3 * H] = s;
+    else if (j < 4 * H + H * D) G[o.W1 + j - 4 * H] = s;
+    else if (j == 4 * H + H * D) G[o.b4] = s;
+    else *loss += s;
+}
+
 // Adam step with bias correction on the flat parameter vector; refreshes
-// the BF16 copies of W2 and W3.
+// the BF16 copies of W2 and W3 (and their transposes where kept).
 __global__ void __launch_bounds__(256) k_adam(int64_t n, float* __restrict__ P, const float* __restrict__ G,
                                               float* __restrict__ m, float* __restrict__ v, float lr, float b1,
                                               float b2, float eps, float c1, float c2, int D, int H,
-                                              __bf16* __restrict__ W2b, __bf16* __restrict__ W3b) {
+                                              __bf16* __restrict__ W2b, __bf16* __restrict__ W3b,
+                                              __bf16* __restrict__ W2t, __bf16* __restrict__ W3t) {
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= n) return;
     const float g = G[k];
@@ -498,18 +738,28 @@ __global__ void __launch_bounds__(256) k_adam(int64_t n, float* __restrict__ P, 
     const float p = P[k] - lr * (mk / c1) / (sqrtf(vk / c2) + eps);
     P[k] = p;
     const MlpOffsets o = mlp_offsets(D, H);
-    if (k >= o.W2 && k < o.W2 + (int64_t)H * H) W2b[k - o.W2] = (__bf16)p;
-    if (k >= o.W3 && k < o.W3 + (int64_t)H * H) W3b[k - o.W3] = (__bf16)p;
+    const bool second = k >= o.W3;
+    const int64_t w = k - (second ? o.W3 : o.W2);
+    if (w >= 0 && w < (int64_t)H * H) {
+        (second ? W3b : W2b)[w] = (__bf16)p;
+        __bf16* const t = second ? W3t : W2t;
+        if (t) t[w % H * H + w / H] = (__bf16)p;
+    }
 }
 
 // BF16 copies of W2, W3 from the master parameters.
 __global__ void __launch_bounds__(256) k_mlp_cast(int D, int H, const float* __restrict__ P, __bf16* __restrict__ W2b,
-                                                  __bf16* __restrict__ W3b) {
+                                                  __bf16* __restrict__ W3b, __bf16* __restrict__ W2t,
+                                                  __bf16* __restrict__ W3t) {
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const MlpOffsets o = mlp_offsets(D, H);
     if (k >= (int64_t)H * H) return;
     W2b[k] = (__bf16)P[o.W2 + k];
     W3b[k] = (__bf16)P[o.W3 + k];
+    if (W2t) {
+        W2t[k % H * H + k / H] = W2b[k];
+        W3t[k % H * H + k / H] = W3b[k];
+    }
 }
 
 __global__ void __launch_bounds__(256) k_fill(float* __restrict__ p, int64_t n, float v) {

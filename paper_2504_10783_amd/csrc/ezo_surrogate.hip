@@ -68,11 +68,13 @@ TrainBufs carve(void* base, int B, int H) {
 // summed in a fixed order by k_sum_slices).
 constexpr int kRowsPerSlice = kGradW1Rows;
 constexpr int kGradSplitK = 16;
+constexpr int kTrainGroups = 256;       // most workgroups of k_mlp_train
 
 size_t partial_floats(int B, int H, int D) {
     const size_t slices = (size_t)(B + kRowsPerSlice - 1) / kRowsPerSlice;
     const size_t col_slices = (size_t)(B + kColRows - 1) / kColRows;
-    return std::max({(size_t)kGradSplitK * H * H, slices * H * std::max(D, 1), col_slices * H});
+    return std::max({(size_t)2 * kGradSplitK * H * H + (size_t)kTrainGroups * train_part_floats(H, D),
+                     slices * H * std::max(D, 1), col_slices * H});
 }
 
 size_t train_bytes(int B, int H, int D) {
@@ -83,23 +85,25 @@ size_t train_bytes(int B, int H, int D) {
 
 // C = A B with the strides' contiguous dimensions picking the staging; split
 // > 1 (GEMM_STORE only) writes partial products over slices of about K /
-// split rows (a multiple of 32) to C + z M ldc.  Returns the slice count.
+// split rows (a multiple of 32) to C + z M ldc, those of A2 B2 (if given) after
+// the first product's.  Returns the slice count of one product.
 template <int EPI>
 int gemm(hipStream_t st, int M, int N, int K, const __bf16* A, int64_t sam, int64_t sak, const __bf16* B, int64_t sbk,
           int64_t sbn, float* C, int64_t ldc, const float* bias, __bf16* Hout, int64_t ldh, const float* Z, int64_t ldz,
-          const int* status = nullptr, int64_t rpb = 0, int64_t rbase = 0, int split = 1) {
-    const int kc = (K / split + 31) / 32 * 32;
-    dim3 grid((unsigned)(N / 64), (unsigned)(M / 64), (unsigned)((K + kc - 1) / kc)), block(256);
+          const int* status = nullptr, int64_t rpb = 0, int64_t rbase = 0, int split = 1, const __bf16* A2 = nullptr,
+          const __bf16* B2 = nullptr) {
+    const int kc = (K / split + 31) / 32 * 32, slices = (K + kc - 1) / kc;
+    dim3 grid((unsigned)(N / 64), (unsigned)(M / 64), (unsigned)(slices * (A2 ? 2 : 1))), block(256);
     const bool ak = sak == 1, bk = sbk == 1;
 #define EZO_GEMM(AKV, BKV)                                                                                          \
     hipLaunchKernelGGL((k_gemm_bf16<EPI, AKV, BKV>), grid, block, 0, st, M, N, K, kc, A, sam, sak, B, sbk, sbn, C, ldc, \
-                       bias, Hout, ldh, Z, ldz, status, rpb, rbase)
+                       bias, Hout, ldh, Z, ldz, status, rpb, rbase, slices, A2, B2)
     if (ak && bk) EZO_GEMM(true, true);
     else if (ak) EZO_GEMM(true, false);
     else if (bk) EZO_GEMM(false, true);
     else EZO_GEMM(false, false);
 #undef EZO_GEMM
-    return (int)grid.z;
+    return slices;
 }
 
 // sum of the row slices of a batch reduction into out[n]
@@ -132,6 +136,27 @@ uint64_t gcd64(uint64_t a, uint64_t b) {
     return a;
 }
 
+// The same for H <= 256: rows forward and back in one kernel, the hidden layers'
+// weight gradients in one launch, every sum's last step in another.
+template <int HB>
+void forward_backward_rows(ezo_surrogate* s, const RowSource& src, const float* target, int B,
+                           const ezo_train_params* hp, const TrainBufs& t, hipStream_t st) {
+    constexpr int H = 64 * HB;
+    const int D = s->D;
+    const int groups = std::min(B / 16, kTrainGroups);
+    float* const sums = t.part + 2 * (size_t)kGradSplitK * H * H;
+    const dim3 grid((unsigned)groups), block(256 * HB);
+    hipLaunchKernelGGL(k_mlp_train<HB>, grid, block, train_lds_bytes<HB>(), st, src.q, (const int*)src.idx,
+                       (int64_t)B, D, (const float*)s->P, (const __bf16*)s->W2b, (const __bf16*)s->W3b,
+                       (const __bf16*)s->W2t, (const __bf16*)s->W3t, target, (float)hp->huber_delta,
+                       (float)hp->clip_lo, (float)hp->clip_hi, t.h1, t.h2, t.d2, t.d3, sums);
+    const int ks = gemm<GEMM_STORE>(st, H, H, B, t.d3, 1, H, t.h2, H, 1, t.part, H, nullptr, nullptr, 0, nullptr, 0,
+                                    nullptr, 0, 0, kGradSplitK, t.d2, t.h1);
+    const int nb = (train_part_floats(H, D) + 63) / 64;
+    hipLaunchKernelGGL(k_mlp_grad_sum, dim3((unsigned)(nb + 2 * H * H / 256)), dim3(256), 0, st, D, H, groups,
+                       (const float*)sums, ks, (const float*)t.part, nb, s->G, t.loss);
+}
+
 // One forward + backward pass over a batch of B rows (src.idx gathers them);
 // leaves the gradient in s->G and adds the summed loss to t.loss.
 ezo_status forward_backward(ezo_ctx* c, ezo_surrogate* s, const RowSource& src, const float* target, int B,
@@ -141,6 +166,14 @@ ezo_status forward_backward(ezo_ctx* c, ezo_surrogate* s, const RowSource& src, 
     float* G = s->G;
     const float* P = s->P;
     const int64_t BH = (int64_t)B * H;
+    if (H <= 256) {
+        if (H == 256) forward_backward_rows<4>(s, src, target, B, hp, t, st);
+        else if (H == 192) forward_backward_rows<3>(s, src, target, B, hp, t, st);
+        else if (H == 128) forward_backward_rows<2>(s, src, target, B, hp, t, st);
+        else forward_backward_rows<1>(s, src, target, B, hp, t, st);
+        HIP_TRY(c, hipGetLastError());
+        return EZO_OK;
+    }
     hipLaunchKernelGGL(k_mlp_layer1, dim3((unsigned)((BH + 255) / 256)), dim3(256), 0, st, src, (int64_t)B, D, H, P,
                        t.z1, t.h1, (const int*)nullptr);
     gemm<GEMM_FWD>(st, B, H, H, t.h1, H, 1, s->W2b, 1, H, t.z2, H, P + o.b2, t.h2, H, nullptr, 0);
@@ -281,7 +314,9 @@ ezo_status ezo_surrogate_create(ezo_ctx* c, int32_t dof, int32_t hidden, uint64_
     if (hipMalloc((void**)&s->P, 4 * P) != hipSuccess || hipMalloc((void**)&s->G, 4 * P) != hipSuccess ||
         hipMalloc((void**)&s->m, 4 * P) != hipSuccess || hipMalloc((void**)&s->v, 4 * P) != hipSuccess ||
         hipMalloc((void**)&s->W2b, 2 * (size_t)hidden * hidden) != hipSuccess ||
-        hipMalloc((void**)&s->W3b, 2 * (size_t)hidden * hidden) != hipSuccess) {
+        hipMalloc((void**)&s->W3b, 2 * (size_t)hidden * hidden) != hipSuccess ||
+        (hidden <= 256 && (hipMalloc((void**)&s->W2t, 2 * (size_t)hidden * hidden) != hipSuccess ||
+                           hipMalloc((void**)&s->W3t, 2 * (size_t)hidden * hidden) != hipSuccess))) {
         ezo_surrogate_destroy(s);
         return ezo_fail(c, EZO_E_NOMEM, "surrogate allocation failed");
     }
@@ -312,7 +347,7 @@ ezo_status ezo_surrogate_create(ezo_ctx* c, int32_t dof, int32_t hidden, uint64_
 void ezo_surrogate_destroy(ezo_surrogate* s) {
     if (!s) return;
     hipError_t e = hipSetDevice(s->device);
-    for (void* p : {(void*)s->P, (void*)s->G, (void*)s->m, (void*)s->v, (void*)s->W2b, (void*)s->W3b, s->tb})
+    for (void* p : {(void*)s->P, (void*)s->G, (void*)s->m, (void*)s->v, (void*)s->W2b, (void*)s->W3b, (void*)s->W2t, (void*)s->W3t, s->tb})
         if (p) e = hipFree(p);
     (void)e;
     (void)hipGetLastError();
@@ -328,7 +363,7 @@ ezo_status ezo_surrogate_set_params(ezo_surrogate* s, const float* params, int64
     HIP_TRY(c, hipMemsetAsync(s->v, 0, 4 * (size_t)n, c->stream));
     const int64_t HH = (int64_t)s->H * s->H;
     hipLaunchKernelGGL(k_mlp_cast, dim3((unsigned)((HH + 255) / 256)), dim3(256), 0, c->stream, s->D, s->H,
-                       (const float*)s->P, s->W2b, s->W3b);
+                       (const float*)s->P, s->W2b, s->W3b, s->W2t, s->W3t);
     HIP_TRY(c, hipGetLastError());
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     s->adam_steps = 0;
@@ -411,7 +446,8 @@ ezo_status ezo_surrogate_train(ezo_ctx* c, ezo_surrogate* s, const float* q, con
             const double c2 = 1.0 - std::pow(hp->beta2, (double)s->adam_steps);
             hipLaunchKernelGGL(k_adam, dim3((unsigned)((s->n_params + 255) / 256)), dim3(256), 0, st, s->n_params, s->P,
                                (const float*)s->G, s->m, s->v, (float)lr, (float)hp->beta1, (float)hp->beta2,
-                               (float)hp->adam_eps, (float)c1, (float)c2, s->D, s->H, s->W2b, s->W3b);
+                               (float)hp->adam_eps, (float)c1, (float)c2, s->D, s->H, s->W2b, s->W3b, s->W2t,
+                               s->W3t);
         }
         HIP_TRY(c, hipGetLastError());
         float hl = 0.f;

@@ -293,3 +293,23 @@ def test_fused_forward_keeps_nonfinite_rows_apart(ezo, ctx):
     keep = torch.ones(n, dtype=torch.bool, device="cuda")
     keep[37] = keep[150] = False
     assert torch.equal(got[keep], ref[keep]) and bool(torch.isnan(got[37])) and bool(torch.isnan(got[150]))
+
+
+@pytest.mark.parametrize("D,H,n", [(7, 256, 64), (8, 192, 4160), (2, 128, 4096), (5, 64, 8256), (7, 320, 128)])
+def test_gradient_matches_oracle_at_tile_edges(ezo, ctx, D, H, n):
+    """One tile per workgroup and several, every layer width of the one-kernel
+    pass and one past it; the tolerance is that of the BF16 activations
+    (2^-8 each, three layers)."""
+    print_case("mlp grad", D, H, n)
+    s = ezo.Surrogate(ctx, D, H, seed=4)
+    q = torch.from_numpy(draw.uniform_q(63, n, np.full(D, -3.0, np.float32), np.full(D, 3.0, np.float32))).cuda()
+    t = (0.1 + 0.35 * torch.sin(q[:, 0] + q[:, -1])).contiguous()
+    loss, g = s.loss_grad(q, t, ezo.make_train_params())
+    again = s.loss_grad(q, t, ezo.make_train_params())
+    assert again[0] == loss and np.array_equal(again[1], g)              # a fixed order of every sum
+    x = f32_up(f32_up(q.cpu().numpy()) / np.pi)
+    lo, go = oracle.mlp_loss_grad(D, H, oracle_view(s.get_params(), D, H), x, f32_up(t.cpu().numpy()))
+    assert abs(loss - lo) <= 2e-2 * abs(lo)
+    cut = np.cumsum([0, H * D, H, H * H, H, H * H, H, H, 1])
+    for a, b in zip(cut[:-1], cut[1:]):                                  # every part of the gradient
+        assert np.linalg.norm(g[a:b] - go[a:b]) <= 3e-2 * np.linalg.norm(go[a:b]) + 1e-4 * np.linalg.norm(go)
