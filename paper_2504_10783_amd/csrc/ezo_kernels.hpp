@@ -1918,12 +1918,78 @@ __global__ void __launch_bounds__(256) k_path_points(int dof, const float* __res
     }
 }
 
-// out[r] = rows[idx[r]] for r < *n (rows of dof floats).
-__global__ void k_gather_rows(int dof, const float* __restrict__ rows, const int* __restrict__ idx,
-                              const int* __restrict__ n, int cap, float* __restrict__ out) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= cap || r >= *n) return;
-    for (int k = 0; k < dof; ++k) out[(size_t)r * dof + k] = rows[(size_t)idx[r] * dof + k];
+// The rows whose flag is set, in order: the first `cap` of them to out, their
+// number to cnt[0] (at most cap) and cnt[1] (all).  A workgroup takes `span`
+// flags (a multiple of kFlagTile; at most kFlagGroups workgroups, whose counts
+// k_flag_count leaves in counts); one workgroup over all flags took 60 us for a
+// path of 180 000 points, the two launches 14.
+constexpr int kFlagTile = 1024, kFlagGroups = 1024;      // flags: 256 threads x 4
+__host__ __device__ inline int64_t flag_span(int64_t n) {
+    const int64_t tiles = (n + kFlagTile - 1) / kFlagTile;
+    return (tiles + kFlagGroups - 1) / kFlagGroups * kFlagTile;
+}
+
+// bit q: flag i + q is set (q < 4, i a multiple of 4; flags 4-byte aligned)
+__device__ __forceinline__ unsigned flags4(const uint8_t* __restrict__ flags, int64_t i, int64_t n) {
+    unsigned m = 0;
+    if (i + 4 <= n) {
+        const unsigned v = *reinterpret_cast<const unsigned*>(flags + i);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) m |= ((v >> (8 * q)) & 255u) != 0u ? 1u << q : 0u;
+    } else {
+        for (int q = 0; q < 4 && i + q < n; ++q) m |= flags[i + q] ? 1u << q : 0u;
+    }
+    return m;
+}
+
+__global__ void __launch_bounds__(256) k_flag_count(const uint8_t* __restrict__ flags, int64_t n, int64_t span,
+                                                    int* __restrict__ counts) {
+    __shared__ int red[4];
+    const int tid = threadIdx.x;
+    const int64_t a = blockIdx.x * span, b = min(n, a + span);
+    int c = 0;
+    for (int64_t i = a + 4 * tid; i < b; i += kFlagTile) c += __popc(flags4(flags, i, n));
+    c = wave_sum_i32(c);
+    if ((tid & 63) == 0) red[tid >> 6] = c;
+    __syncthreads();
+    if (tid == 0) counts[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
+}
+
+__global__ void __launch_bounds__(256) k_flag_rows(const uint8_t* __restrict__ flags, int64_t n, int64_t span,
+                                                   const int* __restrict__ counts, int dof,
+                                                   const float* __restrict__ rows, int cap, float* __restrict__ out,
+                                                   int* __restrict__ cnt) {
+    __shared__ int red[4];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int64_t a = blockIdx.x * span, b = min(n, a + span);
+    int base = 0;
+    for (int i = tid; i < (int)blockIdx.x; i += 256) base += counts[i];
+    base = wave_sum_i32(base);
+    if (lane == 0) red[w] = base;
+    __syncthreads();
+    base = red[0] + red[1] + red[2] + red[3];
+    if (blockIdx.x == gridDim.x - 1 && tid == 0) {
+        const int all = base + counts[blockIdx.x];
+        cnt[0] = min(all, cap);
+        cnt[1] = all;
+    }
+    for (int64_t t = a; t < b && base < cap; t += kFlagTile) {
+        const int64_t i = t + 4 * tid;
+        unsigned m = flags4(flags, i, n);
+        const int c = __popc(m), incl = wave_scan_dpp(c);
+        __syncthreads();                                   // red[] has been read
+        if (lane == 63) red[w] = incl;
+        __syncthreads();
+        int pos = base + incl - c;
+        for (int k = 0; k < 4; ++k) {
+            if (k < w) pos += red[k];
+            base += red[k];
+        }
+        for (; m != 0u && pos < cap; m &= m - 1u, ++pos) {
+            const float* r = rows + (size_t)(i + __builtin_ctz(m)) * dof;
+            for (int k = 0; k < dof; ++k) out[(size_t)pos * dof + k] = r[k];
+        }
+    }
 }
 
 // Row-major [n][dof] -> coordinate-major [dof][n]; empties the candidate list.
@@ -1935,29 +2001,71 @@ __global__ void k_rows_to_coords(int dof, const float* __restrict__ rows, int64_
     for (int k = 0; k < dof; ++k) coords[(size_t)k * n + i] = rows[(size_t)i * dof + k];
 }
 
+// Bit p: this lane's point x[p] satisfies rows 0 .. F - 1 of A x <= b + tol.  Eight
+// rows at a time, lane l holding coefficient l % 8 of row l / 8 and the next
+// eight on their way, every coefficient broadcast from its lane (readlane);
+// the rows end when no point of the wave is left.  Every lane of the wave calls it.
+template <int P>
+__device__ __forceinline__ unsigned wave_inside(const float* __restrict__ A, const float* __restrict__ b, int F, int dof,
+                                                float tol, const float (&x)[P][kMaxDof], unsigned in) {
+    const int lane = threadIdx.x & 63, fr = lane >> 3, j = lane & 7;
+    auto row = [&](int f) { return f < F && j < dof ? A[(size_t)f * dof + j] : 0.f; };
+    auto bound = [&](int f) { return f < F ? b[f] + tol : INFINITY; };
+    float a = row(fr), bb = bound(fr);
+    for (int f0 = 0; f0 < F && __ballot(in != 0u) != 0ull; f0 += 8) {
+        const float an = row(f0 + 8 + fr), bn = bound(f0 + 8 + fr);
+#pragma unroll
+        for (int f = 0; f < 8; ++f) {
+            if (f0 + f >= F) break;
+            float ax[P];
+#pragma unroll
+            for (int p = 0; p < P; ++p) ax[p] = 0.f;
+#pragma unroll
+            for (int k = 0; k < kMaxDof; ++k) {
+                const float c = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(a), 8 * f + k));
+#pragma unroll
+                for (int p = 0; p < P; ++p) ax[p] = fmaf(c, x[p][k], ax[p]);
+            }
+            const float l = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(bb), 8 * f));
+#pragma unroll
+            for (int p = 0; p < P; ++p)
+                if (!(ax[p] <= l)) in &= ~(1u << p);
+        }
+        a = an;
+        bb = bn;
+    }
+    return in;
+}
+
 // flags[e][i] = 1 iff point i (coordinate-major pts [dof][n]) satisfies every
 // row of polytope e and edge e's status is CERTIFIED or MAX_ITERS (a set
-// that can be edited); blockIdx.y = e.
+// that can be edited); blockIdx.y = e, a wave takes 64 kSetPoints points.  Bound
+// by the dot products' VALU work; with one point a lane and a load per
+// coefficient 16 384 points x 96 sets took 174 us, here 17.
+constexpr int kSetPoints = 4;
+
 __global__ void __launch_bounds__(256) k_points_in_sets(int dof, const float* __restrict__ A,
                                                         const float* __restrict__ bvec,
                                                         const int* __restrict__ n_faces, int cap,
                                                         const int* __restrict__ status, const float* __restrict__ pts,
                                                         int64_t n, uint8_t* __restrict__ flags) {
     const int e = blockIdx.y;
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    bool inside = status[e] == 0 || status[e] == 1;
-    const int F = min(max(n_faces[e], 0), cap);
-    float x[kMaxDof];
+    const int64_t i = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * (64 * kSetPoints) + (threadIdx.x & 63);
+    float x[kSetPoints][kMaxDof];
+    unsigned in = 0;
 #pragma unroll
-    for (int k = 0; k < kMaxDof; ++k) x[k] = k < dof ? pts[(size_t)k * n + i] : 0.f;
-    const float* Ae = A + (size_t)e * cap * dof;
-    for (int f = 0; f < F && inside; ++f) {
-        float ax = 0.f;
-        for (int k = 0; k < dof; ++k) ax = fmaf(Ae[(size_t)f * dof + k], x[k], ax);
-        inside = ax <= bvec[(size_t)e * cap + f];
+    for (int p = 0; p < kSetPoints; ++p) {
+        const bool live = i + 64 * p < n;
+        in |= live ? 1u << p : 0u;
+#pragma unroll
+        for (int k = 0; k < kMaxDof; ++k) x[p][k] = live && k < dof ? pts[(size_t)k * n + i + 64 * p] : 0.f;
     }
-    flags[(size_t)e * n + i] = inside ? 1 : 0;
+    if (!(status[e] == 0 || status[e] == 1)) in = 0;
+    const int F = min(max(n_faces[e], 0), cap);
+    in = wave_inside<kSetPoints>(A + (size_t)e * cap * dof, bvec + (size_t)e * cap, F, dof, 0.f, x, in);
+#pragma unroll
+    for (int p = 0; p < kSetPoints; ++p)
+        if (i + 64 * p < n) flags[(size_t)e * n + i + 64 * p] = (in >> p) & 1u;
 }
 
 // Edges with candidates run the placement (status -1), the rest are skipped.
@@ -1979,37 +2087,30 @@ __global__ void k_recover_end(int n_edges, const int* __restrict__ run, const in
     if (planes_added) planes_added[e] = n_placed[e];
 }
 
-// covered[k] = smallest set index whose polytope contains both ends of
-// segment k (A v <= b + tol), -1 if none; blockIdx.x = k.
+// covered[k] (all ones before) = smallest set index whose polytope contains both
+// ends of segment k (A v <= b + tol).  A wave takes 64 segments, one a lane,
+// against every (4 gridDim.y)-th set; a workgroup per segment with a set per
+// lane took 35 us for 959 segments x 96 sets, this 8.
 __global__ void __launch_bounds__(256) k_segments_contained(int dof, const float* __restrict__ A,
                                                             const float* __restrict__ bvec,
                                                             const int* __restrict__ n_faces, int cap, int n_sets,
-                                                            const float* __restrict__ segs, float tol,
-                                                            int* __restrict__ covered) {
-    __shared__ int best;
-    const int k = blockIdx.x;
-    if (threadIdx.x == 0) best = 0x7fffffff;
-    __syncthreads();
-    const float* v = segs + (size_t)k * 2 * dof;
-    for (int e = threadIdx.x; e < n_sets; e += blockDim.x) {
+                                                            const float* __restrict__ segs, int n_segs, float tol,
+                                                            unsigned* __restrict__ covered) {
+    const int lane = threadIdx.x & 63, k = blockIdx.x * 64 + lane;
+    float x[2][kMaxDof];
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int j = 0; j < kMaxDof; ++j) x[p][j] = k < n_segs && j < dof ? segs[((size_t)k * 2 + p) * dof + j] : 0.f;
+    unsigned open = k < n_segs ? 3u : 0u;        // 0 once found: this wave's later sets are larger
+    for (int e = __builtin_amdgcn_readfirstlane(blockIdx.y * 4 + (threadIdx.x >> 6)); e < n_sets; e += 4 * gridDim.y) {
         const int F = min(max(n_faces[e], 0), cap);
         if (F == 0) continue;                    // an edge that holds no set
-        const float* Ae = A + (size_t)e * cap * dof;
-        bool in = true;
-        for (int f = 0; f < F && in; ++f) {
-            float a1 = 0.f, a2 = 0.f;
-            for (int j = 0; j < dof; ++j) {
-                const float a = Ae[(size_t)f * dof + j];
-                a1 = fmaf(a, v[j], a1);
-                a2 = fmaf(a, v[dof + j], a2);
-            }
-            const float bb = bvec[(size_t)e * cap + f] + tol;
-            in = a1 <= bb && a2 <= bb;
+        if (wave_inside<2>(A + (size_t)e * cap * dof, bvec + (size_t)e * cap, F, dof, tol, x, open) == 3u) {
+            atomicMin(&covered[k], (unsigned)e);
+            open = 0u;
         }
-        if (in) atomicMin(&best, e);
     }
-    __syncthreads();
-    if (threadIdx.x == 0) covered[k] = best == 0x7fffffff ? -1 : best;
 }
 
 }  // namespace ezo

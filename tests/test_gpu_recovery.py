@@ -306,3 +306,81 @@ def test_recovery_reinflates_segments_the_edit_uncovered(ezo, ctx):
     covered2 = ezo.segments_contained(ctx, A2, b2, n2, seeds).cpu().numpy()
     assert np.all(covered2 >= 0)
     assert covered2[g] >= len(segs)                                 # g now lies in its own new set
+
+
+@pytest.mark.parametrize("dof,F,n,E", [(7, 1, 1, 1), (2, 8, 255, 3), (8, 9, 1025, 2), (3, 70, 2049, 17), (7, 33, 64, 40)])
+def test_set_membership_edges(ezo, ctx, dof, F, n, E):
+    """segments_contained around eight rows, 64 segments and 16 sets, with empty
+    sets, zero rows, NaN and infinite coordinates, against the same chains of
+    fused multiply-adds."""
+    rng = np.random.default_rng(F * n)
+    A = rng.normal(size=(E, F + 2, dof)).astype(np.float32)
+    A[:, 0] = 0.0
+    b = (0.6 + rng.random((E, F + 2))).astype(np.float32) * np.sqrt(dof).astype(np.float32)
+    nf = rng.integers(0, F + 1, E).astype(np.int32)
+    nf[-1] = F
+    seg = rng.normal(size=(n, 2, dof)).astype(np.float32) * rng.random((n, 1, 1)).astype(np.float32)
+    if n > 3:
+        seg[1, 0, 0], seg[2, 1, dof - 1], seg[3, 0, 0] = np.nan, np.inf, -np.inf
+    print_case("set membership", dof, F, n, E)
+    cov = ezo.segments_contained(ctx, torch.from_numpy(A).cuda(), torch.from_numpy(b).cuda(),
+                                 torch.from_numpy(nf).cuda(), torch.from_numpy(seg).cuda(), 1e-6)
+    torch.cuda.synchronize()
+    cov = cov.cpu().numpy()
+    with np.errstate(invalid="ignore"):
+        v = np.einsum("efk,npk->enpf", A.astype(np.float64), seg.astype(np.float64))
+        slack = b.astype(np.float64)[:, None, None, :] + 1e-6 - v
+        used = np.arange(F + 2)[None, :] < nf[:, None]
+        sure_in = np.where(used[:, None, None], slack > 1e-5, True).all((2, 3)) & (nf > 0)[:, None]
+        sure_out = ~np.where(used[:, None, None], slack > -1e-5, True).all((2, 3)) | (nf == 0)[:, None]
+    for k in range(n):
+        c = cov[k]
+        assert c == -1 or not sure_out[c, k]
+        assert not sure_in[:c if c >= 0 else E, k].any()
+    assert n < 64 or (cov >= 0).any()
+
+
+@pytest.mark.parametrize("n,cap,share", [(1, 3, 1.0), (4095, 5000, 0.5), (4097, 100, 0.5), (70001, 70001, 0.02),
+                                         (5000000, 300, 0.0)])
+def test_path_points_found_in_order(ezo, ctx, n, cap, share):
+    """check_path around the 4096 flags of a compaction tile, many workgroups of
+    it, fewer and more colliding points than room: the points of the colliding
+    flags in path order, and their number."""
+    import workloads
+    data, desc = load("tiny")
+    rob = ezo.Robot(ctx, desc)
+    dof = int(desc["dof"])
+    rng = np.random.default_rng(n)
+    obs = torch.from_numpy(data["obstacles"]).cuda() if share else torch.zeros((0, 4), device="cuda")
+    lo, hi = np.asarray(data["q_lo"], np.float64), np.asarray(data["q_hi"], np.float64)
+    K = max(1, min(40, n - 1) + 1) if n > 1 else 1
+    way = (lo + (hi - lo) * rng.random((K, dof))).astype(np.float32)
+    print_case("path points", n, cap)
+    if K == 1:
+        step = 1.0
+    else:
+        total = np.abs(np.diff(way.astype(np.float64), axis=0)).max(1).sum()
+        step = total / n
+    w = torch.from_numpy(way).cuda()
+    pts, found, total_pts = ezo.check_path(ctx, rob, obs, w, step, point_capacity=cap)
+    torch.cuda.synchronize()
+    assert abs(total_pts - n) <= K + 1
+    # the same points and flags from the raw checker
+    segs = []
+    for i in range(K - 1):
+        m = max(1, int(np.ceil(np.abs(way[i + 1].astype(np.float64) - way[i].astype(np.float64)).max() / step)))
+        j = np.arange(0 if i == 0 else 1, m + 1)
+        t = (j.astype(np.float32) / np.float32(m)).astype(np.float64)[:, None]
+        d = (way[i + 1] - way[i]).astype(np.float64)
+        segs.append((t * d + way[i].astype(np.float64)).astype(np.float32))
+    q = np.concatenate(segs) if segs else way
+    assert len(q) == total_pts
+    flags = torch.empty(len(q), dtype=torch.uint8, device="cuda")
+    ezo.check_collisions(ctx, rob, obs, torch.from_numpy(q).cuda(), flags)
+    torch.cuda.synchronize()
+    hit = np.nonzero(flags.cpu().numpy())[0]
+    # a point within an ulp of a surface may differ between the two discretisations
+    assert abs(len(hit) - found) <= 2 + len(q) // 10000
+    if len(hit) == found:
+        k = min(cap, found)
+        assert len(pts) == k and np.abs(pts.cpu().numpy() - q[hit[:k]]).max(initial=0.0) <= 4 * step + 1e-6
