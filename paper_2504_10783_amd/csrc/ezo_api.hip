@@ -126,24 +126,22 @@ ezo_status prep_obstacles_into(ezo_ctx* c, const ezo_robot* r, const float* obs,
     const bool grid = kind == PREP_GRID;
     // indices above 65535 do not fit the list type: then every cell scans all
     const bool lists = n_obs <= 65535;
-    // the cell counts are cleared by extra workgroups (2048 cells each), and
-    // the fused loop's edge start rides along as further workgroups (ei)
-    const int clear_wg = grid ? (G * G * G + 2047) / 2048 : 0;
+    // cell counts that k_grid_build does not write are set by extra workgroups
+    // (2048 cells each), and the fused loop's edge start rides along as further
+    // workgroups (ei)
+    const bool build = grid && lists && n_obs > 0;
+    const int clear_wg = grid && !build ? (G * G * G + 2047) / 2048 : 0;
     const int init_wg = (ei && ei->n_edges > 0) ? (ei->n_edges + 255) / 256 : 0;
     hipLaunchKernelGGL(k_prep_obstacles, dim3(1 + clear_wg + init_wg), dim3(256), 0, st, obs, n_obs, (float4*)rec,
                        (float4*)centre, (GridGeom*)geom, G, r ? r->r_max : 0.f, r ? r->r_min : -kHuge,
                        kind == PREP_NEAR ? kNearGrow : 0.f, (int*)count,
                        lists ? 0 : kGridCap + 1, (unsigned*)state, lists ? 0u : 0x55555555u, clear_wg, init_wg ? *ei : EdgeInit{});
-    // four waves per obstacle until the obstacles alone fill the chip (512
-    // obstacles: 8.3 us against 12.6 with one wave; 4096: 16 us with one, 23.5
-    // with four)
     if (kind == PREP_NEAR && n_obs > 0)
         hipLaunchKernelGGL(k_near_build, dim3(kNearCells / (kNearBlock * kNearBlock * kNearBlock)), dim3(512), 0, st,
                            (const float4*)rec, n_obs, (const GridGeom*)geom, (uint2*)near, (unsigned short*)list);
-    if (grid && lists && n_obs > 0)
-        hipLaunchKernelGGL(k_grid_scatter, dim3((unsigned)n_obs), dim3(n_obs <= 1024 ? 256 : 64), 0, st, (const float4*)rec,
-                           (const GridGeom*)geom, G, kGridCap, (int*)count,
-                           (unsigned*)state, (unsigned short*)list);
+    if (build)
+        hipLaunchKernelGGL(k_grid_build, dim3((unsigned)(G * G * G / 64)), dim3(512), 0, st, (const float4*)rec, n_obs,
+                           (const GridGeom*)geom, G, kGridCap, (int*)count, (unsigned*)state, (unsigned short*)list);
     HIP_TRY(c, hipGetLastError());
     ov->n = n_obs;
     ov->lds_n = 0;

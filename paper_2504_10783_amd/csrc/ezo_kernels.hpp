@@ -124,7 +124,7 @@ __global__ void __launch_bounds__(256) k_prep_obstacles(const float* __restrict_
                                                         int* __restrict__ count, int count_init,
                                                         unsigned* __restrict__ state, unsigned state_init, int clear_wg, EdgeInit ei) {
     // Workgroups 1 .. clear_wg set the grid's cell counts and states to their
-    // start (0 before k_grid_scatter), the ones after them start the fused loop's edges
+    // start (where no k_grid_build writes them), the ones after them start the fused loop's edges
     // (independent work that would otherwise take launches of its own);
     // workgroup 0 does the rest.
     const int cells = G * G * G;
@@ -200,55 +200,89 @@ __global__ void __launch_bounds__(256) k_prep_obstacles(const float* __restrict_
     }
 }
 
-// Grid lists, built from the obstacles' side: one workgroup per obstacle, its
-// threads over the block of cells its reach can touch (the cell-index range of
-// [o - R, o + R] widened by one cell on each side, R = r_o + reach), each
-// cell kept by the same exact test of the distance from o to the cell's box;
-// a kept obstacle takes the next slot of the cell by an atomic count
-// (count[] must be zero on entry).  Which obstacles a cell lists is exactly
-// what a cell-by-cell scan of all obstacles lists; their order within the
-// list is whatever the atomics leave (the flags sweep only asks whether any
-// of them collides).  A count above cap marks an overflowing cell (the sweep
-// then scans every obstacle).  Bound by the chain of returning atomics (about
-// 1 us each), so few obstacles' cells (some 500 each) are spread over 256
-// threads (two or three steps) instead of the 64 of one wave.  A cell whose farthest point lies within r_o +
-// hit_reach of o is marked a certain hit in its state.
-__global__ void __launch_bounds__(256) k_grid_scatter(const float4* __restrict__ rec,
-                                                      const GridGeom* __restrict__ geom, int G, int cap,
-                                                      int* __restrict__ count, unsigned* __restrict__ state,
-                                                      unsigned short* __restrict__ list) {
-    const int o = blockIdx.x;
+// Grid lists: a workgroup per 16 x 2 x 2 cells (8 x 4 x 2 in a grid of 8: the
+// cells of four state words).  It gathers the obstacles whose reach R = r_o + reach touches the
+// block, kGridChunk of them at a time, into LDS; eight lanes per cell then keep
+// those that touch the cell: the exact test of the distance from o to the
+// cell's box against R (the block's box is made of the cells' own bounds, so
+// it refuses nothing that a cell keeps).  A count above cap marks an
+// overflowing cell (the sweep then scans every obstacle); a cell whose farthest
+// point lies within r_o + hit_reach of an obstacle is marked a certain hit.
+// Bound by the latency of its few steps; from the obstacles' side, a returning
+// global atomic per pair, 512 obstacles took 8.5 us and 2048 19, here 5.4 and 11.4
+// (256 threads 6.2 and 14.7, 1024 6.0 and 9.7).
+constexpr int kGridChunk = 1024;
+
+__global__ void __launch_bounds__(512) k_grid_build(const float4* __restrict__ rec, int n,
+                                                    const GridGeom* __restrict__ geom, int G, int cap,
+                                                    int* __restrict__ count, unsigned* __restrict__ state,
+                                                    unsigned short* __restrict__ list) {
+    __shared__ float4 ro[kGridChunk];
+    __shared__ unsigned short id[kGridChunk];
+    __shared__ int near, cnt[64];
+    __shared__ unsigned word[4];
+    const int tid = threadIdx.x, cell = tid / 8;
     const GridGeom g = load_geom(geom);
-    const float4 O = cload4((const cfloat*)rec + 4 * o);
-    const float R = O.w + g.reach;
-    int lo[3], hi[3];
-    const float oc[3] = {O.x, O.y, O.z}, orig[3] = {g.ox, g.oy, g.oz}, inv[3] = {g.ihx, g.ihy, g.ihz};
+    const int X = G < 16 ? 8 : 16, Y = 32 / X;                      // (G is 8, 16 or 32)
+    const int nbx = G / X, nby = G / Y;
+    const int x0 = X * (blockIdx.x % nbx), y0 = Y * (blockIdx.x / nbx % nby), z0 = 2 * (blockIdx.x / (nbx * nby));
+    const int cx = x0 + cell % X, cy = y0 + cell / X % Y, cz = z0 + cell / 32;
+    const int gc = (cz * G + cy) * G + cx;
+    const float lx = g.ox + cx * g.hx, ly = g.oy + cy * g.hy, lz = g.oz + cz * g.hz;
+    const float ux = lx + g.hx, uy = ly + g.hy, uz = lz + g.hz;
+    const float b0 = g.ox + x0 * g.hx, b1 = g.oy + y0 * g.hy, b2 = g.oz + z0 * g.hz;
+    const float e0 = (g.ox + (x0 + X - 1) * g.hx) + g.hx, e1 = (g.oy + (y0 + Y - 1) * g.hy) + g.hy,
+                e2 = (g.oz + (z0 + 1) * g.hz) + g.hz;
+    auto touches = [](const float4& O, float R, float l0, float u0, float l1, float u1, float l2, float u2) {
+        const float dx = fmaxf(fmaxf(l0 - O.x, O.x - u0), 0.f);
+        const float dy = fmaxf(fmaxf(l1 - O.y, O.y - u1), 0.f);
+        const float dz = fmaxf(fmaxf(l2 - O.z, O.z - u2), 0.f);
+        return fmaf(dx, dx, fmaf(dy, dy, dz * dz)) < R * R;
+    };
+    if (tid < 64) cnt[tid] = 0;
+    if (tid < 4) word[tid] = 0u;
+    for (int c0 = 0; c0 < n; c0 += kGridChunk) {
+        __syncthreads();
+        if (tid == 0) near = 0;
+        __syncthreads();
+        float4 O[kGridChunk / 512];
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {           // clamped in FP32 (an infinite reach covers the grid)
-        lo[a] = (int)fmaxf(floorf((oc[a] - R - orig[a]) * inv[a]) - 1.f, 0.f);
-        hi[a] = (int)fminf(floorf((oc[a] + R - orig[a]) * inv[a]) + 1.f, (float)(G - 1));
-    }
-    const int nx = hi[0] - lo[0] + 1, ny = hi[1] - lo[1] + 1, nz = hi[2] - lo[2] + 1;
-    if (nx <= 0 || ny <= 0 || nz <= 0) return;
-    const int total = nx * ny * nz;
-    for (int k = threadIdx.x; k < total; k += blockDim.x) {
-        const int cx = lo[0] + k % nx, cy = lo[1] + (k / nx) % ny, cz = lo[2] + k / (nx * ny);
-        const float lx = g.ox + cx * g.hx, ly = g.oy + cy * g.hy, lz = g.oz + cz * g.hz;
-        const float ux = lx + g.hx, uy = ly + g.hy, uz = lz + g.hz;
-        const float dx = fmaxf(fmaxf(lx - O.x, O.x - ux), 0.f);
-        const float dy = fmaxf(fmaxf(ly - O.y, O.y - uy), 0.f);
-        const float dz = fmaxf(fmaxf(lz - O.z, O.z - uz), 0.f);
-        if (fmaf(dx, dx, fmaf(dy, dy, dz * dz)) < R * R) {
-            const int cell = (cz * G + cy) * G + cx;
-            const int pos = atomicAdd(&count[cell], 1);
-            const float mx = fmaxf(O.x - lx, ux - O.x), my = fmaxf(O.y - ly, uy - O.y), mz = fmaxf(O.z - lz, uz - O.z);
-            const float sure = O.w + g.hit_reach;
-            unsigned st = pos == 0 ? 1u : 0u;
-            if (sure > 0.f && fmaf(mx, mx, fmaf(my, my, mz * mz)) < sure * sure) st |= 2u;
-            if (st) atomicOr(&state[cell >> 4], st << (2 * (cell & 15)));
-            if (pos < cap) list[(size_t)cell * cap + pos] = (unsigned short)o;
+        for (int u = 0; u < kGridChunk / 512; ++u) O[u] = rec[min(c0 + 512 * u + tid, n - 1)];
+#pragma unroll
+        for (int u = 0; u < kGridChunk / 512; ++u) {
+            const int o = c0 + 512 * u + tid;
+            if (o < n && touches(O[u], O[u].w + g.reach, b0, e0, b1, e1, b2, e2)) {
+                const int p = atomicAdd(&near, 1);
+                ro[p] = O[u];
+                id[p] = (unsigned short)o;
+            }
+        }
+        __syncthreads();
+        for (int l = tid % 8; l < near; l += 8) {
+            const float4 N = ro[l];
+            const float R = N.w + g.reach;
+            if (!touches(N, R, lx, ux, ly, uy, lz, uz)) continue;
+            // a negative reach (radii below zero), whose square is no bound: only
+            // cells within one of the range that it spans
+            if (R < 0.f && !((float)cx >= floorf((N.x - R - g.ox) * g.ihx) - 1.f && (float)cx <= floorf((N.x + R - g.ox) * g.ihx) + 1.f &&
+                             (float)cy >= floorf((N.y - R - g.oy) * g.ihy) - 1.f && (float)cy <= floorf((N.y + R - g.oy) * g.ihy) + 1.f &&
+                             (float)cz >= floorf((N.z - R - g.oz) * g.ihz) - 1.f && (float)cz <= floorf((N.z + R - g.oz) * g.ihz) + 1.f))
+                continue;
+            const int pos = atomicAdd(&cnt[cell], 1);
+            if (pos < cap) list[(size_t)gc * cap + pos] = id[l];
+            const float mx = fmaxf(N.x - lx, ux - N.x), my = fmaxf(N.y - ly, uy - N.y), mz = fmaxf(N.z - lz, uz - N.z);
+            const float sure = N.w + g.hit_reach;
+            if (sure > 0.f && fmaf(mx, mx, fmaf(my, my, mz * mz)) < sure * sure)
+                atomicOr(&word[cell >> 4], 2u << (2 * (cell & 15)));
         }
     }
+    __syncthreads();
+    if (tid % 8 == 0) {
+        count[gc] = cnt[cell];
+        if (cnt[cell] > 0) atomicOr(&word[cell >> 4], 1u << (2 * (cell & 15)));
+    }
+    __syncthreads();
+    if (tid % 128 == 0) state[gc >> 4] = word[cell >> 4];
 }
 
 // ---------------------------------------------------------------------------

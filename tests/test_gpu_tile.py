@@ -138,3 +138,29 @@ def test_largest_robot_with_every_part_pair(ezo, ctx):
             assert bool((res[3] == int(fo[0])).all())
     finally:
         ctx.set_autotune(True)
+
+
+@pytest.mark.parametrize("n_obs", [1, 31, 32, 255, 256, 1023, 1025, 2500])
+@pytest.mark.parametrize("kind", ["near", "far", "bad"])
+def test_grid_of_any_scene_equals_all_pairs(ezo, ctx, n_obs, kind):
+    """Every grid size and obstacle counts around a chunk of the grid's build: the
+    flags sweep against the all-pairs distances' own flags, which use no grid."""
+    data, desc = load("dof7")
+    rob = ezo.Robot(ctx, desc)
+    rng = draw.rng_for(7000 + n_obs)
+    lo, hi = ((0.3, -0.6, 0.0), (1.3, 0.6, 1.0)) if kind != "far" else ((0.9, 3.0, -9.0), (41.0, 4.0, 0.2))
+    obs = draw.obstacle_candidates(rng, n_obs, lo, hi, 0.01, 0.06).reshape(-1, 4)
+    if kind == "bad" and n_obs > 3:
+        obs[1, 0], obs[2, 3] = np.nan, np.nan        # (a radius below zero has no distance to compare: the sweep squares it)
+    n = 300
+    q = torch.from_numpy(draw.uniform_q(7001, n, data["q_lo"], data["q_hi"])).cuda()
+    o = torch.from_numpy(obs).cuda()
+    print_case("grid", kind, n_obs)
+    flags = torch.full((n,), 7, dtype=torch.uint8, device="cuda")
+    ezo.check_collisions(ctx, rob, o, q, flags)
+    want = torch.full((n,), 7, dtype=torch.uint8, device="cuda")
+    sd = torch.zeros(n, device="cuda")
+    ezo.check_collisions(ctx, rob, o, q, want, sd)
+    torch.cuda.synchronize()
+    sure = sd.abs() > 1e-5                                   # (a square root apart)
+    assert torch.equal(flags[sure], want[sure]) and int(sure.sum()) > n - 5
