@@ -417,6 +417,10 @@ bool sample_cfg_valid(const TileCfg& g) {
 constexpr int64_t kSampleWalks16 = 40000;
 constexpr int64_t kSampleWalks4 = 400000;
 
+// LDS that the drawn directions' 128-bit alignment adds (the face capacity's
+// limit does not count it).
+constexpr size_t kSampleAlign = 768;
+
 // `active` (device, may be NULL): number of running edges; when given, the
 // adaptive kernel chooses the lanes per walk on the device each launch.
 ezo_status launch_sample(ezo_ctx* c, int dof, const float* A, const float* b, const int* n_faces, int cap,
@@ -425,7 +429,7 @@ ezo_status launch_sample(ezo_ctx* c, int dof, const float* A, const float* b, co
                          const TileCfg* shape = nullptr, const int* active = nullptr,
                          const int* edge_ids = nullptr) {
     const int D = dof <= 4 ? 4 : 8;
-    if (sample_smem_bytes(D, 16, cap, 256) > c->lds_cap)
+    if (sample_smem_bytes(D, 16, cap, 256) > c->lds_cap + kSampleAlign)
         return ezo_fail(c, EZO_E_UNSUPPORTED, "face capacity %d too large for the sampler", cap);
     if (max_samples <= 0 || E <= 0) return EZO_OK;
     const uint32_t key0 = (uint32_t)seed, key1 = (uint32_t)(seed >> 32);
@@ -1347,7 +1351,7 @@ static ezo_status inflate_core(ezo_ctx* c, const ezo_robot* r, const float* obs,
                             skip);
     }
     const int cap = p->face_capacity;
-    if (sample_smem_bytes(dof <= 4 ? 4 : 8, 16, cap, 256) > c->lds_cap)
+    if (sample_smem_bytes(dof <= 4 ? 4 : 8, 16, cap, 256) > c->lds_cap + kSampleAlign)
         return ezo_fail(c, EZO_E_UNSUPPORTED, "face_capacity %d too large", cap);
     if ((size_t)p->n_p > c->lds_cap - kPlaceStaticLds) return ezo_fail(c, EZO_E_UNSUPPORTED, "n_p %d too large", p->n_p);
     // per-iteration constants, FP64 on the host

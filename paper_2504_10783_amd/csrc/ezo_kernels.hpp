@@ -402,14 +402,21 @@ __global__ void __launch_bounds__(256) k_centres(RobotView rb, ObsView ob, const
 //   L >= 4: the directions of 2 L steps are drawn ahead, lane m of the group
 //   drawing steps m and m + L, into LDS; the walk then reads them, so the
 //   random draws are off the walk's step-to-step dependency chain.
-// Rows stored as [F][D] normals plus b[F].
+// Rows and drawn steps are read from LDS 128 bits at a time: at D = 7 a row with
+// its b and a step with its chord word are eight words (32-bit reads of seven-
+// and eleven-word records: 42.3 us a launch for 10 000 walks of 60 steps, 137
+// for 96 000; this 35.8 and 126).  Bound by VALU issue: per step of 64 walks the
+// draws' integer products, then about 25 slots a row.
 // ---------------------------------------------------------------------------
 __host__ __device__ constexpr int sample_chunk(int L) { return 2 * L; }        // steps drawn ahead (L >= 4)
-__host__ __device__ constexpr int sample_dir_stride(int D) { return D + 4; }   // u[D], chord word, pad
-// Words per walk group's block of drawn steps: one more than the steps' words,
-// so that the groups of a wave, each reading its own block, start on distinct
-// LDS banks (an even block size put them on the same banks).
-__host__ __device__ constexpr int sample_group_words(int D, int L) { return sample_chunk(L) * sample_dir_stride(D) + 1; }
+__host__ __device__ constexpr int sample_dir_stride(int D) { return (D + 4) / 4 * 4; }   // u[D], chord word, pad
+// Words per walk group's block of drawn steps: four more than the steps' words,
+// so that the groups of a wave, each reading its own block 128 bits at a time,
+// start on distinct LDS banks.
+__host__ __device__ constexpr int sample_group_words(int D, int L) {
+    const int w = sample_chunk(L) * sample_dir_stride(D);
+    return w + (w % 8 == 0 ? 4 : 8);
+}
 
 // LDS bytes of k_sample: rows, then (L >= 4) the drawn directions, sized for
 // the most walk groups (L = 4) so that one size serves every L >= 4 (the fused
@@ -517,6 +524,53 @@ __device__ __forceinline__ void group_minmax(float& lo_max, float& hi_min) {
 // +-x_j exactly, so they are evaluated without the dot products (coordinates
 // j = sub, sub + L, ... on this lane), with the same FP32 operations on the
 // same values as the general rows: the chord ends are unchanged bit for bit.
+// Row f of the staged P: for D = 7 the normal and b side by side (two 128-bit
+// reads), else normals [F][D] and b [F].
+__host__ __device__ constexpr int row_stride(int D) { return D == 7 ? 8 : D; }
+template <int D>
+__device__ __forceinline__ float row_bound(const float* rowA, const float* rowb, int f) {
+    return D == 7 ? rowA[8 * f + 7] : rowb[f];
+}
+template <int D>
+__device__ __forceinline__ float load_row(const float* rowA, const float* rowb, int f, float (&a)[D]) {
+    if constexpr (D == 7) {
+        const f4 p = *reinterpret_cast<const f4*>(rowA + 8 * f), q = *reinterpret_cast<const f4*>(rowA + 8 * f + 4);
+        a[0] = p[0]; a[1] = p[1]; a[2] = p[2]; a[3] = p[3];
+        a[4] = q[0]; a[5] = q[1]; a[6] = q[2];
+        return q[3];
+    } else {
+#pragma unroll
+        for (int j = 0; j < D; ++j) a[j] = rowA[f * D + j];
+        return rowb[f];
+    }
+}
+
+// A drawn step (u[D], chord word), 128 bits at a time.
+template <int D>
+__device__ __forceinline__ void put_step(float* d, const float (&u)[D], float w) {
+    static_assert(D == 4 || D == 7 || D == 8, "coordinates of a walk");
+    f4* const v = reinterpret_cast<f4*>(d);
+    v[0] = f4{u[0], u[1], u[2], u[3]};
+    if constexpr (D == 4) d[4] = w;
+    if constexpr (D == 7) v[1] = f4{u[4], u[5], u[6], w};
+    if constexpr (D == 8) {
+        v[1] = f4{u[4], u[5], u[6], u[7]};
+        d[8] = w;
+    }
+}
+template <int D>
+__device__ __forceinline__ float get_step(const float* d, float (&u)[D]) {
+    const f4* const v = reinterpret_cast<const f4*>(d);
+    const f4 p = v[0];
+    u[0] = p[0]; u[1] = p[1]; u[2] = p[2]; u[3] = p[3];
+    if constexpr (D == 4) return d[4];
+    const f4 q = v[1];
+    if constexpr (D > 4) { u[4] = q[0]; u[5] = q[1]; u[6] = q[2]; }
+    if constexpr (D == 7) return q[3];
+    if constexpr (D == 8) u[7] = q[3];
+    return d[D];
+}
+
 template <int D, int L>
 __device__ __forceinline__ void walk_step(const float* rowA, const float* rowb, int F, int sub, const float (&u)[D],
                                           float wt, float (&x)[D], int nbox) {
@@ -535,8 +589,8 @@ __device__ __forceinline__ void walk_step(const float* rowA, const float* rowb, 
         const int j = m * L + sub;
         if (j < nbox) {
             const float r = __builtin_amdgcn_rcpf(uj), rn = __builtin_amdgcn_rcpf(-uj);
-            const float th = (rowb[j] - xj) * r;              // row +e_j <= hi_j
-            const float tl = (rowb[nbox + j] - (-xj)) * rn;   // row -e_j <= -lo_j
+            const float th = (row_bound<D>(rowA, rowb, j) - xj) * r;              // row +e_j <= hi_j
+            const float tl = (row_bound<D>(rowA, rowb, nbox + j) - (-xj)) * rn;   // row -e_j <= -lo_j
             // branch-free: a row that does not bound this side offers +-inf
             const bool pos = uj > 0.f, neg = uj < 0.f;
             thi = tmin(thi, pos ? th : (neg ? tl : INFINITY));
@@ -544,14 +598,14 @@ __device__ __forceinline__ void walk_step(const float* rowA, const float* rowb, 
         }
     }
     for (int f = 2 * nbox + sub; f < F; f += L) {
-        float den = 0.f, ax = 0.f;
+        float den = 0.f, ax = 0.f, a[D];
+        const float b = load_row<D>(rowA, rowb, f, a);
 #pragma unroll
         for (int j = 0; j < D; ++j) {
-            const float a = rowA[f * D + j];
-            den = fmaf(a, u[j], den);
-            ax = fmaf(a, x[j], ax);
+            den = fmaf(a[j], u[j], den);
+            ax = fmaf(a[j], x[j], ax);
         }
-        const float tt = (rowb[f] - ax) * __builtin_amdgcn_rcpf(den);
+        const float tt = (b - ax) * __builtin_amdgcn_rcpf(den);
         thi = tmin(thi, den > 0.f ? tt : INFINITY);     // branch-free, as above
         tlo = tmax(tlo, den < 0.f ? tt : -INFINITY);
     }
@@ -578,9 +632,9 @@ __device__ __forceinline__ void sample_block(char* smem, int dof, const float* _
     const float* Ae = A + (size_t)e * cap * dof;
     for (int i = threadIdx.x; i < F * D; i += blockDim.x) {
         const int f = i / D, j = i % D;
-        rowA[i] = j < dof ? Ae[(size_t)f * dof + j] : 0.f;
+        rowA[row_stride(D) * f + j] = j < dof ? Ae[(size_t)f * dof + j] : 0.f;
     }
-    for (int f = threadIdx.x; f < F; f += blockDim.x) rowb[f] = bvec[(size_t)e * cap + f];
+    for (int f = threadIdx.x; f < F; f += blockDim.x) *(D == 7 ? rowA + 8 * f + 7 : rowb + f) = bvec[(size_t)e * cap + f];
     __syncthreads();
     // the joint box as the first 2 dof rows?  (every polytope of the fused
     // loop starts so; a caller's P may not).  Used with at most four lanes
@@ -591,7 +645,7 @@ __device__ __forceinline__ void sample_block(char* smem, int dof, const float* _
         bool ok = true;
         for (int i = threadIdx.x; i < 2 * dof * dof; i += blockDim.x) {
             const int f = i / dof, j = i % dof;
-            ok = ok && rowA[f * D + j] == (j == f % dof ? (f < dof ? 1.f : -1.f) : 0.f);
+            ok = ok && rowA[row_stride(D) * f + j] == (j == f % dof ? (f < dof ? 1.f : -1.f) : 0.f);
         }
         nbox = (__syncthreads_and(ok ? 1 : 0) && L <= 4) ? dof : 0;
     }
@@ -629,22 +683,13 @@ __device__ __forceinline__ void sample_block(char* smem, int dof, const float* _
                 const int c0 = sub, c1 = sub + L;
                 const float w0 = draw_direction<D>(dof, ii, eid, kk, (uint32_t)(s0 + c0), key0, key1, u);
                 const float w1 = draw_direction<D>(dof, ii, eid, kk, (uint32_t)(s0 + c1), key0, key1, u2);
-                if (c0 < ns) {
-#pragma unroll
-                    for (int j = 0; j < D; ++j) dirs[c0 * SD + j] = u[j];
-                    dirs[c0 * SD + D] = w0;
-                }
-                if (c1 < ns) {
-#pragma unroll
-                    for (int j = 0; j < D; ++j) dirs[c1 * SD + j] = u2[j];
-                    dirs[c1 * SD + D] = w1;
-                }
+                if (c0 < ns) put_step<D>(dirs + c0 * SD, u, w0);
+                if (c1 < ns) put_step<D>(dirs + c1 * SD, u2, w1);
             }
             __syncthreads();
             for (int c = 0; c < ns; ++c) {
-#pragma unroll
-                for (int j = 0; j < D; ++j) u[j] = dirs[c * SD + j];
-                walk_step<D, L>(rowA, rowb, F, sub, u, dirs[c * SD + D], x, nbox);
+                const float wt = get_step<D>(dirs + c * SD, u);
+                walk_step<D, L>(rowA, rowb, F, sub, u, wt, x, nbox);
             }
             __syncthreads();
         }

@@ -264,3 +264,39 @@ def test_sample_count_tuning(ezo, ctx):
         assert not [e for e in ezo.tune_cache_entries() if e["kernel"] == "samples"]
     finally:
         ctx.set_autotune(True)
+
+
+@pytest.mark.parametrize("dof,F_extra,cap_pad", [(1, 0, 0), (3, 5, 0), (4, 40, 1), (5, 3, 2), (6, 17, 3), (7, 1, 0), (7, 90, 1), (8, 33, 0)])
+def test_sampler_widths_and_lanes(ezo, ctx, dof, F_extra, cap_pad):
+    """Every coordinate width, row counts around the lanes, a step count that is
+    no multiple of a chunk: one lane per walk (no staged steps) against the
+    others, bit for bit, and every sample inside."""
+    rng = np.random.default_rng(dof * 100 + F_extra)
+    A = np.vstack([np.eye(dof), -np.eye(dof), rng.normal(size=(F_extra, dof))]).astype(np.float32)
+    edge = (0.1 * rng.normal(size=(1, 2, dof))).astype(np.float32)
+    out_of = np.max(A.astype(np.float64) @ edge[0].astype(np.float64).T, axis=1)
+    b = (out_of + rng.uniform(0.05, 0.6, len(A))).astype(np.float32)
+    F, cap, n = len(b), len(b) + cap_pad, 517
+    At = torch.zeros((1, cap, dof), device="cuda")
+    bt = torch.zeros((1, cap), device="cuda")
+    At[0, :F], bt[0, :F] = torch.from_numpy(A).cuda(), torch.from_numpy(b).cuda()
+    nf = torch.tensor([F], dtype=torch.int32, device="cuda")
+    out = {}
+    ctx.set_autotune(False)
+    try:
+        for L in (1, 2, 4, 8, 16):
+            ezo.tune_cache_clear()
+            ezo.tune_cache_import(json.dumps({"arch": arch(), "kernel": "sample", "dof": dof, "spheres": 0,
+                                              "self_pairs": 0, "obstacles": 0, "log2_items": n.bit_length() - 1, "T": L,
+                                              "W": 4, "stage": 0, "us": 0.0}, separators=(",", ":")))
+            S = torch.full((1, dof, n), -9.0, device="cuda")
+            ezo.sample_polytopes(ctx, dof, At, bt, nf, torch.from_numpy(edge).cuda(), n, 37, seed=5, iteration=1, samples=S)
+            torch.cuda.synchronize()
+            out[L] = S
+        for L in (2, 4, 8, 16):
+            assert torch.equal(out[L], out[1]), L
+        x = out[1][0].cpu().numpy().T.astype(np.float64)
+        assert np.all(x @ A.T.astype(np.float64) <= b + 1e-4)
+    finally:
+        ezo.tune_cache_clear()
+        ctx.set_autotune(True)
