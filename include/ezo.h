@@ -565,8 +565,10 @@ ezo_status ezo_set_autotune(ezo_ctx *ctx, int32_t enable);
  * time per launch).  For "bisect", T counts candidates per workgroup and
  * depth (1..3, optional on import, default 1) the bisection levels checked
  * per round when the candidates fill the device (fewer candidates take more
- * levels), so a tile check holds T (2^depth - 1) configurations.  For
- * "samples" (the sample count N_p of ezo_inflate_edges), T is N_p and
+ * levels), so a tile check holds T (2^depth - 1) configurations.  A "check_sd"
+ * line with "field":1 (optional on import, default 0) is a shape of the
+ * distance field's kernel, which takes large batches; the all-pairs kernel has
+ * entries of its own.  For "samples" (the sample count N_p of ezo_inflate_edges), T is N_p and
  * tune_seed (export only) the Philox key of the timed inflations.  For
  * "sample", T is
  * the number of lanes per walk, W the waves per workgroup, and spheres =

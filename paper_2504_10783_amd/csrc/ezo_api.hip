@@ -366,10 +366,16 @@ bool near_pays(const ezo_ctx* c, const ezo_robot* r, int64_t n, int n_obs) {
     return n_obs == 0 || (n_obs <= 65535 && (double)n * r->S * n_obs >= kNearPairs);
 }
 
-// Its shapes: W waves of T / W configurations each (tuned as the all-pairs
-// shapes are; 4 x 8 otherwise).
+// Its shapes: W waves of T / W configurations each (tuned under keys of their
+// own; 4 x 8 otherwise).
 bool near_shape(const TileCfg& g) {
     return (g.W == 1 || g.W == 2 || g.W == 4) && pow2_tile(g.T) && g.T >= g.W && g.T <= 8 * g.W && g.stage == 0;
+}
+
+TuneKey near_key(const ezo_ctx* c, const ezo_robot* r, int n_obs, int64_t n) {
+    TuneKey k = tune_key(c, r, TUNE_CHECK_SD, n_obs, n);
+    k.field = 1;
+    return k;
 }
 
 ezo_status launch_distances(ezo_ctx* c, const ezo_robot* r, const ObsView& ov, const NearView& nv, const float* q,
@@ -378,7 +384,7 @@ ezo_status launch_distances(ezo_ctx* c, const ezo_robot* r, const ObsView& ov, c
     TileCfg g{32, 4, 0, 1}, tuned;
     if (shape)
         g = *shape;
-    else if (ezo_tune_lookup(tune_key(c, r, TUNE_CHECK_SD, ov.n, n), &tuned) && near_shape(tuned))
+    else if (ezo_tune_lookup(near_key(c, r, ov.n, n), &tuned) && near_shape(tuned))
         g = tuned;
     const int W = g.W, CW = g.T / W;
     const size_t lds = robot_stage_bytes(r->S, r->view.n_blocks, r->P, false) + (size_t)W * sd_wave_bytes(CW);
@@ -606,7 +612,7 @@ ezo_status tune_check_inplace(ezo_ctx* c, const ezo_robot* r, const ObsView& ov,
 ezo_status tune_distances_inplace(ezo_ctx* c, const ezo_robot* r, const ObsView& ov, const NearView& nv, const float* q,
                                   int64_t n, int64_t sn, int64_t sd, uint8_t* flags, float* min_sd,
                                   float* min_sd_self, hipStream_t st) {
-    const TuneKey k = tune_key(c, r, TUNE_CHECK_SD, ov.n, n);
+    const TuneKey k = near_key(c, r, ov.n, n);
     TileCfg g;
     if (!c->autotune || ezo_tune_lookup(k, &g)) return EZO_OK;
     const std::vector<TileCfg> cands = {{32, 4, 0, 1}, {16, 4, 0, 1}, {16, 2, 0, 1}, {8, 2, 0, 1}, {8, 1, 0, 1}};

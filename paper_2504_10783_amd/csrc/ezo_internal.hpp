@@ -52,10 +52,12 @@ enum TuneKind { TUNE_CHECK_FLAGS = 0, TUNE_CHECK_SD = 1, TUNE_BISECT = 2, TUNE_S
 // A tuned shape applies to calls with the same device architecture, kernel,
 // robot size (dof, spheres, self pairs), obstacle count and work size
 // (bucket = floor(log2(items))).  Sampler keys hold the dof and the walk
-// count only (spheres = self pairs = obstacles = 0).
+// count only (spheres = self pairs = obstacles = 0).  field: signed distances
+// by the distance field, whose kernel's shapes are not those of all pairs (the
+// line between the two falls inside a bucket).
 struct TuneKey {
     std::string arch;
-    int kind = 0, dof = 0, S = 0, P = 0, n_obs = 0, bucket = 0, B = 0;
+    int kind = 0, dof = 0, S = 0, P = 0, n_obs = 0, bucket = 0, B = 0, field = 0;
     bool operator<(const TuneKey& o) const;
 };
 

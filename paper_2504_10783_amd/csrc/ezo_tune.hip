@@ -72,9 +72,9 @@ bool find_str(const std::string& line, const char* key, std::string* out) {
 
 bool TuneKey::operator<(const TuneKey& o) const {
     if (arch != o.arch) return arch < o.arch;
-    const int a[7] = {kind, dof, S, P, n_obs, bucket, B};
-    const int b[7] = {o.kind, o.dof, o.S, o.P, o.n_obs, o.bucket, o.B};
-    for (int i = 0; i < 7; ++i)
+    const int a[8] = {kind, dof, S, P, n_obs, bucket, B, field};
+    const int b[8] = {o.kind, o.dof, o.S, o.P, o.n_obs, o.bucket, o.B, o.field};
+    for (int i = 0; i < 8; ++i)
         if (a[i] != b[i]) return a[i] < b[i];
     return false;
 }
@@ -199,6 +199,7 @@ ezo_status ezo_tune_cache_export(char* buf, int64_t capacity, int64_t* length) {
             const Entry& e = kv.second;
             char line[512], seed[64] = "";
             if (e.has_seed) std::snprintf(seed, sizeof(seed), ",\"tune_seed\":%llu", (unsigned long long)e.seed);
+            if (k.field) std::snprintf(seed, sizeof(seed), ",\"field\":1");
             std::snprintf(line, sizeof(line),
                           "{\"arch\":\"%s\",\"kernel\":\"%s\",\"dof\":%d,\"spheres\":%d,\"self_pairs\":%d,"
                           "\"boxes\":%d,\"obstacles\":%d,\"log2_items\":%d,\"T\":%d,\"W\":%d,\"stage\":%d,"
@@ -241,11 +242,13 @@ ezo_status ezo_tune_cache_import(const char* text, int32_t* n_imported) {
         if (ok) find_num(line, "depth", &depth);
         double boxes = 0.0;                          // optional key (robots with boxes)
         if (ok) find_num(line, "boxes", &boxes);
+        double field = 0.0;                          // optional key (signed distances by the field)
+        if (ok) find_num(line, "field", &field);
         const bool count = kind == TUNE_SAMPLE_COUNT;   // T is a sample count, not a tile size
         const bool shape_ok = (count ? (T >= 1 && T <= (1 << 24))
                                      : (T == 1 || T == 2 || T == 4 || T == 8 || T == 16 || T == 32 || T == 64)) &&
                               W >= 1 && W <= 16 && (v[7] == 0 || v[7] == 1) && (depth == 1 || depth == 2 || depth == 3);
-        if (!ok || kind < 0 || !shape_ok) return EZO_E_INVALID;
+        if (!ok || kind < 0 || !shape_ok || !(field == 0 || (field == 1 && kind == TUNE_CHECK_SD))) return EZO_E_INVALID;
         k.kind = kind;
         k.dof = (int)v[0];
         k.S = (int)v[1];
@@ -253,6 +256,7 @@ ezo_status ezo_tune_cache_import(const char* text, int32_t* n_imported) {
         k.n_obs = (int)v[3];
         k.bucket = (int)v[4];
         k.B = (int)boxes;
+        k.field = (int)field;
         Entry e;
         e.cfg.T = T;
         e.cfg.W = W;

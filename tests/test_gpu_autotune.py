@@ -300,3 +300,79 @@ def test_sampler_widths_and_lanes(ezo, ctx, dof, F_extra, cap_pad):
     finally:
         ezo.tune_cache_clear()
         ctx.set_autotune(True)
+
+
+def test_signed_distance_kernels_tune_apart(ezo, ctx):
+    """The line between all pairs and the distance field falls inside a size
+    bucket: calls on both sides of it each leave an entry of their own kernel,
+    and the distances are those of untuned calls."""
+    data, desc = load("dof7")
+    rob = ezo.Robot(ctx, desc)
+    obs = torch.from_numpy(data["obstacles"]).cuda()
+    sizes = (1100, 2100, 3000, 4000, 4100, 6000, 8000)
+    print_case("distance kernels' keys", sizes)
+    q = torch.from_numpy(draw.uniform_q(58, max(sizes), data["q_lo"], data["q_hi"])).cuda()
+    ctx.set_autotune(False)
+    ezo.tune_cache_clear()
+    ref = [run_check(ezo, ctx, rob, obs, q[:n].contiguous(), True) for n in sizes]
+    ctx.set_autotune(True)
+    try:
+        for n, want in zip(sizes, ref):
+            for a, b in zip(run_check(ezo, ctx, rob, obs, q[:n].contiguous(), True), want):
+                assert torch.equal(a, b), n
+        keys = [(e["log2_items"], e.get("field", 0)) for e in ezo.tune_cache_entries() if e["kernel"] == "check_sd"]
+        assert len(set(keys)) == len(keys)
+        assert any((b, 0) in keys and (b, 1) in keys for b in (10, 11, 12)), keys
+    finally:
+        ezo.tune_cache_clear()
+
+
+# shapes that the all-pairs kernel takes, and those of the distance field (W waves
+# of one to eight configurations)
+PAIR_SHAPES = [(T, W) for T in (4, 8, 16, 32) for W in (1, 2, 4, 8)]
+FIELD_SHAPES = [(T, W) for T in (1, 2, 4, 8, 16, 32) for W in (1, 2, 4) if W <= T <= 8 * W]
+
+
+def test_distance_shapes_give_identical_results(ezo, ctx):
+    """All-pairs shapes on a batch below the distance field's line, the field's on
+    one above it; the small batch is the start of the large one, so the two
+    kernels' distances are compared as well."""
+    data, desc = load("dof7")
+    rob = ezo.Robot(ctx, desc)
+    obs = torch.from_numpy(data["obstacles"]).cuda()
+    small, large = 1001, 50_021
+    print_case("distance shapes", small, large)
+    q = torch.from_numpy(draw.uniform_q(59, large, data["q_lo"], data["q_hi"])).cuda()
+    ctx.set_autotune(False)
+    try:
+        ezo.tune_cache_clear()
+        ref = run_check(ezo, ctx, rob, obs, q, True)
+        assert 0.05 < ref[0].float().mean().item() < 0.95
+        for shapes, n, field in ((PAIR_SHAPES, small, 0), (FIELD_SHAPES, large, 1)):
+            for T, W in shapes:
+                ezo.tune_cache_clear()
+                ezo.tune_cache_import(entry("check_sd", desc, len(obs), n, T, W, 0).replace('"us"', f'"field":{field},"us"'))
+                for a, b in zip(run_check(ezo, ctx, rob, obs, q[:n].contiguous(), True), ref):
+                    assert torch.equal(a, b[:n]), (T, W, field)
+    finally:
+        ezo.tune_cache_clear()
+        ctx.set_autotune(True)
+
+
+def test_all_pairs_tuning_fills_cache(ezo, ctx):
+    data, desc = load("dof7")
+    rob = ezo.Robot(ctx, desc)
+    obs = torch.from_numpy(data["obstacles"]).cuda()
+    n = 1024
+    q = torch.from_numpy(draw.uniform_q(60, n, data["q_lo"], data["q_hi"])).cuda()
+    ctx.set_autotune(False)
+    ezo.tune_cache_clear()
+    ref = run_check(ezo, ctx, rob, obs, q, True)
+    ctx.set_autotune(True)
+    try:
+        for a, b in zip(run_check(ezo, ctx, rob, obs, q, True), ref):
+            assert torch.equal(a, b)
+        e, = [e for e in ezo.tune_cache_entries() if e["kernel"] == "check_sd"]
+        assert (e["log2_items"], e["obstacles"], e.get("field", 0)) == (10, len(obs), 0) and e["us"] > 0
+    finally:
+        ezo.tune_cache_clear()

@@ -111,6 +111,25 @@ def test_tuning_cache_rejects_malformed_lines(ezo, bad):
     assert ezo.tune_cache_entries() == []               # nothing imported from a rejected text
 
 
+def test_distance_field_shapes_have_keys_of_their_own(ezo):
+    """Two kernels compute signed distances; an entry of one is not one of the
+    other, also where dof, spheres, obstacles and the batch's size agree."""
+    ezo.tune_cache_clear()
+    allp = TUNE_LINE.replace('"bisect"', '"check_sd"').replace('"stage":1', '"stage":0')
+    field = allp.replace('"us"', '"field":1,"us"').replace('"T":16', '"T":8')
+    try:
+        assert ezo.tune_cache_import(allp + "\n" + field) == 2
+        ents = ezo.tune_cache_entries()
+        assert sorted((e.get("field", 0), e["T"]) for e in ents) == [(0, 16), (1, 8)]
+        text = ezo.tune_cache_export()
+        ezo.tune_cache_clear()
+        assert ezo.tune_cache_import(text) == 2 and ezo.tune_cache_export() == text
+        with pytest.raises(ezo.EzoError):                # the flags check has no such kernel
+            ezo.tune_cache_import(field.replace('"check_sd"', '"check_flags"'))
+    finally:
+        ezo.tune_cache_clear()
+
+
 def test_edge_stats_view_reads_the_c_array(ezo):
     """The per-edge statistics of a call are a view of the C array the
     library filled: dicts on access (indices, negative indices, slices),
