@@ -134,7 +134,7 @@ ezo_status prep_obstacles_into(ezo_ctx* c, const ezo_robot* r, const float* obs,
     const int init_wg = (ei && ei->n_edges > 0) ? (ei->n_edges + 255) / 256 : 0;
     hipLaunchKernelGGL(k_prep_obstacles, dim3(1 + clear_wg + init_wg), dim3(256), 0, st, obs, n_obs, (float4*)rec,
                        (float4*)centre, (GridGeom*)geom, G, r ? r->r_max : 0.f, r ? r->r_min : -kHuge,
-                       kind == PREP_NEAR ? kNearGrow : 0.f, (int*)count,
+                       kind == PREP_NEAR ? kNearGrow : 0.f, kind == PREP_NEAR && r ? r->reach : INFINITY, (int*)count,
                        lists ? 0 : kGridCap + 1, (unsigned*)state, lists ? 0u : 0x55555555u, clear_wg, init_wg ? *ei : EdgeInit{});
     if (kind == PREP_NEAR && n_obs > 0)
         hipLaunchKernelGGL(k_near_build, dim3(kNearCells / (kNearBlock * kNearBlock * kNearBlock)), dim3(512), 0, st,
@@ -381,7 +381,11 @@ TuneKey near_key(const ezo_ctx* c, const ezo_robot* r, int n_obs, int64_t n) {
 ezo_status launch_distances(ezo_ctx* c, const ezo_robot* r, const ObsView& ov, const NearView& nv, const float* q,
                             int64_t n, int64_t sn, int64_t sd, uint8_t* flags, float* min_sd, float* min_sd_self,
                             hipStream_t st, const TileCfg* shape = nullptr) {
-    TileCfg g{32, 4, 0, 1}, tuned;
+    // four waves a workgroup; eight configurations a wave, fewer while that leaves
+    // the chip without 4096 waves (4000 among 512: 63 us with eight, 44 with one;
+    // 16 000: 65, 57 with four, 80 with one; 65 536 among 4096: 182, 197 with four)
+    TileCfg g{4, 4, 0, 1}, tuned;
+    while (g.T < 32 && n > 1024 * (int64_t)g.T) g.T *= 2;
     if (shape)
         g = *shape;
     else if (ezo_tune_lookup(near_key(c, r, ov.n, n), &tuned) && near_shape(tuned))
@@ -615,7 +619,8 @@ ezo_status tune_distances_inplace(ezo_ctx* c, const ezo_robot* r, const ObsView&
     const TuneKey k = near_key(c, r, ov.n, n);
     TileCfg g;
     if (!c->autotune || ezo_tune_lookup(k, &g)) return EZO_OK;
-    const std::vector<TileCfg> cands = {{32, 4, 0, 1}, {16, 4, 0, 1}, {16, 2, 0, 1}, {8, 2, 0, 1}, {8, 1, 0, 1}};
+    const std::vector<TileCfg> cands = {{32, 4, 0, 1}, {16, 4, 0, 1}, {8, 4, 0, 1}, {4, 4, 0, 1},
+                                        {16, 2, 0, 1}, {8, 2, 0, 1}, {8, 1, 0, 1}};
     const int64_t n_t = std::min<int64_t>(n, 1LL << 19);
     auto run = [&](const TileCfg& cfg) {
         return launch_distances(c, r, ov, nv, q, n_t, sn, sd, flags, min_sd, min_sd_self, st, &cfg);
@@ -964,6 +969,16 @@ ezo_status ezo_robot_create(ezo_ctx* c, const ezo_robot_desc* d, ezo_robot** out
         r_max = std::max(r_max, sph[s2].w);
         r_min = std::min(r_min, sph[s2].w);
     }
+    // the reach: the links' lengths up to a sphere's, padded for FP32
+    double reach = 0.0, at = 0.0;
+    for (int j = 0, s2 = 0; j < dof; ++j) {
+        const double slide = (prismatic >> j) & 1u ? std::max(std::fabs(d->q_lo[j]), std::fabs(d->q_hi[j])) : 0.0;
+        at += std::hypot((double)dh[j].x, std::fabs((double)dh[j].y) + slide);
+        for (; s2 < link_begin[j + 1]; ++s2)
+            reach = std::max(reach, at + std::sqrt((double)sph[s2].x * sph[s2].x + (double)sph[s2].y * sph[s2].y +
+                                                   (double)sph[s2].z * sph[s2].z));
+    }
+    reach = reach * (1.0 + 1e-5) + 1e-5;
     // boxes sorted by link (stable); four float4 each: (centre, h_x), (rotation
     // row 0, h_y), (row 1, h_z), (row 2, bounding radius |h| padded for FP32)
     const int B = d->n_boxes, Q = d->n_box_pairs;
@@ -1046,6 +1061,7 @@ ezo_status ezo_robot_create(ezo_ctx* c, const ezo_robot_desc* d, ezo_robot** out
     char* b = reinterpret_cast<char*>(buf);
     r->r_max = r_max;
     r->r_min = r_min;
+    r->reach = std::isfinite(reach) ? (float)reach : INFINITY;
     r->view.dof = dof;
     r->view.prismatic = prismatic;
     r->view.n_spheres = S;

@@ -128,12 +128,17 @@ struct GridGeom {
     float reach;               // r_sphere_max + slack
     float hit_reach;           // r_sphere_min - slack (hugely negative for a robot without spheres)
     float r_max;               // largest obstacle radius
+    // distance field only: magnitude of the coordinates (for rounding), how far
+    // from the robot's base a sphere centre may lie along an axis, the least
+    // distance from there to a far obstacle, the largest radius of the others
+    float extent, limit, far, r_near;
 };
 
 // Grid geometry through scalar loads (wave-uniform, written by earlier kernels).
 __device__ __forceinline__ GridGeom load_geom(const GridGeom* p) {
     const __attribute__((address_space(4))) float* s = (const __attribute__((address_space(4))) float*)p;
-    return GridGeom{s[0], s[1], s[2], s[3], s[4], s[5], s[6], s[7], s[8], s[9], s[10], s[11]};
+    return GridGeom{s[0], s[1], s[2], s[3], s[4], s[5], s[6], s[7], s[8], s[9], s[10], s[11],
+                    s[12], s[13], s[14], s[15]};
 }
 
 struct GridView {

@@ -28,6 +28,7 @@ constexpr int kNearBlock = 4;            // cells per axis of a build workgroup
 constexpr int kNearBlockList = 2048;     // obstacles a build workgroup holds for its block
 constexpr unsigned kNearFull = 0xFFFFu;  // list length of a cell that did not fit: scan all
 constexpr float kNearGrow = 0.35f;       // the field reaches this share of the cloud's largest extent beyond it
+constexpr int kAllSpheres = 8;           // spheres that an obstacle record is read for at once where no list serves
 
 // Field entry: distance of the cell's centre to the nearest obstacle surface
 // (-inf: unknown), nearest obstacle | list length << 16.
@@ -72,8 +73,6 @@ __device__ __forceinline__ float box_far(float4 o, const float (&l)[3], const fl
 // Rounding slack of the field's bounds: coordinates of magnitude up to ext.
 __device__ __forceinline__ float near_slack(float ext) { return 1e-5f + 4e-6f * ext; }
 
-__device__ __forceinline__ float geom_extent(const GridGeom& g) { return fabsf(g.ox) + fabsf(g.oy) + fabsf(g.oz); }
-
 // The field, one workgroup per block of kNearBlock^3 cells: the obstacles that
 // can be nearest from anywhere in the block are copied to LDS (those no farther
 // from the block's box than the least farthest distance of any), and each cell
@@ -91,7 +90,7 @@ __global__ void __launch_bounds__(512) k_near_build(const float4* __restrict__ r
     const GridGeom g = load_geom(geom);
     const int tid = threadIdx.x, lane = tid & 63, w = wave_id();
     const int bx = blockIdx.x % NB, by = (blockIdx.x / NB) % NB, bz = blockIdx.x / (NB * NB);
-    const float sl = near_slack(geom_extent(g));
+    const float sl = near_slack(g.extent);
     const float org[3] = {g.ox, g.oy, g.oz}, h[3] = {g.hx, g.hy, g.hz};
     // a cell's (a block's) box, widened by the rounding of the cell assignment
     auto box = [&](int x, int y, int z, int cells, float (&l)[3], float (&u)[3]) {
@@ -135,7 +134,9 @@ __global__ void __launch_bounds__(512) k_near_build(const float4* __restrict__ r
             }
     }
     __syncthreads();
-    const bool all = s_n > kNearBlockList;           // too many: the cells look at every obstacle
+    // too many: the cells look for the nearest of all obstacles and keep no lists
+    // (which would not fit)
+    const bool all = s_n > kNearBlockList;
     const int m = all ? n : s_n;
     for (int c = w; c < kNearBlock * kNearBlock * kNearBlock; c += 8) {
         const int x = bx * kNearBlock + c % kNearBlock, y = by * kNearBlock + (c / kNearBlock) % kNearBlock,
@@ -146,14 +147,21 @@ __global__ void __launch_bounds__(512) k_near_build(const float4* __restrict__ r
                     mz = g.oz + ((float)z + 0.5f) * g.hz;
         float d = INFINITY, far = INFINITY;
         int at = 0;
-#pragma unroll 2
-        for (int k = lane; k < m; k += 64) {
-            const float4 O = all ? rec[k] : crec[k];
+        auto nearest = [&](float4 O, int k) {
             const float ex = O.x - mx, ey = O.y - my, ez = O.z - mz;
             const float v = __builtin_amdgcn_sqrtf(fmaf(ex, ex, fmaf(ey, ey, ez * ez))) - O.w;
             at = v < d ? k : at;
             d = v < d ? v : d;
-            far = fminf(far, box_far(O, l, u) - O.w);
+        };
+        if (all) {
+#pragma unroll 4
+            for (int k = lane; k < n; k += 64) nearest(rec[k], k);
+        } else {
+#pragma unroll 2
+            for (int k = lane; k < m; k += 64) {
+                nearest(crec[k], k);
+                far = fminf(far, box_far(crec[k], l, u) - crec[k].w);
+            }
         }
         const float dm = wave_min(d);
         far = wave_min(far);
@@ -165,18 +173,18 @@ __global__ void __launch_bounds__(512) k_near_build(const float4* __restrict__ r
         }
         int cnt = 0;
 #pragma unroll 2
-        for (int k0 = 0; k0 < m; k0 += 64) {
+        for (int k0 = 0; !all && k0 < m && cnt <= kNearCap; k0 += 64) {
             const int k = k0 + lane, kk = min(k, m - 1);
-            const float4 O = all ? rec[kk] : crec[kk];
+            const float4 O = crec[kk];
             const bool keep = k < m && box_near(O, l, u) - O.w <= far + sl;
             const unsigned long long b = __ballot(keep);
             const int pos = cnt + __popcll(b & ((1ull << lane) - 1ull));
-            if (keep && pos < kNearCap) list[(size_t)cell * kNearCap + pos] = (unsigned short)(all ? kk : cand[kk]);
+            if (keep && pos < kNearCap) list[(size_t)cell * kNearCap + pos] = cand[kk];
             cnt += __popcll(b);
         }
         if (lane == 0) {
             // a distance past FP32 says nothing: scan all
-            const bool known = dm < 3e38f && cnt <= kNearCap;
+            const bool known = dm < 3e38f && !all && cnt <= kNearCap;
             const unsigned len = known ? (unsigned)cnt : kNearFull;
             near[cell] = make_uint2(__float_as_uint(dm < 3e38f ? dm : -INFINITY), (unsigned)near_o | len << 16);
         }
@@ -238,12 +246,16 @@ struct WaveWalk {
 // Where a point lies in the field: its cell, the nearest obstacle of the
 // cell's centre, and a lower bound of the point's distance to every obstacle's
 // surface.  Outside the field's box the point's projection onto the box is
-// looked up: every centre lies in the box, so |c - o|^2 >= |c - pc|^2 + |pc - o|^2.
+// looked up: along the axes where it differs the centres of the obstacles about the
+// robot lie within the box, so |c - o|^2 >= |c - pc|^2 + |pc - o|^2 for them; the
+// far ones are no nearer than g.far.  A point past the robot's reach (a prismatic
+// joint beyond its limits) keeps every pair.  base: the frame's origin, -base
+// the robot's.
 struct NearAt {
     int cell, o, len;
     float lb;
 };
-__device__ __forceinline__ NearAt near_at(const GridGeom& g, const NearView& nv, float x, float y, float z) {
+__device__ __forceinline__ NearAt near_at(const GridGeom& g, const NearView& nv, float4 base, float x, float y, float z) {
     const float top = (float)kNearG - 0.5f;
     const float fx = fminf(fmaxf((x - g.ox) * g.ihx, 0.f), top + 0.49f), fy = fminf(fmaxf((y - g.oy) * g.ihy, 0.f), top + 0.49f),
                 fz = fminf(fmaxf((z - g.oz) * g.ihz, 0.f), top + 0.49f);
@@ -262,10 +274,12 @@ __device__ __forceinline__ NearAt near_at(const GridGeom& g, const NearView& nv,
     const float d = __uint_as_float(e.x) - __builtin_amdgcn_sqrtf(fmaf(mx, mx, fmaf(my, my, mz * mz)));
     const bool inside = e2 == 0.f;
     if (!inside) r.len = (int)kNearFull;               // (a NaN coordinate too)
-    const float t = fmaxf(d + g.r_max, 0.f);
-    const float lb = inside ? d : __builtin_amdgcn_sqrtf(fmaf(t, t, e2)) - g.r_max;
-    r.lb = lb - near_slack(fabsf(x) + fabsf(y) + fabsf(z) + geom_extent(g)) - 4e-6f * fabsf(lb);
-    if (x != x || y != y || z != z) r.lb = -INFINITY;  // not a number: keeps every pair (their values are ignored)
+    const float t = fmaxf(d + g.r_near, 0.f);
+    const float lb = inside ? d : fminf(__builtin_amdgcn_sqrtf(fmaf(t, t, e2)) - g.r_near, g.far);
+    r.lb = lb - near_slack(fabsf(x) + fabsf(y) + fabsf(z) + g.extent) - 4e-6f * fabsf(lb);
+    const bool past = fmaxf(fmaxf(fabsf(x + base.x), fabsf(y + base.y)), fabsf(z + base.z)) > g.limit;
+    // not a number: keeps every pair (their values are ignored)
+    if (past || x != x || y != y || z != z) r.lb = -INFINITY;
     return r;
 }
 
@@ -342,7 +356,7 @@ __global__ void __launch_bounds__(256, 4) k_distances(RobotView rb, ObsView ob, 
                     const int s = on[u] ? k.k : 0;
                     k.next(nc);
                     C[u] = place(tile_frame(t, c[u], t.link[s]), t.sph[s]);
-                    a[u] = near_at(g, nv, C[u].x, C[u].y, C[u].z);
+                    a[u] = near_at(g, nv, sh, C[u].x, C[u].y, C[u].z);
                 }
 #pragma unroll
                 for (int u = 0; u < 3; ++u) {
@@ -358,19 +372,54 @@ __global__ void __launch_bounds__(256, 4) k_distances(RobotView rb, ObsView ob, 
                     const int c = k.c, s = on ? k.k : 0;
                     k.next(nc);
                     const f4 C = place(tile_frame(t, c, t.link[s]), t.sph[s]);
-                    const NearAt a = near_at(g, nv, C.x, C.y, C.z);
+                    const NearAt a = near_at(g, nv, sh, C.x, C.y, C.z);
                     const float lb = a.lb - C.w;
                     sw.push(on && !(lb >= lds_val(sw.env + c)), c | s << 6, lb, a.cell, a.len);
                 } else if (sw.n > 0) {
-                    // sixteen spheres at a time, four to a row of 16 lanes, each
-                    // over its cell's list
                     wave_lds_sync();
                     const int m = min(sw.n, 64), sub = lane >> 4, li = lane & 15;
+                    // spheres that no list serves: the wave's lanes over all
+                    // obstacles, kAllSpheres of them to a record (their cost is
+                    // that of the all-pairs kernel's pairs)
+                    {
+                        const i4 e = sw.e[sw.n - m + min(lane, m - 1)];
+                        const int c = e.x & 63, s = e.x >> 6;
+                        const f4 C = place(tile_frame(t, c, t.link[s]), t.sph[s]);
+                        unsigned long long left = __ballot(lane < m && e.w == (int)kNearFull);
+                        while (left) {
+                            left &= __ballot(!(__int_as_float(e.y) >= lds_val(sw.env + c)));
+                            if (!left) break;
+                            f4 D[kAllSpheres];
+                            int at[kAllSpheres];
+                            float best[kAllSpheres];
+#pragma unroll
+                            for (int u = 0; u < kAllSpheres; ++u) {
+                                at[u] = left ? __builtin_ctzll(left) : at[u > 0 ? u - 1 : 0];     // (a repeated one changes nothing)
+                                left &= left - 1ull;
+#pragma unroll
+                                for (int k = 0; k < 4; ++k)
+                                    D[u][k] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(C[k]), at[u]));
+                                best[u] = INFINITY;
+                            }
+                            for (int o = lane; o < ob.n; o += 64) {
+                                const float4 O = ob.rec[o];
+#pragma unroll
+                                for (int u = 0; u < kAllSpheres; ++u) best[u] = fminf(best[u], sd_pair(D[u], O));
+                            }
+#pragma unroll
+                            for (int u = 0; u < kAllSpheres; ++u) {
+                                const float v = wave_min(best[u]);
+                                if (lane == 0) lds_min(sw.env + __builtin_amdgcn_readlane(c, at[u]), v);
+                            }
+                            wave_lds_sync();
+                        }
+                    }
+                    // the others sixteen at a time, four to a row of 16 lanes, each
+                    // over its cell's list
                     for (int i0 = 0; i0 < m; i0 += 16) {
                         f4 C[4];
                         int c[4], len[4];
                         const unsigned short* lst[4];
-                        bool full[4];
                         float best[4];
                         int most = 0;
 #pragma unroll
@@ -380,10 +429,9 @@ __global__ void __launch_bounds__(256, 4) k_distances(RobotView rb, ObsView ob, 
                             c[u] = e.x & 63;
                             const int s = e.x >> 6;
                             C[u] = place(tile_frame(t, c[u], t.link[s]), t.sph[s]);
-                            full[u] = e.w == (int)kNearFull;
                             lst[u] = nv.list + (size_t)e.z * kNearCap;
-                            len[u] = full[u] ? ob.n : e.w;
-                            if (i >= m || __int_as_float(e.y) >= lds_val(sw.env + c[u])) len[u] = 0;
+                            len[u] = e.w;
+                            if (i >= m || e.w == (int)kNearFull || __int_as_float(e.y) >= lds_val(sw.env + c[u])) len[u] = 0;
                             most = max(most, len[u]);
                             best[u] = INFINITY;
                         }
@@ -391,7 +439,7 @@ __global__ void __launch_bounds__(256, 4) k_distances(RobotView rb, ObsView ob, 
                             int o[4];
 #pragma unroll
                             for (int u = 0; u < 4; ++u)
-                                o[u] = k2 < len[u] ? (full[u] ? k2 : (int)lst[u][k2]) : -1;
+                                o[u] = k2 < len[u] ? (int)lst[u][k2] : -1;
                             float4 O[4];
 #pragma unroll
                             for (int u = 0; u < 4; ++u) O[u] = ob.rec[max(o[u], 0)];

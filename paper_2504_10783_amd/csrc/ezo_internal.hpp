@@ -106,6 +106,7 @@ struct ezo_robot {
     int slots = 0;                     // LDS pose rows per configuration: S + 4 B
     float r_max = 0.f;                 // largest sphere radius
     float r_min = 0.f;                 // smallest (hugely negative without spheres)
+    float reach = 0.f;                 // no sphere centre is farther from the base (joints within their limits)
     void* buf = nullptr;               // one device allocation holding everything below
     ezo::RobotView view{};
     const int* sorted_to_orig = nullptr;

@@ -115,12 +115,36 @@ __device__ inline void init_edge(const EdgeInit& a, int e) {
 // and largest obstacle radius; records (o', r) with o' = o - centre of the
 // box; geometry of a G^3 grid over the box grown by
 // r_sphere_max + r_obstacle_max + slack.
+//
+// The distance field's box (reach finite: how far from the base a sphere centre
+// can lie) is the box of the obstacles about the robot, within the reach: one
+// obstacle far away, or as large as the ground, does not make its cells too coarse
+// to tell the others apart (4096 obstacles, one of them 200 m away, 65 536
+// configurations: 10.9 ms with cells over the whole cloud).  Along an axis where
+// the two hardly overlap it takes the reach.  Obstacles farther than kNearFar
+// reaches, or larger, are far ones: a lower bound of the distance to all of them
+// stands for them outside the box.
 // ---------------------------------------------------------------------------
 constexpr float kGridSlack = 1e-4f;
+constexpr float kNearFar = 1.5f;
+
+// Least / largest value over the workgroup's four waves (NaN ignored), in every
+// thread; red: four words per value.
+template <int N>
+__device__ __forceinline__ void group_min(float (&v)[N], float (*red)[4]) {
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        const float m = wave_min(v[k]);
+        if ((threadIdx.x & 63) == 0) red[k][threadIdx.x >> 6] = m;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < N; ++k) v[k] = fminf(fminf(red[k][0], red[k][1]), fminf(red[k][2], red[k][3]));
+}
 
 __global__ void __launch_bounds__(256) k_prep_obstacles(const float* __restrict__ obs, int n, float4* __restrict__ rec,
                                                         float4* __restrict__ centre, GridGeom* __restrict__ geom,
-                                                        int G, float r_sphere_max, float r_sphere_min, float grow,
+                                                        int G, float r_sphere_max, float r_sphere_min, float grow, float reach,
                                                         int* __restrict__ count, int count_init,
                                                         unsigned* __restrict__ state, unsigned state_init, int clear_wg, EdgeInit ei) {
     // Workgroups 1 .. clear_wg set the grid's cell counts and states to their
@@ -179,6 +203,29 @@ __global__ void __launch_bounds__(256) k_prep_obstacles(const float* __restrict_
             c[k] = 0.5f * (v[k] + v[3 + k]);
             half[k] = 0.5f * (v[3 + k] - v[k]);
         }
+    // the field: the box and largest radius (negated maxima) of the obstacles about
+    // the robot, and the far ones' least distance from the base
+    float w[8] = {kHuge, kHuge, kHuge, kHuge, kHuge, kHuge, 0.f, INFINITY};
+    if (reach < INFINITY) {
+        __shared__ float wred[8][4];
+        const float lim = kNearFar * reach;
+        for (int o = tid; o < n; o += 4 * blockDim.x) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float* x = obs + 4 * (size_t)min(o + i * (int)blockDim.x, n - 1);
+                const float a = x[0], b = x[1], d = x[2], r = x[3];
+                const bool near = fabsf(a) <= lim && fabsf(b) <= lim && fabsf(d) <= lim && r <= reach;
+                if (near) {
+                    w[0] = fminf(w[0], a); w[1] = fminf(w[1], b); w[2] = fminf(w[2], d);
+                    w[3] = fminf(w[3], -a); w[4] = fminf(w[4], -b); w[5] = fminf(w[5], -d);
+                    w[6] = fminf(w[6], -r);
+                } else {
+                    w[7] = fminf(w[7], __builtin_amdgcn_sqrtf(fmaf(a, a, fmaf(b, b, d * d))) - r);
+                }
+            }
+        }
+        group_min<8>(w, wred);
+    }
     if (tid == 0) {
         centre[0] = make_float4(c[0], c[1], c[2], 0.f);
         const float margin = r_sphere_max + v[6] + kGridSlack + 2.f * grow * fmaxf(half[0], fmaxf(half[1], half[2]));
@@ -191,6 +238,37 @@ __global__ void __launch_bounds__(256) k_prep_obstacles(const float* __restrict_
         g.reach = r_sphere_max + kGridSlack;
         g.r_max = v[6];
         g.hit_reach = r_sphere_min - kGridSlack - 1e-5f * (h[0] + h[1] + h[2]);
+        // coordinates and their differences round with the cloud's, its distance's
+        // and its radii's magnitude
+        g.extent = 0.f;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) g.extent += half[k] + margin + fabsf(c[k]);
+        g.limit = reach + 2e-6f * (fabsf(c[0]) + fabsf(c[1]) + fabsf(c[2]));
+        g.r_near = g.limit < INFINITY ? -w[6] : v[6];
+        g.far = INFINITY;
+        if (g.limit < INFINITY) {
+            // (a point within the limit is at most sqrt(3) limits from the base)
+            g.far = w[7] - 1.7321f * g.limit - 4e-6f * (g.extent + 2.f * g.limit);
+            float l[3], u[3], most = 0.f;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) most = fmaxf(most, -w[3 + k] - w[k]);
+            const float m = r_sphere_max + g.r_near + kGridSlack + grow * most;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const float rl = -c[k] - g.limit, ru = -c[k] + g.limit;
+                l[k] = fmaxf(w[k] - c[k] - m, rl);
+                u[k] = fminf(-w[3 + k] - c[k] + m, ru);
+                if (!(u[k] - l[k] >= 0.1f * g.limit)) {
+                    l[k] = rl;
+                    u[k] = ru;
+                }
+                h[k] = (u[k] - l[k]) / (float)G;
+                g.extent += fmaxf(fabsf(l[k]), fabsf(u[k]));
+            }
+            g.ox = l[0]; g.oy = l[1]; g.oz = l[2];
+            g.hx = h[0]; g.hy = h[1]; g.hz = h[2];
+            g.ihx = 1.f / h[0]; g.ihy = 1.f / h[1]; g.ihz = 1.f / h[2];
+        }
         geom[0] = g;
     }
     for (int o = tid; o < n; o += blockDim.x) {

@@ -104,3 +104,85 @@ def test_field_equals_all_pairs(ezo, ctx, name, n_obs, kind):
                 assert torch.equal(a, b)
     finally:
         ctx.set_obstacle_boxes(None)
+
+
+# ---- scenes and robots at the field's own edges ------------------------------
+
+def field_scene(kind, n_obs, seed=0):
+    """Obstacles about a 1 m arm: spread out; one far away, or a ground sphere of
+    100 m, among them; heaped on one another; some on a point; a radius or a
+    coordinate that is infinite."""
+    rng = draw.rng_for(4000 + n_obs + seed)
+    obs = draw.obstacle_candidates(rng, n_obs, (0.3, -0.5, 0.0), (1.3, 0.5, 1.0), 0.01, 0.06).reshape(-1, 4)
+    if kind == "outlier":
+        obs[1, :3] = (300.0, -40.0, 2.0)
+    if kind == "ground":
+        obs[1] = (0.3, 0.1, -100.3, 100.0)
+    if kind == "heap":
+        obs[:, :3] = np.float32([0.6, 0.0, 0.5]) + np.float32(0.02) * rng.random((n_obs, 3), dtype=np.float32)
+    if kind == "point":
+        obs[: n_obs // 2] = (0.5, 0.1, 0.4, 0.05)
+    if kind == "inf radius":
+        obs[4, 3] = np.inf
+    if kind == "inf centre":
+        obs[4, 1] = -np.inf
+    if kind == "behind":
+        obs[:, 0] += 30.0
+    return obs
+
+
+def field_against_pairs(ezo, ctx, rob, desc, obs, q):
+    """A batch that the field takes (its tuning entry says so) against calls of 64
+    rows of it, which test all pairs: the same values, rows of its start and end."""
+    n, o = len(q), torch.from_numpy(np.ascontiguousarray(obs)).cuda()
+    ezo.tune_cache_clear()
+    ctx.set_autotune(True)
+    try:
+        got = check(ezo, ctx, rob, o, q)
+        assert [e.get("field") for e in ezo.tune_cache_entries() if e["kernel"] == "check_sd"] == [1]
+    finally:
+        ctx.set_autotune(False)
+        ezo.tune_cache_clear()
+    untuned = check(ezo, ctx, rob, o, q)
+    for a, b in zip(untuned, got):
+        assert torch.equal(a, b)
+    for lo in [*range(0, 640, 64), n - 64]:
+        want = check(ezo, ctx, rob, o, q[lo:lo + 64].contiguous())
+        for k, (a, b) in enumerate(zip(got, want)):
+            same = (a[lo:lo + 64] == b) | (a[lo:lo + 64].isnan() & b.isnan())
+            assert bool(same.all()), (k, lo, int((~same).sum()))
+    return got
+
+
+@pytest.mark.parametrize("kind,n_obs,n", [
+    ("spread", 600, 4000), ("outlier", 600, 4000), ("ground", 600, 4000), ("heap", 3000, 2000), ("point", 3000, 2000),
+    ("inf radius", 600, 4000), ("inf centre", 600, 4000), ("behind", 600, 4000), ("spread", 6000, 6000),
+    ("heap", 200, 20000), ("spread", 129, 20000)])
+def test_field_scenes(ezo, ctx, kind, n_obs, n):
+    """Cells whose list is too long, blocks of cells with more obstacles than a
+    workgroup holds, and obstacles far larger or farther than the robot."""
+    data, desc = load("dof7")
+    rob = ezo.Robot(ctx, desc)
+    print_case("field scene", kind, n_obs, n)
+    q = torch.from_numpy(draw.uniform_q(4100, n, data["q_lo"], data["q_hi"])).cuda()
+    q[5, 0], q[6, -1] = float("nan"), float("inf")
+    field_against_pairs(ezo, ctx, rob, desc, field_scene(kind, n_obs), q)
+
+
+@pytest.mark.parametrize("dof,per_link,prismatic,n", [(1, 1, False, 1 << 20), (5, 16, True, 8000), (8, 128, False, 2000)])
+def test_field_robots(ezo, ctx, dof, per_link, prismatic, n):
+    """The smallest and the largest robot (1024 spheres, every part pair), and
+    sliding joints far beyond their limits, where no bound of the field holds."""
+    desc = draw.arm_dh(draw.rng_for(4200 + dof), dof, per_link)
+    if prismatic:
+        desc["joint_type"] = (np.arange(dof) % 3 == 1).astype(np.int32)
+    if per_link == 128:
+        s = np.arange(1024).reshape(16, 64)                # [part][sphere]
+        desc["self_pairs"] = np.array([(s[a, i], s[b, 1 + i]) for a in range(16) for b in range(a, 16) for i in range(3)], np.int32)
+    print_case("field robot", dof, per_link, prismatic, n)
+    q = draw.uniform_q(4300, n, desc["q_lo"], desc["q_hi"])
+    if prismatic:
+        q[::3] *= np.where(desc["joint_type"] == 1, 40.0, 1.0).astype(np.float32)
+    rob = ezo.Robot(ctx, desc)
+    field_against_pairs(ezo, ctx, rob, desc, field_scene("outlier", 700), torch.from_numpy(q).cuda())
+
