@@ -358,12 +358,22 @@ ezo_status launch_check(ezo_ctx* c, const ezo_robot* r, const ObsView& ov, const
 }
 
 // Signed distances of spheres by the distance field (k_distances), or over all
-// pairs: the field's build and launch (20 us for 200 obstacles, 95 for 4096)
-// pay from about kNearPairs pairs on (about 25 us at all pairs).
-constexpr double kNearPairs = 1.0e8;
+// pairs.  Against the all-pairs kernel the field saves, per configuration, its
+// pairs (0.22 ps a pair with an obstacle, 0.5 a self pair, measured on full chips)
+// less what its lookups take (15 ps a sphere and 100); the saving has to pay for
+// its build and launch: 20 us up to 4096 obstacles (where all pairs of a small
+// batch leave most of the chip idle), 0.1 us for each obstacle more (whose blocks
+// keep no lists: 0.3 ms of build at 16 384).  The 7-DOF arm (70 spheres, 1500 self
+// pairs), all pairs and field: 16 obstacles 116 and 133 us at 91 000, 1.58 and
+// 1.54 ms at 1.4 M; 512 obstacles 32 and 44 at 1400, 72 and 45 at 5600; 4096 obstacles
+// 107 and 94 at 400, 172 and 95 at 1400.  A planar arm of 12 spheres, 1 M: 0.15 and
+// 0.34 ms among 20, 0.86 and 0.36 among 300.  Without obstacles only the self
+// pairs are saved (0.42 and 0.33 ms at 500 000, 25 and 31 us at 20 000).
 bool near_pays(const ezo_ctx* c, const ezo_robot* r, int64_t n, int n_obs) {
-    if (r->B > 0 || c->n_ebox > 0 || r->S == 0) return false;
-    return n_obs == 0 || (n_obs <= 65535 && (double)n * r->S * n_obs >= kNearPairs);
+    if (r->B > 0 || c->n_ebox > 0 || r->S == 0 || n_obs > 65535) return false;
+    if (n_obs == 0) return (double)n * r->P >= 1.0e8;
+    const double saved = 0.22e-6 * r->S * n_obs + 0.5e-6 * r->P - 15e-6 * r->S - 1e-4;       // us a configuration
+    return (double)n * saved >= 20.0 + 0.1 * std::max(n_obs - EZO_NOALLOC_MAX_OBSTACLES, 0);
 }
 
 // Its shapes: W waves of T / W configurations each (tuned under keys of their

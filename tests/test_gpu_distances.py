@@ -186,3 +186,42 @@ def test_field_robots(ezo, ctx, dof, per_link, prismatic, n):
     rob = ezo.Robot(ctx, desc)
     field_against_pairs(ezo, ctx, rob, desc, field_scene("outlier", 700), torch.from_numpy(q).cuda())
 
+
+def test_field_without_obstacles(ezo, ctx):
+    """Self distances of a batch past the field's line, against the oracle."""
+    import oracle
+    from gpu_common import BAND, SD_TOL
+    data, desc = load("dof7")
+    rob, orob = ezo.Robot(ctx, desc), oracle.Robot(desc)
+    n, m = 100_003, 2000
+    print_case("field without obstacles", n)
+    q = draw.uniform_q(4400, n, data["q_lo"], data["q_hi"])
+    flags, sd, own = check(ezo, ctx, rob, torch.zeros((0, 4), device="cuda"), torch.from_numpy(q).cuda())
+    assert torch.equal(sd, own) and torch.equal(flags, (own < 0).to(torch.uint8))
+    fo, so, *_ = oracle.check(orob, np.zeros((0, 4)), q[:m].astype(np.float64))
+    assert np.abs(own[:m].cpu().numpy() - so).max() <= SD_TOL
+    sure = np.abs(so) >= BAND
+    assert np.array_equal(flags[:m].cpu().numpy()[sure], fo[sure])
+
+
+@pytest.mark.parametrize("name,n_obs,n,field", [
+    ("dof7", 4, 400_000, 0), ("dof7", 16, 100_000, 0), ("tiny", 20, 1 << 20, 0), ("dof7", 65535, 30, 0),
+    ("dof7", 16384, 200, 0), ("dof7", 0, 20_000, 0), ("forest", 15, 1 << 20, 0),
+    ("dof7", 128, 30_000, 1), ("dof7", 512, 5600, 1), ("dof7", 4096, 700, 1), ("tiny", 300, 300_000, 1)])
+def test_kernel_by_size(ezo, ctx, name, n_obs, n, field):
+    """All pairs where there is little to leave out or the field's build would cost
+    more than the batch (few obstacles, few spheres, few configurations among very
+    many obstacles), the field where it saves."""
+    data, desc = load(name)
+    rob = ezo.Robot(ctx, desc)
+    print_case("kernel by size", name, n_obs, n)
+    obs = torch.from_numpy(field_scene("spread", max(n_obs, 1))[:n_obs].copy()).cuda()
+    q = torch.from_numpy(draw.uniform_q(4500, n, data["q_lo"], data["q_hi"])).cuda()
+    ezo.tune_cache_clear()
+    ctx.set_autotune(True)
+    try:
+        check(ezo, ctx, rob, obs, q)
+        assert [e.get("field", 0) for e in ezo.tune_cache_entries() if e["kernel"] == "check_sd"] == [field]
+    finally:
+        ctx.set_autotune(False)
+        ezo.tune_cache_clear()
