@@ -840,7 +840,7 @@ def inflation_measure(args, name, plain=True, cpu=True):
         instance = f"ezo::k_project_bisect<{box}, false, {'true' if sb['stage'] else 'false'}>" if sb else None
     else:
         sc = shapes.get("check_flags")
-        instance = f"ezo::k_check<false, {box}, {'true' if sc['stage'] else 'false'}>" if sc else None
+        instance = f"ezo::k_check<{box}, {'true' if sc['stage'] else 'false'}>" if sc else None
     roofline = {"bound": "alu", "achieved": achieved, "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s",
                 "frac": achieved / PEAK_FP32_TFLOPS,
                 "traffic": measured_traffic(name, instance, n_p_used) if instance else None,

@@ -316,43 +316,77 @@ std::vector<TileCfg> tile_candidates(const ezo_ctx* c, const ezo_robot* r, int n
 // to seven waves per SIMD that the kernel's registers allow.
 constexpr int kFlagWaves = 2 * kNumCU * 24;
 
-template <bool SD>
 ezo_status launch_check(ezo_ctx* c, const ezo_robot* r, const ObsView& ov, const GridView& gv, const float* q, int64_t n,
-                        int64_t sn, int64_t sd, int64_t q_batch, uint8_t* flags, float* min_sd,
-                        float* min_sd_self, int64_t out_batch, int n_batch, const int* status,
-                        const IterArgs& it, hipStream_t st, const float* pred = nullptr, float margin = 0.f,
-                        EdgeStatsDev* stats = nullptr, const TileCfg* shape = nullptr) {
+                        int64_t sn, int64_t sd, int64_t q_batch, uint8_t* flags, int64_t out_batch, int n_batch,
+                        const int* status, const IterArgs& it, hipStream_t st, const float* pred = nullptr,
+                        float margin = 0.f, EdgeStatsDev* stats = nullptr, const TileCfg* shape = nullptr) {
     TileCfg g;
     if (shape) {
         g = *shape;
     } else {
         const int64_t items = n * n_batch;
-        g = resolve_cfg(c, tune_key(c, r, SD ? TUNE_CHECK_SD : TUNE_CHECK_FLAGS, ov.n, items),
-                        heuristic_check(c, r, ov.n, items, SD), r, ov.n, SD);
+        g = resolve_cfg(c, tune_key(c, r, TUNE_CHECK_FLAGS, ov.n, items), heuristic_check(c, r, ov.n, items, false), r,
+                        ov.n, false);
     }
     const int T = g.T, W = g.W;
     if (T == 0) return ezo_fail(c, EZO_E_UNSUPPORTED, "robot too large for one tile");
     ObsView ovs = ov;
     ovs.lds_n = g.stage ? ov.n : 0;
-    const size_t lds = TileRows(r, ov.n, SD).bytes(T, W) + 16 * (size_t)ovs.lds_n;
+    const size_t lds = TileRows(r, ov.n, false).bytes(T, W) + 16 * (size_t)ovs.lds_n;
     const int64_t tiles = (n + T - 1) / T;
     if (tiles <= 0) return EZO_OK;
-    // one batch in flags mode: at most kFlagWaves waves, each workgroup taking
-    // tiles in turn, so that the copy of the cell states is paid by several
-    const int64_t wgs = SD || n_batch > 1 ? tiles : std::min<int64_t>(tiles, kFlagWaves / W);
+    // one batch: at most kFlagWaves waves, each workgroup taking tiles in turn,
+    // so that the copy of the cell states is paid by several
+    const int64_t wgs = n_batch > 1 ? tiles : std::min<int64_t>(tiles, kFlagWaves / W);
     dim3 grid((unsigned)wgs, (unsigned)n_batch), block(64 * W);
     const bool box = r->B > 0 || ov.n_ebox > 0;
-#define EZO_LAUNCH_CHECK(BB, OO)                                                                                  \
-    EZO_KLAUNCH(c, (k_check<SD, BB, OO>), grid, block, lds, st, r->view, ovs, gv, T, q, n, sn, sd, q_batch, flags, \
-                min_sd, min_sd_self, out_batch, status, it, pred, margin, stats)
-    if (!SD && ovs.lds_n > 0) {
-        if (box) EZO_LAUNCH_CHECK(true, !SD);
-        else EZO_LAUNCH_CHECK(false, !SD);
+#define EZO_LAUNCH_CHECK(BB, OO)                                                                              \
+    EZO_KLAUNCH(c, (k_check<BB, OO>), grid, block, lds, st, r->view, ovs, gv, T, q, n, sn, sd, q_batch, flags, \
+                out_batch, status, it, pred, margin, stats)
+    if (ovs.lds_n > 0) {
+        if (box) EZO_LAUNCH_CHECK(true, true);
+        else EZO_LAUNCH_CHECK(false, true);
     } else {
         if (box) EZO_LAUNCH_CHECK(true, false);
         else EZO_LAUNCH_CHECK(false, false);
     }
 #undef EZO_LAUNCH_CHECK
+    HIP_TRY(c, hipGetLastError());
+    return EZO_OK;
+}
+
+// Signed distances over all pairs.
+ezo_status launch_check_sd(ezo_ctx* c, const ezo_robot* r, const ObsView& ov, const float* q, int64_t n, int64_t sn,
+                           int64_t sd, uint8_t* flags, float* min_sd, float* min_sd_self, hipStream_t st,
+                           const TileCfg* shape = nullptr) {
+    const TileCfg g = shape ? *shape
+                            : resolve_cfg(c, tune_key(c, r, TUNE_CHECK_SD, ov.n, n), heuristic_check(c, r, ov.n, n, true),
+                                          r, ov.n, true);
+    const int T = g.T, W = g.W;
+    if (T == 0) return ezo_fail(c, EZO_E_UNSUPPORTED, "robot too large for one tile");
+    const size_t lds = TileRows(r, ov.n, true).bytes(T, W);
+    const int64_t tiles = (n + T - 1) / T;
+    if (tiles <= 0) return EZO_OK;
+    const dim3 grid((unsigned)tiles), block(64 * W);
+    const bool box = r->B > 0 || ov.n_ebox > 0;
+#define EZO_LAUNCH_SD(TT)                                                                                             \
+    case TT:                                                                                                          \
+        if (box) hipLaunchKernelGGL((k_check_sd<TT, true>), grid, block, lds, st, r->view, ov, q, n, sn, sd, flags,    \
+                                    min_sd, min_sd_self);                                                             \
+        else hipLaunchKernelGGL((k_check_sd<TT, false>), grid, block, lds, st, r->view, ov, q, n, sn, sd, flags,       \
+                                min_sd, min_sd_self);                                                                 \
+        break
+    switch (T) {
+        EZO_LAUNCH_SD(64);
+        EZO_LAUNCH_SD(32);
+        EZO_LAUNCH_SD(16);
+        EZO_LAUNCH_SD(8);
+        EZO_LAUNCH_SD(4);
+        EZO_LAUNCH_SD(2);
+        EZO_LAUNCH_SD(1);
+        default: return ezo_fail(c, EZO_E_INVALID, "tile of %d configurations", T);
+    }
+#undef EZO_LAUNCH_SD
     HIP_TRY(c, hipGetLastError());
     return EZO_OK;
 }
@@ -603,22 +637,31 @@ ezo_status list_candidates(ezo_ctx* c, const int* n_cands, int E, int cand_cap, 
 // configurations (the kernel only writes outputs, so repeated launches are
 // harmless).  The prefix keeps one timing launch to a few milliseconds
 // while leaving far more workgroups than CUs.
-template <bool SD>
 ezo_status tune_check_inplace(ezo_ctx* c, const ezo_robot* r, const ObsView& ov, const GridView& gv, const float* q,
-                              int64_t n, int64_t sn, int64_t sd, uint8_t* flags, float* min_sd, float* min_sd_self,
-                              hipStream_t st) {
-    const TuneKey k = tune_key(c, r, SD ? TUNE_CHECK_SD : TUNE_CHECK_FLAGS, ov.n, n);
+                              int64_t n, int64_t sn, int64_t sd, uint8_t* flags, hipStream_t st) {
+    const TuneKey k = tune_key(c, r, TUNE_CHECK_FLAGS, ov.n, n);
     TileCfg g;
     if (!c->autotune || ezo_tune_lookup(k, &g)) return EZO_OK;
-    const int64_t n_t = SD ? std::min<int64_t>(n, std::max<int64_t>(65536, (1LL << 28) / std::max(ov.n, 256)))
-                           : std::min<int64_t>(n, 1LL << 19);
-    const auto cands = SD ? tile_candidates(c, r, ov.n, true, {1, 2, 4, 8, 16}, n_t)
-                          : tile_candidates(c, r, ov.n, false, {1, 2, 4, 8}, n_t);
+    const int64_t n_t = std::min<int64_t>(n, 1LL << 19);
+    const auto cands = tile_candidates(c, r, ov.n, false, {1, 2, 4, 8}, n_t);
     if (cands.empty()) return EZO_OK;
     IterArgs it{nullptr, 0, 0, 0, 0};
     auto run = [&](const TileCfg& cfg) {
-        return launch_check<SD>(c, r, ov, gv, q, n_t, sn, sd, 0, flags, min_sd, min_sd_self, 0, 1, nullptr, it, st,
-                                nullptr, 0.f, nullptr, &cfg);
+        return launch_check(c, r, ov, gv, q, n_t, sn, sd, 0, flags, 0, 1, nullptr, it, st, nullptr, 0.f, nullptr, &cfg);
+    };
+    return ezo_tune_search(c, k, cands, st, run, &g);
+}
+
+ezo_status tune_check_sd_inplace(ezo_ctx* c, const ezo_robot* r, const ObsView& ov, const float* q, int64_t n, int64_t sn,
+                                 int64_t sd, uint8_t* flags, float* min_sd, float* min_sd_self, hipStream_t st) {
+    const TuneKey k = tune_key(c, r, TUNE_CHECK_SD, ov.n, n);
+    TileCfg g;
+    if (!c->autotune || ezo_tune_lookup(k, &g)) return EZO_OK;
+    const int64_t n_t = std::min<int64_t>(n, std::max<int64_t>(65536, (1LL << 28) / std::max(ov.n, 256)));
+    const auto cands = tile_candidates(c, r, ov.n, true, {1, 2, 4, 8, 16}, n_t);
+    if (cands.empty()) return EZO_OK;
+    auto run = [&](const TileCfg& cfg) {
+        return launch_check_sd(c, r, ov, q, n_t, sn, sd, flags, min_sd, min_sd_self, st, &cfg);
     };
     return ezo_tune_search(c, k, cands, st, run, &g);
 }
@@ -705,8 +748,8 @@ ezo_status tune_inflation(ezo_ctx* c, const ezo_robot* r, const ObsView& ov, con
         return s;
     IterArgs it{nullptr, 0, 0, 0, 0};
     auto run_c = [&](const TileCfg& cfg) {
-        return launch_check<false>(c, r, ov, gv, w_s, S_cap, 1, stride, (int64_t)dof * stride, w_f, nullptr, nullptr,
-                                   stride, E, nullptr, it, st, nullptr, 0.f, nullptr, &cfg);
+        return launch_check(c, r, ov, gv, w_s, S_cap, 1, stride, (int64_t)dof * stride, w_f, stride, E, nullptr, it, st,
+                            nullptr, 0.f, nullptr, &cfg);
     };
     if (need_c) {
         const auto cands = tile_candidates(c, r, ov.n, false, {1, 2, 4, 8}, (int64_t)S_cap * E);
@@ -1142,15 +1185,12 @@ ezo_status ezo_check_collisions(ezo_ctx* c, const ezo_robot* r, const float* obs
                 return s;
             return launch_distances(c, r, ov, nv, q, n, stride_n, stride_d, flags, min_sd, min_sd_self, st);
         }
-        if ((s = tune_check_inplace<true>(c, r, ov, gv, q, n, stride_n, stride_d, flags, min_sd, min_sd_self, st)))
-            return s;
-        return launch_check<true>(c, r, ov, gv, q, n, stride_n, stride_d, 0, flags, min_sd, min_sd_self, 0, 1,
-                                  nullptr, it, st);
+        if ((s = tune_check_sd_inplace(c, r, ov, q, n, stride_n, stride_d, flags, min_sd, min_sd_self, st))) return s;
+        return launch_check_sd(c, r, ov, q, n, stride_n, stride_d, flags, min_sd, min_sd_self, st);
     }
     if ((s = prep_obstacles(c, r, obs, n_obs, st, &ov, &gv))) return s;
-    if ((s = tune_check_inplace<false>(c, r, ov, gv, q, n, stride_n, stride_d, flags, nullptr, nullptr, st))) return s;
-    return launch_check<false>(c, r, ov, gv, q, n, stride_n, stride_d, 0, flags, nullptr, nullptr, 0, 1, nullptr, it,
-                               st);
+    if ((s = tune_check_inplace(c, r, ov, gv, q, n, stride_n, stride_d, flags, st))) return s;
+    return launch_check(c, r, ov, gv, q, n, stride_n, stride_d, 0, flags, 0, 1, nullptr, it, st);
 }
 
 ezo_status ezo_check_collisions_noalloc(ezo_ctx* c, const ezo_robot* r, const float* obs, int32_t n_obs,
@@ -1183,12 +1223,9 @@ ezo_status ezo_check_collisions_noalloc(ezo_ctx* c, const ezo_robot* r, const fl
     }
     // launch shapes: the tuning cache or the size heuristic (never a timing
     // search, which would write the outputs repeatedly)
+    if (sd) return launch_check_sd(c, r, ov, q, n, stride_n, stride_d, flags, min_sd, min_sd_self, st);
     IterArgs it{nullptr, 0, 0, 0, 0};
-    if (min_sd || min_sd_self)
-        return launch_check<true>(c, r, ov, gv, q, n, stride_n, stride_d, 0, flags, min_sd, min_sd_self, 0, 1,
-                                  nullptr, it, st);
-    return launch_check<false>(c, r, ov, gv, q, n, stride_n, stride_d, 0, flags, nullptr, nullptr, 0, 1, nullptr, it,
-                               st);
+    return launch_check(c, r, ov, gv, q, n, stride_n, stride_d, 0, flags, 0, 1, nullptr, it, st);
 }
 
 ezo_status ezo_sphere_centres(ezo_ctx* c, const ezo_robot* r, const float* q, int64_t n, int64_t stride_n,
@@ -1562,10 +1599,9 @@ static ezo_status inflate_core(ezo_ctx* c, const ezo_robot* r, const float* obs,
             gvc.tests = c->d_tests + (size_t)EZO_PHASE_CHECK * kTestSlots;
             gvb.tests = c->d_tests + (size_t)EZO_PHASE_BISECT * kTestSlots;
         }
-        if ((ls = launch_check<false>(c, r, ov, gvc, (const float*)w_s, S_cap, 1, stride, (int64_t)dof * stride,
-                                      (uint8_t*)w_f, nullptr, nullptr, stride, E, edge_status, it, st,
-                                      screen_samples ? (const float*)w_pred : nullptr,
-                                      screen_samples ? p->surrogate->margin : 0.f, (EdgeStatsDev*)w_st))) {
+        if ((ls = launch_check(c, r, ov, gvc, (const float*)w_s, S_cap, 1, stride, (int64_t)dof * stride, (uint8_t*)w_f,
+                               stride, E, edge_status, it, st, screen_samples ? (const float*)w_pred : nullptr,
+                               screen_samples ? p->surrogate->margin : 0.f, (EdgeStatsDev*)w_st))) {
             mark(EZO_NUM_PHASES);
             return ls;
         }
@@ -1985,8 +2021,7 @@ ezo_status ezo_check_path(ezo_ctx* c, const ezo_robot* r, const float* obs, int3
     GridView gv;
     if ((s = prep_obstacles(c, r, obs, n_obs, st, &ov, &gv))) return s;
     IterArgs it{nullptr, 0, 0, 0, 0};
-    if ((s = launch_check<false>(c, r, ov, gv, (const float*)wpts, N, dof, 1, 0, (uint8_t*)wflags, nullptr, nullptr,
-                                 0, 1, nullptr, it, st)))
+    if ((s = launch_check(c, r, ov, gv, (const float*)wpts, N, dof, 1, 0, (uint8_t*)wflags, 0, 1, nullptr, it, st)))
         return s;
     // colliding points in path order: the first point_capacity of them, and their count
     const int64_t span = flag_span(N);

@@ -520,15 +520,14 @@ __device__ __forceinline__ bool wave_all(bool p) {
 // t.red[1][0][c] = self minimum; t.hit[c] = (overall < 0).  Barrier at exit.
 // Distances by v_sqrt_f32 (one instruction, within about 1 ulp; the
 // correctly rounded sqrtf takes several more per pair).
-template <bool BOX>
-__device__ inline void tile_pairs_sd(const RobotView& rb, const ObsView& ob, const TileSmem& t, int T,
-                                     int n_valid) {
+template <int T, bool BOX>
+__device__ inline void tile_pairs_sd(const RobotView& rb, const ObsView& ob, const TileSmem& t, int n_valid) {
     const int tid = threadIdx.x;
     const int W = blockDim.x >> 6;
     const int w = wave_id();
     const int lane = tid & 63;
     const int c = lane % T;
-    const int nsub = 64 / T;
+    constexpr int nsub = 64 / T;
     const int j = lane / T;
     const int S = rb.n_spheres;
     float env = INFINITY, self = INFINITY;
@@ -1120,10 +1119,10 @@ __device__ inline unsigned tile_flags(const RobotView& rb, const ObsView& ob, co
 
 // Whole tile check in signed-distance mode on t.q[0..n_valid): fills t.hit,
 // t.red[c] (overall) and t.red[W*T + c] (self).
-template <bool BOX>
-__device__ inline void tile_check_sd(const RobotView& rb, const ObsView& ob, const TileSmem& t, int T, int n_valid) {
+template <int T, bool BOX>
+__device__ inline void tile_check_sd(const RobotView& rb, const ObsView& ob, const TileSmem& t, int n_valid) {
     tile_fk<BOX>(rb, ob, t, T, n_valid);
-    tile_pairs_sd<BOX>(rb, ob, t, T, n_valid);
+    tile_pairs_sd<T, BOX>(rb, ob, t, n_valid);
 }
 
 }  // namespace ezo

@@ -11,7 +11,7 @@
 // below, each against the obstacles that can be nearest from anywhere in its
 // cell.  Self pairs: link parts by their bounding spheres in the same way.
 //
-// k_check's signed-distance mode (all pairs) stays for batches too small to pay
+// k_check_sd (all pairs) stays for batches too small to pay
 // for the field and for boxes: the same scheme with box bounding spheres and
 // face normals as bounds took 735 us where all pairs take 654 (300 001
 // configurations of the 11-box arm among 194 spheres; a long box's bounds are

@@ -368,11 +368,10 @@ __global__ void __launch_bounds__(512) k_grid_build(const float4* __restrict__ r
 // blockIdx.x = tile.  q_b = q + b * q_batch; flags_b = flags + b * out_batch.
 // n = iteration's |S| when it.cur is set, else n_arg.
 // ---------------------------------------------------------------------------
-template <bool SD, bool BOX, bool OST>
+template <bool BOX, bool OST>
 __global__ void __launch_bounds__(1024, 6) k_check(RobotView rb, ObsView ob, GridView gv, int T, const float* __restrict__ q,
                                                 int64_t n_arg, int64_t stride_n, int64_t stride_d, int64_t q_batch,
-                                                uint8_t* __restrict__ flags, float* __restrict__ min_sd,
-                                                float* __restrict__ min_sd_self, int64_t out_batch,
+                                                uint8_t* __restrict__ flags, int64_t out_batch,
                                                 const int* __restrict__ status, IterArgs it,
                                                 const float* __restrict__ pred, float margin,
                                                 EdgeStatsDev* __restrict__ stats) {
@@ -389,50 +388,59 @@ __global__ void __launch_bounds__(1024, 6) k_check(RobotView rb, ObsView ob, Gri
     if (base >= n) return;
     const int W = blockDim.x >> 6;
     const float* qb = q + b * q_batch;
-    if constexpr (SD) {
+    const FlagTile t = carve_flag_tile(smem, T, W, rb, false, ob, OST ? ob.n : 0, gv.G, nullptr);
+    stage_tables<OST>(rb, false, ob, gv, t);
+    const float4 sh = cload4((const cfloat*)ob.centre);
+    const int j = threadIdx.x & 7;       // eight lanes per configuration, lane j its joint j
+    const float dj = rb.dh[j].y;
+    unsigned ntest = 0;
+    __syncthreads();
+    // a workgroup takes several tiles when the launch has fewer
+    // workgroups than tiles (one copy of the tables serves them)
+    for (; base < n; base += (int64_t)gridDim.x * T) {
         const int nv = (int)((n - base) < T ? (n - base) : T);
-        TileSmem t = carve_tile(smem, T, tile_slots(rb.n_spheres, rb.n_boxes), W);
-        for (int i = threadIdx.x; i < T * rb.dof; i += blockDim.x) {
-            const int c = i % T, j = i / T;
-            if (c < nv) t.q[c * kMaxDof + j] = qb[(base + c) * stride_n + j * stride_d];
-        }
-        __syncthreads();
-        tile_check_sd<BOX>(rb, ob, t, T, nv);
-        if (threadIdx.x < (unsigned)nv) {
-            const int64_t g = b * out_batch + base + threadIdx.x;
-            flags[g] = (uint8_t)t.hit[threadIdx.x];
-            if (min_sd) min_sd[g] = t.red[threadIdx.x];
-            if (min_sd_self) min_sd_self[g] = t.red[W * T + threadIdx.x];
-        }
-    } else {
-        const FlagTile t = carve_flag_tile(smem, T, W, rb, false, ob, OST ? ob.n : 0, gv.G, nullptr);
-        stage_tables<OST>(rb, false, ob, gv, t);
-        const float4 sh = cload4((const cfloat*)ob.centre);
-        const int j = threadIdx.x & 7;       // eight lanes per configuration, lane j its joint j
-        const float dj = rb.dh[j].y;
-        unsigned ntest = 0;
-        __syncthreads();
-        // a workgroup takes several tiles when the launch has fewer
-        // workgroups than tiles (one copy of the tables serves them)
-        for (; base < n; base += (int64_t)gridDim.x * T) {
-            const int nv = (int)((n - base) < T ? (n - base) : T);
-            for (int c = threadIdx.x >> 3; c < nv; c += blockDim.x >> 3) {
-                const int64_t g = base + c;
-                const float qj = qb[g * stride_n + (j < rb.dof ? j : 0) * stride_d];
-                bool s = false;
-                if (pred) {
-                    s = g >= screen_from && pred[b * out_batch + g] >= margin;
-                    if (s && stats && j == 0) atomicAdd((unsigned long long*)&stats[b].screened, 1ull);
-                }
-                *t.scr(c) = s ? 1 : 0;
-                *t.hit(c) = 0;
-                tile_pose(rb, sh, t, c, j, qj, dj);
+        for (int c = threadIdx.x >> 3; c < nv; c += blockDim.x >> 3) {
+            const int64_t g = base + c;
+            const float qj = qb[g * stride_n + (j < rb.dof ? j : 0) * stride_d];
+            bool s = false;
+            if (pred) {
+                s = g >= screen_from && pred[b * out_batch + g] >= margin;
+                if (s && stats && j == 0) atomicAdd((unsigned long long*)&stats[b].screened, 1ull);
             }
-            ntest += tile_flags<BOX, false, OST>(rb, ob, gv, t, nv);
-            if (threadIdx.x < (unsigned)nv) flags[b * out_batch + base + threadIdx.x] = (uint8_t)*t.hit(threadIdx.x);
-            __syncthreads();                 // flags read before the next tile resets them
+            *t.scr(c) = s ? 1 : 0;
+            *t.hit(c) = 0;
+            tile_pose(rb, sh, t, c, j, qj, dj);
         }
-        if (gv.tests) flush_tests(gv.tests, ntest);
+        ntest += tile_flags<BOX, false, OST>(rb, ob, gv, t, nv);
+        if (threadIdx.x < (unsigned)nv) flags[b * out_batch + base + threadIdx.x] = (uint8_t)*t.hit(threadIdx.x);
+        __syncthreads();                 // flags read before the next tile resets them
+    }
+    if (gv.tests) flush_tests(gv.tests, ntest);
+}
+
+// Signed distances over all pairs, one batch: a tile of T configurations (a
+// power of two) per workgroup.
+template <int T, bool BOX>
+__global__ void __launch_bounds__(1024) k_check_sd(RobotView rb, ObsView ob, const float* __restrict__ q, int64_t n,
+                                                   int64_t stride_n, int64_t stride_d, uint8_t* __restrict__ flags,
+                                                   float* __restrict__ min_sd, float* __restrict__ min_sd_self) {
+    extern __shared__ __align__(16) char smem[];
+    const int64_t base = (int64_t)blockIdx.x * T;
+    if (base >= n) return;
+    const int W = blockDim.x >> 6;
+    const int nv = (int)((n - base) < T ? (n - base) : T);
+    TileSmem t = carve_tile(smem, T, tile_slots(rb.n_spheres, rb.n_boxes), W);
+    for (int i = threadIdx.x; i < T * rb.dof; i += blockDim.x) {
+        const int c = i % T, j = i / T;
+        if (c < nv) t.q[c * kMaxDof + j] = q[(base + c) * stride_n + j * stride_d];
+    }
+    __syncthreads();
+    tile_check_sd<T, BOX>(rb, ob, t, nv);
+    if (threadIdx.x < (unsigned)nv) {
+        const int64_t g = base + threadIdx.x;
+        flags[g] = (uint8_t)t.hit[threadIdx.x];
+        if (min_sd) min_sd[g] = t.red[threadIdx.x];
+        if (min_sd_self) min_sd_self[g] = t.red[W * T + threadIdx.x];
     }
 }
 

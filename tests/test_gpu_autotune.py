@@ -376,3 +376,32 @@ def test_all_pairs_tuning_fills_cache(ezo, ctx):
         assert (e["log2_items"], e["obstacles"], e.get("field", 0)) == (10, len(obs), 0) and e["us"] > 0
     finally:
         ezo.tune_cache_clear()
+
+
+def test_box_arm_shapes_give_identical_results(ezo, ctx):
+    """Every tile size of the all-pairs distances and of the flags with boxes."""
+    data, desc = load("boxes")
+    rob = ezo.Robot(ctx, desc)
+    obs = torch.from_numpy(data["obstacles"]).cuda()
+    n = 1021
+    print_case("box shapes", n)
+    q = torch.from_numpy(draw.uniform_q(61, n, data["q_lo"], data["q_hi"])).cuda()
+    ctx.set_autotune(False)
+    ctx.set_obstacle_boxes(data["env_boxes"])
+    try:
+        ezo.tune_cache_clear()
+        ref = run_check(ezo, ctx, rob, obs, q, True)
+        ref_f = run_check(ezo, ctx, rob, obs, q, False)
+        assert 0.05 < ref[0].float().mean().item() < 0.95
+        for T in (1, 2, 4, 8, 16, 32, 64):
+            for W in (1, 4, 8):
+                ezo.tune_cache_clear()
+                for k in ("check_sd", "check_flags"):
+                    ezo.tune_cache_import(entry(k, desc, len(obs), n, T, W, 0).replace('"us"', f'"boxes":{rob.n_boxes},"us"'))
+                for a, b in zip(run_check(ezo, ctx, rob, obs, q, True), ref):
+                    assert torch.equal(a, b), (T, W)
+                assert torch.equal(run_check(ezo, ctx, rob, obs, q, False)[0], ref_f[0]), (T, W)
+    finally:
+        ctx.set_obstacle_boxes(None)
+        ezo.tune_cache_clear()
+        ctx.set_autotune(True)
