@@ -55,15 +55,15 @@ int grid_dim(int n_obs) { return n_obs >= 256 ? 32 : (n_obs >= 32 ? 16 : 8); }
 // LDS of a tile check by mode: signed distances hold every sphere and box of
 // a configuration, flags only the link frames and boxes.
 struct TileRows {
-    int slots, B, n_obs;
+    int slots, S, B, n_blocks, n_obs;
     bool sd;
     size_t tables;             // the robot's tables without the self pairs
     TileRows(const ezo_robot* r, int n_obs_, bool sd_)
-        : slots(r->slots), B(r->B), n_obs(n_obs_), sd(sd_),
+        : slots(r->slots), S(r->S), B(r->B), n_blocks(r->view.n_blocks), n_obs(n_obs_), sd(sd_),
           tables(robot_stage_bytes(r->S, r->view.n_blocks, r->P, false)) {}
     size_t bytes(int T, int W) const {
         return sd ? tile_smem_bytes(T, slots, W)
-                  : flag_tile_bytes(T, B, W) + flag_grid_bytes(n_obs, grid_dim(n_obs), 0) + tables;
+                  : flag_tile_bytes(T, S, B, n_blocks, W) + flag_grid_bytes(S, n_obs, grid_dim(n_obs), 0) + tables;
     }
 };
 
@@ -263,6 +263,9 @@ TileCfg heuristic_check(const ezo_ctx* c, const ezo_robot* r, int n_obs, int64_t
     g.W = sd ? pick_W(n_obs) : 4;
     const TileRows tr(r, n_obs, sd);
     g.T = pick_T(c, items, tr, g.W);
+    // boxes' poses make a tile large: more than 16 configurations leave a CU with
+    // few waves (300 001 of 11 boxes among 194 spheres: 64 took 915 us, 16 502)
+    if (!sd && r->B > 0) g.T = std::min(g.T, 16);
     // 512 records staged: 14.9 us against 15.7 (64 planar configurations); 1024:
     // 24.9 against 20.4 unstaged (10 000 of the 7-DOF arm)
     g.stage = (!sd && n_obs <= 512 && stage_fits(c, g.T, tr, g.W, n_obs)) ? 1 : 0;
@@ -312,9 +315,11 @@ std::vector<TileCfg> tile_candidates(const ezo_ctx* c, const ezo_robot* r, int n
     return v;
 }
 
-// Waves of a flags launch over one batch: twice what the chip holds at the five
-// to seven waves per SIMD that the kernel's registers allow.
-constexpr int kFlagWaves = 2 * kNumCU * 24;
+// Workgroups of W waves and `lds` bytes that the chip holds at once, at the six
+// waves per SIMD that the flags kernels' registers allow.
+int64_t resident_groups(size_t lds, int W) {
+    return (int64_t)kNumCU * std::max<int64_t>(1, std::min<int64_t>(163840 / (int64_t)lds, 24 / W));
+}
 
 ezo_status launch_check(ezo_ctx* c, const ezo_robot* r, const ObsView& ov, const GridView& gv, const float* q, int64_t n,
                         int64_t sn, int64_t sd, int64_t q_batch, uint8_t* flags, int64_t out_batch, int n_batch,
@@ -335,9 +340,12 @@ ezo_status launch_check(ezo_ctx* c, const ezo_robot* r, const ObsView& ov, const
     const size_t lds = TileRows(r, ov.n, false).bytes(T, W) + 16 * (size_t)ovs.lds_n;
     const int64_t tiles = (n + T - 1) / T;
     if (tiles <= 0) return EZO_OK;
-    // one batch: at most kFlagWaves waves, each workgroup taking tiles in turn,
-    // so that the copy of the cell states is paid by several
-    const int64_t wgs = n_batch > 1 ? tiles : std::min<int64_t>(tiles, kFlagWaves / W);
+    // one batch: twice the workgroups that the chip holds, each taking tiles in
+    // turn, so that the copy of the cell states is paid by several (a fixed number of
+    // waves left the box arm, whose tile holds fewer at once, with 2.4 rounds of them);
+    // a robot without spheres copies no states: a workgroup per tile (300 001 of
+    // 11 boxes: 437 us, in turn 493)
+    const int64_t wgs = n_batch > 1 || r->S == 0 ? tiles : std::min<int64_t>(tiles, 2 * resident_groups(lds, W));
     dim3 grid((unsigned)wgs, (unsigned)n_batch), block(64 * W);
     const bool box = r->B > 0 || ov.n_ebox > 0;
 #define EZO_LAUNCH_CHECK(BB, OO)                                                                              \

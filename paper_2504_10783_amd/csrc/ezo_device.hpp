@@ -655,18 +655,23 @@ typedef float f2 __attribute__((ext_vector_type(2)));
 typedef int i2 __attribute__((ext_vector_type(2)));
 
 // A configuration's record in the tile, in 16-byte rows: the links' frames
-// (three rows (R | p) each, shifted frame), the parts' bounding spheres, each
-// joint's (cos, sin), each link's offset d (plus q for a prismatic joint), and
-// (collision flag, 1 = the learned screen cleared its self pairs).  The rows of
-// a record are at fixed offsets (no address arithmetic or registers for them),
-// and 47 rows, 188 words, put the records of a tile on distinct LDS banks.
-constexpr int kRecLb = 3 * kMaxDof, kRecTrig = kRecLb + kMaxParts, kRecD = kRecTrig + kMaxDof / 2,
-              kRecHit = kRecD + kMaxDof / 4, kRecRows = kRecHit + 1;
-static_assert(kRecRows % 2 == 1, "an odd number of 16-byte rows: distinct banks");
+// (three rows (R | p) each, shifted frame), each joint's (cos, sin), each link's
+// offset d (plus q for a prismatic joint), (collision flag, 1 = the learned screen
+// cleared its self pairs), and the parts' bounding spheres, which a box arm
+// without sphere pairs goes without (its tile holds its boxes' poses besides:
+// more waves fit a CU).  The rows of a record are at fixed offsets (no address
+// arithmetic or registers for them), and 47 rows, 188 words (31, 124), put the
+// records of a tile on distinct LDS banks.
+constexpr int kRecTrig = 3 * kMaxDof, kRecD = kRecTrig + kMaxDof / 2, kRecHit = kRecD + kMaxDof / 4,
+              kRecLb = kRecHit + 1, kRecRows = kRecLb + kMaxParts;
+static_assert(kRecRows % 2 == 1 && kRecLb % 2 == 1, "an odd number of 16-byte rows: distinct banks");
+__host__ __device__ inline int rec_rows(int n_boxes, int n_blocks) { return n_boxes > 0 && n_blocks == 0 ? kRecLb : kRecRows; }
 
 struct FlagTile {
-    lds_ptr<f4> rec;        // [T][kRecRows]
-    lds_ptr<f4> box;        // [T][4 B] each box's world pose as four rows (packed like RobotView::box)
+    lds_ptr<f4> rec;        // [T][rows]
+    int rows;
+    lds_ptr<f4> box;        // [4 B][T] each box's world pose as four rows (packed like RobotView::box)
+    int T;
     lds_ptr<unsigned> wl;   // [W][kWaveList] each wave's list
     lds_ptr<unsigned> state;   // [state_words] the grid's cell states
     lds_ptr<f4> obs;        // [lds_n] staged obstacle records (x, y, z, r)
@@ -676,38 +681,42 @@ struct FlagTile {
     lds_ptr<int> link;
     lds_ptr<i2> pairs;
 
-    __device__ __forceinline__ lds_ptr<f4> row(int c) const { return rec + c * kRecRows; }
+    __device__ __forceinline__ lds_ptr<f4> row(int c) const { return rec + c * rows; }
     __device__ __forceinline__ lds_ptr<volatile int> hit(int c) const {
-        return (lds_ptr<volatile int>)(rec + c * kRecRows + kRecHit);
+        return (lds_ptr<volatile int>)(rec + c * rows + kRecHit);
     }
-    __device__ __forceinline__ lds_ptr<int> scr(int c) const { return (lds_ptr<int>)(rec + c * kRecRows + kRecHit) + 1; }
+    __device__ __forceinline__ lds_ptr<int> scr(int c) const { return (lds_ptr<int>)(rec + c * rows + kRecHit) + 1; }
 };
 
 // Entries of a wave's list: a step adds at most 128 (two spheres a lane) to at
 // most 63 left by the step before.
 constexpr int kWaveList = 192;
 
-__host__ __device__ inline size_t flag_tile_bytes(int T, int n_boxes, int W) {
-    return sizeof(float4) * (size_t)T * (kRecRows + 4 * n_boxes) + sizeof(unsigned) * (size_t)kWaveList * W;
+__host__ __device__ inline size_t flag_tile_bytes(int T, int n_spheres, int n_boxes, int n_blocks, int W) {
+    return sizeof(float4) * (size_t)T * (rec_rows(n_boxes, n_blocks) + 4 * n_boxes) +
+           (n_spheres > 0 ? sizeof(unsigned) * (size_t)kWaveList * W : 0);
 }
 
-// The cell states and the staged obstacles follow the tile region, then the
-// robot's tables.
-__host__ __device__ inline size_t flag_grid_bytes(int n_obs, int G, int lds_n) {
-    return (n_obs > 0 ? sizeof(unsigned) * (size_t)state_words(G) : 0) + sizeof(float4) * (size_t)lds_n;
+// The cell states (for spheres) and the staged obstacles follow the tile region,
+// then the robot's tables.
+__host__ __device__ inline size_t flag_grid_bytes(int n_spheres, int n_obs, int G, int lds_n) {
+    return (n_spheres > 0 && n_obs > 0 ? sizeof(unsigned) * (size_t)state_words(G) : 0) + sizeof(float4) * (size_t)lds_n;
 }
 
 // base: the workgroup's LDS (16-byte aligned); *end receives the first byte
 // after the robot's tables.
+template <bool BOX>
 __device__ inline FlagTile carve_flag_tile(char* base, int T, int W, const RobotView& rb, bool pairs, const ObsView& ob,
                                            int lds_n, int G, char** end) {
     FlagTile t;
     lds_ptr<char> p = to_lds(base);
-    t.rec = (lds_ptr<f4>)p;         p += sizeof(f4) * kRecRows * T;
+    t.T = T;
+    t.rows = BOX ? rec_rows(rb.n_boxes, rb.n_blocks) : kRecRows;
+    t.rec = (lds_ptr<f4>)p;         p += (int)sizeof(f4) * t.rows * T;
     t.box = (lds_ptr<f4>)p;         p += sizeof(f4) * 4 * rb.n_boxes * T;
     t.wl = (lds_ptr<unsigned>)p;
-    p = to_lds(base) + (int)flag_tile_bytes(T, rb.n_boxes, W);
-    t.state = (lds_ptr<unsigned>)p; p += ob.n > 0 ? (int)sizeof(unsigned) * state_words(G) : 0;
+    p = to_lds(base) + (int)flag_tile_bytes(T, rb.n_spheres, rb.n_boxes, rb.n_blocks, W);
+    t.state = (lds_ptr<unsigned>)p; p += (int)flag_grid_bytes(rb.n_spheres, ob.n, G, 0);
     t.obs = (lds_ptr<f4>)p;         p += sizeof(f4) * lds_n;
     t.lbound = (lds_ptr<f4>)p;
     t.blocks = (lds_ptr<i4>)(t.lbound + kMaxParts);
@@ -715,7 +724,8 @@ __device__ inline FlagTile carve_flag_tile(char* base, int T, int W, const Robot
     t.link = (lds_ptr<int>)(p + (int)robot_image_off_link(rb.n_spheres, rb.n_blocks));
     t.pairs = (lds_ptr<i2>)(p + (int)robot_image_off_pairs(rb.n_spheres, rb.n_blocks));
     if (end)
-        *end = base + flag_tile_bytes(T, rb.n_boxes, W) + flag_grid_bytes(ob.n, G, lds_n) +
+        *end = base + flag_tile_bytes(T, rb.n_spheres, rb.n_boxes, rb.n_blocks, W) +
+               flag_grid_bytes(rb.n_spheres, ob.n, G, lds_n) +
                robot_stage_bytes(rb.n_spheres, rb.n_blocks, rb.n_self, pairs);
     return t;
 }
@@ -740,7 +750,8 @@ template <bool OST>
 __device__ inline void stage_tables(const RobotView& rb, bool pairs, const ObsView& ob, const GridView& gv,
                                     const FlagTile& t) {
     if (ob.n > 0) {
-        copy_to_lds((lds_ptr<f4>)t.state, reinterpret_cast<const float4*>(gv.state), state_words(gv.G) / 4);
+        if (rb.n_spheres > 0)
+            copy_to_lds((lds_ptr<f4>)t.state, reinterpret_cast<const float4*>(gv.state), state_words(gv.G) / 4);
         if constexpr (OST) copy_to_lds(t.obs, ob.rec, ob.n);
     }
     copy_to_lds(t.lbound, rb.image, (int)(robot_stage_bytes(rb.n_spheres, rb.n_blocks, rb.n_self, pairs) / 16));
@@ -810,6 +821,7 @@ __device__ __forceinline__ void tile_pose(const RobotView& rb, float4 sh, const 
             out[3 * l] = row;
         }
     }
+    if (t.rows == kRecLb) return;
     wave_lds_sync();
     static_assert(kMaxParts == 16 && kPartsPerLink == 2, "two parts a lane");
     const LFrame f0 = tile_frame(t, x, j / kPartsPerLink), f1 = tile_frame(t, x, j / kPartsPerLink + 4);
@@ -990,7 +1002,10 @@ __device__ __forceinline__ void tile_self_pairs(PairF pair, const RobotView& rb,
     }
 }
 
-// The boxes' world poses: a lane per (configuration, box).
+// The boxes' world poses: a lane per (configuration, box).  Row i of a box of
+// neighbouring configurations, which neighbouring lanes read, is contiguous (a
+// configuration's boxes side by side: 300 001 checks of 11 boxes among 194 spheres
+// 948 us, four lanes to a bank).
 __device__ inline void tile_place_boxes(const RobotView& rb, const FlagTile& t, int n_valid) {
     for (ItemWalk w(n_valid); w.k < rb.n_boxes; w.next(n_valid)) {
         const int c = w.c, k = w.k;
@@ -1004,15 +1019,15 @@ __device__ inline void tile_place_boxes(const RobotView& rb, const FlagTile& t, 
         for (int i = 0; i < 4; ++i) {
             f4 r;
             r.x = o[i].x; r.y = o[i].y; r.z = o[i].z; r.w = o[i].w;
-            t.box[4 * (c * rb.n_boxes + k) + i] = r;
+            t.box[(4 * k + i) * t.T + c] = r;
         }
     }
 }
 
-__device__ __forceinline__ DBox flag_box(const FlagTile& t, int n_boxes, int k, int c) {
+__device__ __forceinline__ DBox flag_box(const FlagTile& t, int k, int c) {
     float4 b[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) b[i] = lds_load((lds_ptr<const float4>)t.box, 4 * (c * n_boxes + k) + i);
+    for (int i = 0; i < 4; ++i) b[i] = lds_load((lds_ptr<const float4>)t.box, (4 * k + i) * t.T + c);
     return unpack_box(b[0], b[1], b[2], b[3], make_float3(0.f, 0.f, 0.f));
 }
 
@@ -1031,7 +1046,7 @@ __device__ inline void tile_boxes_flags(const RobotView& rb, const ObsView& ob, 
         const int c = w.c;
         if (*t.hit(c)) continue;
         const int2 pr = rb.box_pairs[w.k];
-        const DBox X = flag_box(t, rb.n_boxes, pr.x, c), Y = flag_box(t, rb.n_boxes, pr.y, c);
+        const DBox X = flag_box(t, pr.x, c), Y = flag_box(t, pr.y, c);
         const float dx = X.c[0] - Y.c[0], dy = X.c[1] - Y.c[1], dz = X.c[2] - Y.c[2];
         const float Rr = X.rb + Y.rb;
         if (fmaf(dx, dx, fmaf(dy, dy, dz * dz)) >= Rr * Rr) continue;
@@ -1040,7 +1055,7 @@ __device__ inline void tile_boxes_flags(const RobotView& rb, const ObsView& ob, 
     for (ItemWalk w(n_valid); w.k < B; w.next(n_valid)) {
         const int c = w.c;
         if (*t.hit(c)) continue;
-        const DBox X = flag_box(t, rb.n_boxes, w.k, c);
+        const DBox X = flag_box(t, w.k, c);
         bool found = false;
         for (int o = 0; o < ob.n && !found; ++o) {
             const float4 O = OST ? lds_load((lds_ptr<const float4>)t.obs, o) : ob.rec[o];

@@ -388,7 +388,7 @@ __global__ void __launch_bounds__(1024, 6) k_check(RobotView rb, ObsView ob, Gri
     if (base >= n) return;
     const int W = blockDim.x >> 6;
     const float* qb = q + b * q_batch;
-    const FlagTile t = carve_flag_tile(smem, T, W, rb, false, ob, OST ? ob.n : 0, gv.G, nullptr);
+    const FlagTile t = carve_flag_tile<BOX>(smem, T, W, rb, false, ob, OST ? ob.n : 0, gv.G, nullptr);
     stage_tables<OST>(rb, false, ob, gv, t);
     const float4 sh = cload4((const cfloat*)ob.centre);
     const int j = threadIdx.x & 7;       // eight lanes per configuration, lane j its joint j
@@ -1082,7 +1082,7 @@ __global__ void __launch_bounds__(1024, SCR ? 4 : 6) k_project_bisect(RobotView 
     if ((int64_t)blockIdx.x * TC >= total) return;
     const int dof = rb.dof, T = shape.Tcap, W = blockDim.x >> 6;
     char* end;
-    const FlagTile t = carve_flag_tile(smem, T, W, rb, true, ob, OST ? ob.n : 0, gv.G, &end);
+    const FlagTile t = carve_flag_tile<BOX>(smem, T, W, rb, true, ob, OST ? ob.n : 0, gv.G, &end);
     // the candidates' state, [rows][8]: colliding end, other end, projection
     const int rows = bisect_state_rows(shape);
     const lds_ptr<float> s_hi = to_lds(reinterpret_cast<float*>(end));
