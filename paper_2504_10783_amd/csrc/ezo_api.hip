@@ -1918,7 +1918,7 @@ ezo_status ezo_collision_map(ezo_ctx* c, const ezo_robot* r, const float* q, int
     const int span = (int)((V + parts - 1) / parts);
     // threads: no more than the (node, body) items need (map and lists of 35 000
     // nodes of the 11-box arm, 16 cm voxels: 242 us, with 512 threads 295)
-    const int items = (r->S + r->B) * kMapNodes * kMapLanes;
+    const int items = (r->S * kMapLanes + r->B * kMapBoxLanes) * kMapNodes;
     const int threads = items <= 128 ? 128 : items <= 256 ? 256 : kMapThreads;
     int T = kMapNodes;
     while (T > 1 && tile_smem_bytes(T, r->slots, threads / 64) + kMapSpan > kMapLds) T >>= 1;

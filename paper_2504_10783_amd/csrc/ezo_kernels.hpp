@@ -1786,7 +1786,9 @@ __device__ __forceinline__ void voxel_range(float x, float R, float lo, float in
 // in one L2.  Bound by the tests' VALU work and the byte stores; a global
 // atomicOr per hit took 1375 us for 35 000 nodes x 36 100 voxels, this 157 (256
 // threads 219, 1024 260; four lanes per sphere 166, one 156).
-constexpr int kMapNodes = 8, kMapLanes = 2, kMapThreads = 512;
+// A box has kMapBoxLanes (5000 nodes of the 11-box arm x 2.3 M voxels, whose spans
+// hold two planes: 4.4 ms with two lanes, a plane each).
+constexpr int kMapNodes = 8, kMapLanes = 2, kMapBoxLanes = 8, kMapThreads = 512;
 
 template <bool BOX>
 __global__ void __launch_bounds__(kMapThreads) k_collision_map(RobotView rb, ObsView ob, const float* __restrict__ q,
@@ -1874,9 +1876,9 @@ __global__ void __launch_bounds__(kMapThreads) k_collision_map(RobotView rb, Obs
             }
         }
         if (BOX) {
-            for (ItemWalk w(nv); w.k < rb.n_boxes * kMapLanes; w.next(nv)) {
+            for (ItemWalk w(nv); w.k < rb.n_boxes * kMapBoxLanes; w.next(nv)) {
                 const int c = w.c;
-                const DBox X = tile_box(t, S, T, w.k / kMapLanes, c);
+                const DBox X = tile_box(t, S, T, w.k / kMapBoxLanes, c);
                 if (!(isfinite(X.c[0]) && isfinite(X.c[1]) && isfinite(X.c[2]))) continue;
                 float e[3];                        // half widths of the box's world AABB
 #pragma unroll
@@ -1886,20 +1888,27 @@ __global__ void __launch_bounds__(kMapThreads) k_collision_map(RobotView rb, Obs
                 voxel_range(X.c[0], e[0] + rv, lo.x, inv, dims.x, &i0, &i1);
                 voxel_range(X.c[1], e[1] + rv, lo.y, inv, dims.y, &j0, &j1);
                 voxel_range(X.c[2], e[2] + rv, lo.z, inv, dims.z, &k0, &k1);
-                k0 = max(k0, kmin) + w.k % kMapLanes;
+                k0 = max(k0, kmin);
                 k1 = min(k1, kmax);
-                for (int k = k0; k <= k1; k += kMapLanes)
-                    for (int j = j0; j <= j1; ++j) {
-                        const int64_t row = ((int64_t)k * dims.y + j) * dims.x - v0;
-                        if (row + i1 < 0 || row + i0 >= count) continue;
-                        for (int i = i0; i <= i1; ++i) {
-                            const float x = fmaf(side, (float)i + 0.5f, lo.x), y = fmaf(side, (float)j + 0.5f, lo.y),
-                                        z = fmaf(side, (float)k + 0.5f, lo.z);
-                            const unsigned v = (unsigned)((int)row + i);
-                            if (v < (unsigned)count && hit_sphere_box(X, x, y, z, rv))
-                                atomicOr(&bits[v >> 2], 1u << (8 * (v & 3) + sub + c));
-                        }
+                const int nj = j1 - j0 + 1;
+                if (nj <= 0) continue;
+                // the rows of all planes over the lanes (a span holds few planes)
+                for (int j = j0 + w.k % kMapBoxLanes, k = k0;; j += kMapBoxLanes) {
+                    while (j > j1) {
+                        j -= nj;
+                        ++k;
                     }
+                    if (k > k1) break;
+                    const int64_t row = ((int64_t)k * dims.y + j) * dims.x - v0;
+                    if (row + i1 < 0 || row + i0 >= count) continue;
+                    for (int i = i0; i <= i1; ++i) {
+                        const float x = fmaf(side, (float)i + 0.5f, lo.x), y = fmaf(side, (float)j + 0.5f, lo.y),
+                                    z = fmaf(side, (float)k + 0.5f, lo.z);
+                        const unsigned v = (unsigned)((int)row + i);
+                        if (v < (unsigned)count && hit_sphere_box(X, x, y, z, rv))
+                            atomicOr(&bits[v >> 2], 1u << (8 * (v & 3) + sub + c));
+                    }
+                }
             }
         }
     }

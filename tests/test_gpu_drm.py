@@ -148,3 +148,10 @@ def test_map_lists_of_any_rows(ezo, ctx, rows, words, density):
     want = np.zeros(rows + 1, np.int64)
     np.cumsum(bits.sum(1), out=want[1:])
     assert np.array_equal(offsets.cpu().numpy(), want) and np.array_equal(ids.cpu().numpy(), c)
+
+
+@pytest.mark.parametrize("name,n,dims,side", [("boxes", 17, (230, 220, 6), 0.012), ("boxes", 3, (40, 1, 900), 0.004),
+                                              ("dof7", 17, (230, 220, 6), 0.012)])
+def test_map_spans_of_part_of_a_plane(ezo, ctx, name, n, dims, side):
+    """Planes wider than a span, and planes of one row: a box's rows over its lanes."""
+    test_map_spans_and_node_bytes(ezo, ctx, name, n, dims, side)
