@@ -491,17 +491,19 @@ __global__ void __launch_bounds__(256) k_centres(RobotView rb, ObsView ob, const
 // Rows and drawn steps are read from LDS 128 bits at a time: at D = 7 a row with
 // its b and a step with its chord word are eight words (32-bit reads of seven-
 // and eleven-word records: 42.3 us a launch for 10 000 walks of 60 steps, 137
-// for 96 000; this 35.8 and 126).  Bound by VALU issue: per step of 64 walks the
+// for 96 000; this 35.8 and 126).  A step of nine words (D = 8) is read 32 bits at a
+// time: the wide reads' latency shows where 16 lanes a walk leave a SIMD one wave
+// (1000 walks: 39.6 us a call, 41.9 with them).  Bound by VALU issue: per step of 64 walks the
 // draws' integer products, then about 25 slots a row.
 // ---------------------------------------------------------------------------
 __host__ __device__ constexpr int sample_chunk(int L) { return 2 * L; }        // steps drawn ahead (L >= 4)
 __host__ __device__ constexpr int sample_dir_stride(int D) { return (D + 4) / 4 * 4; }   // u[D], chord word, pad
-// Words per walk group's block of drawn steps: four more than the steps' words,
-// so that the groups of a wave, each reading its own block 128 bits at a time,
-// start on distinct LDS banks.
+// Words per walk group's block of drawn steps: four more than the steps' words
+// (one more where they are read 32 bits at a time), so that the groups of a wave,
+// each reading its own block, start on distinct LDS banks.
 __host__ __device__ constexpr int sample_group_words(int D, int L) {
     const int w = sample_chunk(L) * sample_dir_stride(D);
-    return w + (w % 8 == 0 ? 4 : 8);
+    return w + (D == 8 ? 1 : w % 8 == 0 ? 4 : 8);
 }
 
 // LDS bytes of k_sample: rows, then (L >= 4) the drawn directions, sized for
@@ -631,30 +633,36 @@ __device__ __forceinline__ float load_row(const float* rowA, const float* rowb, 
     }
 }
 
-// A drawn step (u[D], chord word), 128 bits at a time.
+// A drawn step (u[D], chord word), 128 bits at a time (D = 8: 32).
 template <int D>
 __device__ __forceinline__ void put_step(float* d, const float (&u)[D], float w) {
     static_assert(D == 4 || D == 7 || D == 8, "coordinates of a walk");
+    if constexpr (D == 8) {
+#pragma unroll
+        for (int j = 0; j < D; ++j) d[j] = u[j];
+        d[D] = w;
+        return;
+    }
     f4* const v = reinterpret_cast<f4*>(d);
     v[0] = f4{u[0], u[1], u[2], u[3]};
     if constexpr (D == 4) d[4] = w;
     if constexpr (D == 7) v[1] = f4{u[4], u[5], u[6], w};
-    if constexpr (D == 8) {
-        v[1] = f4{u[4], u[5], u[6], u[7]};
-        d[8] = w;
-    }
 }
 template <int D>
 __device__ __forceinline__ float get_step(const float* d, float (&u)[D]) {
-    const f4* const v = reinterpret_cast<const f4*>(d);
-    const f4 p = v[0];
-    u[0] = p[0]; u[1] = p[1]; u[2] = p[2]; u[3] = p[3];
-    if constexpr (D == 4) return d[4];
-    const f4 q = v[1];
-    if constexpr (D > 4) { u[4] = q[0]; u[5] = q[1]; u[6] = q[2]; }
-    if constexpr (D == 7) return q[3];
-    if constexpr (D == 8) u[7] = q[3];
-    return d[D];
+    if constexpr (D == 8) {
+#pragma unroll
+        for (int j = 0; j < D; ++j) u[j] = d[j];
+        return d[D];
+    } else {
+        const f4* const v = reinterpret_cast<const f4*>(d);
+        const f4 p = v[0];
+        u[0] = p[0]; u[1] = p[1]; u[2] = p[2]; u[3] = p[3];
+        if constexpr (D == 4) return d[4];
+        const f4 q = v[1];
+        if constexpr (D == 7) { u[4] = q[0]; u[5] = q[1]; u[6] = q[2]; }
+        return q[3];
+    }
 }
 
 template <int D, int L>
