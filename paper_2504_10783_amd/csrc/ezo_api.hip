@@ -555,7 +555,7 @@ ezo_status launch_sample(ezo_ctx* c, int dof, const float* A, const float* b, co
     return EZO_OK;
 }
 
-// The candidates come as a list over all edges (cl).
+// The candidates come as lists over the edges (cl), a launch each.
 ezo_status launch_project_bisect(ezo_ctx* c, const ezo_robot* r, const ObsView& ov, const GridView& gv,
                                  const float* edges, int E, const float* S, int64_t stride, const int* cand_idx,
                                  const CandList& cl, int cand_cap, int n_b, float* c_star, float* a_dir, float* t_star,
@@ -598,40 +598,47 @@ ezo_status launch_project_bisect(ezo_ctx* c, const ezo_robot* r, const ObsView& 
     // waves a SIMD); the grid holds every tile of full lists, up to eight
     // rounds of those (a workgroup then takes several)
     bs.resident = kNumCU * std::max(1, std::min((int)(163840 / lds), 24 / W));
-    const int64_t tiles = std::max<int64_t>((items + bs.T - 1) / bs.T, std::min<int64_t>(items, bs.resident));
-    dim3 grid((unsigned)std::min<int64_t>(tiles, 8LL * bs.resident)), block(64 * W);
     const MlpView mv = scr ? *screen : MlpView{0, 0, nullptr, nullptr, nullptr, 0.f};
+    const int lists = list_count(E, cl.group);
+    for (int l = 0; l < lists; ++l) {
+        const int64_t in_list = (int64_t)std::min(E - l * cl.group, cl.group) * cand_cap;
+        const CandList le{cl.e + (size_t)l * cl.group * cl.cap, cl.n + l, cl.group, cl.cap};
+        const int64_t tiles = std::max<int64_t>((in_list + bs.T - 1) / bs.T, std::min<int64_t>(in_list, bs.resident));
+        const dim3 grid((unsigned)std::min<int64_t>(tiles, 8LL * bs.resident)), block(64 * W);
 #define EZO_LAUNCH_PB(BB, SS, OO)                                                                                   \
-    EZO_KLAUNCH(c, (k_project_bisect<BB, SS, OO>), grid, block, lds, st, r->view, ov, gv, bs, cl, edges, S, stride, \
+    EZO_KLAUNCH(c, (k_project_bisect<BB, SS, OO>), grid, block, lds, st, r->view, ov, gv, bs, le, edges, S, stride, \
                 s_edge, cand_idx, cand_cap, n_b, c_star, a_dir, t_star, pcol, pany, mv, stats)
-    if (scr) {
-        if (ost) EZO_LAUNCH_PB(false, true, true);
-        else EZO_LAUNCH_PB(false, true, false);
-    } else if (box) {
-        if (ost) EZO_LAUNCH_PB(true, false, true);
-        else EZO_LAUNCH_PB(true, false, false);
-    } else {
-        if (ost) EZO_LAUNCH_PB(false, false, true);
-        else EZO_LAUNCH_PB(false, false, false);
+        if (scr) {
+            if (ost) EZO_LAUNCH_PB(false, true, true);
+            else EZO_LAUNCH_PB(false, true, false);
+        } else if (box) {
+            if (ost) EZO_LAUNCH_PB(true, false, true);
+            else EZO_LAUNCH_PB(true, false, false);
+        } else {
+            if (ost) EZO_LAUNCH_PB(false, false, true);
+            else EZO_LAUNCH_PB(false, false, false);
+        }
     }
 #undef EZO_LAUNCH_PB
     HIP_TRY(c, hipGetLastError());
     return EZO_OK;
 }
 
-// The candidate list of per-edge counts, in the context's workspace.
-ezo_status list_buffers(ezo_ctx* c, int64_t items, CandList* cl) {
+// The candidate lists of E edges with up to cand_cap candidates each, in the
+// context's workspace.
+ezo_status list_buffers(ezo_ctx* c, int E, int cand_cap, CandList* cl) {
     ezo_status s;
     void *le, *ln;
-    if ((s = ezo_ws_get(c, W_CAND_LIST, sizeof(int2) * (size_t)items, &le)) ||
-        (s = ezo_ws_get(c, W_LIST_N, sizeof(int), &ln)))
+    const int group = list_group(cand_cap);
+    if ((s = ezo_ws_get(c, W_CAND_LIST, sizeof(int2) * (size_t)E * cand_cap, &le)) ||
+        (s = ezo_ws_get(c, W_LIST_N, sizeof(int) * (size_t)list_count(E, group), &ln)))
         return s;
-    *cl = CandList{(int2*)le, (int*)ln};
+    *cl = CandList{(int2*)le, (int*)ln, group, cand_cap};
     return EZO_OK;
 }
 
 ezo_status list_candidates(ezo_ctx* c, const int* n_cands, int E, int cand_cap, const CandList& cl, hipStream_t st) {
-    hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, st, (uint32_t*)cl.n, (int64_t)1, 0u);
+    hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, st, (uint32_t*)cl.n, (int64_t)list_count(E, cl.group), 0u);
     hipLaunchKernelGGL(k_list_candidates, dim3(E), dim3(256), 0, st, n_cands, cand_cap, cl);
     HIP_TRY(c, hipGetLastError());
     return EZO_OK;
@@ -772,14 +779,14 @@ ezo_status tune_inflation(ezo_ctx* c, const ezo_robot* r, const ObsView& ov, con
     const auto cands = tile_candidates(c, r, ov.n, false, {1, 2, 4, 8, 16}, (int64_t)cand_cap * E, true);
     if (cands.empty()) return EZO_OK;
     const int light = std::max(16, (int)std::ceil(2.0 * p->eps * cand_cap));
-    int* w_nc_light = reinterpret_cast<int*>(w_f);      // the flags are free once selected (E <= stride E / 4)
+    int* w_nc_light = reinterpret_cast<int*>(w_f);      // the flags are free once selected (64 bytes an edge at least)
     hipLaunchKernelGGL(k_cap_counts, dim3((E + 255) / 256), dim3(256), 0, st, (const int*)w_nc, w_nc_light, E, light);
     HIP_TRY(c, hipGetLastError());
     // the lists of the full counts (the loop's, emptied again when the edges
-    // are initialised) and of the light ones (their length behind the counts)
+    // are initialised) and of the light ones (their lengths behind the counts)
     void* w_ll;
     if ((s = ezo_ws_get(c, W_LIST_LIGHT, sizeof(int2) * (size_t)E * std::min(light, cand_cap), &w_ll))) return s;
-    const CandList cl_light{(int2*)w_ll, w_nc_light + E};
+    const CandList cl_light{(int2*)w_ll, w_nc_light + E, cl.group, std::min(light, cand_cap)};
     if ((s = list_candidates(c, w_nc, E, cand_cap, cl, st)) ||
         (s = list_candidates(c, w_nc_light, E, cand_cap, cl_light, st)))
         return s;
@@ -1326,7 +1333,7 @@ ezo_status ezo_project_bisect(ezo_ctx* c, const ezo_robot* r, const float* obs, 
     ezo_status s = prep_obstacles(c, r, obs, n_obs, st, &ov, &gv);
     if (s) return s;
     CandList cl;
-    if ((s = list_buffers(c, (int64_t)n_edges * cand_capacity, &cl)) ||
+    if ((s = list_buffers(c, n_edges, cand_capacity, &cl)) ||
         (s = list_candidates(c, n_cands, n_edges, cand_capacity, cl, st)) ||
         (s = tune_bisect_inplace(c, r, ov, gv, edges, n_edges, samples, sample_stride, cand_idx, cl, cand_capacity,
                                  n_b, c_star, a_dir, t_star, proj_collides, st)))
@@ -1466,7 +1473,7 @@ static ezo_status inflate_core(ezo_ctx* c, const ezo_robot* r, const float* obs,
         (s = ezo_ws_get(c, W_ACTIVE, sizeof(int), &w_ac)))
         return s;
     CandList cl;
-    if ((s = list_buffers(c, (int64_t)E * cand_cap, &cl))) return s;
+    if ((s = list_buffers(c, E, cand_cap, &cl))) return s;
     if (p->surrogate) {
         if (p->surrogate->D != dof) return ezo_fail(c, EZO_E_INVALID, "screen dof %d != robot dof %d", p->surrogate->D, dof);
         if ((s = ezo_ws_get(c, W_PRED, sizeof(float) * (size_t)E * stride, &w_pred))) return s;
@@ -1491,7 +1498,7 @@ static ezo_status inflate_core(ezo_ctx* c, const ezo_robot* r, const float* obs,
     // count) is launched with the obstacle preparation; a tuning run in
     // between overwrites it, and then it is launched again below
     const EdgeInit ei{dof, r->q_lo, r->q_hi, edges, E, A, b, n_faces, cap, edge_status, (EdgeStatsDev*)w_st,
-                      (uint8_t*)w_pa, (int4*)w_k, (const int4*)w_tb, (int*)w_ac, cl.n, skip};
+                      (uint8_t*)w_pa, (int4*)w_k, (const int4*)w_tb, (int*)w_ac, cl.n, list_count(E, cl.group), skip};
     if ((s = prep_obstacles(c, r, obs, n_obs, st, &ov, &gv, &ei))) return s;
     bool tuned = false;
     if ((s = tune_inflation(c, r, ov, gv, edges, E, p, S_cap, stride, A, b, n_faces, (float*)w_s, (uint8_t*)w_f,
@@ -1636,7 +1643,7 @@ static ezo_status inflate_core(ezo_ctx* c, const ezo_robot* r, const float* obs,
         mark(EZO_PHASE_ADVANCE);
         if (E != 1)
             EZO_KLAUNCH(c, k_advance, dim3(1), dim3(256), 0, st, (int4*)w_k, (const int4*)w_tb, p->max_iters,
-                        edge_status, E, (int*)w_ac, cl.n, c->pinned_dev, (const EdgeStatsDev*)w_st, host_stats);
+                        edge_status, E, (int*)w_ac, cl.n, list_count(E, cl.group), c->pinned_dev, (const EdgeStatsDev*)w_st, host_stats);
         mark(EZO_NUM_PHASES);
         if (ls == EZO_OK) {
             hipError_t le = hipGetLastError();
@@ -2077,10 +2084,10 @@ ezo_status ezo_update_polytopes(ezo_ctx* c, const ezo_robot* r, const float* obs
         (s = ezo_ws_get(c, W_NPLACED, sizeof(int) * (size_t)E, &w_np)))
         return s;
     CandList cl;
-    if ((s = list_buffers(c, (int64_t)E * N, &cl))) return s;
+    if ((s = list_buffers(c, E, N, &cl))) return s;
     // found collisions inside each editable set, in point order, become the candidates
     hipLaunchKernelGGL(k_rows_to_coords, dim3((N + 255) / 256), dim3(256), 0, st, dof, points, (int64_t)N,
-                       (float*)w_s, cl.n);
+                       (float*)w_s, cl.n, list_count(E, cl.group));
     hipLaunchKernelGGL(k_points_in_sets, dim3((N + 256 * kSetPoints - 1) / (256 * kSetPoints), E), dim3(256), 0, st, dof, A, b, n_faces,
                        face_capacity, edge_status, (const float*)w_s, (int64_t)N, (uint8_t*)w_f);
     IterArgs sel{nullptr, 0, 0, -1, N};

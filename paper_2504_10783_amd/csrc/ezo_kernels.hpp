@@ -66,7 +66,8 @@ struct EdgeInit {
     int4* cur;
     const int4* table;
     int* active;
-    int* list_n;                       // the candidate list's length
+    int* list_n;                       // the candidate lists' lengths
+    int n_lists;
     const uint8_t* skip;
 };
 
@@ -75,7 +76,7 @@ __device__ inline void init_edge(const EdgeInit& a, int e) {
     if (e == 0) {
         *a.cur = a.table[1];
         *a.active = a.n_edges;
-        *a.list_n = 0;
+        for (int g = 0; g < a.n_lists; ++g) a.list_n[g] = 0;
     }
     if (e >= a.n_edges) return;
     if (a.skip && a.skip[e]) {                  // not inflated: final from the start, no rows
@@ -888,10 +889,26 @@ __device__ __forceinline__ int wave_sum_i32(int v) {
 
 // The candidates of all edges as one list (edge, index), so that the bisection
 // fills its tiles across edges; *n (zero before the edges append) their number.
-// Edges append in any order.  e == NULL: no list.
+// Edges append in any order.  e == NULL: no list.  Edges x candidates past
+// kListMost are several lists, of `group` edges each with `cap` entries an edge, so
+// that a list's length fits an int (64-bit counts in the bisection's loop cost
+// its launches 0.5 to 0.9 %).
+constexpr int64_t kListMost = 1 << 28;
+__host__ __device__ constexpr int list_group(int cand_cap) {
+    return (int)(kListMost / (cand_cap > 1 ? cand_cap : 1)) > 1 ? (int)(kListMost / (cand_cap > 1 ? cand_cap : 1)) : 1;
+}
+__host__ __device__ constexpr int list_count(int n_edges, int group) { return (n_edges + group - 1) / group; }
+
 struct CandList {
     int2* e;
     int* n;
+    int group, cap;
+
+    // the list of edge i, and the list's entries
+    __device__ __forceinline__ CandList of(int i) const {
+        const int g = i < group ? 0 : i / group;
+        return CandList{e + (size_t)g * group * cap, n + g, group, cap};
+    }
 };
 
 // ---------------------------------------------------------------------------
@@ -990,9 +1007,10 @@ __global__ void __launch_bounds__(1024) k_test_select(const uint8_t* __restrict_
         taken = s_base < n_p ? s_base : n_p;
     }
     if (cl.e && taken > 0) {                 // the edge's candidates, appended to the list of all edges'
-        if (tid == 0) s_list = atomicAdd(cl.n, taken);
+        const CandList le = cl.of(e);
+        if (tid == 0) s_list = atomicAdd(le.n, taken);
         __syncthreads();
-        for (int i = tid; i < taken; i += blockDim.x) cl.e[s_list + i] = make_int2(e, i);
+        for (int i = tid; i < taken; i += blockDim.x) le.e[s_list + i] = make_int2(e, i);
     }
     if (tid == 0) {
         if (n_cands) n_cands[e] = taken;
@@ -1010,14 +1028,15 @@ __global__ void __launch_bounds__(1024) k_test_select(const uint8_t* __restrict_
     }
 }
 
-// The list for given counts (one workgroup per edge; *cl.n zero before).
+// The lists for given counts (one workgroup per edge; the lengths zero before).
 __global__ void __launch_bounds__(256) k_list_candidates(const int* __restrict__ n_cands, int cand_cap, CandList cl) {
     __shared__ int s_list;
     const int e = blockIdx.x;
     const int n = min(max(n_cands[e], 0), cand_cap);
-    if (threadIdx.x == 0) s_list = n > 0 ? atomicAdd(cl.n, n) : 0;
+    const CandList le = cl.of(e);
+    if (threadIdx.x == 0) s_list = n > 0 ? atomicAdd(le.n, n) : 0;
     __syncthreads();
-    for (int i = threadIdx.x; i < n; i += blockDim.x) cl.e[s_list + i] = make_int2(e, i);
+    for (int i = threadIdx.x; i < n; i += blockDim.x) le.e[s_list + i] = make_int2(e, i);
 }
 
 // ---------------------------------------------------------------------------
@@ -1107,8 +1126,9 @@ __global__ void __launch_bounds__(1024, SCR ? 4 : 6) k_project_bisect(RobotView 
     const float dj = rb.dh[j].y;
     unsigned ntest = 0;
     __syncthreads();
-    for (int base = blockIdx.x * TC; base < total; base += gridDim.x * TC) {
-        const int nv = min(TC, total - base);
+    // (unsigned: one edge's candidates may number up to the largest int)
+    for (unsigned base = blockIdx.x * TC; base < (unsigned)total; base += gridDim.x * TC) {
+        const int nv = min(TC, total - (int)base);
         for (int c = grp; c < nv; c += ngrp) {
             const int2 ej = cl.e[base + c];
             const int idx = min(max(cand_idx[(size_t)ej.x * cand_cap + ej.y], 0), (int)(stride - 1));
@@ -1472,7 +1492,7 @@ struct IterEnd {
     const int4* table;
     int max_iters;
     int* active_count;
-    int* list_n;                      // the candidate list, emptied for the next iteration
+    int* list_n;                      // the candidate list (one edge has one), emptied for the next iteration
     int* host_active;                 // pinned, or NULL
     EdgeStatsDev* host_stats;         // pinned, or NULL
 };
@@ -1594,7 +1614,7 @@ __global__ void k_init_edges(EdgeInit ei) { init_edge(ei, blockIdx.x * blockDim.
 __global__ void __launch_bounds__(256) k_advance(int4* __restrict__ cur, const int4* __restrict__ table, int max_iters,
                                                  int* __restrict__ status,
                                                  int n_edges, int* __restrict__ active_count,
-                                                 int* __restrict__ list_n, int* __restrict__ host_active,
+                                                 int* __restrict__ list_n, int n_lists, int* __restrict__ host_active,
                                                  const EdgeStatsDev* __restrict__ stats,
                                                  EdgeStatsDev* __restrict__ host_stats) {
     // the edges' statistics after this iteration, for the host (pinned)
@@ -1615,7 +1635,7 @@ __global__ void __launch_bounds__(256) k_advance(int4* __restrict__ cur, const i
     __syncthreads();
     if (threadIdx.x == 0) {
         *active_count = cnt;
-        *list_n = 0;
+        for (int g = 0; g < n_lists; ++g) list_n[g] = 0;
         *cur = table[min(k + 1, max_iters + 1)];
         if (host_active) *host_active = cnt;
     }
@@ -2174,11 +2194,12 @@ __global__ void __launch_bounds__(256) k_flag_rows(const uint8_t* __restrict__ f
     }
 }
 
-// Row-major [n][dof] -> coordinate-major [dof][n]; empties the candidate list.
+// Row-major [n][dof] -> coordinate-major [dof][n]; empties the candidate lists.
 __global__ void k_rows_to_coords(int dof, const float* __restrict__ rows, int64_t n, float* __restrict__ coords,
-                                 int* __restrict__ list_n) {
+                                 int* __restrict__ list_n, int n_lists) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i == 0) *list_n = 0;
+    if (i == 0)
+        for (int g = 0; g < n_lists; ++g) list_n[g] = 0;
     if (i >= n) return;
     for (int k = 0; k < dof; ++k) coords[(size_t)k * n + i] = rows[(size_t)i * dof + k];
 }

@@ -103,6 +103,44 @@ def test_bisection_levels_give_identical_results(ezo, ctx):
         ctx.set_autotune(True)
 
 
+def test_bisection_over_several_candidate_lists(ezo, ctx):
+    """So many edges x candidate slots that the candidates come in two lists (4800 x
+    57 344): edges of both and of their ends, against a call with those edges only."""
+    desc = arm(2, 3, 77)
+    rob = ezo.Robot(ctx, desc)
+    rng = draw.rng_for(78)
+    obs = torch.from_numpy(draw.obstacle_candidates(rng, 20, (-0.6, -0.6, -0.2), (0.6, 0.6, 0.2), 0.05, 0.15).reshape(-1, 4)).cuda()
+    E, cap, stride, group = 4800, 57344, 64, (1 << 28) // 57344
+    assert group < E < 2 * group
+    print_case("two candidate lists", E, cap)
+    S = torch.from_numpy(draw.uniform_q(79, E * stride, desc["q_lo"], desc["q_hi"])).cuda().view(E, stride, 2).transpose(1, 2).contiguous()
+    edges = torch.from_numpy(draw.uniform_q(80, 2 * E, desc["q_lo"], desc["q_hi"])).cuda().view(E, 2, 2).contiguous()
+    some = torch.tensor([0, 3, group - 1, group, group + 1, E - 1], device="cuda")
+
+    def run(ids, capacity):
+        n = len(ids)
+        nc = torch.zeros(n, dtype=torch.int32, device="cuda")
+        nc[torch.isin(ids, some)] = torch.tensor([1, 64, 7, 40, 64, 33], dtype=torch.int32, device="cuda")
+        ci = torch.zeros((n, capacity), dtype=torch.int32, device="cuda")
+        ci[:, :64] = torch.arange(64, dtype=torch.int32, device="cuda")
+        out = [torch.full(s, -7.0, device="cuda") for s in ((n, 2, capacity), (n, 2, capacity), (n, capacity))]
+        out.append(torch.full((n, capacity), 9, dtype=torch.uint8, device="cuda"))
+        ezo.project_bisect(ctx, rob, obs, edges[ids].contiguous(), S[ids].contiguous(), ci, nc, 9, *out)
+        torch.cuda.synchronize()
+        return [x[torch.isin(ids, some)][..., :64].clone() for x in out] + [int((out[2] != -7.0).sum())]
+
+    ctx.set_autotune(False)
+    try:
+        big = run(torch.arange(E, device="cuda"), cap)
+        small = run(some, 64)
+        for a, b in zip(big, small):
+            assert torch.equal(a, b) if isinstance(a, torch.Tensor) else a == b
+        assert big[-1] == 1 + 64 + 7 + 40 + 64 + 33
+    finally:
+        ctx.set_autotune(True)
+        torch.cuda.empty_cache()
+
+
 def test_largest_robot_with_every_part_pair(ezo, ctx):
     """Every part pair a block (136 with eight links), 1024 spheres, 64 boxes:
     the bisection's smallest tile passes 64 KB of LDS and is still accepted."""
