@@ -502,7 +502,8 @@ __global__ void __launch_bounds__(256) k_mlp_grad_w1(RowSource src, int64_t B, i
 // Bound by latency at a batch's size (the weights' way from L2 and six barriers
 // a tile): 4096 rows at H = 256 took 260 us of kernels in 19 launches, here 31 us
 // in this one and 20 in the contraction and the sums' last step.  Two blocks of
-// 16 rows a tile do not fit the 128 registers of 16 waves.
+// 16 rows a tile do not fit the 128 registers of 16 waves (83 to 177 spilled); of
+// one block, 26 registers a lane go to scratch at H = 256, 17 at 192, 4 at 128.
 // ---------------------------------------------------------------------------
 __host__ __device__ constexpr int train_part_floats(int H, int D) { return 4 * H + H * D + 2; }
 
@@ -653,8 +654,9 @@ k_mlp_train(const float* __restrict__ q, const int* __restrict__ idx, int64_t B,
                 d[r] = (__bf16)(v[r] * silu_gradf(z1[r]));
                 s1[r] += (float)d[r];
             }
-            put(la, nullptr, r0, d);                             // read back by this wave only
+            put(la, nullptr, r0, d);                             // read back by this wave only, by other lanes
         }
+        wave_lds_sync();
         // dW1: this wave's units against the inputs, the rows as K
 #pragma unroll
         for (int k = 0; k < R / 4; ++k) {
