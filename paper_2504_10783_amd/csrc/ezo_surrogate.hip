@@ -24,7 +24,8 @@ double unit(uint64_t& s) { return (double)(splitmix64(s) >> 11) * (1.0 / 9007199
 
 // Training batch buffers: z1 z2 z3 (FP32), h1 h2 h3 d3 d2 d1 (BF16) of
 // [B][H]; y dy rl (FP32 [B], rl = each row's loss); idx (int [B]); loss
-// (FP32); the column sums' counters (zero between launches).
+// (FP32); the column sums' counters (zero between launches).  The one-kernel pass
+// (H <= 256) keeps h1 h2 d3 d2 and no per-row values: the others are empty.
 struct TrainBufs {
     float *z1, *z2, *z3, *y, *dy, *rl, *loss;
     __bf16 *h1, *h2, *h3, *d3, *d2, *d1;
@@ -43,20 +44,20 @@ TrainBufs carve(void* base, int B, int H) {
         p += (bytes + 255) & ~(size_t)255;
         return q;
     };
-    const size_t bh = (size_t)B * H;
+    const size_t bh = (size_t)B * H, lbh = H > 256 ? bh : 0, lb = H > 256 ? (size_t)B : 0;
     t.cnt = (unsigned*)take(sizeof(unsigned) * kColGroups);     // first: the same place for every B
-    t.z1 = (float*)take(4 * bh);
-    t.z2 = (float*)take(4 * bh);
-    t.z3 = (float*)take(4 * bh);
+    t.z1 = (float*)take(4 * lbh);
+    t.z2 = (float*)take(4 * lbh);
+    t.z3 = (float*)take(4 * lbh);
     t.h1 = (__bf16*)take(2 * bh);
     t.h2 = (__bf16*)take(2 * bh);
-    t.h3 = (__bf16*)take(2 * bh);
+    t.h3 = (__bf16*)take(2 * lbh);
     t.d3 = (__bf16*)take(2 * bh);
     t.d2 = (__bf16*)take(2 * bh);
-    t.d1 = (__bf16*)take(2 * bh);
-    t.y = (float*)take(4 * (size_t)B);
-    t.dy = (float*)take(4 * (size_t)B);
-    t.rl = (float*)take(4 * (size_t)B);
+    t.d1 = (__bf16*)take(2 * lbh);
+    t.y = (float*)take(4 * lb);
+    t.dy = (float*)take(4 * lb);
+    t.rl = (float*)take(4 * lb);
     t.idx = (int*)take(4 * (size_t)B);
     t.loss = (float*)take(256);
     t.part = (float*)take(0);
@@ -73,14 +74,14 @@ constexpr int kTrainGroups = 256;       // most workgroups of k_mlp_train
 size_t partial_floats(int B, int H, int D) {
     const size_t slices = (size_t)(B + kRowsPerSlice - 1) / kRowsPerSlice;
     const size_t col_slices = (size_t)(B + kColRows - 1) / kColRows;
-    return std::max({(size_t)2 * kGradSplitK * H * H + (size_t)kTrainGroups * train_part_floats(H, D),
-                     slices * H * std::max(D, 1), col_slices * H});
+    if (H <= 256) return (size_t)2 * kGradSplitK * H * H + (size_t)kTrainGroups * train_part_floats(H, D);
+    return std::max({(size_t)kGradSplitK * H * H, slices * H * std::max(D, 1), col_slices * H});
 }
 
 size_t train_bytes(int B, int H, int D) {
-    const size_t bh = (size_t)B * H;
-    return 3 * (((4 * bh) + 255) & ~(size_t)255) + 6 * (((2 * bh) + 255) & ~(size_t)255) +
-           4 * ((4 * (size_t)B + 255) & ~(size_t)255) + 256 + 512 + ((4 * partial_floats(B, H, D) + 255) & ~(size_t)255);
+    char* const base = reinterpret_cast<char*>((uintptr_t)256);         // (only its distance to the last array counts)
+    return (size_t)(reinterpret_cast<char*>(carve(base, B, H).part) - base) +
+           ((4 * partial_floats(B, H, D) + 255) & ~(size_t)255);
 }
 
 // C = A B with the strides' contiguous dimensions picking the staging; split

@@ -313,3 +313,25 @@ def test_gradient_matches_oracle_at_tile_edges(ezo, ctx, D, H, n):
     cut = np.cumsum([0, H * D, H, H * H, H, H * H, H, H, 1])
     for a, b in zip(cut[:-1], cut[1:]):                                  # every part of the gradient
         assert np.linalg.norm(g[a:b] - go[a:b]) <= 3e-2 * np.linalg.norm(go[a:b]) + 1e-4 * np.linalg.norm(go)
+
+
+@pytest.mark.parametrize("H,most", [(256, 4 * 2), (320, 3 * 4 + 6 * 2)])
+def test_training_holds_what_its_pass_uses(ezo, ctx, H, most):
+    """A training batch's buffers: four BF16 activations a row for the one-kernel
+    pass, the layers' pre-activations as well for the layered one (`most` bytes a
+    row and unit), plus the sums; then a smaller batch in the same buffers."""
+    n, D = 1 << 18, 7
+    print_case("training buffers", H, n)
+    s = ezo.Surrogate(ctx, D, H, seed=5)
+    q = torch.zeros((n, D), device="cuda").uniform_(-2, 2, generator=torch.Generator(device="cuda").manual_seed(9))
+    t = q[:, 0].contiguous() * 0.1
+    tp = ezo.make_train_params()
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    s.loss_grad(q, t, tp)
+    used = free - torch.cuda.mem_get_info()[0]
+    sums = 4 * max(2 * 16 * H * H + 256 * (4 * H + 7 * H + 2), n // 64 * H * D)
+    assert used <= most * n * H + 16 * n + sums + (64 << 20), used
+    small = s.loss_grad(q[:128].contiguous(), t[:128].contiguous(), tp)
+    fresh = ezo.Surrogate(ctx, D, H, seed=5).loss_grad(q[:128].contiguous(), t[:128].contiguous(), tp)
+    assert small[0] == fresh[0] and np.array_equal(small[1], fresh[1])
