@@ -228,15 +228,16 @@ int tile_configs(const TileCfg& g, bool bisect) {
 
 BisectShape bisect_shape(const TileCfg& g) { return BisectShape{g.T, g.depth, tile_configs(g, true), 0}; }
 
-// Bisection shapes that have a kernel instance.
-bool bisect_shape_built(const TileCfg& g) {
+// Bisection shapes whose tile holds 2 to 64 configurations (an index in a wave's
+// list has six bits for one).
+bool bisect_shape_fits(const TileCfg& g) {
     return (g.depth == 1 && g.T >= 2 && g.T <= 64) || (g.depth == 2 && g.T <= 16) || (g.depth == 3 && g.T <= 8);
 }
 
 // A shape is usable when its LDS fits and staging is possible where asked.
 bool cfg_valid(const ezo_ctx* c, const TileCfg& g, const ezo_robot* r, int n_obs, bool sd, bool bisect = false) {
     if (!pow2_tile(g.T) || g.W < 1 || g.W > 16 || g.depth < 1 || g.depth > 3) return false;
-    if (bisect ? !bisect_shape_built(g) : g.depth != 1) return false;
+    if (bisect ? !bisect_shape_fits(g) : g.depth != 1) return false;
     const int T = tile_configs(g, bisect);
     const TileRows tr(r, n_obs, sd);
     const size_t rs = bisect ? bisect_extra_bytes(r, bisect_state_rows(bisect_shape(g))) : 0;
@@ -299,10 +300,10 @@ TileCfg resolve_cfg(const ezo_ctx* c, const TuneKey& k, const TileCfg& fallback,
 std::vector<TileCfg> tile_candidates(const ezo_ctx* c, const ezo_robot* r, int n_obs, bool sd, std::initializer_list<int> Ws,
                                      int64_t items, bool bisect = false) {
     std::vector<TileCfg> v;
-    // (bisection: one or two levels per round; three, seven points per
-    // candidate and round, never came near the fastest and only lengthened
-    // the first call's search, so the kernel's depth-3 instances are reached
-    // only through a shape given explicitly)
+    // (bisection: one or two levels per round for full lists; three, seven
+    // points per candidate and round, never came near the fastest there and only
+    // lengthened the first call's search.  Short lists take more levels whatever
+    // the shape says.)
     for (int dp = 1; dp <= (bisect ? 2 : 1); ++dp)
         for (int T : {64, 32, 16, 8, 4, 2, 1}) {
             if ((!bisect && T < 4) || (T > 4 && items < 4LL * T)) continue;   // a handful of items: small tiles
@@ -315,10 +316,11 @@ std::vector<TileCfg> tile_candidates(const ezo_ctx* c, const ezo_robot* r, int n
     return v;
 }
 
-// Workgroups of W waves and `lds` bytes that the chip holds at once, at the six
-// waves per SIMD that the flags kernels' registers allow.
-int64_t resident_groups(size_t lds, int W) {
-    return (int64_t)kNumCU * std::max<int64_t>(1, std::min<int64_t>(163840 / (int64_t)lds, 24 / W));
+// Workgroups of W waves and `lds` bytes that the chip holds at once, at the waves
+// per SIMD that the kernel's registers allow (k_check and k_project_bisect six, its
+// screened form four).
+int64_t resident_groups(size_t lds, int W, int waves = 6) {
+    return (int64_t)kNumCU * std::max<int64_t>(1, std::min<int64_t>(163840 / (int64_t)lds, 4 * waves / W));
 }
 
 ezo_status launch_check(ezo_ctx* c, const ezo_robot* r, const ObsView& ov, const GridView& gv, const float* q, int64_t n,
@@ -580,7 +582,7 @@ ezo_status launch_project_bisect(ezo_ctx* c, const ezo_robot* r, const ObsView& 
         g.W = std::max(g.W, 4);
     }
     const int W = g.W;
-    if (!bisect_shape_built(g) || W < 1 || W > 16)
+    if (!bisect_shape_fits(g) || W < 1 || W > 16)
         return ezo_fail(c, EZO_E_INVALID, "bisection shape T=%d W=%d depth=%d", g.T, W, g.depth);
     BisectShape bs = bisect_shape(g);
     bool ost = g.stage && ov.n > 0;
@@ -594,10 +596,9 @@ ezo_status launch_project_bisect(ezo_ctx* c, const ezo_robot* r, const ObsView& 
         }
     }
     if (lds > c->lds_max) return ezo_fail(c, EZO_E_UNSUPPORTED, "robot too large for one tile");
-    // workgroups that run at once: by LDS (160 KB a CU) and by registers (five
-    // waves a SIMD); the grid holds every tile of full lists, up to eight
-    // rounds of those (a workgroup then takes several)
-    bs.resident = kNumCU * std::max(1, std::min((int)(163840 / lds), 24 / W));
+    // the grid holds every tile of full lists, up to eight rounds of the workgroups
+    // that run at once (a workgroup then takes several)
+    bs.resident = (int)resident_groups(lds, W, scr ? 4 : 6);
     const MlpView mv = scr ? *screen : MlpView{0, 0, nullptr, nullptr, nullptr, 0.f};
     const int lists = list_count(E, cl.group);
     for (int l = 0; l < lists; ++l) {
