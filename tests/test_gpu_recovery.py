@@ -384,3 +384,34 @@ def test_path_points_found_in_order(ezo, ctx, n, cap, share):
     if len(hit) == found:
         k = min(cap, found)
         assert len(pts) == k and np.abs(pts.cpu().numpy() - q[hit[:k]]).max(initial=0.0) <= 4 * step + 1e-6
+
+
+@pytest.mark.parametrize("n,cap", [(1023, 2000), (1024, 7), (1025, 2000), (4099, 4096), (1048575, 4096), (1048576, 1100000),
+                                   (1048577, 1100000), (1049601, 100), (2100000, 2100000)])
+def test_colliding_points_in_exact_order(ezo, ctx, n, cap):
+    """Around the 1024 flags of a compaction tile and the 1024 workgroups that
+    take one tile each: a path along one joint from 0 to 1, whose points j / m are
+    the same numbers here, so that the found points are compared one by one."""
+    data, desc = load("tiny")
+    rob = ezo.Robot(ctx, desc)
+    dof, m = int(desc["dof"]), n - 1
+    obs = torch.from_numpy(data["obstacles"]).cuda()
+    way = np.zeros((2, dof), np.float32)
+    way[1, 0] = 1.0
+    t = torch.from_numpy(np.arange(n, dtype=np.float32) / np.float32(m)).cuda()     # correctly rounded quotients
+    for turn in np.linspace(-2.5, 2.5, 41).astype(np.float32):       # a bend of the arm that collides on a part of the way
+        q = torch.zeros((n, dof), device="cuda")
+        q[:, 1], q[:, 0] = float(turn), t
+        flags = torch.empty(n, dtype=torch.uint8, device="cuda")
+        ezo.check_collisions(ctx, rob, obs, q, flags)
+        if 0.1 < flags.float().mean().item() < 0.9:
+            break
+    else:
+        pytest.fail("no bend of the arm collides on a part of the way")
+    way[:, 1] = turn
+    print_case("exact order", n, cap)
+    pts, found, total = ezo.check_path(ctx, rob, obs, torch.from_numpy(way).cuda(), 1.0 / (m - 0.5), point_capacity=cap)
+    torch.cuda.synchronize()
+    hit = flags.bool()
+    assert total == n and found == int(hit.sum())
+    assert torch.equal(pts, q[hit][:cap])
