@@ -77,8 +77,10 @@ __device__ __forceinline__ float near_slack(float ext) { return 1e-5f + 4e-6f * 
 // can be nearest from anywhere in the block are copied to LDS (those no farther
 // from the block's box than the least farthest distance of any), and each cell
 // then looks at those only, a wave per cell.  Bound by load latency: 4096
-// obstacles take 85 us with the records in LDS and eight waves, 199 us
-// with four waves reading them from L2.
+// obstacles take 73 us with the records in LDS and eight waves, 199 us
+// with four waves reading them from L2.  A block with more obstacles than it holds
+// takes the nearest of all for each cell and keeps no lists (4096 heaped up: 80 us,
+// 290 with lists over all of them, which hardly ever fit).
 __global__ void __launch_bounds__(512) k_near_build(const float4* __restrict__ rec, int n,
                                                     const GridGeom* __restrict__ geom, uint2* __restrict__ near,
                                                     unsigned short* __restrict__ list) {
@@ -296,7 +298,7 @@ __device__ __forceinline__ float sd_pair(f4 C, float4 O) {
 // takes four spheres (two part pairs) at a time.  256 k configurations of the
 // 7-DOF arm (70 spheres, 1500 self pairs) among 4096 spheres: all pairs 15.7 ms;
 // one sphere per row at a time 484 us, four 414, in 125 registers (four waves a
-// SIMD; five with spills 516).  With the field's build the call takes 0.51 ms.
+// SIMD; five with spills 516).  With the field's build the call takes 0.46 ms.
 __global__ void __launch_bounds__(256, 4) k_distances(RobotView rb, ObsView ob, NearView nv, int CW,
                                                    const float* __restrict__ q, int64_t n, int64_t stride_n,
                                                    int64_t stride_d, uint8_t* __restrict__ flags,
