@@ -65,8 +65,9 @@ def kernel_source_sha256():
 
 
 def measured_traffic(workload, kernel_instance, n_p):
-    """HBM bytes per launch of `kernel_instance` (that template instance,
-    i.e. that launch shape) from the committed rocprofv3 FETCH_SIZE /
+    """HBM bytes per launch of `kernel_instance` (the template instance; its
+    tile sizes are arguments, and those of the counted run stand in the
+    workload's kernel trace) from the committed rocprofv3 FETCH_SIZE /
     WRITE_SIZE summary of this workload (each counter scaled by its reading
     for a plain 1 GiB copy), or None when there is no summary, the instance
     was not measured, the kernel sources changed since the counters were

@@ -63,7 +63,8 @@ struct TileRows {
           tables(robot_stage_bytes(r->S, r->view.n_blocks, r->P, false)) {}
     size_t bytes(int T, int W) const {
         return sd ? tile_smem_bytes(T, slots, W)
-                  : flag_tile_bytes(T, S, B, n_blocks, W) + flag_grid_bytes(S, n_obs, grid_dim(n_obs), 0) + tables;
+                  : flag_tile_bytes(T, !boxes_only(S, B), B, n_blocks, W) +
+                        flag_grid_bytes(!boxes_only(S, B), n_obs, grid_dim(n_obs), 0) + tables;
     }
 };
 
@@ -132,10 +133,16 @@ ezo_status prep_obstacles_into(ezo_ctx* c, const ezo_robot* r, const float* obs,
     const bool build = grid && lists && n_obs > 0;
     const int clear_wg = grid && !build ? (G * G * G + 2047) / 2048 : 0;
     const int init_wg = (ei && ei->n_edges > 0) ? (ei->n_edges + 255) / 256 : 0;
-    hipLaunchKernelGGL(k_prep_obstacles, dim3(1 + clear_wg + init_wg), dim3(256), 0, st, obs, n_obs, (float4*)rec,
-                       (float4*)centre, (GridGeom*)geom, G, r ? r->r_max : 0.f, r ? r->r_min : -kHuge,
-                       kind == PREP_NEAR ? kNearGrow : 0.f, kind == PREP_NEAR && r ? r->reach : INFINITY, (int*)count,
-                       lists ? 0 : kGridCap + 1, (unsigned*)state, lists ? 0u : 0x55555555u, clear_wg, init_wg ? *ei : EdgeInit{});
+    const dim3 prep_wg(1 + clear_wg + init_wg);
+    const EdgeInit start = init_wg ? *ei : EdgeInit{};
+    if (kind == PREP_NEAR)
+        hipLaunchKernelGGL(k_prep_obstacles<true>, prep_wg, dim3(256), 0, st, obs, n_obs, (float4*)rec, (float4*)centre,
+                           (GridGeom*)geom, G, r->r_max, r->r_min, kNearGrow, r->reach, (int*)count, 0, (unsigned*)state,
+                           0u, clear_wg, start);
+    else
+        hipLaunchKernelGGL(k_prep_obstacles<false>, prep_wg, dim3(256), 0, st, obs, n_obs, (float4*)rec, (float4*)centre,
+                           (GridGeom*)geom, G, r ? r->r_max : 0.f, r ? r->r_min : -kHuge, 0.f, INFINITY, (int*)count,
+                           lists ? 0 : kGridCap + 1, (unsigned*)state, lists ? 0u : 0x55555555u, clear_wg, start);
     if (kind == PREP_NEAR && n_obs > 0)
         hipLaunchKernelGGL(k_near_build, dim3(kNearCells / (kNearBlock * kNearBlock * kNearBlock)), dim3(512), 0, st,
                            (const float4*)rec, n_obs, (const GridGeom*)geom, (uint2*)near, (unsigned short*)list);

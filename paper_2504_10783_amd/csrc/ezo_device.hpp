@@ -692,15 +692,18 @@ struct FlagTile {
 // most 63 left by the step before.
 constexpr int kWaveList = 192;
 
-__host__ __device__ inline size_t flag_tile_bytes(int T, int n_spheres, int n_boxes, int n_blocks, int W) {
+// A robot of boxes only keeps no lists and no cell states.
+__host__ __device__ inline bool boxes_only(int n_spheres, int n_boxes) { return n_spheres == 0 && n_boxes > 0; }
+
+__host__ __device__ inline size_t flag_tile_bytes(int T, bool lists, int n_boxes, int n_blocks, int W) {
     return sizeof(float4) * (size_t)T * (rec_rows(n_boxes, n_blocks) + 4 * n_boxes) +
-           (n_spheres > 0 ? sizeof(unsigned) * (size_t)kWaveList * W : 0);
+           (lists ? sizeof(unsigned) * (size_t)kWaveList * W : 0);
 }
 
-// The cell states (for spheres) and the staged obstacles follow the tile region,
-// then the robot's tables.
-__host__ __device__ inline size_t flag_grid_bytes(int n_spheres, int n_obs, int G, int lds_n) {
-    return (n_spheres > 0 && n_obs > 0 ? sizeof(unsigned) * (size_t)state_words(G) : 0) + sizeof(float4) * (size_t)lds_n;
+// The cell states and the staged obstacles follow the tile region, then the
+// robot's tables.
+__host__ __device__ inline size_t flag_grid_bytes(bool states, int n_obs, int G, int lds_n) {
+    return (states && n_obs > 0 ? sizeof(unsigned) * (size_t)state_words(G) : 0) + sizeof(float4) * (size_t)lds_n;
 }
 
 // base: the workgroup's LDS (16-byte aligned); *end receives the first byte
@@ -709,14 +712,17 @@ template <bool BOX>
 __device__ inline FlagTile carve_flag_tile(char* base, int T, int W, const RobotView& rb, bool pairs, const ObsView& ob,
                                            int lds_n, int G, char** end) {
     FlagTile t;
+    const int n_boxes = BOX ? rb.n_boxes : 0;
+    const bool lists = !BOX || !boxes_only(rb.n_spheres, n_boxes);
+    const size_t tile = flag_tile_bytes(T, lists, n_boxes, rb.n_blocks, W);
     lds_ptr<char> p = to_lds(base);
     t.T = T;
-    t.rows = BOX ? rec_rows(rb.n_boxes, rb.n_blocks) : kRecRows;
+    t.rows = BOX ? rec_rows(n_boxes, rb.n_blocks) : kRecRows;
     t.rec = (lds_ptr<f4>)p;         p += (int)sizeof(f4) * t.rows * T;
-    t.box = (lds_ptr<f4>)p;         p += sizeof(f4) * 4 * rb.n_boxes * T;
+    t.box = (lds_ptr<f4>)p;         p += (int)sizeof(f4) * 4 * n_boxes * T;
     t.wl = (lds_ptr<unsigned>)p;
-    p = to_lds(base) + (int)flag_tile_bytes(T, rb.n_spheres, rb.n_boxes, rb.n_blocks, W);
-    t.state = (lds_ptr<unsigned>)p; p += (int)flag_grid_bytes(rb.n_spheres, ob.n, G, 0);
+    p = to_lds(base) + (int)tile;
+    t.state = (lds_ptr<unsigned>)p; p += (int)flag_grid_bytes(lists, ob.n, G, 0);
     t.obs = (lds_ptr<f4>)p;         p += sizeof(f4) * lds_n;
     t.lbound = (lds_ptr<f4>)p;
     t.blocks = (lds_ptr<i4>)(t.lbound + kMaxParts);
@@ -724,8 +730,7 @@ __device__ inline FlagTile carve_flag_tile(char* base, int T, int W, const Robot
     t.link = (lds_ptr<int>)(p + (int)robot_image_off_link(rb.n_spheres, rb.n_blocks));
     t.pairs = (lds_ptr<i2>)(p + (int)robot_image_off_pairs(rb.n_spheres, rb.n_blocks));
     if (end)
-        *end = base + flag_tile_bytes(T, rb.n_spheres, rb.n_boxes, rb.n_blocks, W) +
-               flag_grid_bytes(rb.n_spheres, ob.n, G, lds_n) +
+        *end = base + tile + flag_grid_bytes(lists, ob.n, G, lds_n) +
                robot_stage_bytes(rb.n_spheres, rb.n_blocks, rb.n_self, pairs);
     return t;
 }
@@ -746,11 +751,11 @@ __device__ __forceinline__ void copy_to_lds(lds_ptr<f4> dst, const float4* src, 
 
 // The workgroup's copies of the cell states, (OST) the obstacle records and
 // the robot's tables; the caller places a barrier before their first use.
-template <bool OST>
+template <bool BOX, bool OST>
 __device__ inline void stage_tables(const RobotView& rb, bool pairs, const ObsView& ob, const GridView& gv,
                                     const FlagTile& t) {
     if (ob.n > 0) {
-        if (rb.n_spheres > 0)
+        if (!BOX || !boxes_only(rb.n_spheres, rb.n_boxes))
             copy_to_lds((lds_ptr<f4>)t.state, reinterpret_cast<const float4*>(gv.state), state_words(gv.G) / 4);
         if constexpr (OST) copy_to_lds(t.obs, ob.rec, ob.n);
     }
