@@ -55,15 +55,15 @@ int grid_dim(int n_obs) { return n_obs >= 256 ? 32 : (n_obs >= 32 ? 16 : 8); }
 // LDS of a tile check by mode: signed distances hold every sphere and box of
 // a configuration, flags only the link frames and boxes.
 struct TileRows {
-    int slots, S, B, n_blocks, n_obs;
+    int slots, S, B, rec_bytes, n_obs;
     bool sd;
     size_t tables;             // the robot's tables without the self pairs
     TileRows(const ezo_robot* r, int n_obs_, bool sd_)
-        : slots(r->slots), S(r->S), B(r->B), n_blocks(r->view.n_blocks), n_obs(n_obs_), sd(sd_),
+        : slots(r->slots), S(r->S), B(r->B), rec_bytes(r->view.rec_bytes), n_obs(n_obs_), sd(sd_),
           tables(robot_stage_bytes(r->S, r->view.n_blocks, r->P, false)) {}
     size_t bytes(int T, int W) const {
         return sd ? tile_smem_bytes(T, slots, W)
-                  : flag_tile_bytes(T, !boxes_only(S, B), B, n_blocks, W) +
+                  : flag_tile_bytes(T, !boxes_only(S, B), rec_bytes, B, W) +
                         flag_grid_bytes(!boxes_only(S, B), n_obs, grid_dim(n_obs), 0) + tables;
     }
 };
@@ -1146,6 +1146,7 @@ ezo_status ezo_robot_create(ezo_ctx* c, const ezo_robot_desc* d, ezo_robot** out
     r->view.n_spheres = S;
     r->view.n_self = P;
     r->view.n_blocks = NB;
+    r->view.rec_bytes = 16 * rec_rows(dof, NB);
     r->view.lbound = reinterpret_cast<const float4*>(b + off_lbd);
     r->view.blocks = reinterpret_cast<const int4*>(b + off_blk);
     r->view.dh = reinterpret_cast<const float4*>(b + off_dh);

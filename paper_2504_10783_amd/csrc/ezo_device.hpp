@@ -56,6 +56,7 @@ struct RobotView {
     int n_spheres;
     int n_self;
     int n_blocks;
+    int rec_bytes;             // of a configuration's record in a flags tile (16 rec_rows)
     const float4* dh;          // [kMaxDof] (a, d, cos alpha, sin alpha), zero past dof
     const int* link_begin;     // [dof + 1] spheres of link i: [link_begin[i], link_begin[i+1])
     const float4* sph;         // [S] local (x, y, z), r -- sorted by link
@@ -654,22 +655,29 @@ typedef lds_i4_t i4;
 typedef float f2 __attribute__((ext_vector_type(2)));
 typedef int i2 __attribute__((ext_vector_type(2)));
 
-// A configuration's record in the tile, in 16-byte rows: the links' frames
-// (three rows (R | p) each, shifted frame), each joint's (cos, sin), each link's
-// offset d (plus q for a prismatic joint), (collision flag, 1 = the learned screen
-// cleared its self pairs), and the parts' bounding spheres, which a box arm
-// without sphere pairs goes without (its tile holds its boxes' poses besides:
-// more waves fit a CU).  The rows of a record are at fixed offsets (no address
-// arithmetic or registers for them), and 47 rows, 188 words (31, 124), put the
-// records of a tile on distinct LDS banks.
-constexpr int kRecTrig = 3 * kMaxDof, kRecD = kRecTrig + kMaxDof / 2, kRecHit = kRecD + kMaxDof / 4,
-              kRecLb = kRecHit + 1, kRecRows = kRecLb + kMaxParts;
-static_assert(kRecRows % 2 == 1 && kRecLb % 2 == 1, "an odd number of 16-byte rows: distinct banks");
-__host__ __device__ inline int rec_rows(int n_boxes, int n_blocks) { return n_boxes > 0 && n_blocks == 0 ? kRecLb : kRecRows; }
+// A configuration's record in the tile, in 16-byte rows: the parts' bounding
+// spheres, (collision flag, 1 = the learned screen cleared its self pairs), each
+// link's offset d (plus q for a prismatic joint), each joint's (cos, sin), and the
+// links' frames (three rows (R | p) each, shifted frame).  The rows of a record are
+// at fixed offsets (no address arithmetic or registers for them); a robot keeps its
+// own links' frames only, and without self pairs of spheres no bounds (the record
+// then starts kMaxParts rows in: more waves fit a CU: 2 M point-robot checks among
+// 15 discs 64 us, 134 with all 47 rows).  The rows of a tile's records lie on distinct
+// LDS banks when their number is odd, and neighbouring records' frames collide least
+// when it is 1 or 7 modulo 8 (4 M configurations of seven joints: 47 rows 1573 us,
+// 45 rows 1587).
+constexpr int kRecLb = 0, kRecHit = kMaxParts, kRecD = kRecHit + 1, kRecTrig = kRecD + kMaxDof / 4,
+              kRecFrame = kRecTrig + kMaxDof / 2, kRecRows = kRecFrame + 3 * kMaxDof;
+__host__ __device__ constexpr int rec_rows(int dof, int n_blocks) {
+    const int r = (kRecFrame + 3 * dof - (n_blocks > 0 ? 0 : kMaxParts)) | 1;
+    return r % 8 == 3 || r % 8 == 5 ? r | 7 : r;
+}
+static_assert(rec_rows(kMaxDof, 1) == kRecRows, "the distance kernel's records are the largest robot's");
 
 struct FlagTile {
-    lds_ptr<f4> rec;        // [T][rows]
-    int rows;
+    lds_ptr<f4> rec;        // [T][rows], kMaxParts rows before the first record that holds no bounds
+    int stride;             // bytes of a record
+    bool bounds;            // records hold the parts' bounding spheres
     lds_ptr<f4> box;        // [4 B][T] each box's world pose as four rows (packed like RobotView::box)
     int T;
     lds_ptr<unsigned> wl;   // [W][kWaveList] each wave's list
@@ -681,11 +689,13 @@ struct FlagTile {
     lds_ptr<int> link;
     lds_ptr<i2> pairs;
 
-    __device__ __forceinline__ lds_ptr<f4> row(int c) const { return rec + c * rows; }
-    __device__ __forceinline__ lds_ptr<volatile int> hit(int c) const {
-        return (lds_ptr<volatile int>)(rec + c * rows + kRecHit);
+    __device__ __forceinline__ lds_ptr<f4> row(int c) const {
+        return (lds_ptr<f4>)((lds_ptr<char>)rec + __umul24(c, stride));
     }
-    __device__ __forceinline__ lds_ptr<int> scr(int c) const { return (lds_ptr<int>)(rec + c * rows + kRecHit) + 1; }
+    __device__ __forceinline__ lds_ptr<volatile int> hit(int c) const {
+        return (lds_ptr<volatile int>)(row(c) + kRecHit);
+    }
+    __device__ __forceinline__ lds_ptr<int> scr(int c) const { return (lds_ptr<int>)(row(c) + kRecHit) + 1; }
 };
 
 // Entries of a wave's list: a step adds at most 128 (two spheres a lane) to at
@@ -695,9 +705,15 @@ constexpr int kWaveList = 192;
 // A robot of boxes only keeps no lists and no cell states.
 __host__ __device__ inline bool boxes_only(int n_spheres, int n_boxes) { return n_spheres == 0 && n_boxes > 0; }
 
-__host__ __device__ inline size_t flag_tile_bytes(int T, bool lists, int n_boxes, int n_blocks, int W) {
-    return sizeof(float4) * (size_t)T * (rec_rows(n_boxes, n_blocks) + 4 * n_boxes) +
-           (lists ? sizeof(unsigned) * (size_t)kWaveList * W : 0);
+// The waves' lists lie first (a record without bounds is addressed from kMaxParts
+// rows before it: at least that much lies there).
+__host__ __device__ inline size_t flag_lists_bytes(bool lists, int W) {
+    return lists ? sizeof(unsigned) * (size_t)kWaveList * W : sizeof(float4) * kMaxParts;
+}
+static_assert(sizeof(unsigned) * kWaveList >= sizeof(float4) * kMaxParts, "room before the first record");
+
+__host__ __device__ inline size_t flag_tile_bytes(int T, bool lists, int rec_bytes, int n_boxes, int W) {
+    return (size_t)T * (rec_bytes + sizeof(float4) * 4 * n_boxes) + flag_lists_bytes(lists, W);
 }
 
 // The cell states and the staged obstacles follow the tile region, then the
@@ -714,13 +730,15 @@ __device__ inline FlagTile carve_flag_tile(char* base, int T, int W, const Robot
     FlagTile t;
     const int n_boxes = BOX ? rb.n_boxes : 0;
     const bool lists = !BOX || !boxes_only(rb.n_spheres, n_boxes);
-    const size_t tile = flag_tile_bytes(T, lists, n_boxes, rb.n_blocks, W);
+    const size_t tile = flag_tile_bytes(T, lists, rb.rec_bytes, n_boxes, W);
     lds_ptr<char> p = to_lds(base);
     t.T = T;
-    t.rows = BOX ? rec_rows(n_boxes, rb.n_blocks) : kRecRows;
-    t.rec = (lds_ptr<f4>)p;         p += (int)sizeof(f4) * t.rows * T;
+    t.stride = rb.rec_bytes;
+    t.bounds = rb.n_blocks > 0;
+    t.wl = (lds_ptr<unsigned>)p;    p += (int)flag_lists_bytes(lists, W);
+    t.rec = (lds_ptr<f4>)p - (t.bounds ? 0 : kMaxParts);
+    p += t.stride * T;
     t.box = (lds_ptr<f4>)p;         p += (int)sizeof(f4) * 4 * n_boxes * T;
-    t.wl = (lds_ptr<unsigned>)p;
     p = to_lds(base) + (int)tile;
     t.state = (lds_ptr<unsigned>)p; p += (int)flag_grid_bytes(lists, ob.n, G, 0);
     t.obs = (lds_ptr<f4>)p;         p += sizeof(f4) * lds_n;
@@ -773,7 +791,7 @@ __device__ __forceinline__ void wave_lds_sync() {
 struct LFrame { f4 r0, r1, r2; };
 
 __device__ __forceinline__ LFrame tile_frame(const FlagTile& t, int c, int link) {
-    const lds_ptr<f4> f = t.row(c) + 3 * link;
+    const lds_ptr<f4> f = t.row(c) + kRecFrame + 3 * link;
     return LFrame{f[0], f[1], f[2]};
 }
 
@@ -814,7 +832,7 @@ __device__ __forceinline__ void tile_pose(const RobotView& rb, float4 sh, const 
         d[1] = rec[kRecD + 1];
         float r0 = j == 0 ? 1.f : 0.f, r1 = j == 1 ? 1.f : 0.f, r2 = j == 2 ? 1.f : 0.f;
         float p = -(j == 0 ? sh.x : (j == 1 ? sh.y : sh.z));
-        const lds_ptr<f4> out = rec + j;
+        const lds_ptr<f4> out = rec + kRecFrame + j;
 #pragma unroll
         for (int l = 0; l < kMaxDof; ++l) {
             if (l >= rb.dof) break;
@@ -826,7 +844,7 @@ __device__ __forceinline__ void tile_pose(const RobotView& rb, float4 sh, const 
             out[3 * l] = row;
         }
     }
-    if (t.rows == kRecLb) return;
+    if (!t.bounds) return;
     wave_lds_sync();
     static_assert(kMaxParts == 16 && kPartsPerLink == 2, "two parts a lane");
     const LFrame f0 = tile_frame(t, x, j / kPartsPerLink), f1 = tile_frame(t, x, j / kPartsPerLink + 4);
@@ -993,7 +1011,8 @@ __device__ __forceinline__ void tile_self_pairs(PairF pair, const RobotView& rb,
             const int c = w.c, bk = on ? w.k : 0;
             w.next(n_valid);
             const i4 blk = t.blocks[bk];
-            const f4 A = t.row(c)[kRecLb + blk.x], B = t.row(c)[kRecLb + blk.y];
+            const lds_ptr<f4> part = t.row(c) + kRecLb;
+            const f4 A = part[blk.x], B = part[blk.y];
             const float dx = A.x - B.x, dy = A.y - B.y, dz = A.z - B.z;
             const float R = A.w + B.w;
             const bool test = on && (*t.hit(c) | *t.scr(c)) == 0;

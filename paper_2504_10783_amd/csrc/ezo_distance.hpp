@@ -316,7 +316,8 @@ __global__ void __launch_bounds__(256, 4) k_distances(RobotView rb, ObsView ob, 
         const int tb = (int)robot_stage_bytes(rb.n_spheres, rb.n_blocks, rb.n_self, false);
         const lds_ptr<char> m = p + tb + w * (int)sd_wave_bytes(CW);
         t.rec = (lds_ptr<f4>)m;
-        t.rows = kRecRows;
+        t.stride = (int)sizeof(f4) * kRecRows;
+        t.bounds = true;
         copy_to_lds(t.lbound, rb.image, tb / 16);
     }
     SdWave sw;

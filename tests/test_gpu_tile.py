@@ -4,6 +4,8 @@ obstacle counts around the grid sizes (none, one, past the 16-bit lists),
 cells whose state is a certain hit, robots without spheres on some links; and
 the bisection's levels per round, which change with the number of candidates
 in the call's list and must not change a result."""
+import json
+
 import numpy as np
 import pytest
 
@@ -61,6 +63,51 @@ def test_flags_at_tile_edges(ezo, ctx, dof, per_link, n_obs, n, prismatic):
     got = flags.cpu().numpy()
     out = np.abs(sd) >= BAND
     assert np.array_equal(got[out], fo[out])
+
+
+@pytest.mark.parametrize("pairs", ["none", "one", "few", "some", "all", "boxes"])
+@pytest.mark.parametrize("dof", range(1, 9))
+def test_flags_by_joints_and_pairs(ezo, ctx, dof, pairs):
+    """A record's size goes by the joints and by whether there are self pairs of
+    spheres (1 to 64 a pair of link parts here); a robot of boxes keeps no lists."""
+    n = 199
+    desc = arm(dof, 16 if pairs != "one" else 2, 700 + dof, dof % 2 == 0)
+    p = np.asarray(desc["self_pairs"], np.int32).reshape(-1, 2)
+    rng = draw.rng_for(710 + dof)
+    if pairs == "none" or pairs == "boxes":
+        p = p[:0]
+    elif pairs in ("few", "some") and len(p):
+        p = p[np.sort(rng.choice(len(p), len(p) // (20 if pairs == "few" else 10), replace=False))]
+    desc["self_pairs"] = p
+    if pairs == "boxes":
+        for k in ("sphere_link", "sphere_xyz", "sphere_r"):
+            desc[k] = desc[k][:0]
+        desc["box_link"] = np.arange(dof, dtype=np.int32)
+        desc["box_pose"] = np.tile(np.concatenate([np.zeros(3), np.eye(3).ravel()]), (dof, 1))
+        desc["box_half"] = rng.uniform(0.03, 0.12, (dof, 3))
+        desc["box_pairs"] = np.array([(i, j) for i in range(dof) for j in range(i + 2, dof)], np.int32).reshape(-1, 2)
+    print_case("joints and pairs", dof, pairs, len(desc["self_pairs"]))
+    obs = draw.obstacle_candidates(rng, 40, (-1.0, -1.0, -0.5), (1.2, 1.0, 1.0), 0.02, 0.06).reshape(-1, 4)
+    q = draw.uniform_q(720 + dof, n, desc["q_lo"], desc["q_hi"])
+    rob, orob = ezo.Robot(ctx, desc), oracle.Robot(desc)
+    ot, qt = torch.from_numpy(obs).cuda(), torch.from_numpy(q).cuda()
+    fo, sd, *_ = oracle.check(orob, obs.astype(np.float64), q.astype(np.float64))
+    sure = np.abs(sd) >= BAND
+    size = dict(arch=torch.cuda.get_device_properties(0).gcnArchName.split(":")[0], kernel="check_flags", dof=dof,
+                spheres=rob.n_spheres, self_pairs=rob.n_self, boxes=rob.n_boxes, obstacles=len(obs), log2_items=7)
+    ctx.set_autotune(False)
+    try:
+        for T, W in ((0, 0), (64, 8), (64, 1), (8, 2), (4, 8)):
+            ezo.tune_cache_clear()
+            if T:
+                assert ezo.tune_cache_import(json.dumps(dict(size, T=T, W=W, stage=0, depth=1, us=0.0),
+                                                        separators=(",", ":"))) == 1
+            flags = torch.full((n,), 7, dtype=torch.uint8, device="cuda")
+            ezo.check_collisions(ctx, rob, ot, qt, flags)
+            assert np.array_equal(flags.cpu().numpy()[sure], fo[sure]), (T, W)
+    finally:
+        ctx.set_autotune(True)
+        ezo.tune_cache_clear()
 
 
 def test_bisection_levels_give_identical_results(ezo, ctx):
