@@ -57,6 +57,7 @@ struct RobotView {
     int n_self;
     int n_blocks;
     int rec_bytes;             // of a configuration's record in a flags tile (16 rec_rows)
+    int item_shift;            // lanes of a part pair there (item_lanes_log2)
     const float4* dh;          // [kMaxDof] (a, d, cos alpha, sin alpha), zero past dof
     const int* link_begin;     // [dof + 1] spheres of link i: [link_begin[i], link_begin[i+1])
     const float4* sph;         // [S] local (x, y, z), r -- sorted by link
@@ -83,9 +84,14 @@ __host__ __device__ inline int tile_slots(int n_spheres, int n_boxes) { return n
 
 // Self-pair broad phase: each link's spheres split into kPartsPerLink parts
 // (consecutive runs of its sphere list), each with its own bounding sphere;
-// a work item (configuration, part pair) is taken by kItemLanes lanes.
+// a work item (configuration, part pair) is taken by 16 lanes, by 8 or 4 when that
+// is all the sphere pairs that a part pair has on average (16 left most lanes of an
+// arm of 30 spheres and 267 pairs idle: 262 144 checks among 40 obstacles 106 and
+// 84 us).
 constexpr int kPartsPerLink = 2;
-constexpr int kItemLanes = 16;
+__host__ __device__ inline int item_lanes_log2(int n_self, int n_blocks) {
+    return n_self > 8 * n_blocks ? 4 : (n_self > 4 * n_blocks ? 3 : 2);
+}
 constexpr int kMaxParts = kPartsPerLink * kMaxDof;
 constexpr int kMaxPartPairs = kMaxParts * (kMaxParts + 1) / 2;   // part pairs, same-part pairs included
 
@@ -628,13 +634,13 @@ __device__ inline void tile_pairs_sd(const RobotView& rb, const ObsView& ob, con
 //      three of them compose the frames, one row each (row r of [R | p]
 //      depends on row r of the previous link's only); all eight place the
 //      link parts' bounding spheres                                    | barrier
-//   2. obstacles: a lane per (configuration, link, sphere group) places its
+//   2. obstacles: a lane per (configuration, sphere), two a step, places its
 //      spheres and looks their grid cells up in the workgroup's copy of the
 //      cell states (8 KB of LDS for 32^3 cells): nothing near, certain hit, or
 //      a list.  Listed spheres go to the wave's own LDS list and are tested
-//      from there with full lanes.  Then self pairs: a lane per
+//      from there with full lanes (one to eight a sphere).  Then self pairs: a lane per
 //      (configuration, part pair) tests the parts' bounding spheres;
-//      overlapping ones go to the wave's list, and kItemLanes lanes each test
+//      overlapping ones go to the wave's list, and up to 16 lanes each test
 //      the sphere pairs of one.  (Boxes: placed, a barrier, their pairs) | barrier
 // Configurations found colliding drop out of everything that follows.  Every
 // pair not tested is provably separated (or its configuration already hit),
@@ -678,6 +684,7 @@ struct FlagTile {
     lds_ptr<f4> rec;        // [T][rows], kMaxParts rows before the first record that holds no bounds
     int stride;             // bytes of a record
     bool bounds;            // records hold the parts' bounding spheres
+    int item_shift;
     lds_ptr<f4> box;        // [4 B][T] each box's world pose as four rows (packed like RobotView::box)
     int T;
     lds_ptr<unsigned> wl;   // [W][kWaveList] each wave's list
@@ -735,6 +742,7 @@ __device__ inline FlagTile carve_flag_tile(char* base, int T, int W, const Robot
     t.T = T;
     t.stride = rb.rec_bytes;
     t.bounds = rb.n_blocks > 0;
+    t.item_shift = rb.item_shift;
     t.wl = (lds_ptr<unsigned>)p;    p += (int)flag_lists_bytes(lists, W);
     t.rec = (lds_ptr<f4>)p - (t.bounds ? 0 : kMaxParts);
     p += t.stride * T;
@@ -968,15 +976,15 @@ __device__ __forceinline__ void tile_obstacles(RecF rec, const RobotView& rb, co
 }
 
 // Tests the sphere pairs of the last m listed (configuration, part pair)
-// items: kItemLanes lanes each, 32 or 64 when there are at most two.
+// items: 2^item_shift lanes each, 32 or 64 when there are at most two.
 template <class PairF>
 __device__ __forceinline__ void drain_parts(WaveList& wl, int m, PairF pair, const FlagTile& t,
                                             unsigned& ntest) {
     wave_lds_sync();
     const int lane = threadIdx.x & 63;
-    const int L = m > 2 ? kItemLanes : (m > 1 ? 32 : 64);
-    const int sub = lane / L, li = lane % L;
-    for (int it0 = 0; it0 < m; it0 += 64 / L) {
+    const int sh = m > 2 ? t.item_shift : (m > 1 ? 5 : 6), L = 1 << sh;       // lanes an item
+    const int sub = lane >> sh, li = lane & (L - 1);
+    for (int it0 = 0; it0 < m; it0 += 64 >> sh) {
         const int it = it0 + sub;
         const unsigned e = wl.e[wl.n - m + min(it, m - 1)];
         const int c = e & 63;

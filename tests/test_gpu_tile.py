@@ -69,7 +69,8 @@ def test_flags_at_tile_edges(ezo, ctx, dof, per_link, n_obs, n, prismatic):
 @pytest.mark.parametrize("dof", range(1, 9))
 def test_flags_by_joints_and_pairs(ezo, ctx, dof, pairs):
     """A record's size goes by the joints and by whether there are self pairs of
-    spheres (1 to 64 a pair of link parts here); a robot of boxes keeps no lists."""
+    spheres; the lanes an overlapping pair of link parts takes by the number of its
+    pairs (1 to 64 a pair of parts here); a robot of boxes keeps no lists."""
     n = 199
     desc = arm(dof, 16 if pairs != "one" else 2, 700 + dof, dof % 2 == 0)
     p = np.asarray(desc["self_pairs"], np.int32).reshape(-1, 2)
