@@ -64,7 +64,7 @@ struct TileRows {
     size_t bytes(int T, int W) const {
         return sd ? tile_smem_bytes(T, slots, W)
                   : flag_tile_bytes(T, !boxes_only(S, B), rec_bytes, B, W) +
-                        flag_grid_bytes(!boxes_only(S, B), n_obs, grid_dim(n_obs), 0) + tables;
+                        flag_grid_bytes(B == 0, n_obs, grid_dim(n_obs), 0) + tables;
     }
 };
 

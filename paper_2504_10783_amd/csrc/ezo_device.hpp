@@ -688,7 +688,7 @@ struct FlagTile {
     lds_ptr<f4> box;        // [4 B][T] each box's world pose as four rows (packed like RobotView::box)
     int T;
     lds_ptr<unsigned> wl;   // [W][kWaveList] each wave's list
-    lds_ptr<unsigned> state;   // [state_words] the grid's cell states
+    lds_ptr<unsigned> state;   // [state_words] the grid's cell states (a robot without boxes)
     lds_ptr<f4> obs;        // [lds_n] staged obstacle records (x, y, z, r)
     // the robot's tables
     lds_ptr<f4> lbound, sph;
@@ -709,7 +709,7 @@ struct FlagTile {
 // most 63 left by the step before.
 constexpr int kWaveList = 192;
 
-// A robot of boxes only keeps no lists and no cell states.
+// A robot of boxes only keeps no lists.
 __host__ __device__ inline bool boxes_only(int n_spheres, int n_boxes) { return n_spheres == 0 && n_boxes > 0; }
 
 // The waves' lists lie first (a record without bounds is addressed from kMaxParts
@@ -724,7 +724,10 @@ __host__ __device__ inline size_t flag_tile_bytes(int T, bool lists, int rec_byt
 }
 
 // The cell states and the staged obstacles follow the tile region, then the
-// robot's tables.
+// robot's tables.  A robot with boxes reads the states from global memory: its box
+// pairs take most of the time and more waves serve them (300 001 of a 7-DOF arm of
+// 70 spheres and 11 boxes among 512 spheres: 1.64 ms with the states in LDS, 1.38
+// without; 194 spheres 664 and 659 us).
 __host__ __device__ inline size_t flag_grid_bytes(bool states, int n_obs, int G, int lds_n) {
     return (states && n_obs > 0 ? sizeof(unsigned) * (size_t)state_words(G) : 0) + sizeof(float4) * (size_t)lds_n;
 }
@@ -748,7 +751,7 @@ __device__ inline FlagTile carve_flag_tile(char* base, int T, int W, const Robot
     p += t.stride * T;
     t.box = (lds_ptr<f4>)p;         p += (int)sizeof(f4) * 4 * n_boxes * T;
     p = to_lds(base) + (int)tile;
-    t.state = (lds_ptr<unsigned>)p; p += (int)flag_grid_bytes(lists, ob.n, G, 0);
+    t.state = (lds_ptr<unsigned>)p; p += (int)flag_grid_bytes(n_boxes == 0, ob.n, G, 0);
     t.obs = (lds_ptr<f4>)p;         p += sizeof(f4) * lds_n;
     t.lbound = (lds_ptr<f4>)p;
     t.blocks = (lds_ptr<i4>)(t.lbound + kMaxParts);
@@ -756,7 +759,7 @@ __device__ inline FlagTile carve_flag_tile(char* base, int T, int W, const Robot
     t.link = (lds_ptr<int>)(p + (int)robot_image_off_link(rb.n_spheres, rb.n_blocks));
     t.pairs = (lds_ptr<i2>)(p + (int)robot_image_off_pairs(rb.n_spheres, rb.n_blocks));
     if (end)
-        *end = base + tile + flag_grid_bytes(lists, ob.n, G, lds_n) +
+        *end = base + tile + flag_grid_bytes(n_boxes == 0, ob.n, G, lds_n) +
                robot_stage_bytes(rb.n_spheres, rb.n_blocks, rb.n_self, pairs);
     return t;
 }
@@ -781,7 +784,7 @@ template <bool BOX, bool OST>
 __device__ inline void stage_tables(const RobotView& rb, bool pairs, const ObsView& ob, const GridView& gv,
                                     const FlagTile& t) {
     if (ob.n > 0) {
-        if (!BOX || !boxes_only(rb.n_spheres, rb.n_boxes))
+        if (!BOX || rb.n_boxes == 0)
             copy_to_lds((lds_ptr<f4>)t.state, reinterpret_cast<const float4*>(gv.state), state_words(gv.G) / 4);
         if constexpr (OST) copy_to_lds(t.obs, ob.rec, ob.n);
     }
@@ -939,8 +942,8 @@ __device__ __forceinline__ void drain_spheres(WaveList& wl, int m, RecF rec, con
 
 // The spheres against the obstacles: a lane per (configuration, sphere), two a
 // step.
-template <class RecF>
-__device__ __forceinline__ void tile_obstacles(RecF rec, const RobotView& rb, const ObsView& ob, const GridView& gv,
+template <class StateF, class RecF>
+__device__ __forceinline__ void tile_obstacles(StateF state, RecF rec, const RobotView& rb, const ObsView& ob, const GridView& gv,
                                                const FlagTile& t, int n_valid, unsigned& ntest) {
     const int S = rb.n_spheres;
     const GridGeom g = load_geom(gv.geom);
@@ -961,8 +964,8 @@ __device__ __forceinline__ void tile_obstacles(RecF rec, const RobotView& rb, co
             const f4 C0 = place(f0, t.sph[s0]), C1 = place(f1, t.sph[s1]);
             bool i0, i1;
             const int k0 = grid_cell(g, G, C0, &i0), k1 = grid_cell(g, G, C1, &i1);
-            const unsigned n0 = a0 && i0 ? t.state[k0 >> 4] >> (2 * (k0 & 15)) : 0u;
-            const unsigned n1 = a1 && i1 ? t.state[k1 >> 4] >> (2 * (k1 & 15)) : 0u;
+            const unsigned n0 = a0 && i0 ? state(k0 >> 4) >> (2 * (k0 & 15)) : 0u;
+            const unsigned n1 = a1 && i1 ? state(k1 >> 4) >> (2 * (k1 & 15)) : 0u;
             if (n0 & 2u) *t.hit(c0) = 1;
             if (n1 & 2u) *t.hit(c1) = 1;
             wl.push((n0 & 3u) == 1u && *t.hit(c0) == 0, (unsigned)c0 | (unsigned)s0 << 6);
@@ -1141,12 +1144,16 @@ __device__ inline unsigned tile_flags(const RobotView& rb, const ObsView& ob, co
     unsigned ntest = 0;
     __syncthreads();
     if (ob.n > 0 && rb.n_spheres > 0) {
+        const lds_ptr<const unsigned> sl = t.state;
+        const unsigned* sg = gv.state;
+        const bool lds_state = !BOX || rb.n_boxes == 0;
+        const auto state = [=](int i) { return lds_state ? sl[i] : sg[i]; };
         if constexpr (OST) {
             const lds_ptr<const float4> rl = (lds_ptr<const float4>)t.obs;
-            tile_obstacles([=](int o) { return lds_load(rl, o); }, rb, ob, gv, t, n_valid, ntest);
+            tile_obstacles(state, [=](int o) { return lds_load(rl, o); }, rb, ob, gv, t, n_valid, ntest);
         } else {
             const float4* rg = ob.rec;
-            tile_obstacles([=](int o) { return rg[o]; }, rb, ob, gv, t, n_valid, ntest);
+            tile_obstacles(state, [=](int o) { return rg[o]; }, rb, ob, gv, t, n_valid, ntest);
         }
     }
     if (rb.n_blocks > 0) {

@@ -65,17 +65,18 @@ def test_flags_at_tile_edges(ezo, ctx, dof, per_link, n_obs, n, prismatic):
     assert np.array_equal(got[out], fo[out])
 
 
-@pytest.mark.parametrize("pairs", ["none", "one", "few", "some", "all", "boxes"])
+@pytest.mark.parametrize("pairs", ["none", "one", "few", "some", "all", "boxes", "boxes too"])
 @pytest.mark.parametrize("dof", range(1, 9))
 def test_flags_by_joints_and_pairs(ezo, ctx, dof, pairs):
     """A record's size goes by the joints and by whether there are self pairs of
     spheres; the lanes an overlapping pair of link parts takes by the number of its
-    pairs (1 to 64 a pair of parts here); a robot of boxes keeps no lists."""
+    pairs (1 to 64 a pair of parts here); a robot of boxes keeps no lists,
+    and one with boxes no cell states."""
     n = 199
     desc = arm(dof, 16 if pairs != "one" else 2, 700 + dof, dof % 2 == 0)
     p = np.asarray(desc["self_pairs"], np.int32).reshape(-1, 2)
     rng = draw.rng_for(710 + dof)
-    if pairs == "none" or pairs == "boxes":
+    if pairs in ("none", "boxes"):
         p = p[:0]
     elif pairs in ("few", "some") and len(p):
         p = p[np.sort(rng.choice(len(p), len(p) // (20 if pairs == "few" else 10), replace=False))]
@@ -83,6 +84,7 @@ def test_flags_by_joints_and_pairs(ezo, ctx, dof, pairs):
     if pairs == "boxes":
         for k in ("sphere_link", "sphere_xyz", "sphere_r"):
             desc[k] = desc[k][:0]
+    if pairs.startswith("boxes"):
         desc["box_link"] = np.arange(dof, dtype=np.int32)
         desc["box_pose"] = np.tile(np.concatenate([np.zeros(3), np.eye(3).ravel()]), (dof, 1))
         desc["box_half"] = rng.uniform(0.03, 0.12, (dof, 3))
