@@ -352,12 +352,12 @@ ezo_status launch_check(ezo_ctx* c, const ezo_robot* r, const ObsView& ov, const
     // one batch: twice the workgroups that the chip holds, each taking tiles in
     // turn, so that the copy of the cell states is paid by several (a fixed number of
     // waves left the box arm, whose tile holds fewer at once, with 2.4 rounds of them);
-    // a robot without spheres copies no states: a workgroup per tile (300 001 of
-    // 11 boxes: 437 us, in turn 493)
+    // a robot with boxes copies no states: a workgroup per tile (300 001 of 11 boxes:
+    // 437 us, in turn 493; of 11 boxes and 70 spheres among 512: 1.31 and 1.38 ms)
     // (up to four such rounds a workgroup per tile as well: 50 000 of the 7-DOF arm
     // among 512 spheres, 1563 tiles for 1536 workgroups, 49.0 us and 50.5 in turn)
     const int64_t held = resident_groups(lds, W);
-    const int64_t wgs = n_batch > 1 || r->S == 0 || tiles <= 4 * held ? tiles : 2 * held;
+    const int64_t wgs = n_batch > 1 || r->B > 0 || tiles <= 4 * held ? tiles : 2 * held;
     dim3 grid((unsigned)wgs, (unsigned)n_batch), block(64 * W);
     const bool box = r->B > 0 || ov.n_ebox > 0;
 #define EZO_LAUNCH_CHECK(BB, OO)                                                                              \

@@ -726,8 +726,8 @@ __host__ __device__ inline size_t flag_tile_bytes(int T, bool lists, int rec_byt
 // The cell states and the staged obstacles follow the tile region, then the
 // robot's tables.  A robot with boxes reads the states from global memory: its box
 // pairs take most of the time and more waves serve them (300 001 of a 7-DOF arm of
-// 70 spheres and 11 boxes among 512 spheres: 1.64 ms with the states in LDS, 1.38
-// without; 194 spheres 664 and 659 us).
+// 70 spheres and 11 boxes among 512 spheres: 1.64 ms with the states in LDS, 1.31
+// without; 194 spheres 664 and 647 us).
 __host__ __device__ inline size_t flag_grid_bytes(bool states, int n_obs, int G, int lds_n) {
     return (states && n_obs > 0 ? sizeof(unsigned) * (size_t)state_words(G) : 0) + sizeof(float4) * (size_t)lds_n;
 }
