@@ -648,10 +648,11 @@ __device__ inline void tile_pairs_sd(const RobotView& rb, const ObsView& ob, con
 // |c - o|^2 < (r_c + r_o)^2 on centres computed by the same FP32 operations
 // wherever they are placed.
 //
-// Bound by VALU issue when there are many configurations (the former tile, with
-// the centres in LDS and every sphere in the grid looking its list up, issued
-// 259 VALU instructions per configuration of the 7-DOF arm among 1024 spheres,
-// 87 % of what the chip issues), by latency when there are few.  Measured: 4 M
+// Bound by VALU issue when there are many configurations (199 instructions of a
+// wave per configuration of the 7-DOF arm among 1024 spheres, 90 % of what the chip
+// issues, 68 % of their lanes active; the former tile, with the centres in LDS and
+// every sphere in the grid looking its list up, issued 259, 87 % and 60 %), by
+// latency when there are few.  Measured: 4 M
 // configurations 2.24 -> 1.55 ms; the check of an inflation's 10 000 samples
 // 10.2 -> 9.8 us, of 96 edges 33.3 -> 27.5 us a launch.
 // ---------------------------------------------------------------------------

@@ -297,7 +297,7 @@ __device__ __forceinline__ float sd_pair(f4 C, float4 O) {
 // Bound by latency of the list and record gathers, which is why a row of lanes
 // takes four spheres (two part pairs) at a time.  256 k configurations of the
 // 7-DOF arm (70 spheres, 1500 self pairs) among 4096 spheres: all pairs 15.7 ms;
-// one sphere per row at a time 484 us, four 414, in 125 registers (four waves a
+// one sphere per row at a time 484 us, four 414, in 127 registers (four waves a
 // SIMD; five with spills 516).  With the field's build the call takes 0.46 ms.
 __global__ void __launch_bounds__(256, 4) k_distances(RobotView rb, ObsView ob, NearView nv, int CW,
                                                    const float* __restrict__ q, int64_t n, int64_t stride_n,

@@ -1071,9 +1071,9 @@ __global__ void __launch_bounds__(256) k_list_candidates(const int* __restrict__
 // states and staged obstacles, the candidates' state, then the robot tables
 // (robot_stage_bytes), read by every one of the dependent checks.
 //
-// Six waves a SIMD: 80 registers, of which one goes to scratch, two or three with
-// boxes (five waves and none in scratch: 30 000 candidates of the 11-box arm 720 us
-// against 705, its inflation at N_p = 10 000 1.34 ms against 1.06).
+// Six waves a SIMD, 80 registers, none in scratch (five waves: 30 000 candidates of
+// the 11-box arm 720 us against 705, its inflation at N_p = 10 000 1.34 ms against
+// 1.06).
 // ---------------------------------------------------------------------------
 constexpr int kMaxLevels = 3;
 
