@@ -1148,6 +1148,7 @@ ezo_status ezo_robot_create(ezo_ctx* c, const ezo_robot_desc* d, ezo_robot** out
     r->view.n_blocks = NB;
     r->view.rec_bytes = 16 * rec_rows(dof, NB);
     r->view.item_shift = item_lanes_log2(P, NB);
+    r->view.deal_blocks = P > 32 * NB ? NB : 1 << 20;       // 2^20: more than any tile
     r->view.lbound = reinterpret_cast<const float4*>(b + off_lbd);
     r->view.blocks = reinterpret_cast<const int4*>(b + off_blk);
     r->view.dh = reinterpret_cast<const float4*>(b + off_dh);

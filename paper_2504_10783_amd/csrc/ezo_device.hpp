@@ -58,6 +58,7 @@ struct RobotView {
     int n_blocks;
     int rec_bytes;             // of a configuration's record in a flags tile (16 rec_rows)
     int item_shift;            // lanes of a part pair there (item_lanes_log2)
+    int deal_blocks;           // its part pairs when they are dealt out over the waves (see tile_self_pairs)
     const float4* dh;          // [kMaxDof] (a, d, cos alpha, sin alpha), zero past dof
     const int* link_begin;     // [dof + 1] spheres of link i: [link_begin[i], link_begin[i+1])
     const float4* sph;         // [S] local (x, y, z), r -- sorted by link
@@ -270,8 +271,9 @@ __device__ inline TileSmem carve_tile(char* base, int T, int S, int W) {
 // workgroup's threads: one division per loop instead of one per item.
 struct ItemWalk {
     int c, k, dc, dk;
-    __device__ ItemWalk(int n) {
-        const int nt = blockDim.x, tid = threadIdx.x;
+    __device__ ItemWalk(int n) : ItemWalk(n, threadIdx.x) {}
+    __device__ ItemWalk(int n, int tid) {
+        const int nt = blockDim.x;
         if ((n & (n - 1)) == 0) {                  // a power of two: shifts
             const int sh = __builtin_ctz(n);
             k = tid >> sh;
@@ -1016,7 +1018,12 @@ template <class PairF>
 __device__ __forceinline__ void tile_self_pairs(PairF pair, const RobotView& rb, const FlagTile& t, int n_valid,
                                                 unsigned& ntest) {
     WaveList wl(t);
-    ItemWalk w(n_valid);
+    // part pairs of many sphere pairs that would fill half the waves or fewer are dealt
+    // out over all of them (an arm of 200 spheres and 4000 pairs, 1000 configurations
+    // among 40 obstacles: 25.0 us a call in order, 19.5 dealt out; with the 25 sphere
+    // pairs a part pair of the 7-DOF arm it costs 2 %)
+    const bool deal = 2 * n_valid * rb.deal_blocks <= (int)blockDim.x;
+    ItemWalk w(n_valid, deal ? (int)(threadIdx.x & 63) * (int)(blockDim.x >> 6) + wave_id() : (int)threadIdx.x);
     while (true) {
         if (wl.n < 64 && __any(w.k < rb.n_blocks)) {
             const bool on = w.k < rb.n_blocks;
